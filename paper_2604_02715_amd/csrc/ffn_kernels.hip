@@ -9,7 +9,8 @@
 //                pairs whose expert has no slot; emits one record per row tile (expert, first
 //                row, rows, slot), tiles with the most rows first
 //   gemm1        per (row tile, 128-column strip): a = X W1 and b = X W3 on two wavefronts
-//                with v_mfma_f32_16x16x32_bf16, h = silu(a) * b rounded to BF16
+//                with v_mfma_f32_16x16x32_bf16, h = silu(a) * b rounded to BF16; with few row tiles
+//                per (row tile, strip, K split), and swiglu_reduce adds the splits and applies SwiGLU
 //   gemm2        per (row tile, 128-column strip, K split): y = h W2, FP32 partial sums
 //   combine      out[t] = sum_k gate[t][k] * sum_splits y[pos(t,k)]   (fixed order)
 //
@@ -266,6 +267,27 @@ __global__ __launch_bounds__(1024) void route_sort_kernel(FfnArgs a) {
         if (p < pairs) place(p, kept[i]);
     }
     for (uint32_t p = tid + 1024u * kKept; p < pairs; p += 1024) place(p, classify(a.topk_ids[p], false));
+}
+
+// The shared expert: every token once, in order, on the one expert in slot 0.  What route_sort_kernel would find out
+// from T identical ids is known, so the lists are written by as many workgroups as they need and nothing is counted.
+__global__ __launch_bounds__(256) void route_identity_kernel(FfnArgs a) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < a.T) {
+        a.sorted_pair[i] = int32_t(i);
+        a.pair_pos[i] = int32_t(i);
+    }
+    const uint32_t n_tiles = (a.T + a.m_tile - 1) / a.m_tile;
+    if (i < a.tiles_cap) {
+        const uint32_t row0 = i * a.m_tile;
+        a.tile_rec[i] = i < n_tiles ? make_int4(0, int32_t(row0), int32_t(min(a.m_tile, a.T - row0)), 0) : make_int4(0, 0, 0, -1);
+    }
+    if (i == 0) {
+        a.expert_count[0] = int32_t(a.T);
+        a.expert_offset[0] = 0;
+        a.expert_offset[1] = int32_t(a.T);
+        a.n_tiles[0] = int32_t(n_tiles);
+    }
 }
 
 // SiLU(g) * u (Sec. 2.1's gated FFN) in FP32 with the hardware's exp2 and reciprocal, each within one
@@ -565,12 +587,31 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
         const int32_t pr = a.sorted_pair[t.row0 + r];
         aoff[i] = 2u * ((uint32_t(pr) / a.K) * a.H + 8u * piece);          // the launcher checks T * H * 2 < 4 GiB
     }
+    // K split blockIdx.z multiplies k rows [k_begin, k_end): whole A blocks, the last split what remains
+    const uint32_t k_per = ((a.H + a.ksplit1 - 1) / a.ksplit1 + kABlock - 1) / kABlock * kABlock;
+    const uint32_t k_begin = min(a.H, blockIdx.z * k_per);
+    const uint32_t k_end = min(a.H, k_begin + k_per);
     StripGemm<MI> g;
     g.zero();
-    const uint32_t n_blocks = a.H / kABlock;
-    g.run_shared(reinterpret_cast<const uint8_t*>(a.tokens), aoff, abuf, w, a.H, col_ok ? n0 : a.F - 8, a.F, 0, n_blocks, lane, wave);
-    g.run(arow, w + (col_ok ? n0 : a.F - 8), a.F, n_blocks * kABlock, a.H, lane);
+    const uint32_t n_blocks = (k_end - k_begin) / kABlock;
+    g.run_shared(reinterpret_cast<const uint8_t*>(a.tokens), aoff, abuf, w, a.H, col_ok ? n0 : a.F - 8, a.F, k_begin, n_blocks, lane, wave);
+    g.run(arow, w + (col_ok ? n0 : a.F - 8), a.F, k_begin + n_blocks * kABlock, k_end, lane);
 
+    if (a.ksplit1 > 1) {                          // partial sums of both matrices, added up by swiglu_reduce_kernel
+        if (!col_ok) return;
+        float* part = a.ybuf + (size_t(blockIdx.z) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int32_t row = mi * 16 + 4 * (lane >> 4) + r;
+                if (row >= t.rows) continue;
+                float4* dst = reinterpret_cast<float4*>(part + size_t(uint32_t(row)) * 2 * a.F);
+                dst[0] = make_float4(g.acc[mi][0][r], g.acc[mi][1][r], g.acc[mi][2][r], g.acc[mi][3][r]);
+                dst[1] = make_float4(g.acc[mi][4][r], g.acc[mi][5][r], g.acc[mi][6][r], g.acc[mi][7][r]);
+            }
+        return;
+    }
     if (mat_id == 1) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
@@ -694,6 +735,32 @@ __global__ __launch_bounds__(256) void gemm2_kernel(FfnArgs a) {
     else if (MI > 4 && t.rows <= 64) gemm2_body<4>(a, t, abuf, col_wg, split);
     else if (MI > 6 && t.rows <= 96) gemm2_body<6>(a, t, abuf, col_wg, split);
     else gemm2_body<MI>(a, t, abuf, col_wg, split);
+}
+
+// h[row][n] = bf16( silu(gate) * up ), gate and up summed over the K splits of the first product in split order.
+// Bound by its launch at the sizes that split (a few hundred kilobytes to 30 MB of sums, still in the caches): a launch
+// of its own is cheaper than the device-wide fence a last-arriver scheme inside the product would take.
+__global__ __launch_bounds__(256) void swiglu_reduce_kernel(FfnArgs a) {
+    const uint32_t per_row = a.F / 8;
+    const uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x;
+    const uint32_t row = uint32_t(i / per_row), n0 = 8u * uint32_t(i % per_row);
+    if (row >= uint32_t(a.expert_offset[a.E])) return;        // rows past the pairs whose expert is mapped
+    float g[8], u[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) g[c] = u[c] = 0.f;
+    const float* part = a.ybuf + size_t(row) * 2 * a.F + n0;
+    for (uint32_t sp = 0; sp < a.ksplit1; ++sp, part += size_t(a.pairs_cap) * 2 * a.F) {
+        const float4 g0 = *reinterpret_cast<const float4*>(part), g1 = *reinterpret_cast<const float4*>(part + 4);
+        const float4 u0 = *reinterpret_cast<const float4*>(part + a.F), u1 = *reinterpret_cast<const float4*>(part + a.F + 4);
+        g[0] += g0.x; g[1] += g0.y; g[2] += g0.z; g[3] += g0.w; g[4] += g1.x; g[5] += g1.y; g[6] += g1.z; g[7] += g1.w;
+        u[0] += u0.x; u[1] += u0.y; u[2] += u0.z; u[3] += u0.w; u[4] += u1.x; u[5] += u1.y; u[6] += u1.z; u[7] += u1.w;
+    }
+    uint4 o;
+    o.x = pack_bf16_rne(swiglu(g[0], u[0]), swiglu(g[1], u[1]));
+    o.y = pack_bf16_rne(swiglu(g[2], u[2]), swiglu(g[3], u[3]));
+    o.z = pack_bf16_rne(swiglu(g[4], u[4]), swiglu(g[5], u[5]));
+    o.w = pack_bf16_rne(swiglu(g[6], u[6]), swiglu(g[7], u[7]));
+    *reinterpret_cast<uint4*>(a.hbuf + size_t(row) * a.F + n0) = o;
 }
 
 // ------------------------------------------------------------------ large row tiles (MFMA bound)
@@ -1145,8 +1212,12 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 // WALK: a workgroup takes several tiles one after the other (see the tile loop at the end); without it the
 // launch has one workgroup per tile number and the code for the upcoming tile falls away.
+// MODE 1: h = SwiGLU(X W1, X W3).  MODE 2: y = h W2, K split ksplit ways.  MODE 3: the first product with K split
+// ksplit1 ways, FP32 partial sums of gate and up instead of h (swiglu_reduce_kernel adds them up).
 template <int MODE, int WAVES, bool WALK>
 __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
+    constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
+    static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
     // WAVES = 8: wavefronts 4 (rows) x 2 (columns), 64 x 128 each, two per SIMD.  WAVES = 4: 2 x 2,
     // 128 x 128 each (256 accumulator registers), one per SIMD: a third less LDS read traffic per MFMA.
     constexpr int kRowTiles = WAVES == 8 ? 2 : 4;            // 32-row MFMA tiles per wavefront
@@ -1156,9 +1227,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
     constexpr int kFrag = kRowTiles + 8;                     // fragment reads per sub-step
     static_assert(WAVES == 8 || WAVES == 4, "wavefront layouts");
     extern __shared__ __align__(16) uint16_t lds[];
-    const uint32_t K = MODE == 1 ? a.H : a.F;
-    const uint32_t N = MODE == 1 ? a.F : a.H;
-    const uint32_t ncols_tile = MODE == 1 ? 128u : 256u;
+    const uint32_t K = kFirst ? a.H : a.F;
+    const uint32_t N = kFirst ? a.F : a.H;
+    const uint32_t ncols_tile = kFirst ? 128u : 256u;
     const uint32_t n_ct = (N + ncols_tile - 1) / ncols_tile;
     const uint32_t n_rt = uint32_t(a.n_tiles[0]);
     // Super-tile of this launch: 32 tiles (one per CU of an XCD) as sm rows x sn columns, sn a power of two
@@ -1167,7 +1238,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
     const uint32_t n_sn = (n_ct + sn - 1) >> sn_log2;
     // Workgroups go to the 8 XCDs round robin, so (super-tile, K split) pair number p runs on XCD
     // p % 8: the splits of one super-tile land on different XCDs
-    const uint32_t n_split = MODE == 2 ? a.ksplit : 1u;
+    const uint32_t n_split = MODE == 2 ? a.ksplit : (MODE == 3 ? a.ksplit1 : 1u);
     // Super-tiles are taken in groups of tiled_group super-rows (the row tiles of about one expert): for
     // each column block of the group, its super-rows run next to each other in time on different XCDs,
     // so the expert's weights for that column block leave HBM once and the other XCDs find them in the
@@ -1252,23 +1323,23 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         if (!s.valid) { s.rows = 1; s.row0 = 0; }
         s.n_base = col_tile * ncols_tile;
         s.split = split;
-        // split K (second product only): this tile multiplies steps [step_lo, step_hi) of the K / 64
-        // and writes its own FP32 partial, which combine_kernel sums in split order
+        // split K: this tile multiplies steps [step_lo, step_hi) of the K / 64
+        // and writes its own FP32 partial, which combine_kernel or swiglu_reduce_kernel sums in split order
         const uint32_t step_lo = uint32_t(uint64_t(n_steps_all) * split / n_split);
         const uint32_t step_hi = uint32_t(uint64_t(n_steps_all) * (split + 1) / n_split);
         const uint32_t k_begin = step_lo * kTK;
-        s.n_steps = MODE == 1 ? 0u : step_hi - step_lo;        // >= 1: the host keeps ksplit <= K / 64
-        s.a_base = MODE == 1 ? nullptr : reinterpret_cast<const uint8_t*>(a.hbuf) + size_t(k_begin) * 2;
+        s.n_steps = MODE == 1 ? 0u : step_hi - step_lo;        // >= 1: the host keeps the splits <= K / 64
+        s.a_base = MODE == 1 ? nullptr : reinterpret_cast<const uint8_t*>(MODE == 3 ? a.tokens : a.hbuf) + size_t(k_begin) * 2;
         const int lane = fresh_lane();
 #pragma unroll
         for (int i = 0; i < kDma; ++i) {
             const int r_lds = 8 * (wave * kDma + i) + (lane >> 3);                 // row of the A tile
             const int32_t r = min(r_lds, s.rows - 1);
-            s.a_off[i] = MODE == 1 ? uint32_t(a.sorted_pair[s.row0 + r]) : uint32_t(s.row0 + r);
+            s.a_off[i] = kFirst ? uint32_t(a.sorted_pair[s.row0 + r]) : uint32_t(s.row0 + r);
         }
         const size_t slot_u = s.valid ? size_t(slot) : 0u;
         s.b_base = reinterpret_cast<const uint8_t*>(
-            MODE == 1 ? a.slots13 + slot_u * 2 * mat : a.slots2 + slot_u * mat + size_t(k_begin) * N);
+            MODE == 1 ? a.slots13 + slot_u * 2 * mat : (MODE == 3 ? a.slots13 + slot_u * 2 * mat : a.slots2 + slot_u * mat) + size_t(k_begin) * N);
     };
     auto finish_state = [&](TileState& s) __attribute__((always_inline)) {
         const int lane = fresh_lane();
@@ -1276,7 +1347,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         for (int i = 0; i < kDma; ++i) {
             const int r_lds = 8 * (wave * kDma + i) + (lane >> 3);              // row of the A tile
             const int piece = (lane & 7) ^ ((r_lds >> 1) & 7);                  // global 16-byte piece held at position lane & 7
-            const uint32_t row_elems = MODE == 1 ? (s.a_off[i] / a.K) * a.H : s.a_off[i] * a.F;
+            const uint32_t row_elems = kFirst ? (s.a_off[i] / a.K) * a.H : s.a_off[i] * a.F;
             s.a_off[i] = 2u * (row_elems + 8u * piece);
         }
 #pragma unroll
@@ -1286,7 +1357,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
             const int unit = (pp >> 2) ^ (k_lds & 3);                           // logical unit of 32 columns
             const uint32_t c = 32u * unit + 8u * (pp & 3);                      // column inside the 256-column tile
             uint32_t elems;
-            if (MODE == 1) elems = (c >= 128 ? uint32_t(mat) : 0u) + min(s.n_base + (c & 127u), N - 8);
+            if (kFirst) elems = (c >= 128 ? uint32_t(mat) : 0u) + min(s.n_base + (c & 127u), N - 8);
             else elems = min(s.n_base + c, N - 8);
             s.b_off[i] = 2u * (elems + uint32_t(k_lds) * N);
         }
@@ -1343,7 +1414,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         // B fragment j of sub-step ks, read t: row 16 ks + 8 h + 4 t + e, unit u(j) ^ e, bytes 32 nh + 8 g
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int unit = MODE == 1 ? ((((2 * wn + (j & 1)) ^ e)) + 4 * (j >> 1)) : (4 * wn + (j ^ e));
+            const int unit = kFirst ? ((((2 * wn + (j & 1)) ^ e)) + 4 * (j >> 1)) : (4 * wn + (j ^ e));
             b_addr[j] = 2 * kStageBytes + (8 * h + e) * 512 + 64 * unit + 32 * nh + 8 * g;
         }
 #pragma unroll
@@ -1469,6 +1540,23 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
                         *reinterpret_cast<uint32_t*>(hrow + 32 * j) = packed;
                 }
             }
+    } else if (MODE == 3) {
+        // partial sums: row r of split s at [s][r][gate | up][F]
+        const uint32_t col0 = c.n_base + 64u * wn + q;
+        float* const plane = a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * 2 * a.F + col0;
+#pragma unroll
+        for (int i = 0; i < kRowTiles; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int32_t row = wm * kWaveRows + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+                if (row >= c.rows) continue;
+                float* const prow = plane + size_t(uint32_t(row)) * 2 * a.F;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (col0 + 32u * (j & 1) >= N) continue;
+                    prow[(j >> 1) * a.F + 32 * (j & 1)] = acc[i][j][r];
+                }
+            }
     } else {
         // one 64-bit address per stored row; the four column groups of a row lie 128 bytes apart
         const uint32_t col0 = c.n_base + 128u * wn + q;
@@ -1584,7 +1672,7 @@ __global__ __launch_bounds__(256) void combine_kernel(FfnArgs a) {
         for (uint32_t j = 0; j < kGroup; ++j) {
             const bool in = k0 + j < a.K;
             pos[j] = in ? a.pair_pos[tok * a.K + k0 + j] : -1;
-            gate[j] = in ? a.topk_w[tok * a.K + k0 + j] : 0.f;
+            gate[j] = in ? (a.identity ? 1.f : a.topk_w[tok * a.K + k0 + j]) : 0.f;
         }
         float4 y[kGroup];
 #pragma unroll
@@ -1653,7 +1741,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
     auto mark = [&](int kind, int begin) { if (hook) hook(user, kind, begin, stream); };
     const size_t sh = (3 * size_t(a.E) + 1024) * sizeof(int32_t);
     mark(1, 1);
-    if (a.n_chunks) {
+    if (a.identity) {
+        hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
+    } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
         hipLaunchKernelGGL(route_sort_kernel<true>, dim3(1), dim3(1024), sh, stream, a);
         hipLaunchKernelGGL(route_scatter_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
@@ -1667,9 +1757,14 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
         else if (a.K <= 8) hipLaunchKernelGGL(combine_kernel<8>, grid, dim3(256), 0, stream, a);
         else hipLaunchKernelGGL(combine_kernel<16>, grid, dim3(256), 0, stream, a);
     };
+    auto launch_reduce = [&]() {
+        const uint64_t n = uint64_t(a.pairs_cap) * (a.F / 8);
+        if (a.ksplit1 > 1) hipLaunchKernelGGL(swiglu_reduce_kernel, dim3(uint32_t((n + 255) / 256)), dim3(256), 0, stream, a);
+    };
+    if (a.ksplit1 == 0 || (a.ksplit1 > 1 && a.ksplit1 > a.H / kTK)) return hipErrorInvalidValue;
     const uint32_t strips1 = (a.F + kStrip - 1) / kStrip;
     const uint32_t strips2 = (a.H + kStrip - 1) / kStrip;
-    const dim3 g1((strips1 + 1) / 2, a.tiles_cap, 1);
+    const dim3 g1((strips1 + 1) / 2, a.tiles_cap, a.ksplit1);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
     if (a.m_tile == 256) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
@@ -1677,6 +1772,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
         const bool d2l4 = a.tiled_waves == 1;                       // LDS-direct loads, four wavefronts of 128 x 128
         const bool d2l = a.tiled_waves == 2 || d2l4;
         if (!d2l && a.ksplit != 1) return hipErrorInvalidValue;     // only the LDS-direct kernels split K
+        if (a.tiled_waves != 2 && a.ksplit1 != 1) return hipErrorInvalidValue;
         if (a.ksplit == 0 || a.ksplit > a.F / kTK) return hipErrorInvalidValue;
         static bool attr_set = false;
         if (!attr_set) {
@@ -1696,6 +1792,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
+            if (e != hipSuccess) return e;
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 8, false>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 4, false>),
@@ -1755,9 +1854,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
             return (walk && a.tiled_persist && all.x > cap) ? dim3(cap, 1, 1) : all;
         };
         if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false>), g, dim3(256), 163840, stream, a); }
+        else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<3, 8, false>), g, dim3(512), 163840, stream, a); }
         else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((gemm_d2l_kernel<1, 8, true>), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<1>, grid_for((a.F + 127) / 128), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<1>, grid_for((a.F + 127) / 128), dim3(512), lds_bytes, stream, a);
+        launch_reduce();
         mark(2, 0);
         mark(3, 1);
         if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false>), g, dim3(256), 163840, stream, a); }
@@ -1780,6 +1881,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
     else if (a.m_tile == 64) hipLaunchKernelGGL(gemm1_swiglu_kernel<4>, g1, dim3(256), 0, stream, a);
     else if (a.m_tile == 96) hipLaunchKernelGGL(gemm1_swiglu_kernel<6>, g1, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(gemm1_swiglu_kernel<8>, g1, dim3(256), 0, stream, a);
+    launch_reduce();
     mark(2, 0);
     mark(3, 1);
     if (a.m_tile == 16) hipLaunchKernelGGL(gemm2_kernel<1>, g2, dim3(256), 0, stream, a);

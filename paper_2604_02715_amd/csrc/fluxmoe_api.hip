@@ -53,7 +53,7 @@ struct StageHalf {
 };
 
 struct FfnPlan {
-    uint32_t m_tile, ksplit, pairs_cap, tiles_cap, n_chunks;
+    uint32_t m_tile, ksplit, ksplit1, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
     uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_chunk, off_h, off_y;
 };
@@ -147,7 +147,10 @@ FfnShape ffn_shape(const fluxmoe_ctx* c, uint32_t n_experts) {
     return FfnShape{n_experts, c->d.hidden, c->d.ffn, c->n_cus, c->tune_tiled_waves};
 }
 
-FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K) {
+// limit: bytes the scratch may take (the call's buffer; the size query leaves it open).  Only the K split of the
+// first product gives way to it, so a buffer that holds the unsplit plan is always enough.
+// mapped: experts of the layer known to be resident, 0 = not known (steers that split only).
+FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
     FfnPlan p{};
     const uint64_t E = c.E, H = c.H, F = c.F;
     const uint64_t pairs = uint64_t(T) * K;
@@ -199,6 +202,40 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K) {
             p.ksplit = uint32_t(k2);
         }
     }
+    // K split of the first product, for launches that would leave most of the chip without a workgroup: the FP32 partial
+    // sums of gate and up cost a write, a read and a launch.  Measured, whole FFN call: one token, top-10 of 512 experts,
+    // H 2048 F 512 (20 workgroups unsplit) 63 -> 36 us; 333 tokens, top-4 of 64, H 2880 F 360 (128) 140 -> 116 us; the
+    // shared expert H 5120 F 1536 with 512 tokens (24 tiles of 256 x 256, split 6 ways; its own grouping below included)
+    // 134 -> 70 us.  Layers whose tiles fill the chip stay unsplit (8 experts of H 4096 F 14336: 448 workgroups).
+    p.ksplit1 = 1;
+    {
+        const uint64_t act = mapped ? std::min<uint64_t>(mapped, E) : E;
+        const uint64_t pairs_act = std::max<uint64_t>(1, pairs * act / E);
+        const uint64_t groups_act = std::max<uint64_t>(1, std::min(act, pairs_act));
+        const uint64_t partial_bytes = pairs_act * 2 * F * 8;             // written and read, per split
+        if (p.m_tile != 256) {
+            // units of k rows of a workgroup (about 30 ns each when the memory system is not saturated)
+            const uint64_t wgs1 = ((F + 127) / 128 + 1) / 2 * std::max<uint64_t>(pairs_act / p.m_tile, groups_act);
+            uint64_t best = ~0ull;
+            for (uint64_t k = 1; k <= 16 && (k == 1 || k * 256 <= H); ++k) {
+                const uint64_t k_per = align_up((H + k - 1) / k, 128);    // the kernel splits at multiples of 128
+                if ((H + k_per - 1) / k_per != k) continue;
+                const uint64_t rounds = (wgs1 * k + n_cus - 1) / n_cus;
+                const uint64_t cost = rounds * (std::min(k_per, H) + 128) + (k > 1 ? 128 + k * partial_bytes / (n_cus * 1024) : 0);
+                if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); }
+            }
+        } else if (c.tiled_waves == 2) {
+            // nanoseconds: 1.2 us a step of 64 k, 3 us to start a tile, 4 us for the extra launch, partial sums at 5 TB/s
+            const uint64_t avg_act = (pairs_act + groups_act - 1) / groups_act;
+            const uint64_t tiles1 = groups_act * ((avg_act + 255) / 256) * ((F + 127) / 128);
+            uint64_t best = ~0ull;
+            for (uint64_t k = 1; k <= 8 && (k == 1 || k * 512 <= H); ++k) {
+                const uint64_t rounds = (tiles1 * k + n_cus - 1) / n_cus;
+                const uint64_t cost = rounds * (H / 64 * 1200 / k + 3000) + (k > 1 ? 4000 + k * partial_bytes / 5000 : 0);
+                if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); }
+            }
+        }
+    }
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
     p.off_count = take((E + 1) * 4);
@@ -210,7 +247,11 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K) {
     p.n_chunks = pairs > kRouteChunkThreshold ? uint32_t((pairs + kRouteChunkPairs - 1) / kRouteChunkPairs) : 0u;
     p.off_chunk = take(uint64_t(p.n_chunks) * E * 4);
     p.off_h = take(uint64_t(p.pairs_cap) * F * 2);
-    p.off_y = take(uint64_t(p.ksplit) * p.pairs_cap * H * 4);
+    // the partial sums of the first product are read before the second product writes its own in the same place
+    const uint64_t y_bytes = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part_bytes = uint64_t(p.pairs_cap) * 2 * F * 4;
+    p.off_y = take(y_bytes);
+    while (p.ksplit1 > 1 && p.off_y + align_up(p.ksplit1 * part_bytes, 256) > limit) --p.ksplit1;
+    if (p.ksplit1 > 1) o = std::max(o, p.off_y + align_up(p.ksplit1 * part_bytes, 256));
     p.bytes = o;
     return p;
 }
@@ -420,14 +461,11 @@ int fluxmoe_query_sizes(const fluxmoe_ctx* c, fluxmoe_sizes* out) {
     return FLUXMOE_OK;
 }
 
-// extra scratch of the shared-expert call: its synthetic routing (ids, gates, one-entry table)
-static uint64_t shared_extra_bytes(uint32_t T) { return 2 * align_up(uint64_t(T) * 4, 256) + 256; }
-
 uint64_t fluxmoe_ffn_workspace_bytes(const fluxmoe_ctx* c, uint32_t T, uint32_t K, int shared_expert) {
     if (!c) return 0;
     uint64_t need = plan_ffn(ffn_shape(c, c->d.n_experts), T, K).bytes;
     if (shared_expert)          // same shapes, a single expert
-        need = std::max(need, plan_ffn(ffn_shape(c, 1), T, 1).bytes + shared_extra_bytes(T));
+        need = std::max(need, plan_ffn(ffn_shape(c, 1), T, 1).bytes);
     return need;
 }
 
@@ -1054,7 +1092,9 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     if (uint64_t(T) * c->d.hidden * 2 >= (1ull << 32))
         return set_error(FLUXMOE_EINVAL, "tokens (T * hidden * 2 bytes) must stay under 4 GiB");
     if ((uintptr_t(tokens) | uintptr_t(out)) & 15) return set_error(FLUXMOE_EINVAL, "tokens/out must be 16-byte aligned");
-    const FfnPlan p = plan_ffn(ffn_shape(c, c->d.n_experts), T, K);
+    uint32_t mapped = 0;
+    for (uint32_t e = 0; e < c->d.n_experts; ++e) mapped += c->pt[size_t(layer) * c->d.n_experts + e] >= 0 ? 1u : 0u;
+    const FfnPlan p = plan_ffn(ffn_shape(c, c->d.n_experts), T, K, w_bytes, mapped);
     if (p.bytes > w_bytes)
         return set_error(FLUXMOE_ENOMEM, "%s holds %llu bytes, T=%u K=%u needs %llu", w_name,
                          (unsigned long long)w_bytes, T, K, (unsigned long long)p.bytes);
@@ -1081,7 +1121,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.hbuf = reinterpret_cast<uint16_t*>(w + p.off_h);
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
-    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.ksplit = p.ksplit;
+    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);
@@ -1134,26 +1174,17 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     if (T > 65535) return set_error(FLUXMOE_EINVAL, "T too large");
     if ((uintptr_t(w13) | uintptr_t(w2) | uintptr_t(tokens) | uintptr_t(out)) & 15)
         return set_error(FLUXMOE_EINVAL, "pointers must be 16-byte aligned");
-    const FfnPlan p = plan_ffn(ffn_shape(c, 1), T, 1);   // this model's shapes, a single always-mapped expert
-    const uint64_t extra = shared_extra_bytes(T);
-    if (c->pool_ws_bytes + p.bytes + extra > c->ws_bytes)
+    // this model's shapes, a single always-mapped expert
+    const FfnPlan p = plan_ffn(ffn_shape(c, 1), T, 1, c->ws_bytes - c->pool_ws_bytes);
+    if (c->pool_ws_bytes + p.bytes > c->ws_bytes)
         return set_error(FLUXMOE_ENOMEM, "workspace has %zu bytes, the shared expert with T=%u needs %llu",
-                         c->ws_bytes, T, (unsigned long long)(c->pool_ws_bytes + p.bytes + extra));
+                         c->ws_bytes, T, (unsigned long long)(c->pool_ws_bytes + p.bytes));
     if (p.tiles_cap > 65535) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     uint8_t* w = c->ws + c->pool_ws_bytes;
-    uint8_t* x = w + p.bytes;
-    int32_t* ids = reinterpret_cast<int32_t*>(x);
-    int32_t* gates = reinterpret_cast<int32_t*>(x + align_up(uint64_t(T) * 4, 256));
-    int32_t* table = reinterpret_cast<int32_t*>(x + 2 * align_up(uint64_t(T) * 4, 256));
-    HIPCHECK(launch_fill_i32(ids, 0, T, stream));
-    HIPCHECK(launch_fill_i32(gates, 0x3F800000, T, stream));      // 1.0f
-    HIPCHECK(launch_fill_i32(table, 0, 1, stream));
     FfnArgs a{};
     a.tokens = tokens;
-    a.topk_ids = ids;
-    a.topk_w = reinterpret_cast<const float*>(gates);
-    a.page_table = table;
+    a.identity = 1;
     a.slots13 = w13;
     a.slots2 = w2;
     a.out = out;
@@ -1170,7 +1201,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.hbuf = reinterpret_cast<uint16_t*>(w + p.off_h);
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
-    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.ksplit = p.ksplit;
+    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);

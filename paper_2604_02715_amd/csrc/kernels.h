@@ -31,9 +31,14 @@ struct FfnArgs {
                                  // turned into the chunk's first position inside the expert's rows by the grouping kernel
     uint32_t n_chunks;           // 0: the grouping kernel counts and scatters the pairs itself (one workgroup)
     uint16_t* hbuf;              // BF16 [pairs_cap][F]
-    float* ybuf;                 // FP32 [ksplit][pairs_cap][H]
+    float* ybuf;                 // FP32 [ksplit][pairs_cap][H]; with ksplit1 > 1 the first product's partial sums
+                                 // [ksplit1][pairs_cap][2][F] (gate, up) lie here before the second product runs
     uint32_t* error_word;
     uint32_t pairs_cap, tiles_cap, m_tile, ksplit;
+    uint32_t ksplit1;            // K splits of the first product; 1: SwiGLU in its epilogue, more: FP32 partial sums
+                                 // that swiglu_reduce_kernel adds up
+    uint32_t identity;           // non-zero: one expert in slot 0 takes every token with gate 1 (K = 1, E = 1); topk_ids,
+                                 // topk_w and page_table are not read
     uint32_t tiled_waves;        // variant of the LDS-tiled kernels (m_tile 256): 2 LDS-direct loads, 8 or 4
                                  // wavefronts with register-staged loads
     uint32_t tiled_persist;      // LDS-direct kernels: workgroups per CU-sized round that walk through the tiles (1 = 256

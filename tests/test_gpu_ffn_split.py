@@ -1,0 +1,57 @@
+"""GPU parity of the expert FFN where the first product is split over K (few workgroups otherwise: a token or two,
+a single expert, narrow ffn) and of the shared expert's own grouping, against the FP64 oracle.  Tolerance as in
+test_gpu_ffn.py: the sums stay FP32, only their order changes."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ffn as offn
+from oracle import paging
+from paper_2604_02715_amd import binding as B
+from paper_2604_02715_amd import inputs
+from test_gpu_ffn import TOL, run_ffn_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=1, top_k=2, hidden=1032, ffn=136),                              # split at 128 k, a last split with a k tail
+    dict(tokens=5, top_k=3, hidden=2056, ffn=72),                               # one strip, partly empty
+    dict(tokens=100, top_k=1, n_experts=1, n_slots=1, hidden=2048, ffn=200),    # one expert, 100 rows in one tile
+    dict(tokens=40, top_k=2, hidden=1024, ffn=264, routing="zipf"),
+    dict(tokens=300, top_k=1, n_experts=1, n_slots=1, hidden=1024, ffn=192),    # LDS-tiled kernels, ragged column tile
+    dict(tokens=700, top_k=2, n_experts=3, n_slots=3, hidden=1600, ffn=320),    # the same, splits of unequal length
+])
+def test_split_first_product(kw):
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=8)
+
+
+def test_split_first_product_in_waves():
+    """Half of the experts resident at a time: pairs of the others are skipped and the sums are only made for the rest."""
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=20, top_k=3, hidden=1024, ffn=136, n_slots=4)
+    run_ffn_case(cfg, seed=9, waves=lambda u: paging.waves(u, 4))
+
+
+@pytest.mark.parametrize("tokens", [1, 100, 129, 257, 600])
+@pytest.mark.parametrize("shape", [(1024, 192), (1096, 200)])
+def test_shared_expert(tokens, shape):
+    """Row tiles of one, several and partly filled; the smaller shape takes the LDS-tiled kernels from 129 rows on."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=2, n_slots=2, shared_expert=True, tokens=tokens, hidden=shape[0], ffn=shape[1])
+    pool, _ = build_pool(cfg)
+    try:
+        s13, s2 = inputs.shared_expert_weights(cfg, 0)
+        x = inputs.activations(cfg)
+        s13d, s2d, xd = s13.cuda(), s2.cuda(), x.cuda()
+        out = torch.full((tokens, cfg.hidden), 5.0, dtype=torch.float32, device="cuda")
+        pool.shared_expert_ffn(s13d, s2d, xd, out)
+        once = out.clone()
+        pool.shared_expert_ffn(s13d, s2d, xd, out, B.FFN_ACCUMULATE)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 0
+        want = offn.moe_ffn(inputs.bits_u16(x), np.zeros((tokens, 1), dtype=np.int32), np.ones((tokens, 1), dtype=np.float32),
+                            lambda e: (inputs.bits_u16(s13), inputs.bits_u16(s2)))
+        assert offn.rel_frobenius(once.cpu().numpy(), want) <= TOL
+        assert torch.equal(out, once + once)
+    finally:
+        pool.close()
