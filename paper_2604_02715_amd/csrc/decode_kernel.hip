@@ -251,11 +251,11 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(DecodeArgs a) {
 
 }  // namespace
 
-hipError_t launch_decode(const DecodeArgs& args, uint32_t n_workgroups, int waves_per_wg, hipStream_t stream) {
+hipError_t launch_decode(const DecodeArgs& args, uint32_t n_workgroups, int waves_per_wg, hipStream_t stream, hipEvent_t done) {
     switch (waves_per_wg) {
-        case 4: hipLaunchKernelGGL(decode_kernel<4>, dim3(n_workgroups), dim3(256), 0, stream, args); break;
-        case 8: hipLaunchKernelGGL(decode_kernel<8>, dim3(n_workgroups), dim3(512), 0, stream, args); break;
-        case 16: hipLaunchKernelGGL(decode_kernel<16>, dim3(n_workgroups), dim3(1024), 0, stream, args); break;
+        case 4: launch_done(decode_kernel<4>, dim3(n_workgroups), dim3(256), 0, stream, done, args); break;
+        case 8: launch_done(decode_kernel<8>, dim3(n_workgroups), dim3(512), 0, stream, done, args); break;
+        case 16: launch_done(decode_kernel<16>, dim3(n_workgroups), dim3(1024), 0, stream, done, args); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -285,7 +285,7 @@ __global__ void apply_updates_inline_kernel(InlineUpdates u) {
 }
 }  // namespace
 
-hipError_t launch_apply_updates_inline(int32_t* page_table, const int32_t* host_upd, uint32_t n, hipStream_t stream) {
+hipError_t launch_apply_updates_inline(int32_t* page_table, const int32_t* host_upd, uint32_t n, hipStream_t stream, hipEvent_t done) {
     if (n == 0) return hipSuccess;
     if (n > kInlineUpdates) return hipErrorInvalidValue;
     InlineUpdates u;
@@ -293,14 +293,13 @@ hipError_t launch_apply_updates_inline(int32_t* page_table, const int32_t* host_
     u.n = n;
     u.pad = 0;
     std::memcpy(u.upd, host_upd, size_t(n) * 8);
-    hipLaunchKernelGGL(apply_updates_inline_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, u);
+    launch_done(apply_updates_inline_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, done, u);
     return hipGetLastError();
 }
 
-hipError_t launch_apply_updates(int32_t* page_table, const void* upd, uint32_t n, hipStream_t stream) {
+hipError_t launch_apply_updates(int32_t* page_table, const void* upd, uint32_t n, hipStream_t stream, hipEvent_t done) {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(apply_updates_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, page_table,
-                       static_cast<const int2*>(upd), n);
+    launch_done(apply_updates_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, done, page_table, static_cast<const int2*>(upd), n);
     return hipGetLastError();
 }
 

@@ -1734,7 +1734,7 @@ hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgr
     return hipGetLastError();
 }
 
-hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHook hook, void* user) {
+hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, SpanHook hook, void* user) {
     (void)n_cus;
     if (args.T == 0) return hipSuccess;
     FfnArgs a = args;
@@ -1752,10 +1752,10 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, SpanHo
     }
     mark(1, 0);
     auto launch_combine = [&](dim3 grid) {
-        if (a.K <= 2) hipLaunchKernelGGL(combine_kernel<2>, grid, dim3(256), 0, stream, a);
-        else if (a.K <= 4) hipLaunchKernelGGL(combine_kernel<4>, grid, dim3(256), 0, stream, a);
-        else if (a.K <= 8) hipLaunchKernelGGL(combine_kernel<8>, grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL(combine_kernel<16>, grid, dim3(256), 0, stream, a);
+        if (a.K <= 2) launch_done(combine_kernel<2>, grid, dim3(256), 0, stream, done, a);
+        else if (a.K <= 4) launch_done(combine_kernel<4>, grid, dim3(256), 0, stream, done, a);
+        else if (a.K <= 8) launch_done(combine_kernel<8>, grid, dim3(256), 0, stream, done, a);
+        else launch_done(combine_kernel<16>, grid, dim3(256), 0, stream, done, a);
     };
     auto launch_reduce = [&]() {
         const uint64_t n = uint64_t(a.pairs_cap) * (a.F / 8);

@@ -104,8 +104,7 @@ struct fluxmoe_ctx {
     StageHalf half[2];                      // layer l stages into half l & 1
     hipEvent_t ev_copied[2] = {};           // copies into the half have completed
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;   // fluxmoe_materialize_two_streams
-    hipEvent_t ev_half_done[2] = {};        // last decode that read the half
-    bool half_done_valid[2] = {false, false};
+    int64_t half_reader[2] = {-1, -1};      // layer whose materialize read the half last (its ev_load), -1 = none
     bool copied_valid[2] = {false, false};  // ev_copied[h] has been recorded
     // launch shape of the decode kernel (FLUXMOE_DECODE_WAVES / FLUXMOE_DECODE_BLOCKS_PER_WAVE override)
     int tune_waves = 8;
@@ -322,7 +321,6 @@ int ensure_events(fluxmoe_ctx* c) {
     HIPCHECK(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
     HIPCHECK(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
     for (int i = 0; i < 2; ++i) {
-        HIPCHECK(hipEventCreateWithFlags(&c->ev_half_done[i], hipEventDisableTiming));
         HIPCHECK(hipEventCreateWithFlags(&c->ev_copied[i], hipEventDisableTiming));
     }
     HIPCHECK(hipHostMalloc(reinterpret_cast<void**>(&c->pinned_cmd), size_t(kRing) * c->cmd_bytes,
@@ -339,6 +337,17 @@ int resolve_static_scratch(int dev) {
     if (!ptr) return set_error(FLUXMOE_EHIP, "hipGetSymbolAddress returned a NULL address");
     g_static_scratch[dev] = static_cast<uint8_t*>(ptr);
     return FLUXMOE_OK;
+}
+
+// The event for a launch that is to complete with it, or nullptr where it has to be recorded after the launch instead:
+// under stream capture a recorded event becomes part of the graph's dependencies, an attached one does not.
+hipEvent_t attachable(hipEvent_t ev, hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return st == hipStreamCaptureStatusNone ? ev : nullptr;
 }
 
 hipError_t span_begin(fluxmoe_ctx* c, int kind, hipStream_t s) {
@@ -432,7 +441,6 @@ int fluxmoe_destroy(fluxmoe_ctx* c) {
         for (auto e : c->ev_infer) if (e) (void)hipEventDestroy(e);
         for (auto e : c->ev_rel) if (e) (void)hipEventDestroy(e);
         for (int i = 0; i < kRing; ++i) if (c->ring_ev[i]) (void)hipEventDestroy(c->ring_ev[i]);
-        for (int i = 0; i < 2; ++i) if (c->ev_half_done[i]) (void)hipEventDestroy(c->ev_half_done[i]);
         for (int i = 0; i < 2; ++i) if (c->ev_copied[i]) (void)hipEventDestroy(c->ev_copied[i]);
         if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
         if (c->ev_join) (void)hipEventDestroy(c->ev_join);
@@ -790,7 +798,7 @@ static int stage_host_blocks(fluxmoe_ctx* c, uint32_t layer, const int32_t* ids,
     if (cursor > half_bytes)
         return set_error(FLUXMOE_ENOMEM, "staging half holds %llu bytes, layer %u needs %llu",
                          (unsigned long long)half_bytes, layer, (unsigned long long)cursor);
-    if (c->half_done_valid[h]) HIPCHECK(hipStreamWaitEvent(s, c->ev_half_done[h], 0));
+    if (c->half_reader[h] >= 0) HIPCHECK(hipStreamWaitEvent(s, c->ev_load[c->half_reader[h]], 0));
     // an earlier staging into this half may have been issued on another stream (a prefetch on the copy
     // stream, then a materialize of other experts that restages on its own stream): its copies must
     // have landed before these overwrite the half with a different layout
@@ -947,7 +955,9 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     const uint64_t decode_blocks = uint64_t(cmd->total_blocks[0]) + cmd->total_blocks[1];
     const size_t jobs_bytes[2] = {cmd->n_jobs[0] * sizeof(DecodeJob), cmd->n_jobs[1] * sizeof(DecodeJob)};
     const size_t packed = sizeof(DecodeCmd) + jobs_bytes[0] + jobs_bytes[1] + touched.size() * 8;
-    if (decode_blocks > 0 && packed <= kInlineCmdBytes) {
+    const bool uploaded = !(decode_blocks > 0 && packed <= kInlineCmdBytes);
+    hipEvent_t load_done = attachable(c->ev_load[layer], stream);      // nullptr: recorded at the end
+    if (!uploaded) {
         uint8_t* w = reinterpret_cast<uint8_t*>(args.inline_words);
         std::memcpy(w, cmd, sizeof(DecodeCmd));
         args.jobs_offset[0] = uint32_t(sizeof(DecodeCmd));
@@ -973,8 +983,9 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     const uint64_t total = uint64_t(cmd->total_blocks[0]) + cmd->total_blocks[1];
     if (total == 0) {
         // every listed tensor is an uncompressed host tensor: nothing to decode, only the page table changes
+        load_done = nullptr;
         if (!touched.empty())
-            HIPCHECK(launch_apply_updates(page_table, dcmd + upd_off, uint32_t(touched.size()), stream));
+            HIPCHECK(launch_apply_updates(page_table, dcmd + upd_off, uint32_t(touched.size()), stream, nullptr));
     } else {
     // blocks per workgroup: a few per wavefront, fewer when that would leave CUs without work
     const uint64_t fill = total / (3ull * uint64_t(std::max(c->n_cus, 1)));
@@ -990,12 +1001,14 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
         const uint32_t n2 = wgs_for(cmd->total_blocks[1]);
         a2.wg_split = n2;                       // every workgroup serves the type-2 list
         a2.apply_updates = 0;
-        HIPCHECK(launch_decode(a2, n2, waves_per_wg, stream2));
-        HIPCHECK(hipEventRecord(c->ev_join, stream2));
+        hipEvent_t join = attachable(c->ev_join, stream2);
+        HIPCHECK(launch_decode(a2, n2, waves_per_wg, stream2, join));
+        if (!join) HIPCHECK(hipEventRecord(c->ev_join, stream2));
         args.wg_split = 0;                      // every workgroup serves the type-1 list
         args.apply_updates = 1;
         HIPCHECK(span_begin(c, 0, stream));
-        HIPCHECK(launch_decode(args, wgs_for(cmd->total_blocks[0]), waves_per_wg, stream));
+        load_done = nullptr;                    // the load is done when both launches are
+        HIPCHECK(launch_decode(args, wgs_for(cmd->total_blocks[0]), waves_per_wg, stream, nullptr));
         HIPCHECK(span_end(c, stream));
         HIPCHECK(hipStreamWaitEvent(stream, c->ev_join, 0));
     } else {
@@ -1005,19 +1018,18 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
         args.wg_split = split;
         args.apply_updates = 1;
         HIPCHECK(span_begin(c, 0, stream));
-        HIPCHECK(launch_decode(args, n_wg, waves_per_wg, stream));
+        HIPCHECK(launch_decode(args, n_wg, waves_per_wg, stream, load_done));
         HIPCHECK(span_end(c, stream));
     }
     }
-    HIPCHECK(hipEventRecord(c->ring_ev[slot], stream));
-    c->ring_used[slot] = true;
-    c->ring_next = (slot + 1) % kRing;
-    if (need_host) {
-        HIPCHECK(hipEventRecord(c->ev_half_done[half], stream));
-        c->half_done_valid[half] = true;
+    if (uploaded) {                             // only then does the device read the ring slot
+        HIPCHECK(hipEventRecord(c->ring_ev[slot], stream));
+        c->ring_used[slot] = true;
+        c->ring_next = (slot + 1) % kRing;
     }
-    HIPCHECK(hipEventRecord(c->ev_load[layer], stream));
+    if (!load_done) HIPCHECK(hipEventRecord(c->ev_load[layer], stream));
     c->load_valid[layer] = 1;
+    if (need_host) c->half_reader[half] = layer;
     return FLUXMOE_OK;
 }
 
@@ -1065,17 +1077,18 @@ int fluxmoe_release(fluxmoe_ctx* c, uint32_t layer, const int32_t* expert_ids, u
     // the entries are read by the layer's FFN and written by its materialize, possibly on other streams
     if (c->infer_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[layer], 0));
     if (c->load_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
+    const hipEvent_t done = attachable(c->ev_rel[layer], stream);
     if (m <= kInlineUpdates) {
-        HIPCHECK(launch_apply_updates_inline(page_table, upd, m, stream));     // the pairs travel in the kernel arguments
+        HIPCHECK(launch_apply_updates_inline(page_table, upd, m, stream, done));     // the pairs travel in the kernel arguments
     } else {
         HIPCHECK(hipMemcpyAsync(dcmd, hcmd, size_t(m) * 8, hipMemcpyHostToDevice, stream));
-        HIPCHECK(launch_apply_updates(page_table, dcmd, m, stream));
+        HIPCHECK(launch_apply_updates(page_table, dcmd, m, stream, done));
+        HIPCHECK(hipEventRecord(c->ring_ev[slot], stream));
+        c->ring_used[slot] = true;
+        c->ring_next = (slot + 1) % kRing;
     }
-    HIPCHECK(hipEventRecord(c->ev_rel[layer], stream));
+    if (!done) HIPCHECK(hipEventRecord(c->ev_rel[layer], stream));
     c->rel_valid[layer] = 1;
-    HIPCHECK(hipEventRecord(c->ring_ev[slot], stream));
-    c->ring_used[slot] = true;
-    c->ring_next = (slot + 1) % kRing;
     return FLUXMOE_OK;
 }
 
@@ -1128,8 +1141,9 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
 
     if (c->load_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
     if (c->rel_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
-    HIPCHECK(launch_ffn(a, c->n_cus, stream, c->profiling ? ffn_span_hook : nullptr, c));
-    HIPCHECK(hipEventRecord(c->ev_infer[layer], stream));
+    const hipEvent_t done = attachable(c->ev_infer[layer], stream);
+    HIPCHECK(launch_ffn(a, c->n_cus, stream, done, c->profiling ? ffn_span_hook : nullptr, c));
+    if (!done) HIPCHECK(hipEventRecord(c->ev_infer[layer], stream));
     c->infer_valid[layer] = 1;
     const int64_t lo = int64_t(layer) * c->d.n_experts, hi = lo + c->d.n_experts;
     for (uint32_t s = 0; s < c->d.n_slots; ++s)
@@ -1205,7 +1219,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);
-    HIPCHECK(launch_ffn(a, c->n_cus, stream, c->profiling ? ffn_span_hook : nullptr, c));
+    HIPCHECK(launch_ffn(a, c->n_cus, stream, nullptr, c->profiling ? ffn_span_hook : nullptr, c));
     return FLUXMOE_OK;
 }
 
