@@ -96,6 +96,11 @@ struct fluxmoe_ctx {
     // Alg. 1 state
     std::vector<hipEvent_t> ev_load, ev_infer, ev_rel;   // per layer: last materialize / FFN / release
     std::vector<uint8_t> load_valid, infer_valid, rel_valid;
+    // Order in which the calls behind those events were made (0 = under stream capture or never).  A later call of a layer
+    // has waited for the earlier event, so its own event covers both and one wait is enough: a wait for another stream
+    // holds the queue for about 10 us even when the event completed long ago.
+    std::vector<uint64_t> load_seq, infer_seq, rel_seq;
+    uint64_t seq = 0;
     std::vector<int32_t> slot_last_reader; // layer whose FFN last read the slot, or -1
     bool events_ready = false;
     // host-tier staging
@@ -408,6 +413,9 @@ int fluxmoe_create(const fluxmoe_desc* desc, fluxmoe_ctx** out_ctx) {
     c->load_valid.assign(d.n_layers, 0);
     c->infer_valid.assign(d.n_layers, 0);
     c->rel_valid.assign(d.n_layers, 0);
+    c->load_seq.assign(d.n_layers, 0);
+    c->infer_seq.assign(d.n_layers, 0);
+    c->rel_seq.assign(d.n_layers, 0);
     compute_layout(c);
     if (const char* v = std::getenv("FLUXMOE_DECODE_WAVES")) {
         const int w = std::atoi(v);
@@ -940,8 +948,11 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     cmd->n_pt_updates = uint32_t(touched.size());
 
     // enqueue: WAR waits, host-tier copies, command upload, decode, events
-    for (int32_t lr : wait_layers) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[lr], 0));
-    // a release of this layer issued on another stream writes the same page-table row
+    // (a release of this layer, which writes the same page-table row, may have been issued on another stream; one made
+    // after the layer's FFN waited for it)
+    const bool rel_covers_infer = c->rel_valid[layer] && c->rel_seq[layer] > c->infer_seq[layer] && c->infer_seq[layer];
+    for (int32_t lr : wait_layers)
+        if (!(uint32_t(lr) == layer && rel_covers_infer)) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[lr], 0));
     if (c->rel_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     if (wait_copy) HIPCHECK(hipStreamWaitEvent(stream, c->ev_copied[half], 0));
 
@@ -957,6 +968,7 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     const size_t packed = sizeof(DecodeCmd) + jobs_bytes[0] + jobs_bytes[1] + touched.size() * 8;
     const bool uploaded = !(decode_blocks > 0 && packed <= kInlineCmdBytes);
     hipEvent_t load_done = attachable(c->ev_load[layer], stream);      // nullptr: recorded at the end
+    const bool capturing = !load_done;
     if (!uploaded) {
         uint8_t* w = reinterpret_cast<uint8_t*>(args.inline_words);
         std::memcpy(w, cmd, sizeof(DecodeCmd));
@@ -1029,6 +1041,7 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     }
     if (!load_done) HIPCHECK(hipEventRecord(c->ev_load[layer], stream));
     c->load_valid[layer] = 1;
+    c->load_seq[layer] = capturing ? 0 : ++c->seq;
     if (need_host) c->half_reader[half] = layer;
     return FLUXMOE_OK;
 }
@@ -1076,7 +1089,8 @@ int fluxmoe_release(fluxmoe_ctx* c, uint32_t layer, const int32_t* expert_ids, u
     if (m == 0) return FLUXMOE_OK;
     // the entries are read by the layer's FFN and written by its materialize, possibly on other streams
     if (c->infer_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[layer], 0));
-    if (c->load_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
+    const bool infer_covers_load = c->infer_valid[layer] && c->infer_seq[layer] > c->load_seq[layer] && c->load_seq[layer];
+    if (c->load_valid[layer] && !infer_covers_load) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
     const hipEvent_t done = attachable(c->ev_rel[layer], stream);
     if (m <= kInlineUpdates) {
         HIPCHECK(launch_apply_updates_inline(page_table, upd, m, stream, done));     // the pairs travel in the kernel arguments
@@ -1089,6 +1103,7 @@ int fluxmoe_release(fluxmoe_ctx* c, uint32_t layer, const int32_t* expert_ids, u
     }
     if (!done) HIPCHECK(hipEventRecord(c->ev_rel[layer], stream));
     c->rel_valid[layer] = 1;
+    c->rel_seq[layer] = done ? ++c->seq : 0;
     return FLUXMOE_OK;
 }
 
@@ -1139,12 +1154,15 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);
 
-    if (c->load_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
-    if (c->rel_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
+    const bool load_covers_rel = c->load_seq[layer] > c->rel_seq[layer] && c->rel_seq[layer];
+    const bool rel_covers_load = c->rel_seq[layer] > c->load_seq[layer] && c->load_seq[layer];
+    if (c->load_valid[layer] && !rel_covers_load) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
+    if (c->rel_valid[layer] && !load_covers_rel) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     const hipEvent_t done = attachable(c->ev_infer[layer], stream);
     HIPCHECK(launch_ffn(a, c->n_cus, stream, done, c->profiling ? ffn_span_hook : nullptr, c));
     if (!done) HIPCHECK(hipEventRecord(c->ev_infer[layer], stream));
     c->infer_valid[layer] = 1;
+    c->infer_seq[layer] = done ? ++c->seq : 0;
     const int64_t lo = int64_t(layer) * c->d.n_experts, hi = lo + c->d.n_experts;
     for (uint32_t s = 0; s < c->d.n_slots; ++s)
         if (c->slot_owner[s] >= lo && c->slot_owner[s] < hi) c->slot_last_reader[s] = int32_t(layer);
