@@ -210,6 +210,8 @@ int fluxmoe_prefetch_host(fluxmoe_ctx* ctx, uint32_t layer, const int32_t* exper
  * i: slot dst_slots[i] holds exactly the original bytes of both tensors of expert_ids[i],
  * page_table[layer][expert_ids[i]] = dst_slots[i], the entry of whichever (layer, expert)
  * owned that slot before is -1; nothing else changes.  n = 0 is valid and enqueues nothing.
+ * If the layer's last fluxmoe_expert_ffn skipped unmapped experts (a wave) and has not been released since, the call
+ * also waits until that FFN has read the page table: the next wave may be loaded into other slots while it runs.
  */
 int fluxmoe_materialize(fluxmoe_ctx* ctx, uint32_t layer, const int32_t* expert_ids,
                         uint32_t n, int32_t* page_table, const int32_t* dst_slots,

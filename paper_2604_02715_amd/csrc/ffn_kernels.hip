@@ -1734,7 +1734,7 @@ hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgr
     return hipGetLastError();
 }
 
-hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, SpanHook hook, void* user) {
+hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, SpanHook hook, void* user) {
     (void)n_cus;
     if (args.T == 0) return hipSuccess;
     FfnArgs a = args;
@@ -1746,9 +1746,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
         hipLaunchKernelGGL(route_sort_kernel<true>, dim3(1), dim3(1024), sh, stream, a);
-        hipLaunchKernelGGL(route_scatter_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
+        launch_done(route_scatter_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, routed, a);
     } else {
-        hipLaunchKernelGGL(route_sort_kernel<false>, dim3(1), dim3(1024), sh, stream, a);
+        launch_done(route_sort_kernel<false>, dim3(1), dim3(1024), sh, stream, routed, a);
     }
     mark(1, 0);
     auto launch_combine = [&](dim3 grid) {

@@ -94,14 +94,22 @@ struct fluxmoe_ctx {
     std::vector<int32_t> pt;
     std::vector<int64_t> slot_owner;      // layer * E + expert, or -1
     // Alg. 1 state
-    std::vector<hipEvent_t> ev_load, ev_infer, ev_rel;   // per layer: last materialize / FFN / release
-    std::vector<uint8_t> load_valid, infer_valid, rel_valid;
+    std::vector<hipEvent_t> ev_load, ev_rel;   // per layer: last materialize / release
+    // Per layer: the last two FFN calls (call g records event g & 1), so that a materialize into slots the one before the
+    // last read does not wait for the last; ev_routed: the last wave-mode call has read the page table.
+    std::vector<std::array<hipEvent_t, 2>> ev_infer;
+    std::vector<hipEvent_t> ev_routed;
+    std::vector<uint64_t> infer_gen;           // FFN calls of the layer so far; 0 = none
+    std::vector<uint64_t> routed_gen;          // the call behind ev_routed, 0 = none
+    std::vector<uint8_t> load_valid, rel_valid;
     // Order in which the calls behind those events were made (0 = under stream capture or never).  A later call of a layer
     // has waited for the earlier event, so its own event covers both and one wait is enough: a wait for another stream
     // holds the queue for about 10 us even when the event completed long ago.
-    std::vector<uint64_t> load_seq, infer_seq, rel_seq;
+    std::vector<uint64_t> load_seq, rel_seq;
+    std::vector<std::array<uint64_t, 2>> infer_seq;
     uint64_t seq = 0;
     std::vector<int32_t> slot_last_reader; // layer whose FFN last read the slot, or -1
+    std::vector<uint64_t> slot_reader_gen; // which of that layer's FFN calls it was
     bool events_ready = false;
     // host-tier staging
     uint8_t* staging = nullptr;
@@ -314,11 +322,13 @@ int ensure_events(fluxmoe_ctx* c) {
     if (c->events_ready) return FLUXMOE_OK;
     const uint32_t N = c->d.n_layers;
     c->ev_load.assign(N, nullptr);
-    c->ev_infer.assign(N, nullptr);
+    c->ev_infer.assign(N, {nullptr, nullptr});
+    c->ev_routed.assign(N, nullptr);
     c->ev_rel.assign(N, nullptr);
     for (uint32_t i = 0; i < N; ++i) {
         HIPCHECK(hipEventCreateWithFlags(&c->ev_load[i], hipEventDisableTiming));
-        HIPCHECK(hipEventCreateWithFlags(&c->ev_infer[i], hipEventDisableTiming));
+        for (hipEvent_t& e : c->ev_infer[i]) HIPCHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        HIPCHECK(hipEventCreateWithFlags(&c->ev_routed[i], hipEventDisableTiming));
         HIPCHECK(hipEventCreateWithFlags(&c->ev_rel[i], hipEventDisableTiming));
     }
     for (int i = 0; i < kRing; ++i)
@@ -410,11 +420,13 @@ int fluxmoe_create(const fluxmoe_desc* desc, fluxmoe_ctx** out_ctx) {
     c->pt.assign(size_t(d.n_layers) * d.n_experts, -1);
     c->slot_owner.assign(d.n_slots, -1);
     c->slot_last_reader.assign(d.n_slots, -1);
+    c->slot_reader_gen.assign(d.n_slots, 0);
     c->load_valid.assign(d.n_layers, 0);
-    c->infer_valid.assign(d.n_layers, 0);
+    c->infer_gen.assign(d.n_layers, 0);
+    c->routed_gen.assign(d.n_layers, 0);
     c->rel_valid.assign(d.n_layers, 0);
     c->load_seq.assign(d.n_layers, 0);
-    c->infer_seq.assign(d.n_layers, 0);
+    c->infer_seq.assign(d.n_layers, {0, 0});
     c->rel_seq.assign(d.n_layers, 0);
     compute_layout(c);
     if (const char* v = std::getenv("FLUXMOE_DECODE_WAVES")) {
@@ -446,7 +458,8 @@ int fluxmoe_destroy(fluxmoe_ctx* c) {
     if (!c) return FLUXMOE_OK;
     if (c->events_ready) {
         for (auto e : c->ev_load) if (e) (void)hipEventDestroy(e);
-        for (auto e : c->ev_infer) if (e) (void)hipEventDestroy(e);
+        for (auto& pair : c->ev_infer) for (auto e : pair) if (e) (void)hipEventDestroy(e);
+        for (auto e : c->ev_routed) if (e) (void)hipEventDestroy(e);
         for (auto e : c->ev_rel) if (e) (void)hipEventDestroy(e);
         for (int i = 0; i < kRing; ++i) if (c->ring_ev[i]) (void)hipEventDestroy(c->ring_ev[i]);
         for (int i = 0; i < 2; ++i) if (c->ev_copied[i]) (void)hipEventDestroy(c->ev_copied[i]);
@@ -918,7 +931,7 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
 
     // page-table transitions on the host mirror; the touched entries go to the device
     std::vector<int64_t> touched;
-    std::vector<int32_t> wait_layers;
+    std::vector<std::pair<int32_t, uint64_t>> wait_reads;      // (layer, FFN call) that read a target slot last
     for (uint32_t i = 0; i < n; ++i) {
         const int64_t key = int64_t(layer) * E + expert_ids[i];
         const int32_t s = dst_slots[i];
@@ -933,9 +946,12 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
         c->slot_owner[s] = key;
         touched.push_back(key);
         const int32_t lr = c->slot_last_reader[s];
-        if (lr >= 0 && c->infer_valid[lr] &&
-            std::find(wait_layers.begin(), wait_layers.end(), lr) == wait_layers.end())
-            wait_layers.push_back(lr);
+        if (lr >= 0) {
+            // a layer's FFN calls run in order: one older than the last two is covered by the older of those
+            const uint64_t last = c->infer_gen[lr];
+            const std::pair<int32_t, uint64_t> read{lr, c->slot_reader_gen[s] >= last ? last : last - 1};
+            if (std::find(wait_reads.begin(), wait_reads.end(), read) == wait_reads.end()) wait_reads.push_back(read);
+        }
         c->slot_last_reader[s] = -1;
     }
     std::sort(touched.begin(), touched.end());
@@ -950,9 +966,15 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     // enqueue: WAR waits, host-tier copies, command upload, decode, events
     // (a release of this layer, which writes the same page-table row, may have been issued on another stream; one made
     // after the layer's FFN waited for it)
-    const bool rel_covers_infer = c->rel_valid[layer] && c->rel_seq[layer] > c->infer_seq[layer] && c->infer_seq[layer];
-    for (int32_t lr : wait_layers)
-        if (!(uint32_t(lr) == layer && rel_covers_infer)) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[lr], 0));
+    auto rel_covers = [&](uint64_t g) {
+        const uint64_t at = c->infer_seq[layer][g & 1];
+        return c->rel_valid[layer] && at && c->rel_seq[layer] > at;
+    };
+    for (const auto& [lr, g] : wait_reads)
+        if (!(uint32_t(lr) == layer && rel_covers(g))) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[lr][g & 1], 0));
+    // a wave of this layer still to be released: its FFN must have read the page table before this call's entries appear there
+    const uint64_t last_ffn = c->infer_gen[layer];
+    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn)) HIPCHECK(hipStreamWaitEvent(stream, c->ev_routed[layer], 0));
     if (c->rel_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     if (wait_copy) HIPCHECK(hipStreamWaitEvent(stream, c->ev_copied[half], 0));
 
@@ -1088,8 +1110,9 @@ int fluxmoe_release(fluxmoe_ctx* c, uint32_t layer, const int32_t* expert_ids, u
     }
     if (m == 0) return FLUXMOE_OK;
     // the entries are read by the layer's FFN and written by its materialize, possibly on other streams
-    if (c->infer_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[layer], 0));
-    const bool infer_covers_load = c->infer_valid[layer] && c->infer_seq[layer] > c->load_seq[layer] && c->load_seq[layer];
+    const uint64_t last_ffn = c->infer_gen[layer];
+    if (last_ffn) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[layer][last_ffn & 1], 0));
+    const bool infer_covers_load = last_ffn && c->load_seq[layer] && c->infer_seq[layer][last_ffn & 1] > c->load_seq[layer];
     if (c->load_valid[layer] && !infer_covers_load) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
     const hipEvent_t done = attachable(c->ev_rel[layer], stream);
     if (m <= kInlineUpdates) {
@@ -1158,14 +1181,18 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     const bool rel_covers_load = c->rel_seq[layer] > c->load_seq[layer] && c->load_seq[layer];
     if (c->load_valid[layer] && !rel_covers_load) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
     if (c->rel_valid[layer] && !load_covers_rel) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
-    const hipEvent_t done = attachable(c->ev_infer[layer], stream);
-    HIPCHECK(launch_ffn(a, c->n_cus, stream, done, c->profiling ? ffn_span_hook : nullptr, c));
-    if (!done) HIPCHECK(hipEventRecord(c->ev_infer[layer], stream));
-    c->infer_valid[layer] = 1;
-    c->infer_seq[layer] = done ? ++c->seq : 0;
+    const uint64_t gen = c->infer_gen[layer] + 1;
+    const hipEvent_t ev = c->ev_infer[layer][gen & 1], done = attachable(ev, stream);
+    // a call that skips unmapped experts is a wave: the next wave's materialize, into other slots, may follow before the release
+    const hipEvent_t routed = done && (flags & FLUXMOE_FFN_SKIP_UNMAPPED) ? c->ev_routed[layer] : nullptr;
+    HIPCHECK(launch_ffn(a, c->n_cus, stream, done, routed, c->profiling ? ffn_span_hook : nullptr, c));
+    if (!done) HIPCHECK(hipEventRecord(ev, stream));
+    c->infer_gen[layer] = gen;
+    c->infer_seq[layer][gen & 1] = done ? ++c->seq : 0;
+    if (routed) c->routed_gen[layer] = gen;
     const int64_t lo = int64_t(layer) * c->d.n_experts, hi = lo + c->d.n_experts;
     for (uint32_t s = 0; s < c->d.n_slots; ++s)
-        if (c->slot_owner[s] >= lo && c->slot_owner[s] < hi) c->slot_last_reader[s] = int32_t(layer);
+        if (c->slot_owner[s] >= lo && c->slot_owner[s] < hi) { c->slot_last_reader[s] = int32_t(layer); c->slot_reader_gen[s] = gen; }
     return FLUXMOE_OK;
 }
 
@@ -1237,7 +1264,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);
-    HIPCHECK(launch_ffn(a, c->n_cus, stream, nullptr, c->profiling ? ffn_span_hook : nullptr, c));
+    HIPCHECK(launch_ffn(a, c->n_cus, stream, nullptr, nullptr, c->profiling ? ffn_span_hook : nullptr, c));
     return FLUXMOE_OK;
 }
 
