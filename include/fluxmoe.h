@@ -444,7 +444,8 @@ int fluxmoe_device_errors(fluxmoe_ctx* ctx, uint32_t* out_flags);
 /*
  * The launch plan fluxmoe_expert_ffn takes for T tokens with K experts each (host only; for tests
  * and reports): rows per tile of the grouped products (16..128 = weight-streaming kernels, 256 =
- * LDS-tiled MFMA kernels) and the number of K splits of the second product.  The plan depends on the
+ * LDS-tiled MFMA kernels, which also take 128-row tiles where few workgroups would run) and the number
+ * of K splits of the second product.  The plan depends on the
  * shapes, on T * K / n_experts and on the CU count of the device (256 until a bind call has
  * queried it).
  */

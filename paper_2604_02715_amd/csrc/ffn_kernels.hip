@@ -1214,22 +1214,30 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // launch has one workgroup per tile number and the code for the upcoming tile falls away.
 // MODE 1: h = SwiGLU(X W1, X W3).  MODE 2: y = h W2, K split ksplit ways.  MODE 3: the first product with K split
 // ksplit1 ways, FP32 partial sums of gate and up instead of h (swiglu_reduce_kernel adds them up).
-template <int MODE, int WAVES, bool WALK>
-__global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
+// TILE: rows and columns of a workgroup's tile.  256: one workgroup per CU (160 KiB of LDS).  128, with WAVES = 4 as 2 x 2
+// of 64 x 64: two per CU, a quarter of the work per tile, for products whose 256 x 256 tiles leave most CUs without one.
+template <int MODE, int WAVES, bool WALK, int TILE>
+__global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kernel(FfnArgs a) {
     constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
     static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
     // WAVES = 8: wavefronts 4 (rows) x 2 (columns), 64 x 128 each, two per SIMD.  WAVES = 4: 2 x 2,
     // 128 x 128 each (256 accumulator registers), one per SIMD: a third less LDS read traffic per MFMA.
-    constexpr int kRowTiles = WAVES == 8 ? 2 : 4;            // 32-row MFMA tiles per wavefront
+    constexpr int kRowTiles = WAVES == 8 || TILE == 128 ? 2 : 4;   // 32-row MFMA tiles per wavefront
+    constexpr int kColTiles = TILE == 256 ? 4 : 2;           // 32-column MFMA tiles per wavefront
     constexpr int kWaveRows = 32 * kRowTiles;
-    constexpr int kDma = 32 / WAVES;                         // 1 KiB loads per wavefront, operand and step
-    constexpr int kMfma = 4 * kRowTiles;                     // MFMAs per sub-step
-    constexpr int kFrag = kRowTiles + 8;                     // fragment reads per sub-step
+    constexpr int kStageBytes = TILE * 128;                  // one operand, one step: TILE rows (columns) x 64 k
+    constexpr int kRowB = TILE * 2;                          // bytes of a k row of B
+    constexpr int kDma = kStageBytes / 1024 / WAVES;         // 1 KiB loads per wavefront, operand and step
+    constexpr int kMfma = kColTiles * kRowTiles;             // MFMAs per sub-step
+    constexpr int kDmaEvery = kMfma / kDma;                  // MFMAs between two loads of a sub-step
+    constexpr int kFrag = kRowTiles + 2 * kColTiles;         // fragment reads per sub-step
+    constexpr uint32_t kHalfTile = TILE / 2;                 // gate columns of a tile of the first product, as many up columns
     static_assert(WAVES == 8 || WAVES == 4, "wavefront layouts");
+    static_assert(TILE == 256 || (TILE == 128 && WAVES == 4 && !WALK), "tile sizes");
     extern __shared__ __align__(16) uint16_t lds[];
     const uint32_t K = kFirst ? a.H : a.F;
     const uint32_t N = kFirst ? a.F : a.H;
-    const uint32_t ncols_tile = kFirst ? 128u : 256u;
+    const uint32_t ncols_tile = kFirst ? kHalfTile : uint32_t(TILE);
     const uint32_t n_ct = (N + ncols_tile - 1) / ncols_tile;
     const uint32_t n_rt = uint32_t(a.n_tiles[0]);
     // Super-tile of this launch: 32 tiles (one per CU of an XCD) as sm rows x sn columns, sn a power of two
@@ -1294,7 +1302,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         asm volatile("" : "+v"(x));
         return x & 63;
     };
-    constexpr int kStageBytes = 32768;
     uint8_t* const lds_b8 = reinterpret_cast<uint8_t*>(lds);
     const size_t mat = size_t(a.H) * a.F;
     const uint32_t n_steps_all = K / kTK;
@@ -1352,12 +1359,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         }
 #pragma unroll
         for (int i = 0; i < kDma; ++i) {
-            const int k_lds = 2 * (wave * kDma + i) + (lane >> 5);                 // k row of the B tile
-            const int pp = lane & 31;                                           // physical 16-byte piece in the row
+            const int k_lds = (1024 / kRowB) * (wave * kDma + i) + lane / (kRowB / 16);   // k row of the B tile
+            const int pp = lane & (kRowB / 16 - 1);                             // physical 16-byte piece in the row
             const int unit = (pp >> 2) ^ (k_lds & 3);                           // logical unit of 32 columns
-            const uint32_t c = 32u * unit + 8u * (pp & 3);                      // column inside the 256-column tile
+            const uint32_t c = 32u * unit + 8u * (pp & 3);                      // column inside the tile
             uint32_t elems;
-            if (kFirst) elems = (c >= 128 ? uint32_t(mat) : 0u) + min(s.n_base + (c & 127u), N - 8);
+            if (kFirst) elems = (c >= kHalfTile ? uint32_t(mat) : 0u) + min(s.n_base + (c & (kHalfTile - 1u)), N - 8);
             else elems = min(s.n_base + c, N - 8);
             s.b_off[i] = 2u * (elems + uint32_t(k_lds) * N);
         }
@@ -1397,8 +1404,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
     // ---- fragment addresses (bytes from the start of stage 0 of the operand's region); the k loop moves
     // them from stage to stage, so every tile starts from these values again
     int a_addr[kRowTiles][4];
-    int b_addr[4];
-    f32x16 acc[kRowTiles][4];
+    int b_addr[kColTiles];
+    f32x16 acc[kRowTiles][kColTiles];
     int b_next_delta = kStageBytes;
     int a_own = 0, b_own = 0;                                // byte offsets of the current step's stages
     auto begin_tile = [&]() __attribute__((always_inline)) {
@@ -1413,14 +1420,16 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         }
         // B fragment j of sub-step ks, read t: row 16 ks + 8 h + 4 t + e, unit u(j) ^ e, bytes 32 nh + 8 g
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int unit = kFirst ? ((((2 * wn + (j & 1)) ^ e)) + 4 * (j >> 1)) : (4 * wn + (j ^ e));
-            b_addr[j] = 2 * kStageBytes + (8 * h + e) * 512 + 64 * unit + 32 * nh + 8 * g;
+        for (int j = 0; j < kColTiles; ++j) {
+            // the wavefront's columns as units: gate and up units of the same h columns, or kColTiles in a row
+            const int unit = TILE == 128 ? (kFirst ? wn + 2 * j : 2 * wn + j) ^ e
+                                         : (kFirst ? ((((2 * wn + (j & 1)) ^ e)) + 4 * (j >> 1)) : (4 * wn + (j ^ e)));
+            b_addr[j] = 2 * kStageBytes + (8 * h + e) * kRowB + 64 * unit + 32 * nh + 8 * g;
         }
 #pragma unroll
         for (int i = 0; i < kRowTiles; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < kColTiles; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
         b_next_delta = kStageBytes;
@@ -1429,7 +1438,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
     };
 
     bf16x8 fa[2][kRowTiles];
-    i16x4 fb_lo[2][4], fb_hi[2][4];
+    i16x4 fb_lo[2][kColTiles], fb_hi[2][kColTiles];
     // item n of the kFrag fragment reads of sub-step ks from `stage` into register set `set`: first the
     // A tiles, then the two halves (k 0..3 and 4..7 of the lane's 8) of the four B fragments
     // OTHER: read from the next step's stage instead of the one the address registers point at
@@ -1440,13 +1449,13 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         } else {
             const int j = (n - kRowTiles) >> 1, tt = (n - kRowTiles) & 1;
             const i16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (lds_i16x4*)(lds_b8 + ((b_addr[j] + (other ? b_next_delta : 0)) + ks * 8192 + tt * 2048)));
+                (lds_i16x4*)(lds_b8 + ((b_addr[j] + (other ? b_next_delta : 0)) + ks * 16 * kRowB + tt * 4 * kRowB)));
             if (tt == 0) fb_lo[set][j] = v; else fb_hi[set][j] = v;
         }
     };
     typedef short i16x8 __attribute__((ext_vector_type(8)));
     auto mfma_item = [&](int set, int n) __attribute__((always_inline)) {
-        const int i = n >> 2, j = n & 3;
+        const int i = n / kColTiles, j = n % kColTiles;
         const i16x8 full = __builtin_shufflevector(fb_lo[set][j], fb_hi[set][j], 0, 1, 2, 3, 4, 5, 6, 7);
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i], __builtin_bit_cast(bf16x8, full), acc[i][j], 0, 0, 0);
     };
@@ -1470,8 +1479,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
             for (int n = 0; n < kMfma; ++n) {
                 if (ACT.value) mfma_item(set, n);
                 if (READ.value && ACT.value && n < kFrag && !(FLUXMOE_D2L_PROBE & 1)) lfrag_item(other, next_ks, set ^ 1, n);
-                if (DMA_B.value && (n & 1) && !(FLUXMOE_D2L_PROBE & 4)) dma_b(cur, k0 + 2 * kTK, b_plus2, n >> 1);
-                if (DMA_A.value && (n & 1) && !(FLUXMOE_D2L_PROBE & 2)) dma_a(cur, k0 + 2 * kTK, a_own, n >> 1);
+                if (DMA_B.value && n % kDmaEvery == kDmaEvery - 1 && !(FLUXMOE_D2L_PROBE & 4)) dma_b(cur, k0 + 2 * kTK, b_plus2, n / kDmaEvery);
+                if (DMA_A.value && n % kDmaEvery == kDmaEvery - 1 && !(FLUXMOE_D2L_PROBE & 2)) dma_a(cur, k0 + 2 * kTK, a_own, n / kDmaEvery);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (READ.value && ACT.value && !(FLUXMOE_D2L_PROBE & 1)) {
@@ -1498,7 +1507,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) a_addr[i][ks] ^= kStageBytes;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b_addr[j] += b_next_delta;
+        for (int j = 0; j < kColTiles; ++j) b_addr[j] += b_next_delta;
         a_own ^= kStageBytes;
         b_own = b_own == 2 * kStageBytes ? 0 : b_own + kStageBytes;
         b_next_delta = b_own == 2 * kStageBytes ? -2 * kStageBytes : kStageBytes;
@@ -1519,7 +1528,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
         // v_perm_b32(other, own, sel): selector bytes 0..3 pick from own, 4..7 from other
         const uint32_t pair_sel = (q & 1) ? 0x03020706u : 0x05040100u;
         // one 64-bit address per stored row; the two column groups of a row lie 64 bytes apart
-        const uint32_t col0 = c.n_base + 64u * wn + (q & ~1);
+        const uint32_t col0 = c.n_base + (TILE / 4u) * wn + (q & ~1);
         uint16_t* const hlane = a.hbuf + size_t(c.row0) * a.F + col0;
 #pragma unroll
         for (int i = 0; i < kRowTiles; ++i)
@@ -1528,12 +1537,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
                 const int32_t row = wm * kWaveRows + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3) + (q & 1);
                 uint16_t* const hrow = hlane + size_t(uint32_t(row)) * a.F;
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < kColTiles / 2; ++j) {
                     // own = (row r, row r + 1) of this lane's column; the neighbouring lane's pair comes by DPP
                     // (quad_perm 1,0,3,2); an even lane keeps both lanes' row-r values, an odd lane both
                     // lanes' row-(r + 1) values, lower column first: one byte permute with a per-lane selector
-                    const uint32_t own = pack_bf16_rne(swiglu(acc[i][j][r], acc[i][j + 2][r]),
-                                                       swiglu(acc[i][j][r + 1], acc[i][j + 2][r + 1]));
+                    const uint32_t own = pack_bf16_rne(swiglu(acc[i][j][r], acc[i][j + kColTiles / 2][r]),
+                                                       swiglu(acc[i][j][r + 1], acc[i][j + kColTiles / 2][r + 1]));
                     const uint32_t other = uint32_t(__builtin_amdgcn_update_dpp(0, int(own), 0xB1, 0xF, 0xF, true));
                     const uint32_t packed = __builtin_amdgcn_perm(other, own, pair_sel);
                     if (row < c.rows && col0 + 32u * j < N)
@@ -1542,7 +1551,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
             }
     } else if (MODE == 3) {
         // partial sums: row r of split s at [s][r][gate | up][F]
-        const uint32_t col0 = c.n_base + 64u * wn + q;
+        constexpr int kGate = kColTiles / 2;                 // column tiles of each matrix
+        const uint32_t col0 = c.n_base + (TILE / 4u) * wn + q;
         float* const plane = a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * 2 * a.F + col0;
 #pragma unroll
         for (int i = 0; i < kRowTiles; ++i)
@@ -1552,14 +1562,14 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
                 if (row >= c.rows) continue;
                 float* const prow = plane + size_t(uint32_t(row)) * 2 * a.F;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (col0 + 32u * (j & 1) >= N) continue;
-                    prow[(j >> 1) * a.F + 32 * (j & 1)] = acc[i][j][r];
+                for (int j = 0; j < kColTiles; ++j) {
+                    if (col0 + 32u * (j % kGate) >= N) continue;
+                    prow[(j / kGate) * a.F + 32 * (j % kGate)] = acc[i][j][r];
                 }
             }
     } else {
         // one 64-bit address per stored row; the four column groups of a row lie 128 bytes apart
-        const uint32_t col0 = c.n_base + 128u * wn + q;
+        const uint32_t col0 = c.n_base + (TILE / 2u) * wn + q;
         float* const ylane = a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
 #pragma unroll
         for (int i = 0; i < kRowTiles; ++i)
@@ -1569,7 +1579,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_d2l_kernel(FfnArgs a) {
                 if (row >= c.rows) continue;
                 float* const yrow = ylane + size_t(uint32_t(row)) * a.H;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < kColTiles; ++j) {
                     if (col0 + 32u * j >= N) continue;
                     yrow[32 * j] = acc[i][j][r];
                 }
@@ -1766,13 +1776,15 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const uint32_t strips2 = (a.H + kStrip - 1) / kStrip;
     const dim3 g1((strips1 + 1) / 2, a.tiles_cap, a.ksplit1);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
-    if (a.m_tile == 256) {
+    if (a.tiled) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
         const bool four = a.tiled_waves == 4;
+        const bool small = a.m_tile == 128;                         // LDS-direct loads, tiles of 128 x 128
         const bool d2l4 = a.tiled_waves == 1;                       // LDS-direct loads, four wavefronts of 128 x 128
         const bool d2l = a.tiled_waves == 2 || d2l4;
         if (!d2l && a.ksplit != 1) return hipErrorInvalidValue;     // only the LDS-direct kernels split K
-        if (a.tiled_waves != 2 && a.ksplit1 != 1) return hipErrorInvalidValue;
+        if (a.tiled_waves != 2 && (a.ksplit1 != 1 || small)) return hipErrorInvalidValue;
+        if (!small && a.m_tile != 256) return hipErrorInvalidValue;
         if (a.ksplit == 0 || a.ksplit > a.F / kTK) return hipErrorInvalidValue;
         static bool attr_set = false;
         if (!attr_set) {
@@ -1788,19 +1800,24 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tiled4_kernel<2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
             if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 8, false>),
+            for (const void* f : {reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 4, false, 128>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 4, false, 128>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 4, false, 128>)}) {
+                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 81920);
+                if (e != hipSuccess) return e;
+            }
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 8, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 4, false>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 4, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 4, false>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 4, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
             attr_set = true;
@@ -1831,7 +1848,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             }
             a.tiled_sn_log2 = best_log2;
             const uint32_t sm = 32u >> best_log2;
-            const uint64_t per_super_row = 256ull * sm;
+            const uint64_t per_super_row = uint64_t(a.m_tile) * sm;
             a.tiled_group = !grouped ? 1u : uint32_t(std::min<uint64_t>(8, std::max<uint64_t>(1,
                 args.tiled_group ? args.tiled_group : (avg_rows + per_super_row / 2) / per_super_row)));
             const uint32_t n_sm = ((a.tiles_cap + sm - 1) / sm + a.tiled_group - 1) / a.tiled_group * a.tiled_group;
@@ -1853,16 +1870,22 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             const uint32_t cap = a.tiled_persist * 256u;
             return (walk && a.tiled_persist && all.x > cap) ? dim3(cap, 1, 1) : all;
         };
-        if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false>), g, dim3(256), 163840, stream, a); }
-        else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<3, 8, false>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((gemm_d2l_kernel<1, 8, true>), g, dim3(512), 163840, stream, a); }
+        if (small) {
+            const dim3 g = d2l_grid(d2l_all((a.F + 63) / 64, a.ksplit1, false, false), false);
+            if (a.ksplit1 > 1) hipLaunchKernelGGL((gemm_d2l_kernel<3, 4, false, 128>), g, dim3(256), 81920, stream, a);
+            else hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 128>), g, dim3(256), 81920, stream, a);
+        }
+        else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 256>), g, dim3(256), 163840, stream, a); }
+        else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<3, 8, false, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((gemm_d2l_kernel<1, 8, true, 256>), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<1>, grid_for((a.F + 127) / 128), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<1>, grid_for((a.F + 127) / 128), dim3(512), lds_bytes, stream, a);
         launch_reduce();
         mark(2, 0);
         mark(3, 1);
-        if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false>), g, dim3(256), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 8, false>), g, dim3(512), 163840, stream, a); }
+        if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
+        else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 8, false, 256>), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
         mark(3, 0);

@@ -53,6 +53,7 @@ struct StageHalf {
 };
 
 struct FfnPlan {
+    bool tiled;
     uint32_t m_tile, ksplit, ksplit1, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
     uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_chunk, off_h, off_y;
@@ -159,15 +160,18 @@ FfnShape ffn_shape(const fluxmoe_ctx* c, uint32_t n_experts) {
     return FfnShape{n_experts, c->d.hidden, c->d.ffn, c->n_cus, c->tune_tiled_waves};
 }
 
-// limit: bytes the scratch may take (the call's buffer; the size query leaves it open).  Only the K split of the
-// first product gives way to it, so a buffer that holds the unsplit plan is always enough.
-// mapped: experts of the layer known to be resident, 0 = not known (steers that split only).
-FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
+// split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.
+FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_t mapped, bool split, uint64_t limit) {
     FfnPlan p{};
     const uint64_t E = c.E, H = c.H, F = c.F;
     const uint64_t pairs = uint64_t(T) * K;
     const uint64_t groups = std::max<uint64_t>(1, std::min<uint64_t>(E, pairs));
     const uint64_t avg = (pairs + groups - 1) / groups;
+    const uint64_t n_cus = uint64_t(std::max(c.n_cus, 1));
+    // what a call with only `mapped` experts resident multiplies
+    const uint64_t act = mapped ? std::min<uint64_t>(mapped, E) : E;
+    const uint64_t pairs_act = std::max<uint64_t>(1, pairs * act / E);
+    const uint64_t groups_act = std::max<uint64_t>(1, std::min(act, pairs_act));
     // Row tile of the weight-streaming kernels: every extra tile of an expert streams that expert's
     // weights again, and routing can be far from even, so tiles hold up to 128 rows (the kernel takes a
     // cheaper body for tiles with fewer rows).  With so many rows per expert that even 128-row tiles are
@@ -176,12 +180,38 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0u
     // the LDS-tiled MFMA kernels (256-row tiles, k extents that are multiples of 64) costs relative to
     // a streaming pass at these sizes.
     auto p_over = [&](double m) { return 0.5 * std::erfc((m + 0.5 - double(avg)) / std::sqrt(2.0 * double(avg))); };
+    const bool tileable = H % 64 == 0 && F % 64 == 0;
     p.m_tile = 128;
-    if (p_over(128) > 0.02 && 1.0 + p_over(128) + p_over(256) + p_over(384) > 1.6 && H % 64 == 0 && F % 64 == 0)
+    if (p_over(128) > 0.02 && 1.0 + p_over(128) + p_over(256) + p_over(384) > 1.6 && tileable)
         p.m_tile = 256;
+    bool forced = false;
     if (const char* v = std::getenv("FLUXMOE_FFN_MTILE")) {
         const int m = std::atoi(v);
-        if (m == 16 || m == 32 || m == 64 || m == 96 || m == 128 || (m == 256 && H % 64 == 0 && F % 64 == 0)) p.m_tile = uint32_t(m);
+        if (m == 16 || m == 32 || m == 64 || m == 96 || m == 128 || (m == 256 && tileable)) { p.m_tile = uint32_t(m); forced = true; }
+    }
+    p.tiled = p.m_tile == 256;
+    // Where the launch would leave CUs without a workgroup.  All figures: microseconds per call, weights out of HBM.
+    if (split && !forced && tileable && c.tiled_waves == 2) {
+        const double avg_act = double(pairs_act) / double(groups_act);
+        const bool few_strips = 2 * ((F + 255) / 256) * groups_act <= n_cus;       // strip workgroups before any K split
+        if (p.tiled) {
+            // A single expert in 256 x 256 tiles: tiles of 128 x 128, two workgroups per CU, while the large ones make one and
+            // a half rounds at most.  H 5120 F 1536, tiles of 256 / 128: 160 rows 56 / 53, 512 71 / 68, 2048 160 / 153,
+            // 8192 470 / 460, 16384 792 / 921; H 2048 F 512: 256 rows 46 / 30, 2048 67 / 51.  Several experts with several
+            // row tiles each stay (20 of H 5120 F 1536, 205 rows each: 383 / 451).
+            if (groups_act == 1 && 2 * ((pairs_act + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
+        } else if (few_strips && groups_act > 1 && 0.5 * std::erfc((128.5 - avg_act) / std::sqrt(2.0 * avg_act)) > 0.02) {
+            // Experts that often need a second 128-row strip tile: 8 of H 4096 F 1792, 128 rows each: strips 172, tiles of 256 121.
+            p.tiled = true;
+            p.m_tile = 256;
+        } else if (few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20) : H <= 2048 && avg_act >= 16)) {
+            // Row counts that make a matrix tile worth while and K too short for the strips' start-up, strips / tiles of 128:
+            // one expert of H 5120 F 1536: 64 rows 47 / 46, 128 59 / 51; of H 2048 F 512: 32 rows 28 / 25; 32 experts of that
+            // shape, 20 rows each 61 / 60, 40 71 / 65, 94 85 / 75, a quarter of 128 experts under skewed routing 91 / 70.
+            // Longer K favours the strips: 20 of H 5120 F 384, 51 rows each: 79 / 99; 8 of H 4096 F 1792, 64 rows: 101 / 109.
+            p.tiled = true;
+            p.m_tile = 128;
+        }
     }
     p.pairs_cap = uint32_t(std::max<uint64_t>(pairs, 1));
     p.tiles_cap = uint32_t(pairs / p.m_tile + groups + 1);
@@ -191,7 +221,6 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0u
     // start-up cost) + the FP32 partials it writes and combine_kernel reads back.
     const uint64_t strips2 = (H + 127) / 128;
     const uint64_t est_tiles = std::max<uint64_t>(1, std::max<uint64_t>(pairs / p.m_tile, std::min(groups, pairs)));
-    const uint64_t n_cus = uint64_t(std::max(c.n_cus, 1));
     uint64_t ks = 1, best_cost = ~0ull;
     for (uint64_t k = 1; k <= 8 && k <= std::max<uint64_t>(1, F / 256); ++k) {
         const uint64_t wgs = (strips2 + 3) / 4 * est_tiles * k;
@@ -201,12 +230,29 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0u
         if (cost < best_cost) { best_cost = cost; ks = k; }
     }
     p.ksplit = uint32_t(ks);
-    if (p.m_tile == 256) {
-        // LDS-tiled kernels: one 256 x 256 tile per workgroup.  When the second product has fewer tiles
-        // than the chip has CUs, the LDS-direct kernel splits K so that about one workgroup per CU runs
-        // (each split keeps at least 8 steps of 64)
+    p.ksplit1 = 1;
+    // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when
+    // split k ways.  A tile costs 3 us to start; a step 1.4 us (256 x 256, one workgroup per CU), or 0.56 us (128 x 128)
+    // alone on a CU and 0.88 us for each of two.  Partial sums are written and read at 10 TB/s (mostly in the caches).
+    const uint64_t row_tiles = groups_act == 1 ? (pairs_act + p.m_tile - 1) / p.m_tile
+                                               : std::max(groups_act, pairs_act / p.m_tile + groups_act / 2);
+    auto tile_ns = [&](uint64_t tiles, uint64_t steps, uint64_t k) {
+        const uint64_t wgs = tiles * k, per = (steps + k - 1) / k;
+        if (p.m_tile == 256) return (wgs + n_cus - 1) / n_cus * (per * 1400 + 3000);
+        const uint64_t full = wgs / (2 * n_cus), rest = wgs % (2 * n_cus);
+        return full * (per * 880 + 3000) + (rest == 0 ? 0 : per * (rest <= n_cus ? 560 : 880) + 3000);
+    };
+    if (p.tiled) {
+        // When the second product has fewer tiles than the chip has CUs, the LDS-direct kernels split K so that about one
+        // workgroup per CU runs (each split keeps at least 8 steps of 64)
         p.ksplit = 1;
-        if (c.tiled_waves == 2 || c.tiled_waves == 1) {
+        if (p.m_tile == 128) {
+            uint64_t best = ~0ull;
+            for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 512 <= F && row_tiles * ((H + 127) / 128) * k <= 2 * n_cus)); ++k) {
+                const uint64_t cost = tile_ns(row_tiles * ((H + 127) / 128), F / 64, k) + k * pairs_act * H * 8 / 10000;
+                if (cost < best) { best = cost; p.ksplit = uint32_t(k); }
+            }
+        } else if (c.tiled_waves == 2 || c.tiled_waves == 1) {
             const uint64_t tiles2 = groups * ((avg + 255) / 256) * ((H + 255) / 256);
             uint64_t k2 = std::max<uint64_t>(1, n_cus / tiles2);
             k2 = std::min<uint64_t>(k2, 8);
@@ -216,19 +262,14 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0u
     }
     // K split of the first product, for launches that would leave most of the chip without a workgroup: the FP32 partial
     // sums of gate and up cost a write, a read and a launch.  Measured, whole FFN call: one token, top-10 of 512 experts,
-    // H 2048 F 512 (20 workgroups unsplit) 63 -> 36 us; 333 tokens, top-4 of 64, H 2880 F 360 (128) 140 -> 116 us; the
-    // shared expert H 5120 F 1536 with 512 tokens (24 tiles of 256 x 256, split 6 ways; its own grouping below included)
-    // 134 -> 70 us.  Layers whose tiles fill the chip stay unsplit (8 experts of H 4096 F 14336: 448 workgroups).
-    p.ksplit1 = 1;
-    {
-        const uint64_t act = mapped ? std::min<uint64_t>(mapped, E) : E;
-        const uint64_t pairs_act = std::max<uint64_t>(1, pairs * act / E);
-        const uint64_t groups_act = std::max<uint64_t>(1, std::min(act, pairs_act));
+    // H 2048 F 512 (20 workgroups unsplit) 63 -> 36 us; 333 tokens, top-4 of 64, H 2880 F 360 (128) 140 -> 116 us.  Layers
+    // whose tiles fill the chip stay unsplit (8 experts of H 4096 F 14336: 448 workgroups).
+    if (split && (!p.tiled || c.tiled_waves == 2)) {
         const uint64_t partial_bytes = pairs_act * 2 * F * 8;             // written and read, per split
-        if (p.m_tile != 256) {
+        uint64_t best = ~0ull;
+        if (!p.tiled) {
             // units of k rows of a workgroup (about 30 ns each when the memory system is not saturated)
             const uint64_t wgs1 = ((F + 127) / 128 + 1) / 2 * std::max<uint64_t>(pairs_act / p.m_tile, groups_act);
-            uint64_t best = ~0ull;
             for (uint64_t k = 1; k <= 16 && (k == 1 || k * 256 <= H); ++k) {
                 const uint64_t k_per = align_up((H + k - 1) / k, 128);    // the kernel splits at multiples of 128
                 if ((H + k_per - 1) / k_per != k) continue;
@@ -236,14 +277,11 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0u
                 const uint64_t cost = rounds * (std::min(k_per, H) + 128) + (k > 1 ? 128 + k * partial_bytes / (n_cus * 1024) : 0);
                 if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); }
             }
-        } else if (c.tiled_waves == 2) {
-            // nanoseconds: 1.2 us a step of 64 k, 3 us to start a tile, 4 us for the extra launch, partial sums at 5 TB/s
-            const uint64_t avg_act = (pairs_act + groups_act - 1) / groups_act;
-            const uint64_t tiles1 = groups_act * ((avg_act + 255) / 256) * ((F + 127) / 128);
-            uint64_t best = ~0ull;
-            for (uint64_t k = 1; k <= 8 && (k == 1 || k * 512 <= H); ++k) {
-                const uint64_t rounds = (tiles1 * k + n_cus - 1) / n_cus;
-                const uint64_t cost = rounds * (H / 64 * 1200 / k + 3000) + (k > 1 ? 4000 + k * partial_bytes / 5000 : 0);
+        } else {
+            const uint64_t cols = p.m_tile / 2;
+            const uint64_t tiles1 = row_tiles * ((F + cols - 1) / cols), room = p.m_tile == 256 ? n_cus : 2 * n_cus;
+            for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 512 <= H && tiles1 * k <= room)); ++k) {
+                const uint64_t cost = tile_ns(tiles1, H / 64, k) + (k > 1 ? 4500 + k * partial_bytes / 10000 : 0);
                 if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); }
             }
         }
@@ -259,13 +297,26 @@ FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0u
     p.n_chunks = pairs > kRouteChunkThreshold ? uint32_t((pairs + kRouteChunkPairs - 1) / kRouteChunkPairs) : 0u;
     p.off_chunk = take(uint64_t(p.n_chunks) * E * 4);
     p.off_h = take(uint64_t(p.pairs_cap) * F * 2);
+    p.off_y = o;
     // the partial sums of the first product are read before the second product writes its own in the same place
-    const uint64_t y_bytes = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part_bytes = uint64_t(p.pairs_cap) * 2 * F * 4;
-    p.off_y = take(y_bytes);
-    while (p.ksplit1 > 1 && p.off_y + align_up(p.ksplit1 * part_bytes, 256) > limit) --p.ksplit1;
-    if (p.ksplit1 > 1) o = std::max(o, p.off_y + align_up(p.ksplit1 * part_bytes, 256));
-    p.bytes = o;
+    auto end = [&]() {
+        const uint64_t y = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4 : 0;
+        return p.off_y + align_up(std::max(y, part), 256);
+    };
+    if (split) {
+        while (p.ksplit1 > 1 && end() > limit) --p.ksplit1;
+        while (p.tiled && p.m_tile == 128 && p.ksplit > 1 && end() > limit) --p.ksplit;
+    }
+    p.bytes = end();
     return p;
+}
+
+// limit: bytes the scratch may take (the call's buffer; the size query leaves it open): the splits give way to it, and then
+// the small tiles do, so a buffer that holds the plan without them is always enough.
+// mapped: experts of the layer known to be resident, 0 = not known (it steers speed, not what is accepted).
+FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
+    const FfnPlan p = plan_ffn_rules(c, T, K, mapped, true, limit);
+    return p.bytes <= limit ? p : plan_ffn_rules(c, T, K, mapped, false, limit);
 }
 
 // Pair table of the decode kernel, indexed by the next 12 stream bits (first stream bit in bit 0).
@@ -492,9 +543,13 @@ int fluxmoe_query_sizes(const fluxmoe_ctx* c, fluxmoe_sizes* out) {
 
 uint64_t fluxmoe_ffn_workspace_bytes(const fluxmoe_ctx* c, uint32_t T, uint32_t K, int shared_expert) {
     if (!c) return 0;
-    uint64_t need = plan_ffn(ffn_shape(c, c->d.n_experts), T, K).bytes;
-    if (shared_expert)          // same shapes, a single expert
-        need = std::max(need, plan_ffn(ffn_shape(c, 1), T, 1).bytes);
+    // enough for the plan a call prefers and for the one it can fall back on
+    auto need_of = [&](uint32_t n_experts, uint32_t k) {
+        const FfnShape sh = ffn_shape(c, n_experts);
+        return std::max(plan_ffn_rules(sh, T, k, 0, true, ~0ull).bytes, plan_ffn_rules(sh, T, k, 0, false, ~0ull).bytes);
+    };
+    uint64_t need = need_of(c->d.n_experts, K);
+    if (shared_expert) need = std::max(need, need_of(1, 1));          // same shapes, a single expert
     return need;
 }
 
@@ -1172,7 +1227,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.hbuf = reinterpret_cast<uint16_t*>(w + p.off_h);
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
-    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
+    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);
@@ -1260,7 +1315,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.hbuf = reinterpret_cast<uint16_t*>(w + p.off_h);
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
-    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
+    a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);

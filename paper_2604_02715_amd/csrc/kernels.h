@@ -39,7 +39,8 @@ struct FfnArgs {
                                  // that swiglu_reduce_kernel adds up
     uint32_t identity;           // non-zero: one expert in slot 0 takes every token with gate 1 (K = 1, E = 1); topk_ids,
                                  // topk_w and page_table are not read
-    uint32_t tiled_waves;        // variant of the LDS-tiled kernels (m_tile 256): 2 LDS-direct loads, 8 or 4
+    uint32_t tiled;              // non-zero: LDS-tiled kernels (m_tile 256, or 128 for tiles of 128 x 128), else strip kernels
+    uint32_t tiled_waves;        // variant of the LDS-tiled kernels: 2 LDS-direct loads, 8 or 4
                                  // wavefronts with register-staged loads
     uint32_t tiled_persist;      // LDS-direct kernels: workgroups per CU-sized round that walk through the tiles (1 = 256
                                  // workgroups), 0 = one workgroup per tile

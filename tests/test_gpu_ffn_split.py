@@ -55,3 +55,40 @@ def test_shared_expert(tokens, shape):
         assert torch.equal(out, once + once)
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=64, top_k=1, n_experts=1, n_slots=1, hidden=512, ffn=64),       # one tile of 128 x 128, gate and up 64 columns each
+    dict(tokens=129, top_k=1, n_experts=1, n_slots=1, hidden=1088, ffn=576),    # second row tile of one row, ragged column tiles, splits
+    dict(tokens=600, top_k=1, n_experts=1, n_slots=1, hidden=64, ffn=128),      # one and two k steps
+    dict(tokens=100, top_k=4, n_experts=6, n_slots=6, hidden=320, ffn=192),     # several experts
+    dict(tokens=150, top_k=5, n_experts=30, n_slots=30, hidden=1024, ffn=256, routing="zipf"),   # row tiles from 1 to 128 rows
+    dict(tokens=400, top_k=2, n_experts=6, n_slots=6, hidden=1024, ffn=512),    # 133 rows each on few strips: tiles of 256
+])
+def test_tiles_of_launches_with_few_strips(kw):
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=10)
+
+
+def test_a_buffer_for_the_plan_without_splits_is_enough():
+    """The scratch a call prefers depends on how many experts are resident; one that holds the plan without K splits of
+    the first product must do, and give the same result to rounding."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=3, top_k=2, hidden=2048, ffn=128)
+    pool, dense = build_pool(cfg)
+    try:
+        x = inputs.activations(cfg).cuda()
+        ids, g = inputs.routing(cfg)
+        idd, gd = torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda()
+        pool.reset_page_table()
+        pool.materialize(0, np.arange(8), np.arange(8))
+        outs = []
+        for spare in (pool.ws_bytes, int(pool.sizes.pool_workspace_bytes) + 4096 + 2 * 6 * 128 + 6 * 2048 * 4):
+            B.fluxmoe_bind_arenas(pool.ctx, pool.slots13.data_ptr(), pool.slots2.data_ptr(), pool.workspace.data_ptr(), spare)
+            out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+            pool.expert_ffn(0, x, idd, gd, out)
+            torch.cuda.synchronize()
+            outs.append(out.cpu().numpy())
+        assert pool.device_errors() == 0
+        assert offn.rel_frobenius(outs[1], outs[0]) <= TOL
+    finally:
+        pool.close()
