@@ -45,6 +45,7 @@ union Frag {
 
 constexpr int kStrip = 128;        // output columns per wavefront
 constexpr int kChunk = 32;         // k per MFMA step
+constexpr uint32_t kRoutedPairs = 64;   // batches of up to this many pairs are grouped by the first product's workgroups
 constexpr int kNonTemporal = 2;    // cache policy operand of the buffer loads: bit 1 = nt
 
 // ------------------------------------------------------------------ routing / grouping
@@ -557,8 +558,9 @@ __device__ __forceinline__ bool tile_info(const FfnArgs& a, uint32_t tile, TileI
 // W3 (up), the odd one hands its accumulators over through LDS and the even one applies
 // SwiGLU and stores.  Splitting the two matrices over two wavefronts halves the accumulator
 // registers per wavefront, which is what leaves room for the deep load ring.
-template <int MI>
-__device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileInfo& t, float (*xch)[64], uint16_t* abuf) {
+// LISTED: the tile's pairs are in pair_list (LDS), row by row; otherwise they are read from a.sorted_pair.
+template <int MI, bool LISTED>
+__device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileInfo& t, float (*xch)[64], uint16_t* abuf, const int32_t* pair_list) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));   // uniform: scalar address arithmetic
     const int pair = wave >> 1;
@@ -571,7 +573,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
         const int32_t r = min(mi * 16 + (lane & 15), t.rows - 1);
-        const int32_t pr = a.sorted_pair[t.row0 + r];
+        const int32_t pr = LISTED ? pair_list[r] : a.sorted_pair[t.row0 + r];
         const uint32_t tok = uint32_t(pr) / a.K;
         arow[mi] = a.tokens + size_t(tok) * a.H;
     }
@@ -584,7 +586,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
         const int32_t r = min(i * 16 + int(threadIdx.x >> 4), t.rows - 1);
-        const int32_t pr = a.sorted_pair[t.row0 + r];
+        const int32_t pr = LISTED ? pair_list[r] : a.sorted_pair[t.row0 + r];
         aoff[i] = 2u * ((uint32_t(pr) / a.K) * a.H + 8u * piece);          // the launcher checks T * H * 2 < 4 GiB
     }
     // K split blockIdx.z multiplies k rows [k_begin, k_end): whole A blocks, the last split what remains
@@ -647,22 +649,74 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
 // Row tiles hold up to 16 MI rows so that an expert's weights are streamed once even when routing is
 // skewed (an expert with 231 of 2560 pairs next to hundreds with five); a tile with fewer rows takes a
 // body compiled for fewer 16-row MFMA tiles (less matrix work per chunk, same registers reserved).
-template <int MI>
+// ROUTE (at most kRoutedPairs pairs): there is no grouping kernel in front; every workgroup groups the pairs for itself, a
+// pair per lane, and the first ones write the lists the later kernels read.  A decode step of a token or two is launches:
+// the grouping kernel was 6 of the 34 us of one token's top-10 of 512 experts (H 2048, F 512), 29 without it.
+// Tiles are the distinct experts in order of first appearance (one tile each: no more rows than a strip tile holds).
+template <int MI, bool ROUTE>
 __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     // the accumulator exchange of the epilogue ([pair][mi, c, r][lane] floats) reuses the memory of
     // the shared A blocks: every wavefront has passed the last block's barrier by then
     constexpr size_t kXchBytes = sizeof(float) * 2 * MI * 8 * 4 * 64;
     constexpr size_t kABytes = sizeof(uint16_t) * 2 * StripGemm<MI>::kABufElems;
     __shared__ __align__(16) uint8_t smem[kXchBytes > kABytes ? kXchBytes : kABytes];
+    __shared__ int32_t pair_list[ROUTE ? kRoutedPairs : 1];
     float (*xch)[64] = reinterpret_cast<float (*)[64]>(smem);
     uint16_t* abuf = reinterpret_cast<uint16_t*>(smem);
     TileInfo t;
-    if (!tile_info(a, blockIdx.y, t)) return;     // uniform over the workgroup
-    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1>(a, t, xch, abuf);
-    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2>(a, t, xch, abuf);
-    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4>(a, t, xch, abuf);
-    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6>(a, t, xch, abuf);
-    else gemm1_swiglu_body<MI>(a, t, xch, abuf);
+    if (ROUTE) {
+        static_assert(!ROUTE || (16 * MI >= int(kRoutedPairs) && kRoutedPairs == 64), "a pair per lane, an expert's pairs in one tile");
+        const int lane = threadIdx.x & 63;
+        const uint32_t pairs = a.T * a.K, tile = blockIdx.y;
+        const bool lists = blockIdx.x == 0 && blockIdx.z == 0;              // uniform
+        const int32_t id = uint32_t(lane) < pairs ? a.topk_ids[lane] : -1;
+        const bool known = id >= 0 && uint32_t(id) < a.E;
+        const int32_t slot = known ? a.page_table[id] : -1;
+        const bool valid = slot >= 0;
+        const uint64_t valid_mask = __ballot(valid);
+        // the first valid pair with the same expert
+        int leader = lane;
+        for (int q = int(pairs) - 1; q >= 0; --q)
+            if (__builtin_amdgcn_readlane(id, q) == id) leader = q;
+        const uint64_t leaders = __ballot(valid && leader == lane);
+        const uint32_t n_tiles = uint32_t(__popcll(leaders));
+        if (lists && tile == 0 && threadIdx.x < 64) {
+            if (uint32_t(lane) < pairs && !valid && (!known || !(a.flags & 2u))) atomicOr(a.error_word, 2u);
+            // position of the lane's pair: pairs of earlier experts, then its own expert's earlier pairs
+            int32_t pos = 0;
+            for (uint32_t q = 0; q < pairs; ++q) {
+                const int lq = __builtin_amdgcn_readlane(leader, q);
+                if (((valid_mask >> q) & 1u) && (lq < leader || (lq == leader && int(q) < lane))) ++pos;
+            }
+            if (uint32_t(lane) < pairs) a.pair_pos[lane] = valid ? pos : -1;
+            if (lane == 0) {
+                a.expert_offset[a.E] = int32_t(__popcll(valid_mask));
+                a.n_tiles[0] = int32_t(n_tiles);
+            }
+        }
+        if (tile >= n_tiles) {
+            if (lists && threadIdx.x == 0) a.tile_rec[tile] = make_int4(0, 0, 0, -1);
+            return;
+        }
+        uint64_t rest = leaders;
+        for (uint32_t i = 0; i < tile; ++i) rest &= rest - 1;
+        const int first = __builtin_ctzll(rest);
+        const uint64_t mine = __ballot(valid && leader == first);
+        t.expert = __builtin_amdgcn_readlane(id, first);
+        t.slot = __builtin_amdgcn_readlane(slot, first);
+        t.rows = __popcll(mine);
+        t.row0 = __popcll(__ballot(valid && leader < first));
+        if (lists && threadIdx.x == 0) a.tile_rec[tile] = make_int4(t.expert, t.row0, t.rows, t.slot);
+        if (threadIdx.x < 64 && valid && leader == first) pair_list[__popcll(mine & ((1ull << lane) - 1ull))] = lane;
+        __syncthreads();
+    } else if (!tile_info(a, blockIdx.y, t)) {
+        return;                                       // uniform over the workgroup
+    }
+    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE>(a, t, xch, abuf, pair_list);
+    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE>(a, t, xch, abuf, pair_list);
+    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE>(a, t, xch, abuf, pair_list);
+    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE>(a, t, xch, abuf, pair_list);
+    else gemm1_swiglu_body<MI, ROUTE>(a, t, xch, abuf, pair_list);
 }
 
 // y[split][row][n] = h[row][k range] W2[k range][n]
@@ -1750,8 +1804,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     FfnArgs a = args;
     auto mark = [&](int kind, int begin) { if (hook) hook(user, kind, begin, stream); };
     const size_t sh = (3 * size_t(a.E) + 1024) * sizeof(int32_t);
+    // strip kernels, few pairs: the first product's workgroups do the grouping
+    const bool routes_itself = !a.identity && !a.tiled && a.m_tile >= kRoutedPairs && uint64_t(a.T) * a.K <= kRoutedPairs;
     mark(1, 1);
-    if (a.identity) {
+    if (routes_itself) {
+    } else if (a.identity) {
         hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
     } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
@@ -1899,11 +1956,12 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     // the strip kernels address activations and one expert matrix with 32-bit byte offsets
     if (uint64_t(a.T) * a.H * 2 >= (1ull << 32) || uint64_t(a.H) * a.F * 2 >= (1ull << 31)) return hipErrorInvalidValue;
     mark(2, 1);
-    if (a.m_tile == 16) hipLaunchKernelGGL(gemm1_swiglu_kernel<1>, g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 32) hipLaunchKernelGGL(gemm1_swiglu_kernel<2>, g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 64) hipLaunchKernelGGL(gemm1_swiglu_kernel<4>, g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 96) hipLaunchKernelGGL(gemm1_swiglu_kernel<6>, g1, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL(gemm1_swiglu_kernel<8>, g1, dim3(256), 0, stream, a);
+    if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true>, g1, dim3(256), 0, stream, routed, a);
+    else if (a.m_tile == 16) hipLaunchKernelGGL((gemm1_swiglu_kernel<1, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 32) hipLaunchKernelGGL((gemm1_swiglu_kernel<2, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 64) hipLaunchKernelGGL((gemm1_swiglu_kernel<4, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 96) hipLaunchKernelGGL((gemm1_swiglu_kernel<6, false>), g1, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false>), g1, dim3(256), 0, stream, a);
     launch_reduce();
     mark(2, 0);
     mark(3, 1);

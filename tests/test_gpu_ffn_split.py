@@ -92,3 +92,52 @@ def test_a_buffer_for_the_plan_without_splits_is_enough():
         assert offn.rel_frobenius(outs[1], outs[0]) <= TOL
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=1, top_k=1),
+    dict(tokens=32, top_k=2),                                                    # 64 pairs, the most that are grouped this way
+    dict(tokens=64, top_k=1, n_experts=2, n_slots=2, hidden=136, ffn=264),       # tiles of 17 to 64 rows, ragged edges
+    dict(tokens=13, top_k=5, n_experts=300, n_slots=300, hidden=64, ffn=72),     # one more pair: the grouping kernel
+    dict(tokens=6, top_k=10, n_experts=200, n_slots=200, hidden=520, ffn=72, routing="uniform"),
+])
+def test_few_pairs(kw):
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=11)
+
+
+def test_few_pairs_on_one_expert_on_absent_ones_and_on_ids_out_of_range():
+    """Grouping by the first product's own workgroups: every pair on one expert; half of the experts absent, skipped or
+    flagged; ids out of range are flagged and add nothing."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=20, top_k=3)
+    run_ffn_case(inputs.scaled(cfg, tokens=60, top_k=1), seed=12, ids_override=lambda ids: np.full_like(ids, 5))
+    run_ffn_case(cfg, seed=13, waves=lambda u: paging.waves(u, 4))
+    pool, dense = build_pool(cfg)
+    try:
+        w13, w2 = dense[0]
+        x = inputs.activations(cfg)
+        ids, g = inputs.routing(cfg)
+        ids[3, 1], ids[7, 0], ids[19, 2] = -1, 8, 2 ** 31 - 1
+        pool.reset_page_table()
+        pool.materialize(0, np.arange(8), np.arange(8))
+        out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+        gd = torch.from_numpy(g).cuda()
+        pool.expert_ffn(0, x.cuda(), torch.from_numpy(ids).cuda(), gd, out, B.FFN_SKIP_UNMAPPED)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 2                     # skipping covers absent experts, not bad ids
+        bad = (ids < 0) | (ids >= 8)
+        kept, good_ids = np.where(bad, 0, g).astype(np.float32), ids.copy()
+        for t, k in np.argwhere(bad):                        # an expert the token does not list, with gate 0
+            good_ids[t, k] = next(e for e in range(8) if e not in ids[t])
+        want = offn.moe_ffn(inputs.bits_u16(x), good_ids, kept, lambda e: (inputs.bits_u16(w13[e]), inputs.bits_u16(w2[e])))
+        assert offn.rel_frobenius(out.cpu().numpy(), want) <= TOL
+        pool.release(0, [0, 1, 2, 3])
+        good = torch.from_numpy(good_ids).cuda()
+        pool.expert_ffn(0, x.cuda(), good, gd, out)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 2
+        pool.expert_ffn(0, x.cuda(), good, gd, out, B.FFN_SKIP_UNMAPPED)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 0
+    finally:
+        pool.close()
