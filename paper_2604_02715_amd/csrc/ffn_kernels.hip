@@ -380,9 +380,12 @@ struct StripGemm {
     // piece (tid % 16) ^ (tid / 16 % 16) of row 16 i + tid / 16 (clamped to the tile's last row).
     // B: bmat points at the [k_rows][ldb] matrix (uniform over the wavefront, under 4 GiB), col is the
     // lane's first column; a four-deep register ring as in run().
+    // HALVES: the two pairs of wavefronts multiply different k of the same columns.  A buffer then holds two blocks, one
+    // after the other; pair `half` takes the second of each two if it is 1.  n_blocks counts pairs of blocks.
+    template <bool HALVES>
     __device__ __forceinline__ void run_shared(const uint8_t* abase, const uint32_t (&aoff)[MI], uint16_t* abuf,
                                                const uint16_t* bmat, uint32_t k_rows, uint32_t col, uint32_t ldb,
-                                               uint32_t k_begin, uint32_t n_blocks, int lane, int wave) {
+                                               uint32_t k_begin, uint32_t n_blocks, int lane, int wave, uint32_t half) {
         if (n_blocks == 0) return;
         const uint32_t kg = 8u * (uint32_t(lane) >> 4);
         const uint32_t row_bytes = 2u * ldb;
@@ -397,19 +400,25 @@ struct StripGemm {
         const uint8_t* const abuf8 = reinterpret_cast<const uint8_t*>(abuf);
         const uint32_t abuf_lds = uint32_t(uintptr_t((__attribute__((address_space(3))) void*)abuf));
         uint4 bst[4][8];
+        constexpr uint32_t kBlockBytes = uint32_t(kABufElems) * 2, kBufBytes = kBlockBytes * (HALVES ? 2 : 1);
+        const uint32_t my_block = HALVES ? half * kBlockBytes : 0u;
         // M0 carries the LDS destination of an LDS-direct load and is read when the instruction
         // issues; the compiler reserves it, so its value is put back
         auto a_dma = [&](uint32_t blk, uint32_t buf_bytes) __attribute__((always_inline)) {
-            const uint8_t* src = abase + (size_t(k_begin) + size_t(blk) * kABlock) * 2;
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
+            for (int n = 0; n < (HALVES ? 2 : 1) * MI; ++n) {
+                const int i = n % MI, sub = n / MI;
+                const uint8_t* src = abase + (size_t(k_begin) + (size_t(blk) * (HALVES ? 2 : 1) + sub) * kABlock) * 2;
                 uint32_t saved_m0;
-                const uint32_t dst = abuf_lds + buf_bytes + uint32_t(i * 4 + wave) * 1024u;
+                const uint32_t dst = abuf_lds + buf_bytes + uint32_t(sub) * kBlockBytes + uint32_t(i * 4 + wave) * 1024u;
                 asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
                              : "=&s"(saved_m0) : "v"(aoff[i]), "s"(src), "s"(dst) : "memory");
             }
         };
-        constexpr uint32_t kBufBytes = uint32_t(kABufElems) * 2;
+        // the wavefront's chunk number L (four to a block) -> byte offset of its first row
+        auto chunk_at = [&](uint32_t L) __attribute__((always_inline)) {
+            return first_bytes + (HALVES ? ((L >> 2) * 2 + half) * 4 + (L & 3u) : L) * chunk_bytes;
+        };
         // one block of four chunks; PREFETCH: all four B loads three chunks ahead are inside the
         // shared range and the next A block exists
         auto block = [&](uint32_t cur_bytes, uint32_t nxt_bytes, uint32_t blk, auto PREFETCH) __attribute__((always_inline)) {
@@ -417,11 +426,11 @@ struct StripGemm {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const uint32_t chunk = blk * 4 + c;
-                if (PREFETCH.value || chunk + 3 < n_blocks * 4) load_b(bst[(c + 3) & 3], rsrc, voff, first_bytes + (chunk + 3) * chunk_bytes, row_bytes);
+                if (PREFETCH.value || chunk + 3 < n_blocks * 4) load_b(bst[(c + 3) & 3], rsrc, voff, chunk_at(chunk + 3), row_bytes);
                 uint4 af[MI];
 #pragma unroll
                 for (int mi = 0; mi < MI; ++mi)
-                    af[mi] = *reinterpret_cast<const uint4*>(abuf8 + cur_bytes + ((a_fr ^ (64 * c)) + 4096 * mi));
+                    af[mi] = *reinterpret_cast<const uint4*>(abuf8 + cur_bytes + my_block + ((a_fr ^ (64 * c)) + 4096 * mi));
                 mma_b(bst[c], af);
             }
             // the A block fetched above was issued before this block's 32 B loads and loads return in
@@ -431,7 +440,7 @@ struct StripGemm {
         };
         a_dma(0, 0);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) load_b(bst[c], rsrc, voff, first_bytes + uint32_t(c) * chunk_bytes, row_bytes);
+        for (int c = 0; c < 3; ++c) load_b(bst[c], rsrc, voff, chunk_at(uint32_t(c)), row_bytes);
         asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
         __syncthreads();
         uint32_t blk = 0;
@@ -559,13 +568,18 @@ __device__ __forceinline__ bool tile_info(const FfnArgs& a, uint32_t tile, TileI
 // SwiGLU and stores.  Splitting the two matrices over two wavefronts halves the accumulator
 // registers per wavefront, which is what leaves room for the deep load ring.
 // LISTED: the tile's pairs are in pair_list (LDS), row by row; otherwise they are read from a.sorted_pair.
-template <int MI, bool LISTED>
-__device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileInfo& t, float (*xch)[64], uint16_t* abuf, const int32_t* pair_list) {
+// HALVES: the workgroup has one strip, and its two pairs of wavefronts take half of the k range each: as many bytes in
+// flight per workgroup, twice the workgroups, no empty second strip where their number is odd, and no partial sums.
+// 64 experts of H 2880 F 360, 333 tokens, top-4 (three strips; split two ways over K before): 115 -> 106 us a call with the
+// numbering of workgroups below, one token's top-10 of 512 experts (H 2048 F 512) 28.9 -> 28.4.
+template <int MI, bool LISTED, bool HALVES>
+__device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileInfo& t, float (*xch)[64], uint16_t* abuf, const int32_t* pair_list,
+                                                  uint32_t col_wg, uint32_t split) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));   // uniform: scalar address arithmetic
     const int pair = wave >> 1;
     const int mat_id = wave & 1;
-    const uint32_t strip = blockIdx.x * 2 + pair;
+    const uint32_t strip = HALVES ? col_wg : col_wg * 2 + pair;
     const uint32_t n0 = strip * kStrip + 8u * (lane & 15);
     const bool col_ok = n0 < a.F;                 // strips past F still run (barrier below)
 
@@ -589,19 +603,48 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
         const int32_t pr = LISTED ? pair_list[r] : a.sorted_pair[t.row0 + r];
         aoff[i] = 2u * ((uint32_t(pr) / a.K) * a.H + 8u * piece);          // the launcher checks T * H * 2 < 4 GiB
     }
-    // K split blockIdx.z multiplies k rows [k_begin, k_end): whole A blocks, the last split what remains
-    const uint32_t k_per = ((a.H + a.ksplit1 - 1) / a.ksplit1 + kABlock - 1) / kABlock * kABlock;
-    const uint32_t k_begin = min(a.H, blockIdx.z * k_per);
+    // K split `split` multiplies k rows [k_begin, k_end): whole A blocks, the last split what remains
+    constexpr uint32_t kUnit = HALVES ? 2 * kABlock : kABlock;
+    const uint32_t k_per = ((a.H + a.ksplit1 - 1) / a.ksplit1 + kUnit - 1) / kUnit * kUnit;
+    const uint32_t k_begin = min(a.H, split * k_per);
     const uint32_t k_end = min(a.H, k_begin + k_per);
     StripGemm<MI> g;
     g.zero();
-    const uint32_t n_blocks = (k_end - k_begin) / kABlock;
-    g.run_shared(reinterpret_cast<const uint8_t*>(a.tokens), aoff, abuf, w, a.H, col_ok ? n0 : a.F - 8, a.F, k_begin, n_blocks, lane, wave);
-    g.run(arow, w + (col_ok ? n0 : a.F - 8), a.F, k_begin + n_blocks * kABlock, k_end, lane);
+    const uint32_t n_blocks = (k_end - k_begin) / kUnit;
+    g.template run_shared<HALVES>(reinterpret_cast<const uint8_t*>(a.tokens), aoff, abuf, w, a.H, col_ok ? n0 : a.F - 8, a.F, k_begin, n_blocks, lane, wave, uint32_t(pair));
+    // what is left is less than a block, or two with HALVES: one to each pair, the tail to the second
+    uint32_t k_left = k_begin + n_blocks * kUnit, k_stop = k_end;
+    if (HALVES) {
+        const uint32_t mid = min(k_end, k_left + kABlock);
+        if (pair == 0) k_stop = mid; else k_left = mid;
+    }
+    g.run(arow, w + (col_ok ? n0 : a.F - 8), a.F, k_left, k_stop, lane);
+
+    if (HALVES) {                                 // the second pair's sums are added to the first's
+        mfma_drain();
+        if (pair == 1) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) xch[mat_id * (MI * 32) + (mi * 8 + c) * 4 + r][lane] = g.acc[mi][c][r];
+        }
+        __syncthreads();
+        if (pair == 0) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) g.acc[mi][c][r] += xch[mat_id * (MI * 32) + (mi * 8 + c) * 4 + r][lane];
+        }
+        __syncthreads();                          // the memory is used again below
+    }
 
     if (a.ksplit1 > 1) {                          // partial sums of both matrices, added up by swiglu_reduce_kernel
-        if (!col_ok) return;
-        float* part = a.ybuf + (size_t(blockIdx.z) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
+        if (!col_ok || (HALVES && pair == 1)) return;
+        float* part = a.ybuf + (size_t(split) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -614,7 +657,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
             }
         return;
     }
-    if (mat_id == 1) {
+    if (mat_id == 1 && !(HALVES && pair == 1)) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -623,7 +666,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
                 for (int r = 0; r < 4; ++r) xch[pair * (MI * 32) + (mi * 8 + c) * 4 + r][lane] = g.acc[mi][c][r];
     }
     __syncthreads();
-    if (mat_id == 1 || !col_ok) return;
+    if (mat_id == 1 || !col_ok || (HALVES && pair == 1)) return;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -653,17 +696,30 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
 // pair per lane, and the first ones write the lists the later kernels read.  A decode step of a token or two is launches:
 // the grouping kernel was 6 of the 34 us of one token's top-10 of 512 experts (H 2048, F 512), 29 without it.
 // Tiles are the distinct experts in order of first appearance (one tile each: no more rows than a strip tile holds).
-template <int MI, bool ROUTE>
+template <int MI, bool ROUTE, bool HALVES>
 __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     // the accumulator exchange of the epilogue ([pair][mi, c, r][lane] floats) reuses the memory of
     // the shared A blocks: every wavefront has passed the last block's barrier by then
     constexpr size_t kXchBytes = sizeof(float) * 2 * MI * 8 * 4 * 64;
-    constexpr size_t kABytes = sizeof(uint16_t) * 2 * StripGemm<MI>::kABufElems;
+    constexpr size_t kABytes = sizeof(uint16_t) * (HALVES ? 4 : 2) * StripGemm<MI>::kABufElems;
     __shared__ __align__(16) uint8_t smem[kXchBytes > kABytes ? kXchBytes : kABytes];
     __shared__ int32_t pair_list[ROUTE ? kRoutedPairs : 1];
     float (*xch)[64] = reinterpret_cast<float (*)[64]>(smem);
     uint16_t* abuf = reinterpret_cast<uint16_t*>(smem);
     TileInfo t;
+    // column workgroup, row tile, K split: the three dimensions of the grid, or (a.g1_xcd) numbered as in gemm2_kernel so that
+    // the column workgroups of a (tile, split) share an XCD and find the tile's activations, and where rows of the weights
+    // are not whole 128-byte lines the line that two strips share, in its L2
+    uint32_t col_wg = blockIdx.x, tile_no = blockIdx.y, split = blockIdx.z;
+    if (!ROUTE && a.g1_xcd) {
+        const uint32_t n_cw = HALVES ? (a.F + kStrip - 1) / kStrip : (a.F + 2 * kStrip - 1) / (2 * kStrip);
+        const uint32_t xcd = blockIdx.x % 8u, q = blockIdx.x / 8u;
+        col_wg = q % n_cw;
+        const uint32_t unit = (q / n_cw) * 8u + xcd;
+        if (unit >= a.tiles_cap * a.ksplit1) return;
+        tile_no = unit / a.ksplit1;
+        split = unit % a.ksplit1;
+    }
     if (ROUTE) {
         static_assert(!ROUTE || (16 * MI >= int(kRoutedPairs) && kRoutedPairs == 64), "a pair per lane, an expert's pairs in one tile");
         const int lane = threadIdx.x & 63;
@@ -709,14 +765,14 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
         if (lists && threadIdx.x == 0) a.tile_rec[tile] = make_int4(t.expert, t.row0, t.rows, t.slot);
         if (threadIdx.x < 64 && valid && leader == first) pair_list[__popcll(mine & ((1ull << lane) - 1ull))] = lane;
         __syncthreads();
-    } else if (!tile_info(a, blockIdx.y, t)) {
+    } else if (!tile_info(a, tile_no, t)) {
         return;                                       // uniform over the workgroup
     }
-    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE>(a, t, xch, abuf, pair_list);
-    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE>(a, t, xch, abuf, pair_list);
-    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE>(a, t, xch, abuf, pair_list);
-    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE>(a, t, xch, abuf, pair_list);
-    else gemm1_swiglu_body<MI, ROUTE>(a, t, xch, abuf, pair_list);
+    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
+    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
+    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
+    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
+    else gemm1_swiglu_body<MI, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
 }
 
 // y[split][row][n] = h[row][k range] W2[k range][n]
@@ -750,8 +806,8 @@ __device__ __forceinline__ void gemm2_body(const FfnArgs& a, const TileInfo& t, 
     StripGemm<MI> g;
     g.zero();
     const uint32_t n_blocks = (k_end - k_begin) / kABlock;
-    g.run_shared(reinterpret_cast<const uint8_t*>(a.hbuf + size_t(t.row0) * a.F), aoff, abuf, w2, a.F, col_ok ? n0 : a.H - 8, a.H,
-                 k_begin, n_blocks, lane, wave);
+    g.template run_shared<false>(reinterpret_cast<const uint8_t*>(a.hbuf + size_t(t.row0) * a.F), aoff, abuf, w2, a.F, col_ok ? n0 : a.H - 8, a.H,
+                 k_begin, n_blocks, lane, wave, 0);
     g.run(arow, w2 + (col_ok ? n0 : a.H - 8), a.H, k_begin + n_blocks * kABlock, k_end, lane);
 
     if (!col_ok) return;
@@ -1831,7 +1887,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     if (a.ksplit1 == 0 || (a.ksplit1 > 1 && a.ksplit1 > a.H / kTK)) return hipErrorInvalidValue;
     const uint32_t strips1 = (a.F + kStrip - 1) / kStrip;
     const uint32_t strips2 = (a.H + kStrip - 1) / kStrip;
-    const dim3 g1((strips1 + 1) / 2, a.tiles_cap, a.ksplit1);
+    if (a.halves && (a.tiled || a.m_tile != 128)) return hipErrorInvalidValue;
+    const uint32_t cols1 = a.halves ? strips1 : (strips1 + 1) / 2;
+    const dim3 g1 = a.g1_xcd && !routes_itself ? dim3((a.tiles_cap * a.ksplit1 + 7) / 8 * 8 * cols1, 1, 1) : dim3(cols1, a.tiles_cap, a.ksplit1);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
     if (a.tiled) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
@@ -1956,12 +2014,14 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     // the strip kernels address activations and one expert matrix with 32-bit byte offsets
     if (uint64_t(a.T) * a.H * 2 >= (1ull << 32) || uint64_t(a.H) * a.F * 2 >= (1ull << 31)) return hipErrorInvalidValue;
     mark(2, 1);
-    if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true>, g1, dim3(256), 0, stream, routed, a);
-    else if (a.m_tile == 16) hipLaunchKernelGGL((gemm1_swiglu_kernel<1, false>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 32) hipLaunchKernelGGL((gemm1_swiglu_kernel<2, false>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 64) hipLaunchKernelGGL((gemm1_swiglu_kernel<4, false>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 96) hipLaunchKernelGGL((gemm1_swiglu_kernel<6, false>), g1, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false>), g1, dim3(256), 0, stream, a);
+    if (routes_itself && a.halves) launch_done(gemm1_swiglu_kernel<4, true, true>, g1, dim3(256), 0, stream, routed, a);
+    else if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true, false>, g1, dim3(256), 0, stream, routed, a);
+    else if (a.halves) hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, true>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 16) hipLaunchKernelGGL((gemm1_swiglu_kernel<1, false, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 32) hipLaunchKernelGGL((gemm1_swiglu_kernel<2, false, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 64) hipLaunchKernelGGL((gemm1_swiglu_kernel<4, false, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 96) hipLaunchKernelGGL((gemm1_swiglu_kernel<6, false, false>), g1, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false>), g1, dim3(256), 0, stream, a);
     launch_reduce();
     mark(2, 0);
     mark(3, 1);

@@ -37,6 +37,9 @@ struct FfnArgs {
     uint32_t pairs_cap, tiles_cap, m_tile, ksplit;
     uint32_t ksplit1;            // K splits of the first product; 1: SwiGLU in its epilogue, more: FP32 partial sums
                                  // that swiglu_reduce_kernel adds up
+    uint32_t halves;             // non-zero (strip kernels, m_tile 128): a workgroup of the first product has one strip and its
+                                 // pairs of wavefronts half of the k range each, instead of two strips
+    uint32_t g1_xcd;             // non-zero (strip kernels): the first product's column workgroups of a row tile share an XCD
     uint32_t identity;           // non-zero: one expert in slot 0 takes every token with gate 1 (K = 1, E = 1); topk_ids,
                                  // topk_w and page_table are not read
     uint32_t tiled;              // non-zero: LDS-tiled kernels (m_tile 256, or 128 for tiles of 128 x 128), else strip kernels

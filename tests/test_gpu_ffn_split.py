@@ -141,3 +141,15 @@ def test_few_pairs_on_one_expert_on_absent_ones_and_on_ids_out_of_range():
         assert pool.device_errors() == 0
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=100, top_k=2, hidden=264, ffn=64),                               # one strip, one pair of k blocks and a tail of 8
+    dict(tokens=100, top_k=2, hidden=392, ffn=360, n_experts=3, n_slots=3),      # three strips, a block and a tail left over
+    dict(tokens=90, top_k=4, hidden=1288, ffn=136, n_experts=20, n_slots=20, routing="zipf"),   # tiles of every size, ragged strip
+    dict(tokens=100, top_k=2, hidden=120, ffn=72),                               # less than a block of k
+    dict(tokens=2, top_k=4, hidden=1544, ffn=264),                               # grouped by its own workgroups
+])
+def test_halves_of_k_in_one_workgroup(kw):
+    """Few or an odd number of strips: the two pairs of wavefronts of a workgroup share a strip and halve its k range."""
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=14)
