@@ -1918,6 +1918,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
+            if (e != hipSuccess) return e;
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
@@ -1974,12 +1977,10 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // LDS-direct kernels: the launch covers `tiled_total` tile numbers; a workgroup walks through the numbers
         // blockIdx.x, + gridDim.x, ... and overlaps a tile's epilogue with the next one's first loads.  One
         // workgroup fits on a CU, so the first product runs tiled_persist x 256 workgroups (a multiple of 256
-        // keeps a workgroup's numbers on its XCD); with tiled_persist = 0, and for the second product, one
-        // workgroup per number.  The fixed hand-out loses when the last column block of a super-tile row is
-        // partly empty (workgroups with no tile there idle): measured on H 5120 / F 1536, 2048 rows per expert,
-        // the first product gains 7 % (its tiles are short: 80 steps, and each needs a row gather first), the
-        // second, whose 20 column tiles leave half of every third block empty, loses 11 %; on H 4096 / F 14336
-        // both change by under 1 %.
+        // keeps a workgroup's numbers on its XCD); with tiled_persist = 0, and for the second product where its tiles are
+        // long, one workgroup per number.  Measured on the first product of H 5120 / F 1536, 2048 rows per expert: 7 % (its
+        // tiles need a row gather first); on H 4096 / F 14336 under 1 %.  The fixed hand-out loses when the last column block of
+        // a super-tile row is partly empty (workgroups with no tile there idle), hence the choice of shapes above.
         auto d2l_grid = [&](const dim3& all, bool walk) {
             a.tiled_total = all.x;
             const uint32_t cap = a.tiled_persist * 256u;
@@ -1998,8 +1999,13 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         launch_reduce();
         mark(2, 0);
         mark(3, 1);
+        // The second product's workgroups walk where its tiles are short (at most 32 steps: the next tile's first loads hide
+        // behind the 256 KiB a tile stores).  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
+        // 1137 / 1104, 20 of H 5120 F 1536, 1638 rows 1642 / 1615, 160 of those 512 rows 4637 / 4581, 205 rows 2127 / 2126.
+        const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
+        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((gemm_d2l_kernel<2, 8, true, 256>), g, dim3(512), 163840, stream, a); }
         else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 8, false, 256>), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);

@@ -56,7 +56,7 @@ struct FfnPlan {
     bool tiled, halves, g1_xcd;
     uint32_t m_tile, ksplit, ksplit1, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
-    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_chunk, off_h, off_y;
+    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y;
 };
 
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -304,8 +304,7 @@ FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_t mappe
     p.off_tile = take(uint64_t(p.tiles_cap) * 16);
     p.off_ntiles = take(4);
     p.n_chunks = pairs > kRouteChunkThreshold ? uint32_t((pairs + kRouteChunkPairs - 1) / kRouteChunkPairs) : 0u;
-    p.off_chunk = take(uint64_t(p.n_chunks) * E * 4);
-    p.off_h = take(uint64_t(p.pairs_cap) * F * 2);
+    p.off_h = take(std::max<uint64_t>(uint64_t(p.pairs_cap) * F * 2, uint64_t(p.n_chunks) * E * 4));
     p.off_y = o;
     // the partial sums of the first product are read before the second product writes its own in the same place
     auto end = [&]() {
@@ -1231,7 +1230,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.pair_pos = reinterpret_cast<int32_t*>(w + p.off_pos);
     a.tile_rec = reinterpret_cast<int4*>(w + p.off_tile);
     a.n_tiles = reinterpret_cast<int32_t*>(w + p.off_ntiles);
-    a.chunk_count = reinterpret_cast<int32_t*>(w + p.off_chunk);
+    a.chunk_count = reinterpret_cast<int32_t*>(w + p.off_h);
     a.n_chunks = p.n_chunks;
     a.hbuf = reinterpret_cast<uint16_t*>(w + p.off_h);
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
@@ -1319,7 +1318,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.pair_pos = reinterpret_cast<int32_t*>(w + p.off_pos);
     a.tile_rec = reinterpret_cast<int4*>(w + p.off_tile);
     a.n_tiles = reinterpret_cast<int32_t*>(w + p.off_ntiles);
-    a.chunk_count = reinterpret_cast<int32_t*>(w + p.off_chunk);
+    a.chunk_count = reinterpret_cast<int32_t*>(w + p.off_h);
     a.n_chunks = p.n_chunks;
     a.hbuf = reinterpret_cast<uint16_t*>(w + p.off_h);
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);

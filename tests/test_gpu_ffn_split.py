@@ -153,3 +153,19 @@ def test_few_pairs_on_one_expert_on_absent_ones_and_on_ids_out_of_range():
 def test_halves_of_k_in_one_workgroup(kw):
     """Few or an odd number of strips: the two pairs of wavefronts of a workgroup share a strip and halve its k range."""
     run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=14)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=7168, top_k=2, hidden=64, ffn=128),                              # 14336 pairs: the most one workgroup groups
+    dict(tokens=7169, top_k=2, hidden=64, ffn=64, n_experts=40, n_slots=40, routing="zipf"),    # several, the last chunk short
+])
+def test_edges_of_the_grouping_by_several_workgroups(kw):
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=15)
+
+
+@pytest.mark.parametrize("shape", [(2048, 64, 2), (1856, 192, 5)])
+def test_walking_second_product(shape):
+    """Short K and more 256 x 256 tiles of the second product than workgroups: a workgroup takes several, ragged last
+    column tile and row tiles with few rows among them."""
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=9000, top_k=1, n_experts=shape[2], n_slots=shape[2], hidden=shape[0], ffn=shape[1])
+    run_ffn_case(cfg, seed=16)
