@@ -611,15 +611,14 @@ def bench_streaming(cfg, args):
         setup_s = time.time() - t1
         print("placement %s bound (%.0f s)" % (placement, setup_s), file=sys.stderr, flush=True)
 
-        # parity on the fly: one overlapped pass, then the slots of the last two layers' last waves
-        # still hold their experts; compare them with regenerated originals
+        # parity on the fly: one overlapped pass, then the slots of the pass's last two waves (one in each
+        # slot half) still hold their experts; compare them with regenerated originals
         proxy.run_pass()
         torch.cuda.synchronize()
         assert pool.device_errors() == 0
         if not args.no_check:
-            for layer in (cfg.n_layers - 2, cfg.n_layers - 1):
+            for layer, (w, slots) in [(layer, wave) for layer, (_, waves) in enumerate(proxy.plan) for wave in waves][-2:]:
                 w13, w2 = inputs.layer_weights(cfg, layer, device="cuda")
-                w, slots = proxy.plan[layer][1][-1]
                 for e, s_ in zip(w, slots):
                     assert torch.equal(pool.slot13(int(s_)), w13[int(e)].reshape(-1).view(torch.int16)), "decode mismatch"
                     assert torch.equal(pool.slot2(int(s_)), w2[int(e)].reshape(-1).view(torch.int16)), "decode mismatch"

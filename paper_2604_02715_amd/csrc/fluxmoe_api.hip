@@ -1057,6 +1057,7 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     const bool uploaded = !(decode_blocks > 0 && packed <= kInlineCmdBytes);
     hipEvent_t load_done = attachable(c->ev_load[layer], stream);      // nullptr: recorded at the end
     const bool capturing = !load_done;
+    if (c->profiling && (c->profile_mask & 1u)) load_done = nullptr;   // the kernel's span is to hold the kernel alone
     if (!uploaded) {
         uint8_t* w = reinterpret_cast<uint8_t*>(args.inline_words);
         std::memcpy(w, cmd, sizeof(DecodeCmd));
@@ -1248,13 +1249,15 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     if (c->load_valid[layer] && !rel_covers_load) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
     if (c->rel_valid[layer] && !load_covers_rel) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     const uint64_t gen = c->infer_gen[layer] + 1;
-    const hipEvent_t ev = c->ev_infer[layer][gen & 1], done = attachable(ev, stream);
+    const hipEvent_t ev = c->ev_infer[layer][gen & 1], free_ev = attachable(ev, stream);
+    const bool timed = c->profiling && (c->profile_mask & 0x1Eu);       // the kernels' spans are to hold the kernels alone
+    const hipEvent_t done = timed ? nullptr : free_ev;
     // a call that skips unmapped experts is a wave: the next wave's materialize, into other slots, may follow before the release
-    const hipEvent_t routed = done && (flags & FLUXMOE_FFN_SKIP_UNMAPPED) ? c->ev_routed[layer] : nullptr;
+    const hipEvent_t routed = free_ev && (flags & FLUXMOE_FFN_SKIP_UNMAPPED) ? c->ev_routed[layer] : nullptr;
     HIPCHECK(launch_ffn(a, c->n_cus, stream, done, routed, c->profiling ? ffn_span_hook : nullptr, c));
     if (!done) HIPCHECK(hipEventRecord(ev, stream));
     c->infer_gen[layer] = gen;
-    c->infer_seq[layer][gen & 1] = done ? ++c->seq : 0;
+    c->infer_seq[layer][gen & 1] = free_ev ? ++c->seq : 0;
     if (routed) c->routed_gen[layer] = gen;
     const int64_t lo = int64_t(layer) * c->d.n_experts, hi = lo + c->d.n_experts;
     for (uint32_t s = 0; s < c->d.n_slots; ++s)
