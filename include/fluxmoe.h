@@ -212,6 +212,7 @@ int fluxmoe_prefetch_host(fluxmoe_ctx* ctx, uint32_t layer, const int32_t* exper
  * owned that slot before is -1; nothing else changes.  n = 0 is valid and enqueues nothing.
  * If the layer's last fluxmoe_expert_ffn skipped unmapped experts (a wave) and has not been released since, the call
  * also waits until that FFN has read the page table: the next wave may be loaded into other slots while it runs.
+ * Under stream capture this wait is made between calls of one capture only.
  */
 int fluxmoe_materialize(fluxmoe_ctx* ctx, uint32_t layer, const int32_t* expert_ids,
                         uint32_t n, int32_t* page_table, const int32_t* dst_slots,

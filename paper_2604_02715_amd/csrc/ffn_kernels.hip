@@ -1854,7 +1854,8 @@ hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgr
     return hipGetLastError();
 }
 
-hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, SpanHook hook, void* user) {
+hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, bool attach_routed,
+                      SpanHook hook, void* user) {
     (void)n_cus;
     if (args.T == 0) return hipSuccess;
     FfnArgs a = args;
@@ -1862,6 +1863,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const size_t sh = (3 * size_t(a.E) + 1024) * sizeof(int32_t);
     // strip kernels, few pairs: the first product's workgroups do the grouping
     const bool routes_itself = !a.identity && !a.tiled && a.m_tile >= kRoutedPairs && uint64_t(a.T) * a.K <= kRoutedPairs;
+    const hipEvent_t with_routing = attach_routed ? routed : nullptr;
+    auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     mark(1, 1);
     if (routes_itself) {
     } else if (a.identity) {
@@ -1869,11 +1872,13 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
         hipLaunchKernelGGL(route_sort_kernel<true>, dim3(1), dim3(1024), sh, stream, a);
-        launch_done(route_scatter_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, routed, a);
+        launch_done(route_scatter_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, with_routing, a);
     } else {
-        launch_done(route_sort_kernel<false>, dim3(1), dim3(1024), sh, stream, routed, a);
+        launch_done(route_sort_kernel<false>, dim3(1), dim3(1024), sh, stream, with_routing, a);
     }
     mark(1, 0);
+    if (!routes_itself)
+        if (hipError_t e = record_routed(); e != hipSuccess) return e;
     auto launch_combine = [&](dim3 grid) {
         if (a.K <= 2) launch_done(combine_kernel<2>, grid, dim3(256), 0, stream, done, a);
         else if (a.K <= 4) launch_done(combine_kernel<4>, grid, dim3(256), 0, stream, done, a);
@@ -2020,14 +2025,16 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     // the strip kernels address activations and one expert matrix with 32-bit byte offsets
     if (uint64_t(a.T) * a.H * 2 >= (1ull << 32) || uint64_t(a.H) * a.F * 2 >= (1ull << 31)) return hipErrorInvalidValue;
     mark(2, 1);
-    if (routes_itself && a.halves) launch_done(gemm1_swiglu_kernel<4, true, true>, g1, dim3(256), 0, stream, routed, a);
-    else if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true, false>, g1, dim3(256), 0, stream, routed, a);
+    if (routes_itself && a.halves) launch_done(gemm1_swiglu_kernel<4, true, true>, g1, dim3(256), 0, stream, with_routing, a);
+    else if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true, false>, g1, dim3(256), 0, stream, with_routing, a);
     else if (a.halves) hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, true>), g1, dim3(256), 0, stream, a);
     else if (a.m_tile == 16) hipLaunchKernelGGL((gemm1_swiglu_kernel<1, false, false>), g1, dim3(256), 0, stream, a);
     else if (a.m_tile == 32) hipLaunchKernelGGL((gemm1_swiglu_kernel<2, false, false>), g1, dim3(256), 0, stream, a);
     else if (a.m_tile == 64) hipLaunchKernelGGL((gemm1_swiglu_kernel<4, false, false>), g1, dim3(256), 0, stream, a);
     else if (a.m_tile == 96) hipLaunchKernelGGL((gemm1_swiglu_kernel<6, false, false>), g1, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false>), g1, dim3(256), 0, stream, a);
+    if (routes_itself)
+        if (hipError_t e = record_routed(); e != hipSuccess) return e;
     launch_reduce();
     mark(2, 0);
     mark(3, 1);

@@ -105,6 +105,7 @@ struct fluxmoe_ctx {
     std::vector<hipEvent_t> ev_routed;
     std::vector<uint64_t> infer_gen;           // FFN calls of the layer so far; 0 = none
     std::vector<uint64_t> routed_gen;          // the call behind ev_routed, 0 = none
+    std::vector<uint64_t> routed_capture;      // the stream capture it was made in, 0 = none
     std::vector<uint8_t> load_valid, rel_valid;
     // Order in which the calls behind those events were made (0 = under stream capture or never).  A later call of a layer
     // has waited for the earlier event, so its own event covers both and one wait is enough: a wait for another stream
@@ -416,16 +417,21 @@ int resolve_static_scratch(int dev) {
     return FLUXMOE_OK;
 }
 
+// The capture a stream is part of (0: none).  kNoCaptureId where that cannot be told.
+constexpr uint64_t kNoCaptureId = ~0ull;
+uint64_t capture_of(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return kNoCaptureId;
+    }
+    return st == hipStreamCaptureStatusNone ? 0 : (st == hipStreamCaptureStatusActive && id ? id : kNoCaptureId);
+}
+
 // The event for a launch that is to complete with it, or nullptr where it has to be recorded after the launch instead:
 // under stream capture a recorded event becomes part of the graph's dependencies, an attached one does not.
-hipEvent_t attachable(hipEvent_t ev, hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    return st == hipStreamCaptureStatusNone ? ev : nullptr;
-}
+hipEvent_t attachable(hipEvent_t ev, hipStream_t s) { return capture_of(s) == 0 ? ev : nullptr; }
 
 hipError_t span_begin(fluxmoe_ctx* c, int kind, hipStream_t s) {
     c->span_open = c->profiling && ((c->profile_mask >> kind) & 1u);
@@ -486,6 +492,7 @@ int fluxmoe_create(const fluxmoe_desc* desc, fluxmoe_ctx** out_ctx) {
     c->load_valid.assign(d.n_layers, 0);
     c->infer_gen.assign(d.n_layers, 0);
     c->routed_gen.assign(d.n_layers, 0);
+    c->routed_capture.assign(d.n_layers, 0);
     c->rel_valid.assign(d.n_layers, 0);
     c->load_seq.assign(d.n_layers, 0);
     c->infer_seq.assign(d.n_layers, {0, 0});
@@ -1038,11 +1045,14 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     };
     for (const auto& [lr, g] : wait_reads)
         if (!(uint32_t(lr) == layer && rel_covers(g))) HIPCHECK(hipStreamWaitEvent(stream, c->ev_infer[lr][g & 1], 0));
-    // a wave of this layer still to be released: its FFN must have read the page table before this call's entries appear there
-    const uint64_t last_ffn = c->infer_gen[layer];
-    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn)) HIPCHECK(hipStreamWaitEvent(stream, c->ev_routed[layer], 0));
     if (c->rel_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     if (wait_copy) HIPCHECK(hipStreamWaitEvent(stream, c->ev_copied[half], 0));
+    // a wave of this layer still to be released: its FFN must have read the page table before this call's entries appear
+    // there.  Both outside capture, or both in one capture: an event cannot be waited for across (the runtime refuses the
+    // one direction and waits for nothing in the other), and ordering a graph against other work is its launcher's part.
+    const uint64_t last_ffn = c->infer_gen[layer];
+    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn) && c->routed_capture[layer] == capture_of(stream))
+        HIPCHECK(hipStreamWaitEvent(stream, c->ev_routed[layer], 0));
 
     DecodeArgs args{};
     args.lut[0] = reinterpret_cast<const uint32_t*>(c->ws + c->lut_off + (uint64_t(layer) * 2 + 0) * kLutBytes);
@@ -1249,16 +1259,17 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     if (c->load_valid[layer] && !rel_covers_load) HIPCHECK(hipStreamWaitEvent(stream, c->ev_load[layer], 0));
     if (c->rel_valid[layer] && !load_covers_rel) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     const uint64_t gen = c->infer_gen[layer] + 1;
-    const hipEvent_t ev = c->ev_infer[layer][gen & 1], free_ev = attachable(ev, stream);
+    const uint64_t capture = capture_of(stream);
+    const hipEvent_t ev = c->ev_infer[layer][gen & 1], free_ev = capture == 0 ? ev : nullptr;
     const bool timed = c->profiling && (c->profile_mask & 0x1Eu);       // the kernels' spans are to hold the kernels alone
     const hipEvent_t done = timed ? nullptr : free_ev;
     // a call that skips unmapped experts is a wave: the next wave's materialize, into other slots, may follow before the release
-    const hipEvent_t routed = free_ev && (flags & FLUXMOE_FFN_SKIP_UNMAPPED) ? c->ev_routed[layer] : nullptr;
-    HIPCHECK(launch_ffn(a, c->n_cus, stream, done, routed, c->profiling ? ffn_span_hook : nullptr, c));
+    const hipEvent_t routed = flags & FLUXMOE_FFN_SKIP_UNMAPPED ? c->ev_routed[layer] : nullptr;
+    HIPCHECK(launch_ffn(a, c->n_cus, stream, done, routed, capture == 0, c->profiling ? ffn_span_hook : nullptr, c));
     if (!done) HIPCHECK(hipEventRecord(ev, stream));
     c->infer_gen[layer] = gen;
     c->infer_seq[layer][gen & 1] = free_ev ? ++c->seq : 0;
-    if (routed) c->routed_gen[layer] = gen;
+    if (routed) { c->routed_gen[layer] = gen; c->routed_capture[layer] = capture; }
     const int64_t lo = int64_t(layer) * c->d.n_experts, hi = lo + c->d.n_experts;
     for (uint32_t s = 0; s < c->d.n_slots; ++s)
         if (c->slot_owner[s] >= lo && c->slot_owner[s] < hi) { c->slot_last_reader[s] = int32_t(layer); c->slot_reader_gen[s] = gen; }
@@ -1333,7 +1344,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
     a.tiled_persist = uint32_t(c->tune_tiled_persist);
-    HIPCHECK(launch_ffn(a, c->n_cus, stream, nullptr, nullptr, c->profiling ? ffn_span_hook : nullptr, c));
+    HIPCHECK(launch_ffn(a, c->n_cus, stream, nullptr, nullptr, false, c->profiling ? ffn_span_hook : nullptr, c));
     return FLUXMOE_OK;
 }
 

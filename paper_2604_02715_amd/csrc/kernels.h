@@ -62,8 +62,10 @@ constexpr uint32_t kRouteChunkPairs = 4096;
 // hook(user, kind, begin, stream) is called around every kernel when timing is on
 // (kinds: 1 grouping, 2 gate/up product + SwiGLU, 3 down product, 4 combine)
 typedef void (*SpanHook)(void* user, int kind, int begin, hipStream_t stream);
-// done: completes with the call's last kernel; routed: with the kernel that reads the page table last (nullptr: none)
-hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, SpanHook hook, void* user);
+// done: completes with the call's last kernel; routed: with the kernel that reads the page table last (nullptr: none).
+// done is attached to its launch; routed too if attach_routed, else it is recorded behind it (stream capture).
+hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, bool attach_routed,
+                      SpanHook hook, void* user);
 hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgroups, uint32_t iters,
                              hipStream_t stream);
 // The decode kernel's launch shape and memory accesses without its work (probe_kernels.hip): n_blocks blocks of

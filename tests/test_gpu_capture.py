@@ -1,0 +1,60 @@
+"""Waves on several streams under stream capture: the recorded graph must hold the order that the calls have outside
+capture, above all that a wave's FFN reads the page table before the next wave's entries appear there.  The inference
+stream is held back before every FFN inside the graph, so that a load without that edge would overtake it and its experts
+be taken twice.  Every replay is compared with an eager pass of another context, with eager work in between."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ffn as offn
+from paper_2604_02715_amd import harness, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tokens", [16, 48, 3600])          # grouped by the first product, by one workgroup, by several
+def test_a_captured_pass_in_waves_replays_as_the_eager_one(tokens):
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=12, n_slots=8, n_layers=2, tokens=tokens, top_k=4, ffn=128)
+    routings = [inputs.routing(cfg, layer) for layer in range(2)]
+    xs = [inputs.activations(cfg, layer) for layer in range(2)]
+    pools, proxies = [], []
+    try:
+        for _ in range(2):                                   # one pass is eager, the other pool's first pass is captured
+            pool, dense = build_pool(cfg)
+            pools.append(pool)
+            pool.reset_page_table()
+            pool.poison_slots()
+            outs = [torch.full((tokens, cfg.hidden), float("nan"), device="cuda") for _ in range(2)]
+            proxies.append(harness.StreamingProxy(pool, routings, [x.cuda() for x in xs], outs))
+        eager, captured = proxies
+        assert [len(waves) for _, waves in captured.plan] == [3, 3]
+        torch.cuda.synchronize()
+        eager.run_pass()
+        torch.cuda.synchronize()
+        for layer in range(2):
+            w13, w2 = dense[layer]
+            some = slice(0, min(tokens, 48))
+            want = offn.moe_ffn(inputs.bits_u16(xs[layer][some]), routings[layer][0][some], routings[layer][1][some],
+                                lambda e: (inputs.bits_u16(w13[e]), inputs.bits_u16(w2[e])))
+            assert offn.rel_frobenius(eager.outs[layer][some].cpu().numpy(), want) <= 1e-3
+
+        graph = torch.cuda.CUDAGraph()
+        infer, load = captured.infer_stream, captured.load_stream
+        with torch.cuda.graph(graph, stream=infer, capture_error_mode="relaxed"):
+            load.wait_stream(infer)
+            captured.run_pass(ffn_delay_cycles=300000)
+            infer.wait_stream(load)
+        for _ in range(4):
+            for out in captured.outs:
+                out.fill_(float("nan"))
+            pools[1].poison_slots()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(captured.outs, eager.outs))
+            assert (pools[1].page_table == -1).all()
+        assert pools[0].device_errors() == 0 and pools[1].device_errors() == 0
+    finally:
+        for pool in pools:
+            pool.close()
