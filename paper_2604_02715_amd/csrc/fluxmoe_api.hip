@@ -45,7 +45,8 @@ using namespace fluxmoe;
 namespace {
 constexpr int kRing = 4;
 // Events between kernels of this device: no fence towards the host and other devices, which holds the stream for another
-// 1.5 us (one token's FFN call 29.5 -> 27.8 us).  Loads keep it (a layer's load can end with copies), as do host-tier copies.
+// 1.5 us (one token's FFN call 29.5 -> 27.8 us).  Loads keep it (a layer's load can end with copies), as do host-tier copies
+// and the fork to a second stream (a command upload, staged blocks or the caller's own copies can lie in front of it).
 constexpr unsigned kOrderOnly = hipEventDisableTiming | hipEventDisableSystemFence;
 constexpr uint32_t kLutBytes = kLutEntries * 4;
 
@@ -396,7 +397,7 @@ int ensure_events(fluxmoe_ctx* c) {
     }
     for (int i = 0; i < kRing; ++i)
         HIPCHECK(hipEventCreateWithFlags(&c->ring_ev[i], hipEventDisableTiming));
-    HIPCHECK(hipEventCreateWithFlags(&c->ev_fork, kOrderOnly));
+    HIPCHECK(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
     HIPCHECK(hipEventCreateWithFlags(&c->ev_join, kOrderOnly));
     for (int i = 0; i < 2; ++i) {
         HIPCHECK(hipEventCreateWithFlags(&c->ev_copied[i], hipEventDisableTiming));

@@ -64,3 +64,34 @@ def test_rank_local_shard_two_streams(name):
             assert np.array_equal(got, parts[0])
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("staged", [False, True])
+@pytest.mark.parametrize("n_exp", [8, 160])       # a command inside the kernel arguments, and one that is uploaded
+def test_two_streams_behind_copies(n_exp, staged):
+    """Host-tier blocks and the job list reach the second stream's decode through the fork from the first: blocks copied
+    by the call itself on the first stream, or on a copy stream that only the first stream waits for.  Other experts with
+    each call, so that what a buffer held before would be the wrong bytes."""
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=n_exp, n_slots=n_exp // 2, host_fraction=0.75)
+    pool = harness.ExpertPool(cfg)
+    try:
+        w13, w2 = harness.make_layer_on_host(cfg)
+        _, n_host = pool.bind_layer(0, pool.encode_layer(0, w13, w2), cfg.host_fraction)
+        pool.bind_staging(2 * (n_host + 1) * 4096)
+        s1, s2, copy = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+        pool.reset_page_table()
+        for call in range(6):
+            ids = np.sort(np.random.default_rng(call).permutation(n_exp)[:n_exp // 2]).astype(np.int32)
+            slots = inputs.slot_permutation(n_exp // 2, "behind copies", call)
+            pool.poison_slots()
+            torch.cuda.synchronize()
+            if staged:
+                pool.prefetch_host(0, ids, copy)
+            pool.materialize_two_streams(0, ids, slots, s1, s2)
+            torch.cuda.synchronize()
+            assert pool.device_errors() == 0
+            for e, s_ in zip(ids, slots):
+                assert torch.equal(pool.slot13(int(s_)).cpu(), w13[int(e)].reshape(-1).view(torch.int16))
+                assert torch.equal(pool.slot2(int(s_)).cpu(), w2[int(e)].reshape(-1).view(torch.int16))
+    finally:
+        pool.close()
