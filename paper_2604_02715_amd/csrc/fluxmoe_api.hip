@@ -123,7 +123,10 @@ struct fluxmoe_ctx {
     StageHalf half[2];                      // layer l stages into half l & 1
     hipEvent_t ev_copied[2] = {};           // copies into the half have completed
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;   // fluxmoe_materialize_two_streams
-    int64_t half_reader[2] = {-1, -1};      // layer whose materialize read the half last (its ev_load), -1 = none
+    // The load event of the materialize that read the half last (nullptr: none) and the stream capture it was made in.  A
+    // later load of that layer covers it, except across a capture's border: that one records the spare event instead.
+    hipEvent_t half_read[2] = {}, half_spare[2] = {};
+    uint64_t half_capture[2] = {0, 0};
     bool copied_valid[2] = {false, false};  // ev_copied[h] has been recorded
     // launch shape of the decode kernel (FLUXMOE_DECODE_WAVES / FLUXMOE_DECODE_BLOCKS_PER_WAVE override)
     int tune_waves = 8;
@@ -401,6 +404,7 @@ int ensure_events(fluxmoe_ctx* c) {
     HIPCHECK(hipEventCreateWithFlags(&c->ev_join, kOrderOnly));
     for (int i = 0; i < 2; ++i) {
         HIPCHECK(hipEventCreateWithFlags(&c->ev_copied[i], hipEventDisableTiming));
+        HIPCHECK(hipEventCreateWithFlags(&c->half_spare[i], hipEventDisableTiming));
     }
     HIPCHECK(hipHostMalloc(reinterpret_cast<void**>(&c->pinned_cmd), size_t(kRing) * c->cmd_bytes,
                            hipHostMallocDefault));
@@ -533,6 +537,7 @@ int fluxmoe_destroy(fluxmoe_ctx* c) {
         for (auto e : c->ev_rel) if (e) (void)hipEventDestroy(e);
         for (int i = 0; i < kRing; ++i) if (c->ring_ev[i]) (void)hipEventDestroy(c->ring_ev[i]);
         for (int i = 0; i < 2; ++i) if (c->ev_copied[i]) (void)hipEventDestroy(c->ev_copied[i]);
+        for (int i = 0; i < 2; ++i) if (c->half_spare[i]) (void)hipEventDestroy(c->half_spare[i]);
         if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
         if (c->ev_join) (void)hipEventDestroy(c->ev_join);
         if (c->pinned_cmd) (void)hipHostFree(c->pinned_cmd);
@@ -893,7 +898,7 @@ static int stage_host_blocks(fluxmoe_ctx* c, uint32_t layer, const int32_t* ids,
     if (cursor > half_bytes)
         return set_error(FLUXMOE_ENOMEM, "staging half holds %llu bytes, layer %u needs %llu",
                          (unsigned long long)half_bytes, layer, (unsigned long long)cursor);
-    if (c->half_reader[h] >= 0) HIPCHECK(hipStreamWaitEvent(s, c->ev_load[c->half_reader[h]], 0));
+    if (c->half_read[h]) HIPCHECK(hipStreamWaitEvent(s, c->half_read[h], 0));
     // an earlier staging into this half may have been issued on another stream (a prefetch on the copy
     // stream, then a materialize of other experts that restages on its own stream): its copies must
     // have landed before these overwrite the half with a different layout
@@ -1066,8 +1071,10 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     const size_t jobs_bytes[2] = {cmd->n_jobs[0] * sizeof(DecodeJob), cmd->n_jobs[1] * sizeof(DecodeJob)};
     const size_t packed = sizeof(DecodeCmd) + jobs_bytes[0] + jobs_bytes[1] + touched.size() * 8;
     const bool uploaded = !(decode_blocks > 0 && packed <= kInlineCmdBytes);
-    hipEvent_t load_done = attachable(c->ev_load[layer], stream);      // nullptr: recorded at the end
-    const bool capturing = !load_done;
+    const uint64_t capture = capture_of(stream);
+    if (!need_host && c->half_read[half] == c->ev_load[layer] && c->half_capture[half] != capture)
+        std::swap(c->ev_load[layer], c->half_spare[half]);
+    hipEvent_t load_done = capture == 0 ? c->ev_load[layer] : nullptr; // nullptr: recorded at the end
     if (c->profiling && (c->profile_mask & 1u)) load_done = nullptr;   // the kernel's span is to hold the kernel alone
     if (!uploaded) {
         uint8_t* w = reinterpret_cast<uint8_t*>(args.inline_words);
@@ -1141,8 +1148,11 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     }
     if (!load_done) HIPCHECK(hipEventRecord(c->ev_load[layer], stream));
     c->load_valid[layer] = 1;
-    c->load_seq[layer] = capturing ? 0 : ++c->seq;
-    if (need_host) c->half_reader[half] = layer;
+    c->load_seq[layer] = capture ? 0 : ++c->seq;
+    if (need_host) {
+        c->half_read[half] = c->ev_load[layer];
+        c->half_capture[half] = capture;
+    }
     return FLUXMOE_OK;
 }
 

@@ -58,3 +58,42 @@ def test_a_captured_pass_in_waves_replays_as_the_eager_one(tokens):
     finally:
         for pool in pools:
             pool.close()
+
+
+def test_a_captured_load_leaves_the_staging_half_guarded():
+    """A load that reads the staging half is still waiting to run when another load of its layer, without host-tier blocks,
+    is captured; the next fetch into that half must wait for the first one all the same."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_layers=3, host_fraction=0.15)     # the down tensors of experts 0 to 3
+    pool, dense = build_pool(cfg, host_fraction=cfg.host_fraction)
+    try:
+        pool.bind_staging(64 << 20)
+        pool.reset_page_table()
+        pool.poison_slots()
+        load, side, copy = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+        pool.prefetch_host(0, [0, 1, 2, 3], copy)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(load):
+            torch.cuda._sleep(400000000)
+        pool.materialize(0, [0, 1, 2, 3], [0, 1, 2, 3], load)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            graph.capture_begin(capture_error_mode="relaxed")
+            pool.materialize(0, [6, 7], [6, 7], side)
+            graph.capture_end()
+        pool.prefetch_host(2, [0, 1, 2, 3], copy)
+        assert not load.query()                              # or the wait was not needed
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 0
+        for e in (0, 1, 2, 3, 6, 7):
+            assert torch.equal(pool.slot13(e).cpu(), dense[0][0][e].reshape(-1).view(torch.int16))
+            assert torch.equal(pool.slot2(e).cpu(), dense[0][1][e].reshape(-1).view(torch.int16))
+        pool.materialize(2, [0, 1, 2, 3], [3, 2, 1, 0], load)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 0
+        for e in range(4):
+            assert torch.equal(pool.slot2(3 - e).cpu(), dense[2][1][e].reshape(-1).view(torch.int16))
+    finally:
+        pool.close()
