@@ -106,13 +106,13 @@ struct fluxmoe_ctx {
     std::vector<hipEvent_t> ev_routed;
     std::vector<uint64_t> infer_gen;           // FFN calls of the layer so far; 0 = none
     std::vector<uint64_t> routed_gen;          // the call behind ev_routed, 0 = none
-    std::vector<uint64_t> routed_capture;      // the stream capture it was made in, 0 = none
     std::vector<uint8_t> load_valid, rel_valid;
     // Order in which the calls behind those events were made (0 = under stream capture or never).  A later call of a layer
     // has waited for the earlier event, so its own event covers both and one wait is enough: a wait for another stream
     // holds the queue for about 10 us even when the event completed long ago.
     std::vector<uint64_t> load_seq, rel_seq;
     std::vector<std::array<uint64_t, 2>> infer_seq;
+    std::vector<std::array<uint64_t, 2>> infer_capture;    // the stream capture the call behind ev_infer was made in, 0 = none
     uint64_t seq = 0;
     std::vector<int32_t> slot_last_reader; // layer whose FFN last read the slot, or -1
     std::vector<uint64_t> slot_reader_gen; // which of that layer's FFN calls it was
@@ -497,10 +497,10 @@ int fluxmoe_create(const fluxmoe_desc* desc, fluxmoe_ctx** out_ctx) {
     c->load_valid.assign(d.n_layers, 0);
     c->infer_gen.assign(d.n_layers, 0);
     c->routed_gen.assign(d.n_layers, 0);
-    c->routed_capture.assign(d.n_layers, 0);
     c->rel_valid.assign(d.n_layers, 0);
     c->load_seq.assign(d.n_layers, 0);
     c->infer_seq.assign(d.n_layers, {0, 0});
+    c->infer_capture.assign(d.n_layers, {0, 0});
     c->rel_seq.assign(d.n_layers, 0);
     compute_layout(c);
     if (const char* v = std::getenv("FLUXMOE_DECODE_WAVES")) {
@@ -1026,9 +1026,11 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
         touched.push_back(key);
         const int32_t lr = c->slot_last_reader[s];
         if (lr >= 0) {
-            // a layer's FFN calls run in order: one older than the last two is covered by the older of those
+            // a layer's FFN calls run in order: one older than the last two is covered by the older of those, and with a
+            // capture's border between the two by the last
             const uint64_t last = c->infer_gen[lr];
-            const std::pair<int32_t, uint64_t> read{lr, c->slot_reader_gen[s] >= last ? last : last - 1};
+            const bool older = c->slot_reader_gen[s] < last && c->infer_capture[lr][0] == c->infer_capture[lr][1];
+            const std::pair<int32_t, uint64_t> read{lr, older ? last - 1 : last};
             if (std::find(wait_reads.begin(), wait_reads.end(), read) == wait_reads.end()) wait_reads.push_back(read);
         }
         c->slot_last_reader[s] = -1;
@@ -1054,10 +1056,10 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     if (c->rel_valid[layer]) HIPCHECK(hipStreamWaitEvent(stream, c->ev_rel[layer], 0));
     if (wait_copy) HIPCHECK(hipStreamWaitEvent(stream, c->ev_copied[half], 0));
     // a wave of this layer still to be released: its FFN must have read the page table before this call's entries appear
-    // there.  Both outside capture, or both in one capture: an event cannot be waited for across (the runtime refuses the
-    // one direction and waits for nothing in the other), and ordering a graph against other work is its launcher's part.
+    // there.  Both outside capture, or both in one capture: a wait across a capture's border orders nothing (or is refused),
+    // and ordering a graph against other work is its launcher's part.
     const uint64_t last_ffn = c->infer_gen[layer];
-    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn) && c->routed_capture[layer] == capture_of(stream))
+    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn) && c->infer_capture[layer][last_ffn & 1] == capture_of(stream))
         HIPCHECK(hipStreamWaitEvent(stream, c->ev_routed[layer], 0));
 
     DecodeArgs args{};
@@ -1280,7 +1282,8 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     if (!done) HIPCHECK(hipEventRecord(ev, stream));
     c->infer_gen[layer] = gen;
     c->infer_seq[layer][gen & 1] = free_ev ? ++c->seq : 0;
-    if (routed) { c->routed_gen[layer] = gen; c->routed_capture[layer] = capture; }
+    c->infer_capture[layer][gen & 1] = capture;
+    if (routed) c->routed_gen[layer] = gen;
     const int64_t lo = int64_t(layer) * c->d.n_experts, hi = lo + c->d.n_experts;
     for (uint32_t s = 0; s < c->d.n_slots; ++s)
         if (c->slot_owner[s] >= lo && c->slot_owner[s] < hi) { c->slot_last_reader[s] = int32_t(layer); c->slot_reader_gen[s] = gen; }

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle import ffn as offn
+from paper_2604_02715_amd import binding as B
 from paper_2604_02715_amd import harness, inputs
 
 pytestmark = pytest.mark.gpu
@@ -95,5 +96,47 @@ def test_a_captured_load_leaves_the_staging_half_guarded():
         assert pool.device_errors() == 0
         for e in range(4):
             assert torch.equal(pool.slot2(3 - e).cpu(), dense[2][1][e].reshape(-1).view(torch.int16))
+    finally:
+        pool.close()
+
+
+def test_slots_last_read_before_a_capture_are_loaded_inside_it():
+    """The slots that an eager, timed FFN call read are taken by a captured load of another layer, after the layer's experts
+    were loaded elsewhere and its FFN captured: the load waits for the captured call, and not for the eager one, whose event
+    was recorded on the same stream and is refused inside a capture."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_layers=2, n_slots=16)
+    pool, _ = build_pool(cfg)
+    try:
+        pool.reset_page_table()
+        xs = [inputs.activations(cfg, layer).cuda() for layer in range(2)]
+        routings = [[torch.from_numpy(r).cuda() for r in inputs.routing(cfg, layer)] for layer in range(2)]
+        outs = [torch.zeros((cfg.tokens, cfg.hidden), device="cuda") for _ in range(2)]
+        every = np.arange(8)
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        pool.materialize(0, every, every)
+        B.fluxmoe_profile_enable(pool.ctx, True)
+        pool.expert_ffn(0, xs[0], *routings[0], outs[0], stream=side)
+        B.fluxmoe_profile_enable(pool.ctx, False)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            pool.materialize(0, every, 8 + every, side)
+            pool.expert_ffn(0, xs[0], *routings[0], outs[0], stream=side)
+            pool.materialize(1, every, every, side)
+            pool.expert_ffn(1, xs[1], *routings[1], outs[1], stream=side)
+        results = []
+        for _ in range(3):
+            pool.poison_slots()
+            for out in outs:
+                out.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            results.append([out.clone() for out in outs])
+        pool.expert_ffn(0, xs[0], *routings[0], outs[0])         # all sixteen experts are resident now
+        pool.expert_ffn(1, xs[1], *routings[1], outs[1])
+        torch.cuda.synchronize()
+        assert all(torch.equal(got, out) for result in results for got, out in zip(result, outs))
+        assert pool.device_errors() == 0
     finally:
         pool.close()
