@@ -1132,7 +1132,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int kTile = kTM * kLdsPitch;
 
     // global -> register staging.  A: 8 lanes cover one row's 64 k; rows tid / 8 + 32 i.
-    const uint16_t* a_base = MODE == 1 ? a.tokens : a.hbuf;
+    const uint16_t* a_base = MODE == 1 ? a.tokens : a.hbuf + size_t(uint32_t(t.row0)) * a.F;
     uint32_t a_off[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -1141,7 +1141,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             const int32_t pr = a.sorted_pair[t.row0 + r];
             a_off[i] = (uint32_t(pr) / a.K) * a.H + 8 * (tid & 7);
         } else {
-            a_off[i] = uint32_t(t.row0 + r) * a.F + 8 * (tid & 7);
+            a_off[i] = uint32_t(r) * a.F + 8 * (tid & 7);
         }
     }
     const int a_dst = (tid >> 3) * kLdsPitch + 8 * (tid & 7);          // + 32 i rows
@@ -1420,7 +1420,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // per step) from bases that are uniform over the workgroup, the step range, where the results go.
     struct TileState {
         uint32_t a_off[kDma], b_off[kDma];   // until finish_state(): a_off = pair numbers of the lane's rows as loaded
-                                             // (first product) or their row numbers (second), b_off unset
+                                             // (first product) or their rows in the tile (second), b_off unset
         const uint8_t* a_base;
         const uint8_t* b_base;
         int32_t rows, row0;
@@ -1446,13 +1446,15 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const uint32_t step_hi = uint32_t(uint64_t(n_steps_all) * (split + 1) / n_split);
         const uint32_t k_begin = step_lo * kTK;
         s.n_steps = MODE == 1 ? 0u : step_hi - step_lo;        // >= 1: the host keeps the splits <= K / 64
-        s.a_base = MODE == 1 ? nullptr : reinterpret_cast<const uint8_t*>(MODE == 3 ? a.tokens : a.hbuf) + size_t(k_begin) * 2;
+        // rows of h are counted from the tile's first: offsets inside all of h would not fit 32 bits
+        s.a_base = MODE == 1 ? nullptr
+                             : reinterpret_cast<const uint8_t*>(MODE == 3 ? a.tokens : a.hbuf + size_t(uint32_t(s.row0)) * a.F) + size_t(k_begin) * 2;
         const int lane = fresh_lane();
 #pragma unroll
         for (int i = 0; i < kDma; ++i) {
             const int r_lds = 8 * (wave * kDma + i) + (lane >> 3);                 // row of the A tile
             const int32_t r = min(r_lds, s.rows - 1);
-            s.a_off[i] = kFirst ? uint32_t(a.sorted_pair[s.row0 + r]) : uint32_t(s.row0 + r);
+            s.a_off[i] = kFirst ? uint32_t(a.sorted_pair[s.row0 + r]) : uint32_t(r);
         }
         const size_t slot_u = s.valid ? size_t(slot) : 0u;
         s.b_base = reinterpret_cast<const uint8_t*>(
