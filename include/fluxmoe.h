@@ -300,6 +300,7 @@ int fluxmoe_expert_ffn_static(fluxmoe_ctx* ctx, uint32_t layer, const uint16_t* 
  *   flags: 0 or FLUXMOE_FFN_ACCUMULATE (out += result, e.g. after fluxmoe_expert_ffn)
  * Uses the bound workspace (fluxmoe_ffn_workspace_bytes with shared_expert != 0) and the
  * stream's order only; it takes no part in the slot event protocol.
+ * T <= 65535 and T * hidden * 2 bytes under 4 GiB, as above (EINVAL, nothing enqueued).
  */
 int fluxmoe_shared_expert_ffn(fluxmoe_ctx* ctx, const uint16_t* w13, const uint16_t* w2,
                               const uint16_t* tokens, uint32_t T, float* out, uint32_t flags,

@@ -1325,6 +1325,8 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     if (!w13 || !w2 || !tokens || !out) return set_error(FLUXMOE_EINVAL, "NULL argument");
     if (flags & ~1u) return set_error(FLUXMOE_EINVAL, "only FLUXMOE_FFN_ACCUMULATE is accepted");
     if (T > 65535) return set_error(FLUXMOE_EINVAL, "T too large");
+    if (uint64_t(T) * c->d.hidden * 2 >= (1ull << 32))
+        return set_error(FLUXMOE_EINVAL, "tokens (T * hidden * 2 bytes) must stay under 4 GiB");
     if ((uintptr_t(w13) | uintptr_t(w2) | uintptr_t(tokens) | uintptr_t(out)) & 15)
         return set_error(FLUXMOE_EINVAL, "pointers must be 16-byte aligned");
     // this model's shapes, a single always-mapped expert

@@ -4,7 +4,8 @@ import pytest
 import torch
 
 from oracle import ffn as offn
-from paper_2604_02715_amd import inputs
+from paper_2604_02715_amd import binding as B
+from paper_2604_02715_amd import harness, inputs
 from test_gpu_ffn import TOL
 
 pytestmark = pytest.mark.gpu
@@ -37,5 +38,21 @@ def test_rows_of_h_past_four_gigabytes(variant, top_k, ffn, monkeypatch):
         want = offn.moe_ffn(inputs.bits_u16(x[torch.from_numpy(some)]), ids[some], g[some],
                             lambda e: (inputs.bits_u16(w13[e]), inputs.bits_u16(w2[e])))
         assert offn.rel_frobenius(out.cpu().numpy()[some], want) <= TOL
+    finally:
+        pool.close()
+
+
+def test_tokens_past_four_gigabytes_are_refused():
+    """T * hidden * 2 bytes: the limit of the routed call holds for the shared expert too; nothing is enqueued."""
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=2, n_slots=1, hidden=32832, ffn=64, tokens=1, top_k=1, shared_expert=True)
+    pool = harness.ExpertPool(cfg)
+    try:
+        some = pool.slots13.data_ptr()
+        tokens = (1 << 32) // (2 * cfg.hidden) + 1
+        for call in (lambda: B.fluxmoe_shared_expert_ffn(pool.ctx, some, some, some, tokens, some, 0, 0),
+                     lambda: B.fluxmoe_expert_ffn(pool.ctx, 0, some, tokens, some, some, 1, some, some, 0, 0)):
+            with pytest.raises(B.FluxmoeError) as ei:
+                call()
+            assert ei.value.status == -1 and "4 GiB" in str(ei.value)
     finally:
         pool.close()
