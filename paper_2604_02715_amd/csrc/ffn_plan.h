@@ -1,0 +1,201 @@
+// Launch plan of the expert FFN: which kernels, tiles and K splits a call takes, and how its scratch is laid out.
+// Host arithmetic only, without HIP, so that the rules can be tested on their own.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <cstdlib>
+
+namespace fluxmoe {
+
+// Batches with more pairs than this are counted and scattered by one workgroup per kRouteChunkPairs pairs
+// around the single workgroup that scans the experts.  Microseconds, one workgroup / several (three launches), 8 to 512
+// experts: 12288 pairs 17.3 / 18.3, 16384 20.7 / 18.7, 32768 35.4 / 20.6, 163840 - / 31.
+constexpr uint32_t kRouteChunkThreshold = 14336;
+constexpr uint32_t kRouteChunkPairs = 4096;
+
+struct FfnPlan {
+    bool tiled, halves, g1_xcd;
+    uint32_t m_tile, ksplit, ksplit1, pairs_cap, tiles_cap, n_chunks;
+    uint64_t bytes;
+    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y;
+};
+
+inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
+
+// Shapes and launch parameters the FFN plan depends on (a routed layer, or one always-mapped expert
+// for the shared-expert call).
+struct FfnShape {
+    uint64_t E, H, F;
+    int n_cus, tiled_waves;
+};
+
+// split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.
+inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_t mapped, bool split, uint64_t limit) {
+    FfnPlan p{};
+    const uint64_t E = c.E, H = c.H, F = c.F;
+    const uint64_t pairs = uint64_t(T) * K;
+    const uint64_t groups = std::max<uint64_t>(1, std::min<uint64_t>(E, pairs));
+    const uint64_t avg = (pairs + groups - 1) / groups;
+    const uint64_t n_cus = uint64_t(std::max(c.n_cus, 1));
+    // what a call with only `mapped` experts resident multiplies
+    const uint64_t act = mapped ? std::min<uint64_t>(mapped, E) : E;
+    const uint64_t pairs_act = std::max<uint64_t>(1, pairs * act / E);
+    const uint64_t groups_act = std::max<uint64_t>(1, std::min(act, pairs_act));
+    // Row tile of the weight-streaming kernels: every extra tile of an expert streams that expert's
+    // weights again, and routing can be far from even, so tiles hold up to 128 rows (the kernel takes a
+    // cheaper body for tiles with fewer rows).  With so many rows per expert that even 128-row tiles are
+    // exceeded often (an expert's row count taken as normal with mean and variance avg), 128-row tiles
+    // stay the choice while the expected number of passes per expert is below 1.6 - what one pass of
+    // the LDS-tiled MFMA kernels (256-row tiles, k extents that are multiples of 64) costs relative to
+    // a streaming pass at these sizes.
+    auto p_over = [&](double m) { return 0.5 * std::erfc((m + 0.5 - double(avg)) / std::sqrt(2.0 * double(avg))); };
+    const bool tileable = H % 64 == 0 && F % 64 == 0;
+    p.m_tile = 128;
+    if (p_over(128) > 0.02 && 1.0 + p_over(128) + p_over(256) + p_over(384) > 1.6 && tileable)
+        p.m_tile = 256;
+    bool forced = false;
+    if (const char* v = std::getenv("FLUXMOE_FFN_MTILE")) {
+        const int m = std::atoi(v);
+        if (m == 16 || m == 32 || m == 64 || m == 96 || m == 128 || (m == 256 && tileable)) { p.m_tile = uint32_t(m); forced = true; }
+    }
+    p.tiled = p.m_tile == 256;
+    // Where the launch would leave CUs without a workgroup.  All figures: microseconds per call, weights out of HBM.
+    if (split && !forced && tileable && c.tiled_waves == 2) {
+        const double avg_act = double(pairs_act) / double(groups_act);
+        const bool few_strips = 2 * ((F + 255) / 256) * groups_act <= n_cus;       // strip workgroups before any K split
+        if (p.tiled) {
+            // A single expert in 256 x 256 tiles: tiles of 128 x 128, two workgroups per CU, while the large ones make one and
+            // a half rounds at most.  H 5120 F 1536, tiles of 256 / 128: 160 rows 56 / 53, 512 71 / 68, 2048 160 / 153,
+            // 8192 470 / 460, 16384 792 / 921; H 2048 F 512: 256 rows 46 / 30, 2048 67 / 51.  Several experts with several
+            // row tiles each stay (20 of H 5120 F 1536, 205 rows each: 383 / 451).
+            if (groups_act == 1 && 2 * ((pairs_act + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
+        } else if (few_strips && groups_act > 1 && 0.5 * std::erfc((128.5 - avg_act) / std::sqrt(2.0 * avg_act)) > 0.02) {
+            // Experts that often need a second 128-row strip tile: 8 of H 4096 F 1792, 128 rows each: strips 172, tiles of 256 121.
+            p.tiled = true;
+            p.m_tile = 256;
+        } else if (few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20) : H <= 2048 && avg_act >= 16)) {
+            // Row counts that make a matrix tile worth while and K too short for the strips' start-up, strips / tiles of 128:
+            // one expert of H 5120 F 1536: 64 rows 47 / 46, 128 59 / 51; of H 2048 F 512: 32 rows 28 / 25; 32 experts of that
+            // shape, 20 rows each 61 / 60, 40 71 / 65, 94 85 / 75, a quarter of 128 experts under skewed routing 91 / 70.
+            // Longer K favours the strips: 20 of H 5120 F 384, 51 rows each: 79 / 99; 8 of H 4096 F 1792, 64 rows: 101 / 109.
+            p.tiled = true;
+            p.m_tile = 128;
+        }
+    }
+    p.pairs_cap = uint32_t(std::max<uint64_t>(pairs, 1));
+    p.tiles_cap = uint32_t(pairs / p.m_tile + groups + 1);
+    // Split K of the second product (strip kernels).  One workgroup (four strips, one per SIMD) fits on a
+    // CU at a time, so the launch runs in rounds of n_cus workgroups; the split is the one with the
+    // smallest estimated time in units of k rows per workgroup: rounds x (rows per split + a fixed
+    // start-up cost) + the FP32 partials it writes and combine_kernel reads back.
+    const uint64_t strips2 = (H + 127) / 128;
+    const uint64_t est_tiles = std::max<uint64_t>(1, std::max<uint64_t>(pairs / p.m_tile, std::min(groups, pairs)));
+    uint64_t ks = 1, best_cost = ~0ull;
+    for (uint64_t k = 1; k <= 8 && k <= std::max<uint64_t>(1, F / 256); ++k) {
+        const uint64_t wgs = (strips2 + 3) / 4 * est_tiles * k;
+        const uint64_t rounds = (wgs + n_cus - 1) / n_cus;
+        const uint64_t partials = k > 1 ? k * pairs * H * 8 / (n_cus * 1024) : 0;
+        const uint64_t cost = rounds * ((F + k - 1) / k + 384) + partials;
+        if (cost < best_cost) { best_cost = cost; ks = k; }
+    }
+    p.ksplit = uint32_t(ks);
+    p.ksplit1 = 1;
+    // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when
+    // split k ways.  A tile costs 3 us to start; a step 1.4 us (256 x 256, one workgroup per CU), or 0.56 us (128 x 128)
+    // alone on a CU and 0.88 us for each of two.  Partial sums are written and read at 10 TB/s (mostly in the caches).
+    const uint64_t row_tiles = groups_act == 1 ? (pairs_act + p.m_tile - 1) / p.m_tile
+                                               : std::max(groups_act, pairs_act / p.m_tile + groups_act / 2);
+    auto tile_ns = [&](uint64_t tiles, uint64_t steps, uint64_t k) {
+        const uint64_t wgs = tiles * k, per = (steps + k - 1) / k;
+        if (p.m_tile == 256) return (wgs + n_cus - 1) / n_cus * (per * 1400 + 3000);
+        const uint64_t full = wgs / (2 * n_cus), rest = wgs % (2 * n_cus);
+        return full * (per * 880 + 3000) + (rest == 0 ? 0 : per * (rest <= n_cus ? 560 : 880) + 3000);
+    };
+    if (p.tiled) {
+        // When the second product has fewer tiles than the chip has CUs, the LDS-direct kernels split K so that about one
+        // workgroup per CU runs (each split keeps at least 8 steps of 64)
+        p.ksplit = 1;
+        if (p.m_tile == 128) {
+            uint64_t best = ~0ull;
+            for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 512 <= F && row_tiles * ((H + 127) / 128) * k <= 2 * n_cus)); ++k) {
+                const uint64_t cost = tile_ns(row_tiles * ((H + 127) / 128), F / 64, k) + k * pairs_act * H * 8 / 10000;
+                if (cost < best) { best = cost; p.ksplit = uint32_t(k); }
+            }
+        } else if (c.tiled_waves == 2 || c.tiled_waves == 1) {
+            const uint64_t tiles2 = groups * ((avg + 255) / 256) * ((H + 255) / 256);
+            uint64_t k2 = std::max<uint64_t>(1, n_cus / tiles2);
+            k2 = std::min<uint64_t>(k2, 8);
+            k2 = std::min<uint64_t>(k2, std::max<uint64_t>(1, F / 512));
+            p.ksplit = uint32_t(k2);
+        }
+    }
+    // K split of the first product, for launches that would leave most of the chip without a workgroup: the FP32 partial
+    // sums of gate and up cost a write, a read and a launch.  Measured, whole FFN call: one token, top-10 of 512 experts,
+    // H 2048 F 512 (20 workgroups unsplit) 63 -> 36 us; 333 tokens, top-4 of 64, H 2880 F 360 (128) 140 -> 116 us.  Layers
+    // whose tiles fill the chip stay unsplit (8 experts of H 4096 F 14336: 448 workgroups).
+    if (split && (!p.tiled || c.tiled_waves == 2)) {
+        const uint64_t partial_bytes = pairs_act * 2 * F * 8;             // written and read, per split
+        uint64_t best = ~0ull;
+        if (!p.tiled) {
+            // units of k rows of a workgroup (about 30 ns each when the memory system is not saturated)
+            const uint64_t strips1 = (F + 127) / 128, tiles1 = std::max<uint64_t>(pairs_act / p.m_tile, groups_act);
+            auto consider = [&](bool halves) {
+                const uint64_t wgs1 = (halves ? strips1 : (strips1 + 1) / 2) * tiles1, unit = halves ? 256 : 128;
+                for (uint64_t k = 1; k <= 16 && (k == 1 || k * 256 <= H); ++k) {
+                    const uint64_t k_per = align_up((H + k - 1) / k, unit);    // the kernel splits at multiples of that
+                    if ((H + k_per - 1) / k_per != k) continue;
+                    const uint64_t rounds = (wgs1 * k + n_cus - 1) / n_cus;
+                    const uint64_t cost = rounds * (std::min(k_per, H) / (halves ? 2 : 1) + 128) + (k > 1 ? 128 + k * partial_bytes / (n_cus * 1024) : 0);
+                    if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); p.halves = halves; }
+                }
+            };
+            consider(false);
+            if (p.m_tile == 128 && !forced && (strips1 % 2 || (strips1 + 1) / 2 * tiles1 < n_cus)) consider(true);
+        } else {
+            const uint64_t cols = p.m_tile / 2;
+            const uint64_t tiles1 = row_tiles * ((F + cols - 1) / cols), room = p.m_tile == 256 ? n_cus : 2 * n_cus;
+            for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 512 <= H && tiles1 * k <= room)); ++k) {
+                const uint64_t cost = tile_ns(tiles1, H / 64, k) + (k > 1 ? 4500 + k * partial_bytes / 10000 : 0);
+                if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); }
+            }
+        }
+    }
+    // Strips whose rows are not whole 128-byte lines share a line with their neighbours: on one XCD they find it in its L2
+    // (64 experts of H 2880 F 360, 333 tokens, top-4: 112 -> 106 us).  With aligned rows, or two strips a workgroup, it is
+    // 0.5 to 2 % slower.  Enough (tile, split) units to fill the 8 XCDs evenly.
+    p.g1_xcd = p.halves && F % 64 != 0 && groups_act * p.ksplit1 >= 64;
+    uint64_t o = 0;
+    auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
+    p.off_count = take((E + 1) * 4);
+    p.off_offset = take((E + 2) * 4);
+    p.off_sorted = take(uint64_t(p.pairs_cap) * 4);
+    p.off_pos = take(uint64_t(p.pairs_cap) * 4);
+    p.off_tile = take(uint64_t(p.tiles_cap) * 16);
+    p.off_ntiles = take(4);
+    p.n_chunks = pairs > kRouteChunkThreshold ? uint32_t((pairs + kRouteChunkPairs - 1) / kRouteChunkPairs) : 0u;
+    p.off_h = take(std::max<uint64_t>(uint64_t(p.pairs_cap) * F * 2, uint64_t(p.n_chunks) * E * 4));
+    p.off_y = o;
+    // the partial sums of the first product are read before the second product writes its own in the same place
+    auto end = [&]() {
+        const uint64_t y = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4 : 0;
+        return p.off_y + align_up(std::max(y, part), 256);
+    };
+    if (split) {
+        while (p.ksplit1 > 1 && end() > limit) --p.ksplit1;
+        while (p.tiled && p.m_tile == 128 && p.ksplit > 1 && end() > limit) --p.ksplit;
+    }
+    p.bytes = end();
+    return p;
+}
+
+// limit: bytes the scratch may take (the call's buffer; the size query leaves it open): the splits give way to it, and then
+// the small tiles do, so a buffer that holds the plan without them is always enough.
+// mapped: experts of the layer known to be resident, 0 = not known (it steers speed, not what is accepted).
+inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
+    const FfnPlan p = plan_ffn_rules(c, T, K, mapped, true, limit);
+    return p.bytes <= limit ? p : plan_ffn_rules(c, T, K, mapped, false, limit);
+}
+
+}  // namespace fluxmoe

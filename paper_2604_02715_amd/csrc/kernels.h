@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "decode_args.h"
+#include "ffn_plan.h"
 
 namespace fluxmoe {
 
@@ -52,12 +53,6 @@ struct FfnArgs {
     uint32_t tiled_group;        // super-rows of the LDS-direct gate/up kernel that share a column block in time;
                                  // 0 = launch_ffn derives it from the rows per expert
 };
-
-// Batches with more pairs than this are counted and scattered by one workgroup per kRouteChunkPairs pairs
-// around the single workgroup that scans the experts.  Microseconds, one workgroup / several (three launches), 8 to 512
-// experts: 12288 pairs 17.3 / 18.3, 16384 20.7 / 18.7, 32768 35.4 / 20.6, 163840 - / 31.
-constexpr uint32_t kRouteChunkThreshold = 14336;
-constexpr uint32_t kRouteChunkPairs = 4096;
 
 // hook(user, kind, begin, stream) is called around every kernel when timing is on
 // (kinds: 1 grouping, 2 gate/up product + SwiGLU, 3 down product, 4 combine)
