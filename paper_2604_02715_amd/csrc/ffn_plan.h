@@ -14,6 +14,8 @@ namespace fluxmoe {
 // experts: 12288 pairs 17.3 / 18.3, 16384 20.7 / 18.7, 32768 35.4 / 20.6, 163840 - / 31.
 constexpr uint32_t kRouteChunkThreshold = 14336;
 constexpr uint32_t kRouteChunkPairs = 4096;
+// Row tiles a call may have (the y dimension of the strip kernels' grid).
+constexpr uint32_t kMaxRowTiles = 65535;
 
 struct FfnPlan {
     bool tiled, halves, g1_xcd;
@@ -191,11 +193,12 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
 }
 
 // limit: bytes the scratch may take (the call's buffer; the size query leaves it open): the splits give way to it, and then
-// the small tiles do, so a buffer that holds the plan without them is always enough.
+// the small tiles do, so a buffer that holds the plan without them is always enough.  The small tiles also give way where
+// there would be too many of them.
 // mapped: experts of the layer known to be resident, 0 = not known (it steers speed, not what is accepted).
 inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
     const FfnPlan p = plan_ffn_rules(c, T, K, mapped, true, limit);
-    return p.bytes <= limit ? p : plan_ffn_rules(c, T, K, mapped, false, limit);
+    return p.bytes <= limit && p.tiles_cap <= kMaxRowTiles ? p : plan_ffn_rules(c, T, K, mapped, false, limit);
 }
 
 }  // namespace fluxmoe

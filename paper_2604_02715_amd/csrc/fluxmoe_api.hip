@@ -1057,7 +1057,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     if (p.bytes > w_bytes)
         return set_error(FLUXMOE_ENOMEM, "%s holds %llu bytes, T=%u K=%u needs %llu", w_name,
                          (unsigned long long)w_bytes, T, K, (unsigned long long)p.bytes);
-    if (p.tiles_cap > 65535) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
+    if (p.tiles_cap > kMaxRowTiles) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     FfnArgs a{};
     a.tokens = tokens;
@@ -1152,7 +1152,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     if (c->pool_ws_bytes + p.bytes > c->ws_bytes)
         return set_error(FLUXMOE_ENOMEM, "workspace has %zu bytes, the shared expert with T=%u needs %llu",
                          c->ws_bytes, T, (unsigned long long)(c->pool_ws_bytes + p.bytes));
-    if (p.tiles_cap > 65535) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
+    if (p.tiles_cap > kMaxRowTiles) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     uint8_t* w = c->ws + c->pool_ws_bytes;
     FfnArgs a{};

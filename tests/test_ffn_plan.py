@@ -142,3 +142,19 @@ def test_splits_of_the_first_product(rules):
     assert rules.plan(T=1, K=10, E=512, H=2048, F=512, waves=8).ksplit1 == token.ksplit1       # strips: no matter
     shared = rules.plan(T=512, K=1, E=1, H=5120, F=1536)
     assert shared.tiled and shared.ksplit1 > 1 and rules.plan(T=512, K=1, E=1, H=5120, F=1536, waves=8).ksplit1 == 1
+
+
+def test_small_tiles_do_not_run_out_of_tile_numbers(rules):
+    """The launcher takes 65535 row tiles at most, a call with more is refused: the choice of tiles never makes it so."""
+    c = dict(T=65535, K=200, E=200, H=64, F=64)                              # 13.1 million pairs
+    assert rules.plain(**c).tiles_cap <= 65535
+    for mapped in (0, 1, 2, 200):
+        p = rules.plan(**c, mapped=mapped)
+        check(p, dict(c, waves=2))
+        assert p.tiles_cap <= 65535
+    rng = random.Random(6)
+    for _ in range(2000):
+        c = random_call(rng)
+        c.update(T=rng.randrange(20000, 65536), K=rng.randrange(1, min(c["E"], 400) + 1))
+        if rules.plain(**c).tiles_cap <= 65535:
+            assert rules.plan(**c).tiles_cap <= 65535
