@@ -72,7 +72,8 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             // a half rounds at most.  H 5120 F 1536, tiles of 256 / 128: 160 rows 56 / 53, 512 71 / 68, 2048 160 / 153,
             // 8192 470 / 460, 16384 792 / 921; H 2048 F 512: 256 rows 46 / 30, 2048 67 / 51.  Several experts with several
             // row tiles each stay (20 of H 5120 F 1536, 205 rows each: 383 / 451).
-            if (groups_act == 1 && 2 * ((pairs_act + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
+            // T rows, not the mean of what one of several experts gets: a batch may be routed to it alone.
+            if (groups_act == 1 && 2 * ((uint64_t(T) + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
         } else if (few_strips && groups_act > 1 && 0.5 * std::erfc((128.5 - avg_act) / std::sqrt(2.0 * avg_act)) > 0.02) {
             // Experts that often need a second 128-row strip tile: 8 of H 4096 F 1792, 128 rows each: strips 172, tiles of 256 121.
             p.tiled = true;

@@ -158,3 +158,10 @@ def test_small_tiles_do_not_run_out_of_tile_numbers(rules):
         c.update(T=rng.randrange(20000, 65536), K=rng.randrange(1, min(c["E"], 400) + 1))
         if rules.plain(**c).tiles_cap <= 65535:
             assert rules.plan(**c).tiles_cap <= 65535
+
+
+def test_a_single_resident_expert_that_every_token_takes(rules):
+    """128 x 128 tiles lose at many rows (H 5120 F 1536, 16384 rows: 921 us against 792).  With one of several experts resident
+    its share of the pairs is not known; no token lists it twice, so T rows must still be few enough."""
+    of = lambda T, E, mapped: rules.plan(T=T, K=2, E=E, H=5120, F=1536, mapped=mapped).m_tile
+    assert of(16384, 8, 1) == 256 and of(8193, 8, 1) == 256 and of(8192, 8, 1) == 128
