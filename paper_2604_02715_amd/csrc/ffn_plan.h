@@ -78,10 +78,15 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             // Experts that often need a second 128-row strip tile: 8 of H 4096 F 1792, 128 rows each: strips 172, tiles of 256 121.
             p.tiled = true;
             p.m_tile = 256;
-        } else if (few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20) : H <= 2048 && avg_act >= 16)) {
+        } else if (few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20)
+                                                  : 8 * groups_act <= n_cus && avg_act >= 16 && H <= (mapped && mapped < E ? 2048u : 1024u))) {
             // Row counts that make a matrix tile worth while and K too short for the strips' start-up, strips / tiles of 128:
-            // one expert of H 5120 F 1536: 64 rows 47 / 46, 128 59 / 51; of H 2048 F 512: 32 rows 28 / 25; 32 experts of that
-            // shape, 20 rows each 61 / 60, 40 71 / 65, 94 85 / 75, a quarter of 128 experts under skewed routing 91 / 70.
+            // one expert of H 5120 F 1536: 64 rows 47 / 46, 128 59 / 51; of H 2048 F 512: 32 rows 28 / 25.  32 experts of
+            // H 1024 F 256, 40 rows each: 39 / 36, behind a kernel that filled the caches with other data 46 / 48; 87 rows 59 / 40
+            // and 65 / 52.  The tiles bear such caches badly: 32 of H 2048 F 512, 16 rows each: 55 / 58 and 62 / 93, and 64 of
+            // them, 20 rows: 85 / 106 and 91 / 154.  A wave (part of the layer resident) runs beside the next wave's load,
+            // and there they win, as a strip workgroup needs 128 KiB of LDS on a CU and a tile 80: a pass over three layers of
+            // 128 of H 2048 F 512 in waves of 32, 1024 tokens: 2217 / 2040; in waves of 64 they lose (1620 / 1690).
             // Longer K favours the strips: 20 of H 5120 F 384, 51 rows each: 79 / 99; 8 of H 4096 F 1792, 64 rows: 101 / 109.
             p.tiled = true;
             p.m_tile = 128;

@@ -123,12 +123,14 @@ def test_tiles_of_experts_that_are_resident(rules):
     """The rules look at the resident experts: waves of a quarter of 128 small experts, H 2048 F 512."""
     shape = dict(K=10, E=128, H=2048, F=512)
     of = lambda T, mapped, **kw: (lambda p: (bool(p.tiled), p.m_tile))(rules.plan(T=T, mapped=mapped, **dict(shape, **kw)))
-    assert of(256, 32) == (True, 128)                    # 20 rows each, 128 strip workgroups
-    assert of(256, 64) == (True, 128) and of(256, 65) == (False, 128)        # 2 * 2 * 64 = 256 CUs' worth
+    assert of(256, 32) == (True, 128) and of(256, 33) == (False, 128)        # 20 rows each, an eighth of the CUs
     assert of(256, 0) == (False, 128) and of(256, 128) == (False, 128)       # the whole layer fills the chip
     assert of(204, 32) == (False, 128)                   # 15.9 rows each
     assert of(256, 32, H=2112) == (False, 128)           # longer K: strips
-    assert of(1638, 32) == (True, 256)                   # 128 rows each: a second strip tile too often
+    assert of(64, 32, E=32) == (False, 128) and of(64, 0, E=32) == (False, 128)        # no wave: every expert is resident
+    assert of(64, 32, E=32, H=1024) == (True, 128) and of(64, 0, E=32, H=1088) == (False, 128)
+    assert of(1638, 64) == (True, 256) and of(1638, 65) == (False, 128)      # 128 rows each: a second strip tile too often
+    assert of(1638, 2) == (True, 256) and of(1638, 1) == (True, 128)         # one: small tiles
     assert of(1200, 32) == (True, 128)
 
 
