@@ -572,7 +572,7 @@ __device__ __forceinline__ bool tile_info(const FfnArgs& a, uint32_t tile, TileI
 // flight per workgroup, twice the workgroups, no empty second strip where their number is odd, and no partial sums.
 // 64 experts of H 2880 F 360, 333 tokens, top-4 (three strips; split two ways over K before): 115 -> 106 us a call with the
 // numbering of workgroups below, one token's top-10 of 512 experts (H 2048 F 512) 28.9 -> 28.4.
-template <int MI, bool LISTED, bool HALVES>
+template <int MI, bool LISTED, bool HALVES, bool SPLIT>
 __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileInfo& t, float (*xch)[64], uint16_t* abuf, const int32_t* pair_list,
                                                   uint32_t col_wg, uint32_t split) {
     const int lane = threadIdx.x & 63;
@@ -612,13 +612,15 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
     g.zero();
     const uint32_t n_blocks = (k_end - k_begin) / kUnit;
     g.template run_shared<HALVES>(reinterpret_cast<const uint8_t*>(a.tokens), aoff, abuf, w, a.H, col_ok ? n0 : a.F - 8, a.F, k_begin, n_blocks, lane, wave, uint32_t(pair));
-    // what is left is less than a block, or two with HALVES: one to each pair, the tail to the second
-    uint32_t k_left = k_begin + n_blocks * kUnit, k_stop = k_end;
+    // what is left is less than a block, or two with HALVES: one to each pair, the tail to the second (written as a remainder,
+    // so that the compiler knows how short it is and drops the long loop of run())
+    uint32_t left = (k_end - k_begin) % kUnit, k_left = k_end - left;
     if (HALVES) {
-        const uint32_t mid = min(k_end, k_left + kABlock);
-        if (pair == 0) k_stop = mid; else k_left = mid;
+        const uint32_t first = min(left, uint32_t(kABlock));
+        if (pair == 0) left = first;
+        else { k_left += first; left -= first; }
     }
-    g.run(arow, w + (col_ok ? n0 : a.F - 8), a.F, k_left, k_stop, lane);
+    g.run(arow, w + (col_ok ? n0 : a.F - 8), a.F, k_left, k_left + left, lane);
 
     if (HALVES) {                                 // the second pair's sums are added to the first's
         mfma_drain();
@@ -642,7 +644,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
         __syncthreads();                          // the memory is used again below
     }
 
-    if (a.ksplit1 > 1) {                          // partial sums of both matrices, added up by swiglu_reduce_kernel
+    if (SPLIT && a.ksplit1 > 1) {                 // partial sums of both matrices, added up by swiglu_reduce_kernel
         if (!col_ok || (HALVES && pair == 1)) return;
         float* part = a.ybuf + (size_t(split) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
 #pragma unroll
@@ -696,7 +698,9 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
 // pair per lane, and the first ones write the lists the later kernels read.  A decode step of a token or two is launches:
 // the grouping kernel was 6 of the 34 us of one token's top-10 of 512 experts (H 2048, F 512), 29 without it.
 // Tiles are the distinct experts in order of first appearance (one tile each: no more rows than a strip tile holds).
-template <int MI, bool ROUTE, bool HALVES>
+// SPLIT: a launch that may split K.  Without it the store of partial sums is not compiled in: next to the other epilogue it
+// costs the 128-row kernel 61 spilled registers instead of 8 (8 experts of H 4096 F 14336, 128 rows each: 794 -> 775 us a call).
+template <int MI, bool ROUTE, bool HALVES, bool SPLIT>
 __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     // the accumulator exchange of the epilogue ([pair][mi, c, r][lane] floats) reuses the memory of
     // the shared A blocks: every wavefront has passed the last block's barrier by then
@@ -768,11 +772,11 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     } else if (!tile_info(a, tile_no, t)) {
         return;                                       // uniform over the workgroup
     }
-    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
-    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
-    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
-    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
-    else gemm1_swiglu_body<MI, ROUTE, HALVES>(a, t, xch, abuf, pair_list, col_wg, split);
+    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
+    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
+    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
+    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
+    else gemm1_swiglu_body<MI, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
 }
 
 // y[split][row][n] = h[row][k range] W2[k range][n]
@@ -2027,14 +2031,16 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     // the strip kernels address activations and one expert matrix with 32-bit byte offsets
     if (uint64_t(a.T) * a.H * 2 >= (1ull << 32) || uint64_t(a.H) * a.F * 2 >= (1ull << 31)) return hipErrorInvalidValue;
     mark(2, 1);
-    if (routes_itself && a.halves) launch_done(gemm1_swiglu_kernel<4, true, true>, g1, dim3(256), 0, stream, with_routing, a);
-    else if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true, false>, g1, dim3(256), 0, stream, with_routing, a);
-    else if (a.halves) hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, true>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 16) hipLaunchKernelGGL((gemm1_swiglu_kernel<1, false, false>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 32) hipLaunchKernelGGL((gemm1_swiglu_kernel<2, false, false>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 64) hipLaunchKernelGGL((gemm1_swiglu_kernel<4, false, false>), g1, dim3(256), 0, stream, a);
-    else if (a.m_tile == 96) hipLaunchKernelGGL((gemm1_swiglu_kernel<6, false, false>), g1, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false>), g1, dim3(256), 0, stream, a);
+    if (routes_itself && a.halves) launch_done(gemm1_swiglu_kernel<4, true, true, true>, g1, dim3(256), 0, stream, with_routing, a);
+    else if (routes_itself) launch_done(gemm1_swiglu_kernel<4, true, false, true>, g1, dim3(256), 0, stream, with_routing, a);
+    else if (a.halves && a.ksplit1 > 1) hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, true, true>), g1, dim3(256), 0, stream, a);
+    else if (a.halves) hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, true, false>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 16) hipLaunchKernelGGL((gemm1_swiglu_kernel<1, false, false, true>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 32) hipLaunchKernelGGL((gemm1_swiglu_kernel<2, false, false, true>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 64) hipLaunchKernelGGL((gemm1_swiglu_kernel<4, false, false, true>), g1, dim3(256), 0, stream, a);
+    else if (a.m_tile == 96) hipLaunchKernelGGL((gemm1_swiglu_kernel<6, false, false, true>), g1, dim3(256), 0, stream, a);
+    else if (a.ksplit1 > 1) hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false, true>), g1, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false, false>), g1, dim3(256), 0, stream, a);
     if (routes_itself)
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
     launch_reduce();
