@@ -68,12 +68,14 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         const double avg_act = double(pairs_act) / double(groups_act);
         const bool few_strips = 2 * ((F + 255) / 256) * groups_act <= n_cus;       // strip workgroups before any K split
         if (p.tiled) {
-            // A single expert in 256 x 256 tiles: tiles of 128 x 128, two workgroups per CU, while the large ones make one and
-            // a half rounds at most.  H 5120 F 1536, tiles of 256 / 128: 160 rows 56 / 53, 512 71 / 68, 2048 160 / 153,
-            // 8192 470 / 460, 16384 792 / 921; H 2048 F 512: 256 rows 46 / 30, 2048 67 / 51.  Several experts with several
-            // row tiles each stay (20 of H 5120 F 1536, 205 rows each: 383 / 451).
+            // A single expert in 256 x 256 tiles: tiles of 128 x 128, two workgroups per CU, while the large ones fill three
+            // quarters of the CUs at most.  H 5120 F 1536, tiles of 256 / 128: 512 rows (24 large tiles) 70 / 67, 2048 (96)
+            // 157 / 144, 4096 (192) 262 / 235, 16384 792 / 921; H 2048 F 512: 256 rows 46 / 29, 2048 65 / 48.  H 4096 F 1792,
+            // 4096 rows (224): 194 / 220; H 4096 F 4096, 2048 rows (256): 199 / 225.  Up to 512 rows the weights' way out of HBM
+            // bounds the call and two workgroups keep more loads in flight, up to a round and a half: H 4096 F 14336, 512 rows
+            // (224): 255 / 237.  Several experts with several row tiles each stay (20 of H 5120 F 1536, 205 rows: 383 / 451).
             // T rows, not the mean of what one of several experts gets: a batch may be routed to it alone.
-            if (groups_act == 1 && 2 * ((uint64_t(T) + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
+            if (groups_act == 1 && (T <= 512 ? 2 : 4) * ((uint64_t(T) + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
         } else if (few_strips && groups_act > 1 && 0.5 * std::erfc((128.5 - avg_act) / std::sqrt(2.0 * avg_act)) > 0.02) {
             // Experts that often need a second 128-row strip tile: 8 of H 4096 F 1792, 128 rows each: strips 172, tiles of 256 121.
             p.tiled = true;

@@ -110,11 +110,13 @@ def test_random_calls_at_any_buffer_size(rules):
 
 
 def test_tiles_of_a_single_expert(rules):
-    """128 x 128 tiles while 256 x 256 ones make a round and a half at most: 2 * row tiles * column tiles <= 3 * 256."""
+    """128 x 128 tiles while 256 x 256 ones fill three quarters of the CUs at most: 4 * row tiles * column tiles <= 3 * 256."""
     of = lambda T, **kw: (lambda p: (bool(p.tiled), p.m_tile))(rules.plan(T=T, K=1, E=1, H=5120, F=1536, **kw))
-    assert of(8192) == (True, 128) and of(8193) == (True, 256)               # 32 and 33 row tiles, 12 column tiles
+    assert of(4096) == (True, 128) and of(4097) == (True, 256)               # 16 and 17 row tiles, 12 column tiles
     assert of(64) == (True, 128) and of(63) == (False, 128)                  # fewer rows: weight strips
-    assert of(8192, waves=1) == (True, 256) and of(64, waves=8) == (False, 128)
+    wide = lambda T, F: rules.plan(T=T, K=1, E=1, H=4096, F=F).m_tile        # up to 512 rows: a round and a half
+    assert wide(512, 24576) == 128 and wide(512, 24640) == 256 and wide(513, 8192) == 128 and wide(513, 8256) == 256
+    assert of(4096, waves=1) == (True, 256) and of(64, waves=8) == (False, 128)
     big = lambda T, F: rules.plan(T=T, K=1, E=1, H=5120, F=F).tiled          # strips again where the matrices are large
     assert big(64, 2176) and not big(64, 2240)                               # 6 H F on both sides of 64 MiB
 
@@ -166,4 +168,4 @@ def test_a_single_resident_expert_that_every_token_takes(rules):
     """128 x 128 tiles lose at many rows (H 5120 F 1536, 16384 rows: 921 us against 792).  With one of several experts resident
     its share of the pairs is not known; no token lists it twice, so T rows must still be few enough."""
     of = lambda T, E, mapped: rules.plan(T=T, K=2, E=E, H=5120, F=1536, mapped=mapped).m_tile
-    assert of(16384, 8, 1) == 256 and of(8193, 8, 1) == 256 and of(8192, 8, 1) == 128
+    assert of(16384, 8, 1) == 256 and of(4097, 8, 1) == 256 and of(4096, 8, 1) == 128
