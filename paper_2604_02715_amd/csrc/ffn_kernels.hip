@@ -49,6 +49,21 @@ constexpr uint32_t kRoutedPairs = 64;   // batches of up to this many pairs are 
 constexpr int kNonTemporal = 2;    // cache policy operand of the buffer loads: bit 1 = nt
 
 // ------------------------------------------------------------------ routing / grouping
+// K splits of the first product that work (the launch covers ksplit1), for weight strips and tiles of 128 x 128
+__device__ __forceinline__ uint32_t first_splits(const FfnArgs& a, uint32_t n_tiles) { return n_tiles <= a.split_tiles ? a.ksplit1 : 1u; }
+// and for tiles of 256 x 256 into n_tiles[1], by one wavefront of the grouping kernel with a candidate in each lane: done by
+// the product's workgroups it held each back for half a microsecond, and there are up to seven for a CU (131 -> 144 us a call).
+__device__ __forceinline__ void choose_splits(const FfnArgs& a, uint32_t n_tiles, uint32_t rows, uint32_t lane) {
+    uint32_t k = lane + 1;
+    float cost = k <= a.ksplit1 ? tiled_cost(SplitShape{a.H, a.F, a.n_cus}, n_tiles, rows, k) : 3e38f;
+    for (int d = 4; d > 0; d >>= 1) {        // at most 8 splits
+        const float c2 = __shfl_xor(cost, d);
+        const uint32_t k2 = uint32_t(__shfl_xor(int(k), d));
+        if (c2 < cost || (c2 == cost && k2 < k)) { cost = c2; k = k2; }
+    }
+    if (lane == 0) a.n_tiles[1] = int32_t(n_tiles <= a.split_tiles ? a.ksplit1 : k);
+}
+
 // Row tiles are handed out by size class: the body a tile runs and the time it takes grow with its rows,
 // and a launch ends when its last workgroup does, so the tiles with the most rows are numbered (and
 // therefore started) first and the many small ones fill in behind them.
@@ -143,7 +158,7 @@ __global__ __launch_bounds__(1024) void route_scatter_kernel(FfnArgs a) {
     }
 }
 
-template <bool CHUNKED>
+template <bool CHUNKED, bool CHOOSE>
 __global__ __launch_bounds__(1024) void route_sort_kernel(FfnArgs a) {
     extern __shared__ int32_t sh[];          // count[E], cursor[E], slot[E], scan scratch
     int32_t* count = sh;
@@ -252,6 +267,7 @@ __global__ __launch_bounds__(1024) void route_sort_kernel(FfnArgs a) {
         a.expert_offset[a.E] = row_base;
         a.n_tiles[0] = min(n_tiles, int32_t(a.tiles_cap));
     }
+    if (CHOOSE && tid < 64) choose_splits(a, uint32_t(n_tiles), uint32_t(row_base), uint32_t(tid));
     if (CHUNKED) return;                     // route_scatter_kernel puts the pairs in place
     __syncthreads();
     auto place = [&](uint32_t p, int32_t e) {
@@ -288,6 +304,7 @@ __global__ __launch_bounds__(256) void route_identity_kernel(FfnArgs a) {
         a.expert_offset[0] = 0;
         a.expert_offset[1] = int32_t(a.T);
         a.n_tiles[0] = int32_t(n_tiles);
+        a.n_tiles[1] = int32_t(a.ksplit1);
     }
 }
 
@@ -574,7 +591,7 @@ __device__ __forceinline__ bool tile_info(const FfnArgs& a, uint32_t tile, TileI
 // numbering of workgroups below, one token's top-10 of 512 experts (H 2048 F 512) 28.9 -> 28.4.
 template <int MI, bool LISTED, bool HALVES, bool SPLIT>
 __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileInfo& t, float (*xch)[64], uint16_t* abuf, const int32_t* pair_list,
-                                                  uint32_t col_wg, uint32_t split) {
+                                                  uint32_t col_wg, uint32_t split, uint32_t n_split) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));   // uniform: scalar address arithmetic
     const int pair = wave >> 1;
@@ -605,8 +622,8 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
     }
     // K split `split` multiplies k rows [k_begin, k_end): whole A blocks, the last split what remains
     constexpr uint32_t kUnit = HALVES ? 2 * kABlock : kABlock;
-    const uint32_t k_per = ((a.H + a.ksplit1 - 1) / a.ksplit1 + kUnit - 1) / kUnit * kUnit;
-    const uint32_t k_begin = min(a.H, split * k_per);
+    const uint32_t k_per = SPLIT ? ((a.H + n_split - 1) / n_split + kUnit - 1) / kUnit * kUnit : a.H;
+    const uint32_t k_begin = SPLIT ? min(a.H, split * k_per) : 0u;
     const uint32_t k_end = min(a.H, k_begin + k_per);
     StripGemm<MI> g;
     g.zero();
@@ -644,7 +661,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
         __syncthreads();                          // the memory is used again below
     }
 
-    if (SPLIT && a.ksplit1 > 1) {                 // partial sums of both matrices, added up by swiglu_reduce_kernel
+    if (SPLIT && n_split > 1) {                   // partial sums of both matrices, added up by swiglu_reduce_kernel
         if (!col_ok || (HALVES && pair == 1)) return;
         float* part = a.ybuf + (size_t(split) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
 #pragma unroll
@@ -724,6 +741,7 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
         tile_no = unit / a.ksplit1;
         split = unit % a.ksplit1;
     }
+    const uint32_t n_tiles_all = SPLIT && !ROUTE ? uint32_t(a.n_tiles[0]) : 0u;      // travels together with the tile's record
     if (ROUTE) {
         static_assert(!ROUTE || (16 * MI >= int(kRoutedPairs) && kRoutedPairs == 64), "a pair per lane, an expert's pairs in one tile");
         const int lane = threadIdx.x & 63;
@@ -772,11 +790,13 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     } else if (!tile_info(a, tile_no, t)) {
         return;                                       // uniform over the workgroup
     }
-    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
-    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
-    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
-    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
-    else gemm1_swiglu_body<MI, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split);
+    const uint32_t n_split = !SPLIT ? 1u : (ROUTE ? a.ksplit1 : first_splits(a, n_tiles_all));
+    if (SPLIT && split >= n_split) return;
+    if (MI > 1 && t.rows <= 16) gemm1_swiglu_body<1, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split, n_split);
+    else if (MI > 2 && t.rows <= 32) gemm1_swiglu_body<2, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split, n_split);
+    else if (MI > 4 && t.rows <= 64) gemm1_swiglu_body<4, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split, n_split);
+    else if (MI > 6 && t.rows <= 96) gemm1_swiglu_body<6, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split, n_split);
+    else gemm1_swiglu_body<MI, ROUTE, HALVES, SPLIT>(a, t, xch, abuf, pair_list, col_wg, split, n_split);
 }
 
 // y[split][row][n] = h[row][k range] W2[k range][n]
@@ -858,12 +878,13 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(FfnArgs a) {
     const uint32_t per_row = a.F / 8;
     const uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x;
     const uint32_t row = uint32_t(i / per_row), n0 = 8u * uint32_t(i % per_row);
-    if (row >= uint32_t(a.expert_offset[a.E])) return;        // rows past the pairs whose expert is mapped
+    const uint32_t n_split = a.tiled && a.m_tile == 256 ? uint32_t(a.n_tiles[1]) : first_splits(a, uint32_t(a.n_tiles[0]));
+    if (n_split == 1 || row >= uint32_t(a.expert_offset[a.E])) return;       // h is there already; rows past the pairs whose expert is mapped
     float g[8], u[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) g[c] = u[c] = 0.f;
     const float* part = a.ybuf + size_t(row) * 2 * a.F + n0;
-    for (uint32_t sp = 0; sp < a.ksplit1; ++sp, part += size_t(a.pairs_cap) * 2 * a.F) {
+    for (uint32_t sp = 0; sp < n_split; ++sp, part += size_t(a.pairs_cap) * 2 * a.F) {
         const float4 g0 = *reinterpret_cast<const float4*>(part), g1 = *reinterpret_cast<const float4*>(part + 4);
         const float4 u0 = *reinterpret_cast<const float4*>(part + a.F), u1 = *reinterpret_cast<const float4*>(part + a.F + 4);
         g[0] += g0.x; g[1] += g0.y; g[2] += g0.z; g[3] += g0.w; g[4] += g1.x; g[5] += g1.y; g[6] += g1.z; g[7] += g1.w;
@@ -1327,7 +1348,7 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // WALK: a workgroup takes several tiles one after the other (see the tile loop at the end); without it the
 // launch has one workgroup per tile number and the code for the upcoming tile falls away.
 // MODE 1: h = SwiGLU(X W1, X W3).  MODE 2: y = h W2, K split ksplit ways.  MODE 3: the first product with K split
-// ksplit1 ways, FP32 partial sums of gate and up instead of h (swiglu_reduce_kernel adds them up).
+// up to ksplit1 ways, FP32 partial sums of gate and up instead of h (swiglu_reduce_kernel adds them up), or h if that is 1.
 // TILE: rows and columns of a workgroup's tile.  256: one workgroup per CU (160 KiB of LDS).  128, with WAVES = 4 as 2 x 2
 // of 64 x 64: two per CU, a quarter of the work per tile, for products whose 256 x 256 tiles leave most CUs without one.
 template <int MODE, int WAVES, bool WALK, int TILE>
@@ -1360,7 +1381,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     const uint32_t n_sn = (n_ct + sn - 1) >> sn_log2;
     // Workgroups go to the 8 XCDs round robin, so (super-tile, K split) pair number p runs on XCD
     // p % 8: the splits of one super-tile land on different XCDs
-    const uint32_t n_split = MODE == 2 ? a.ksplit : (MODE == 3 ? a.ksplit1 : 1u);
+    const uint32_t n_split = MODE == 2 ? a.ksplit : (MODE == 1 ? 1u : (TILE == 256 ? uint32_t(a.n_tiles[1]) : first_splits(a, n_rt)));
     // Super-tiles are taken in groups of tiled_group super-rows (the row tiles of about one expert): for
     // each column block of the group, its super-rows run next to each other in time on different XCDs,
     // so the expert's weights for that column block leave HBM once and the other XCDs find them in the
@@ -1637,7 +1658,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // epilogue.  D layout of the 32x32 MFMA: column q = lane % 32, rows 8 (r / 4) + 4 (lane / 32) + r % 4;
     // fragment j of this wavefront holds tile columns 128 wn + 32 j + q (MODE 2) or, in MODE 1,
     // gate (j = 0, 1) and up (j = 2, 3) of h columns 64 wn + 32 (j & 1) + q
-    if (MODE == 1) {
+    if (MODE == 1 || (MODE == 3 && n_split == 1)) {
         // a lane holds one h column; neighbouring lanes swap values (DPP) so that even lanes store
         // columns (q, q + 1) of an even row and odd lanes columns (q - 1, q) of the next row: 4-byte
         // stores instead of 2-byte ones
@@ -1871,16 +1892,19 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const bool routes_itself = !a.identity && !a.tiled && a.m_tile >= kRoutedPairs && uint64_t(a.T) * a.K <= kRoutedPairs;
     const hipEvent_t with_routing = attach_routed ? routed : nullptr;
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
+    const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
+    if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
     mark(1, 1);
     if (routes_itself) {
     } else if (a.identity) {
         hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
     } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
-        hipLaunchKernelGGL(route_sort_kernel<true>, dim3(1), dim3(1024), sh, stream, a);
+        if (chooses) hipLaunchKernelGGL((route_sort_kernel<true, true>), dim3(1), dim3(1024), sh, stream, a);
+        else hipLaunchKernelGGL((route_sort_kernel<true, false>), dim3(1), dim3(1024), sh, stream, a);
         launch_done(route_scatter_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, with_routing, a);
     } else {
-        launch_done(route_sort_kernel<false>, dim3(1), dim3(1024), sh, stream, with_routing, a);
+        launch_done(chooses ? route_sort_kernel<false, true> : route_sort_kernel<false, false>, dim3(1), dim3(1024), sh, stream, with_routing, a);
     }
     mark(1, 0);
     if (!routes_itself)

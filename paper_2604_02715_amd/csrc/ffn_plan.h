@@ -17,9 +17,35 @@ constexpr uint32_t kRouteChunkPairs = 4096;
 // Row tiles a call may have (the y dimension of the strip kernels' grid).
 constexpr uint32_t kMaxRowTiles = 65535;
 
+#if defined(__HIPCC__)
+#define FLUXMOE_HD __host__ __device__
+#else
+#define FLUXMOE_HD
+#endif
+
+// Splitting the first product's K pays while the row tiles leave CUs without work.  The plan goes by the mean of what an expert
+// gets; skewed routing makes more tiles, and then every split is another round.  So the kernels, which see the count,
+// decide: up to split_tiles row tiles the plan's ksplit1 splits work; past them a single one, and with 256 x 256 tiles the
+// number with the least tiled_cost.  Microseconds per call, always ksplit1 / decided (never split): 1024 tokens that all take
+// the two resident of 8 experts of H 4096 F 3584 266 / 212 (206), the four resident of 160 of H 5120 F 1536 480 / 380 (340),
+// 4096 tokens on the eight resident of 128 of H 2048 F 512 445 / 344 (335); 20 experts of H 5120 F 384, 410 rows each 250 / 230
+// (236), where the model sees a second round that the tile count does not show.
+struct SplitShape {
+    uint32_t H, F, n_cus;
+};
+// Nanoseconds of the first product in 256 x 256 tiles with K split k ways: 3 us to start a tile, 1.4 us a step of 64 k, partial
+// sums at 10 TB/s.  (Super-tile of 4 x 8 tiles, split) pairs are dealt to the 8 XCDs; the fullest XCD counts.
+FLUXMOE_HD inline float tiled_cost(const SplitShape& s, uint32_t n_tiles, uint32_t rows, uint32_t k) {
+    const uint32_t n_ct = (s.F + 127) / 128, per_xcd = s.n_cus / 8 ? s.n_cus / 8 : 1;
+    const uint32_t pairs = ((n_tiles + 3) / 4) * ((n_ct + 7) / 8) * k;
+    const uint32_t tiles = (pairs + 7) / 8 * (n_tiles < 4 ? n_tiles : 4u) * (n_ct < 8 ? n_ct : 8u);
+    const float steps = float((s.H / 64 + k - 1) / k);
+    return float((tiles + per_xcd - 1) / per_xcd) * (steps * 1400.f + 3000.f) + (k > 1 ? 4500.f + float(k) * float(rows) * float(s.F) * 16.f / 10000.f : 0.f);
+}
+
 struct FfnPlan {
     bool tiled, halves, g1_xcd;
-    uint32_t m_tile, ksplit, ksplit1, pairs_cap, tiles_cap, n_chunks;
+    uint32_t m_tile, ksplit, ksplit1, split_tiles, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
     uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y;
 };
@@ -183,7 +209,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     p.off_sorted = take(uint64_t(p.pairs_cap) * 4);
     p.off_pos = take(uint64_t(p.pairs_cap) * 4);
     p.off_tile = take(uint64_t(p.tiles_cap) * 16);
-    p.off_ntiles = take(4);
+    p.off_ntiles = take(8);
     p.n_chunks = pairs > kRouteChunkThreshold ? uint32_t((pairs + kRouteChunkPairs - 1) / kRouteChunkPairs) : 0u;
     p.off_h = take(std::max<uint64_t>(uint64_t(p.pairs_cap) * F * 2, uint64_t(p.n_chunks) * E * 4));
     p.off_y = o;
@@ -194,6 +220,16 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     };
     if (split) {
         while (p.ksplit1 > 1 && end() > limit) --p.ksplit1;
+        if (p.ksplit1 > 1 && p.tiled && p.m_tile == 256) {
+            const SplitShape s{uint32_t(H), uint32_t(F), uint32_t(n_cus)};
+            const auto cost = [&](uint32_t k) { return tiled_cost(s, uint32_t(row_tiles), uint32_t(pairs_act), k); };
+            p.split_tiles = uint32_t(row_tiles);
+            for (uint32_t k = 1; k < p.ksplit1; ++k) if (cost(k) <= cost(p.ksplit1)) p.split_tiles = 0;
+        } else if (p.ksplit1 > 1) {
+            const uint64_t cols = p.tiled ? (F + 63) / 64 : (p.halves ? (F + 127) / 128 : (F + 255) / 256);
+            const uint64_t planned = p.tiled ? row_tiles : std::max<uint64_t>(pairs_act / p.m_tile, groups_act);
+            p.split_tiles = uint32_t(std::max((n_cus - 1) / cols, planned));
+        }
         while (p.tiled && p.m_tile == 128 && p.ksplit > 1 && end() > limit) --p.ksplit;
     }
     p.bytes = end();

@@ -27,7 +27,7 @@ struct FfnArgs {
     int32_t* sorted_pair;        // [pairs_cap]  pair index (t * K + k), grouped by expert
     int32_t* pair_pos;           // [pairs_cap]  position of a pair in sorted order, -1 = skipped
     int4* tile_rec;              // [tiles_cap]  (expert, first sorted row, rows, slot); rows = 0 past the last tile
-    int32_t* n_tiles;            // [1]
+    int32_t* n_tiles;            // [2]  row tiles; K splits of the first product that work (256 x 256 tiles)
     int32_t* chunk_count;        // [n_chunks][E] in the place of hbuf, which is written later.  Large batches: pairs per (chunk of kRouteChunkPairs pairs, expert),
                                  // turned into the chunk's first position inside the expert's rows by the grouping kernel
     uint32_t n_chunks;           // 0: the grouping kernel counts and scatters the pairs itself (one workgroup)
@@ -36,8 +36,10 @@ struct FfnArgs {
                                  // [ksplit1][pairs_cap][2][F] (gate, up) lie here before the second product runs
     uint32_t* error_word;
     uint32_t pairs_cap, tiles_cap, m_tile, ksplit;
-    uint32_t ksplit1;            // K splits of the first product; 1: SwiGLU in its epilogue, more: FP32 partial sums
-                                 // that swiglu_reduce_kernel adds up
+    uint32_t ksplit1;            // most K splits of the first product (the launch covers as many, first_splits says how many work).
+                                 // 1: SwiGLU in its epilogue, more: FP32 partial sums that swiglu_reduce_kernel adds up
+    uint32_t split_tiles;        // up to so many row tiles ksplit1 splits work
+    uint32_t n_cus;
     uint32_t halves;             // non-zero (strip kernels, m_tile 128): a workgroup of the first product has one strip and its
                                  // pairs of wavefronts half of the k range each, instead of two strips
     uint32_t g1_xcd;             // non-zero (strip kernels): the first product's column workgroups of a row tile share an XCD

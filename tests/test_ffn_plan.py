@@ -10,7 +10,7 @@ from types import SimpleNamespace
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_02715_amd", "csrc")
-FIELDS = ("tiled", "halves", "g1_xcd", "m_tile", "ksplit", "ksplit1", "pairs_cap", "tiles_cap", "n_chunks", "bytes",
+FIELDS = ("tiled", "halves", "g1_xcd", "m_tile", "ksplit", "ksplit1", "split_tiles", "pairs_cap", "tiles_cap", "n_chunks", "bytes",
           "off_count", "off_offset", "off_sorted", "off_pos", "off_tile", "off_ntiles", "off_h", "off_y")
 SHIM = """
 #include "ffn_plan.h"
@@ -18,6 +18,11 @@ using namespace fluxmoe;
 static void put(const FfnPlan& p, uint64_t* o) { %s }
 extern "C" void plan(uint64_t E, uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint32_t K, uint64_t limit, uint32_t mapped, uint64_t* o) {
     put(plan_ffn(FfnShape{E, H, F, n_cus, waves}, T, K, limit, mapped), o);
+}
+extern "C" uint32_t least_cost(uint32_t H, uint32_t F, uint32_t n_cus, uint32_t n_tiles, uint32_t rows, uint32_t most) {
+    uint32_t best = 1;
+    for (uint32_t k = 2; k <= most; ++k) if (tiled_cost(SplitShape{H, F, n_cus}, n_tiles, rows, k) < tiled_cost(SplitShape{H, F, n_cus}, n_tiles, rows, best)) best = k;
+    return best;
 }
 extern "C" void plain(uint64_t E, uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint32_t K, uint32_t mapped, uint64_t* o) {
     put(plan_ffn_rules(FfnShape{E, H, F, n_cus, waves}, T, K, mapped, false, ~0ull), o);
@@ -45,7 +50,7 @@ def rules(tmp_path_factory):
         o = out()
         so.plain(E, H, F, n_cus, waves, T, K, mapped, o)
         return SimpleNamespace(**dict(zip(FIELDS, o)))
-    return SimpleNamespace(plan=plan, plain=plain)
+    return SimpleNamespace(plan=plan, plain=plain, least_cost=so.least_cost)
 
 
 @pytest.fixture(autouse=True)
@@ -79,7 +84,7 @@ def check(p, c):
         assert p.ksplit1 == 1 or p.ksplit1 * 64 <= H
     assert not p.g1_xcd or p.halves
     sizes = [("off_count", (c["E"] + 1) * 4), ("off_offset", (c["E"] + 2) * 4), ("off_sorted", pairs * 4), ("off_pos", pairs * 4),
-             ("off_tile", p.tiles_cap * 16), ("off_ntiles", 4), ("off_h", max(pairs * F * 2, p.n_chunks * c["E"] * 4)),
+             ("off_tile", p.tiles_cap * 16), ("off_ntiles", 8), ("off_h", max(pairs * F * 2, p.n_chunks * c["E"] * 4)),
              ("off_y", max(p.ksplit * pairs * H * 4, p.ksplit1 * pairs * 2 * F * 4 if p.ksplit1 > 1 else 0))]
     ends = [getattr(p, name) + size for name, size in sizes]
     starts = [getattr(p, name) for name, _ in sizes[1:]] + [p.bytes]
@@ -169,3 +174,24 @@ def test_a_single_resident_expert_that_every_token_takes(rules):
     its share of the pairs is not known; no token lists it twice, so T rows must still be few enough."""
     of = lambda T, E, mapped: rules.plan(T=T, K=2, E=E, H=5120, F=1536, mapped=mapped).m_tile
     assert of(16384, 8, 1) == 256 and of(4097, 8, 1) == 256 and of(4096, 8, 1) == 128
+
+
+def test_splits_give_way_to_more_row_tiles_than_planned(rules):
+    """Strips and 128 x 128 tiles: split while the tiles leave CUs without work, or as many as the plan expected."""
+    p = rules.plan(T=1024, K=8, E=160, H=5120, F=1536, mapped=4)             # 51 rows each planned, 1024 if all take these
+    assert p.halves and p.ksplit1 > 1 and p.split_tiles == 255 // 12
+    p = rules.plan(T=1024, K=10, E=128, H=2048, F=512, mapped=8)
+    assert p.tiled and p.m_tile == 128 and p.ksplit1 > 1 and p.split_tiles == 255 // 8
+    p = rules.plan(T=256, K=2, E=8, H=4096, F=14336)
+    assert p.ksplit1 == 1 and p.split_tiles == 0
+    # 256 x 256 tiles: a plan that the model shares is kept, and past it the model decides
+    p = rules.plan(T=512, K=2, E=8, H=4096, F=1792)
+    assert p.tiled and p.m_tile == 256 and (p.ksplit1, p.split_tiles) == (2, 8)
+    assert rules.least_cost(4096, 1792, 256, 8, 1024, 2) == 2                # 4 pairs of (super-tile, split) on each of 8 XCDs' 32 CUs
+    assert rules.least_cost(4096, 1792, 256, 9, 1024, 2) == 1                # 12 pairs: a second round on four of them
+    p = rules.plan(T=1024, K=8, E=20, H=5120, F=384)
+    assert p.ksplit1 == 2 and p.split_tiles == 0 and rules.least_cost(5120, 384, 256, 40, 8192, 2) == 1
+    assert rules.least_cost(5120, 384, 256, 20, 3200, 4) > 1
+    for n_tiles in (0, 1, 3, 4, 5, 1000, 65535):                             # any count is a valid question
+        assert 1 <= rules.least_cost(64, 64, 256, n_tiles, n_tiles * 256, 8) <= 8
+    assert rules.least_cost(4096, 1792, 4, 8, 1024, 2) in (1, 2)             # fewer CUs than XCDs

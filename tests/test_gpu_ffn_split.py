@@ -169,3 +169,18 @@ def test_walking_second_product(shape):
     column tile and row tiles with few rows among them."""
     cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=9000, top_k=1, n_experts=shape[2], n_slots=shape[2], hidden=shape[0], ffn=shape[1])
     run_ffn_case(cfg, seed=16)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=2000, top_k=2, n_experts=64, hidden=1024, ffn=2056),             # strips: 32 row tiles where one or two were planned
+    dict(tokens=300, top_k=2, n_experts=64, hidden=1024, ffn=2056),              # few enough to split as planned
+    dict(tokens=5000, top_k=1, n_experts=64, hidden=2048, ffn=1024),             # tiles of 128 x 128: 40 where one was planned
+    dict(tokens=1200, top_k=2, n_experts=8, hidden=2048, ffn=512),               # tiles of 256 x 256: four splits,
+    dict(tokens=3000, top_k=2, n_experts=8, hidden=2048, ffn=512),               # two of the four that were planned,
+    dict(tokens=6000, top_k=2, n_experts=8, hidden=2048, ffn=512),               # one
+])
+def test_every_token_on_the_resident_experts(kw):
+    """The plan counts on the resident experts' mean share of the pairs; here they get all of them, and the kernels, which
+    see the row tiles, decide how many splits of the first product work."""
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_slots=2, **kw)
+    run_ffn_case(cfg, seed=17, ids_override=lambda ids: np.broadcast_to(np.arange(ids.shape[1], dtype=np.int32), ids.shape).copy())
