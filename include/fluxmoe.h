@@ -494,11 +494,12 @@ int fluxmoe_mfma_probe(const void* operands, float* out, uint32_t n_workgroups, 
                        void* stream);
 
 /*
- * Kernel timing for benchmarks.  While enabled, every kernel the library launches is
- * bracketed by HIP events on its own stream.  fluxmoe_profile_collect waits for them, adds
+ * Kernel timing for benchmarks.  While enabled, the library's launches of each kind are
+ * bracketed by HIP events on their own stream.  fluxmoe_profile_collect waits for them, adds
  * the elapsed milliseconds and launch counts per kind and forgets them:
- *   kind 0 decode + paged scatter, 1 token grouping, 2 gate/up product + SwiGLU,
- *   3 down product, 4 gated combine.
+ *   kind 0 decode + paged scatter, 1 token grouping, 2 gate/up product + SwiGLU (with the sum of its
+ *   K splits where it has them), 3 down product, 4 gated combine.
+ * A call of up to 64 pairs groups them inside kind 2 and has no launch of kind 1.
  * on: 0 = off, 1 = every kind, FLUXMOE_PROFILE_ONLY(mask) = only the kinds whose bit is set in
  * mask (an event between two kernels costs a few microseconds of idle device time; a benchmark
  * that times whole steps brackets only the kernel it reports).

@@ -1894,7 +1894,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
-    mark(1, 1);
+    if (!routes_itself) mark(1, 1);
     if (routes_itself) {
     } else if (a.identity) {
         hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
@@ -1906,9 +1906,10 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     } else {
         launch_done(chooses ? route_sort_kernel<false, true> : route_sort_kernel<false, false>, dim3(1), dim3(1024), sh, stream, with_routing, a);
     }
-    mark(1, 0);
-    if (!routes_itself)
+    if (!routes_itself) {
+        mark(1, 0);
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
+    }
     auto launch_combine = [&](dim3 grid) {
         if (a.K <= 2) launch_done(combine_kernel<2>, grid, dim3(256), 0, stream, done, a);
         else if (a.K <= 4) launch_done(combine_kernel<4>, grid, dim3(256), 0, stream, done, a);

@@ -48,3 +48,27 @@ def test_profile_brackets_only_the_selected_kinds():
         assert pool.device_errors() == 0
     finally:
         pool.close()
+
+
+def test_a_kind_without_a_kernel_counts_no_launch():
+    """Up to 64 pairs the gate/up product's workgroups group the pairs: no launch of kind "grouping" and no time."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=33)
+    pool, _ = build_pool(cfg)
+    try:
+        x = inputs.activations(cfg).cuda()
+        ids, g = inputs.routing(cfg)
+        idd, gd = torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda()
+        out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+        pool.reset_page_table()
+        pool.materialize(0, list(range(8)), list(range(8)))
+        B.fluxmoe_profile_enable(pool.ctx, True)
+        for tokens, launches in ((32, 0), (33, 1)):
+            B.fluxmoe_profile_collect(pool.ctx)
+            pool.expert_ffn(0, x, idd[:tokens], gd[:tokens], out)
+            prof = B.fluxmoe_profile_collect(pool.ctx)
+            assert prof["grouping"][1] == launches and (prof["grouping"][0] > 0) == (launches > 0)
+            assert all(prof[k][1] == 1 and prof[k][0] > 0 for k in ("gemm1_swiglu", "gemm2", "combine"))
+        assert pool.device_errors() == 0
+    finally:
+        pool.close()
