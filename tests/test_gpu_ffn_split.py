@@ -9,6 +9,7 @@ from oracle import ffn as offn
 from oracle import paging
 from paper_2604_02715_amd import binding as B
 from paper_2604_02715_amd import inputs
+from test_ffn_plan import rules  # noqa: F401 (fixture)
 from test_gpu_ffn import TOL, run_ffn_case
 
 pytestmark = pytest.mark.gpu
@@ -69,27 +70,48 @@ def test_tiles_of_launches_with_few_strips(kw):
     run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=10)
 
 
-def test_a_buffer_for_the_plan_without_splits_is_enough():
-    """The scratch a call prefers depends on how many experts are resident; one that holds the plan without K splits of
-    the first product must do, and give the same result to rounding."""
+@pytest.mark.parametrize("kw,refused_below", [
+    (dict(tokens=3, top_k=2, hidden=1024, ffn=512), True),                                      # strips, four splits
+    (dict(tokens=300, top_k=1, n_experts=1, n_slots=1, hidden=2048, ffn=1024), False),          # tiles of 128, both products split
+    (dict(tokens=600, top_k=2, n_experts=4, n_slots=4, hidden=2048, ffn=512), True),            # tiles of 256, four splits
+])
+def test_a_buffer_for_the_plan_without_splits_is_enough(kw, refused_below, rules):
+    """A call prefers a plan that takes more scratch than the one without K splits of the first product; a buffer of that
+    plan's size must do, as must one in between, and give the same result to rounding.  One byte less is refused, except
+    where the small tiles need less still."""
     from gpu_common import build_pool
-    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=3, top_k=2, hidden=2048, ffn=128)
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw)
+    call = dict(T=cfg.tokens, K=cfg.top_k, E=cfg.n_experts, H=cfg.hidden, F=cfg.ffn, mapped=cfg.n_experts)
+    best, least = rules.plan(**call), rules.plain(**call)
+    assert best.ksplit1 > rules.plan(**call, limit=least.bytes).ksplit1 and least.bytes < best.bytes
     pool, dense = build_pool(cfg)
     try:
+        assert pool.ws_bytes - int(pool.sizes.pool_workspace_bytes) >= best.bytes
         x = inputs.activations(cfg).cuda()
         ids, g = inputs.routing(cfg)
         idd, gd = torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda()
         pool.reset_page_table()
-        pool.materialize(0, np.arange(8), np.arange(8))
+        every = np.arange(cfg.n_experts)
+        pool.materialize(0, every, every)
+        bind = lambda scratch: B.fluxmoe_bind_arenas(pool.ctx, pool.slots13.data_ptr(), pool.slots2.data_ptr(), pool.workspace.data_ptr(),
+                                                     int(pool.sizes.pool_workspace_bytes) + scratch)
         outs = []
-        for spare in (pool.ws_bytes, int(pool.sizes.pool_workspace_bytes) + 4096 + 2 * 6 * 128 + 6 * 2048 * 4):
-            B.fluxmoe_bind_arenas(pool.ctx, pool.slots13.data_ptr(), pool.slots2.data_ptr(), pool.workspace.data_ptr(), spare)
+        for scratch in (best.bytes, (best.bytes + least.bytes) // 2, least.bytes):
+            bind(scratch)
+            pool.workspace[int(pool.sizes.pool_workspace_bytes):].fill_(0x7F)
             out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
             pool.expert_ffn(0, x, idd, gd, out)
             torch.cuda.synchronize()
+            assert (pool.workspace[int(pool.sizes.pool_workspace_bytes) + scratch:] == 0x7F).all()
             outs.append(out.cpu().numpy())
         assert pool.device_errors() == 0
-        assert offn.rel_frobenius(outs[1], outs[0]) <= TOL
+        want = offn.moe_ffn(inputs.bits_u16(x.cpu()), ids, g, lambda e: (inputs.bits_u16(dense[0][0][e]), inputs.bits_u16(dense[0][1][e])))
+        for out in outs:
+            assert offn.rel_frobenius(out, want) <= TOL
+        bind(least.bytes - 1 if refused_below else least.bytes // 4)
+        with pytest.raises(B.FluxmoeError) as ei:
+            pool.expert_ffn(0, x, idd, gd, torch.zeros((cfg.tokens, cfg.hidden), device="cuda"))
+        assert ei.value.status == -2
     finally:
         pool.close()
 
