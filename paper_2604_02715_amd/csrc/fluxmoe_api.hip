@@ -876,8 +876,9 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     // a wave of this layer still to be released: its FFN must have read the page table before this call's entries appear
     // there.  Both outside capture, or both in one capture: a wait across a capture's border orders nothing (or is refused),
     // and ordering a graph against other work is its launcher's part.
+    const uint64_t capture = capture_of(stream);       // after the waits above: one of them may have taken the stream into a capture
     const uint64_t last_ffn = c->infer_gen[layer];
-    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn) && c->infer_capture[layer][last_ffn & 1] == capture_of(stream))
+    if (last_ffn && c->routed_gen[layer] == last_ffn && !rel_covers(last_ffn) && c->infer_capture[layer][last_ffn & 1] == capture)
         HIPCHECK(hipStreamWaitEvent(stream, c->ev_routed[layer], 0));
 
     DecodeArgs args{};
@@ -891,7 +892,6 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     const size_t jobs_bytes[2] = {cmd->n_jobs[0] * sizeof(DecodeJob), cmd->n_jobs[1] * sizeof(DecodeJob)};
     const size_t packed = sizeof(DecodeCmd) + jobs_bytes[0] + jobs_bytes[1] + touched.size() * 8;
     const bool uploaded = !(decode_blocks > 0 && packed <= kInlineCmdBytes);
-    const uint64_t capture = capture_of(stream);
     if (!need_host && c->half_read[half] == c->ev_load[layer] && c->half_capture[half] != capture)
         std::swap(c->ev_load[layer], c->half_spare[half]);
     hipEvent_t load_done = capture == 0 ? c->ev_load[layer] : nullptr; // nullptr: recorded at the end
