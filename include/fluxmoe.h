@@ -262,7 +262,10 @@ int fluxmoe_release(fluxmoe_ctx* ctx, uint32_t layer, const int32_t* expert_ids,
  *   out      device float [T][hidden]
  * out_t = sum_k topk_w[t][k] * ( (silu(x_t W1_e) * (x_t W3_e)) W2_e ),  e = topk_ids[t][k];
  * BF16 inputs, FP32 accumulation, the SwiGLU product rounded to BF16 before the second
- * product.  Deterministic (fixed summation order).  T = 0 is valid.
+ * product.  T = 0 is valid.  Deterministic: the same call with the same experts resident and the same
+ * scratch gives the same bits.  How many of the layer's experts are resident, how the routing loads them
+ * and how much scratch there is choose tiles and K splits, and with them the order of the FP32 sums (and
+ * the rounding of an h element that lies at a BF16 tie); not the precision they are kept in.
  * Limits (the kernels address activations and one expert matrix with 32-bit byte offsets):
  * T <= 65535 and T * hidden * 2 bytes under 4 GiB here (EINVAL, nothing enqueued); hidden * ffn * 2
  * bytes under 2 GiB is checked by fluxmoe_create.
@@ -273,8 +276,8 @@ int fluxmoe_expert_ffn(fluxmoe_ctx* ctx, uint32_t layer, const uint16_t* tokens,
 
 /*
  * fluxmoe_expert_ffn for callers that cannot allocate or bring a workspace (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): same arguments, same result, same
- * event protocol, but the FFN scratch (pair order, tile list, the SwiGLU product h, split-K partials)
+ * capture, tight serving loops, harnesses that forbid hipMalloc): same arguments, same result (to
+ * rounding, where the other size of the scratch leads to other K splits), same event protocol, but the FFN scratch (pair order, tile list, the SwiGLU product h, split-K partials)
  * lives in a static device array of FLUXMOE_STATIC_SCRATCH_BYTES bytes that is part of the loaded
  * library (every GPU the library runs on holds its own copy until the process ends) instead of the
  * bound workspace.  The call itself allocates nothing and frees nothing; the array's device address
@@ -444,12 +447,14 @@ int fluxmoe_device_errors(fluxmoe_ctx* ctx, uint32_t* out_flags);
  * ------------------------------------------------------------------------------------------ */
 
 /*
- * The launch plan fluxmoe_expert_ffn takes for T tokens with K experts each (host only; for tests
- * and reports): rows per tile of the grouped products (16..128 = weight-streaming kernels, 256 =
- * LDS-tiled MFMA kernels, which also take 128-row tiles where few workgroups would run) and the number
- * of K splits of the second product.  The plan depends on the
- * shapes, on T * K / n_experts and on the CU count of the device (256 until a bind call has
- * queried it).
+ * The launch plan fluxmoe_expert_ffn takes for T tokens with K experts each when every expert is
+ * resident and scratch is ample (host only; for tests and reports): rows per tile of the grouped
+ * products (16..128 = weight-streaming kernels, 256 = LDS-tiled MFMA kernels; these also take 128-row
+ * tiles where few workgroups would run, which this number does not tell apart) and the number of K
+ * splits of the second product.  The plan depends on the shapes, on T * K / n_experts and on the CU
+ * count of the device (256 until a bind call has queried it); a call also goes by the number of
+ * resident experts and the bytes of scratch it has, and splits K of the first product by the row tiles
+ * it finds.
  */
 int fluxmoe_ffn_plan(const fluxmoe_ctx* ctx, uint32_t T, uint32_t K, uint32_t* rows_per_tile,
                      uint32_t* k_splits);
@@ -499,7 +504,8 @@ int fluxmoe_mfma_probe(const void* operands, float* out, uint32_t n_workgroups, 
  * the elapsed milliseconds and launch counts per kind and forgets them:
  *   kind 0 decode + paged scatter, 1 token grouping, 2 gate/up product + SwiGLU (with the sum of its
  *   K splits where it has them), 3 down product, 4 gated combine.
- * A call of up to 64 pairs groups them inside kind 2 and has no launch of kind 1.
+ * On the weight-streaming kernels a call of up to 64 pairs groups them inside kind 2 and has no launch
+ * of kind 1.
  * on: 0 = off, 1 = every kind, FLUXMOE_PROFILE_ONLY(mask) = only the kinds whose bit is set in
  * mask (an event between two kernels costs a few microseconds of idle device time; a benchmark
  * that times whole steps brackets only the kernel it reports).

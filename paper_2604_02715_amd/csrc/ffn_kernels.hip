@@ -1333,7 +1333,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // which global piece each lane fetches: A rows (128 bytes = 8 pieces) hold piece p ^ ((row >> 1) & 7)
 // at position p; B rows (512 bytes = 8 units of 32 columns) hold unit u ^ (k & 3) at position u.
 // LDS: [A stage 0 | A stage 1 | B stage 0 | B stage 1 | B stage 2], 32 KiB each = all 160 KiB.  Same
-// eight wavefronts, wave tiles and sub-step schedule as gemm_tiled_kernel.
+// eight wavefronts, wave tiles and sub-step schedule as gemm_tiled_kernel.  (Tiles of 128 x 128: B rows of 256 bytes = 4 units,
+// stages of 16 KiB, 80 KiB in all.)
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // Measurement aid, compile time only (python -m paper_2604_02715_amd.build -DFLUXMOE_D2L_PROBE=<bits>): parts of
@@ -1520,7 +1521,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     };
     // a_stage_off / b_stage_off: byte offset of the destination stage inside the operand's region, uniform
     auto dma_a = [&](const TileState& s, uint32_t k0, int a_stage_off, int n) __attribute__((always_inline)) {
-        // (the first product never splits K: its A base and step count are the same for every tile)
+        // (MODE 1 does not split K: its A base and step count are the same for every tile)
         const uint8_t* base = MODE == 1 ? reinterpret_cast<const uint8_t*>(a.tokens) : s.a_base;
         dma16(base + size_t(k0) * 2 + s.a_off[n], lds_base + a_stage_off + (wave * kDma + n) * 1024);
     };
@@ -2035,8 +2036,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         launch_reduce();
         mark(2, 0);
         mark(3, 1);
-        // The second product's workgroups walk where its tiles are short (at most 32 steps: the next tile's first loads hide
-        // behind the 256 KiB a tile stores).  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
+        // The second product's workgroups walk where its tiles are short (at most 32 steps): the next tile's record, offsets and
+        // first loads are on their way while the 256 KiB a tile stores leave.  The stores themselves are not hidden: the wait for
+        // the record at the end of a tile covers them.  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
         // 1137 / 1104, 20 of H 5120 F 1536, 1638 rows 1642 / 1615, 160 of those 512 rows 4637 / 4581, 205 rows 2127 / 2126.
         const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
