@@ -109,8 +109,10 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         } else if (few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20)
                                                   : 8 * groups_act <= n_cus && avg_act >= 16 && H <= (mapped && mapped < E ? 2048u : 1024u))) {
             // Row counts that make a matrix tile worth while and K too short for the strips' start-up, strips / tiles of 128:
-            // one expert of H 5120 F 1536: 64 rows 47 / 46, 128 59 / 51; of H 2048 F 512: 32 rows 28 / 25.  32 experts of
-            // H 1024 F 256, 40 rows each: 39 / 36, behind a kernel that filled the caches with other data 46 / 48; 87 rows 59 / 40
+            // one expert, weights out of HBM and behind a kernel that filled the caches with other data: H 2048 F 512, 64 rows
+            // 30 / 26 and 36 / 35, 128 44 / 27 and 52 / 37; H 5120 F 1536, 64 rows 45 / 45 and 48 / 57, 96 54 / 48 and 57 / 59,
+            // 128 63 / 51 and 66 / 63.  Past 64 MiB of weights they gain in the one state what they lose in the other: H 4096
+            // F 4096, 96 rows 63 / 61 and 68 / 81, F 14336 115 / 146 and 120 / 190.  32 experts of H 1024 F 256, 40 rows each: 39 / 36, behind a kernel that filled the caches with other data 46 / 48; 87 rows 59 / 40
             // and 65 / 52.  The tiles bear such caches badly: 32 of H 2048 F 512, 16 rows each: 55 / 58 and 62 / 93, and 64 of
             // them, 20 rows: 85 / 106 and 91 / 154.  A wave (part of the layer resident) runs beside the next wave's load,
             // and there they win, as a strip workgroup needs 128 KiB of LDS on a CU and a tile 80: a pass over three layers of
@@ -199,8 +201,10 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         }
     }
     // Strips whose rows are not whole 128-byte lines share a line with their neighbours: on one XCD they find it in its L2
-    // (64 experts of H 2880 F 360, 333 tokens, top-4: 112 -> 106 us).  With aligned rows, or two strips a workgroup, it is
-    // 0.5 to 2 % slower.  Enough (tile, split) units to fill the 8 XCDs evenly.
+    // (64 experts of H 2880 F 360, 333 tokens, top-4: 112 -> 107 us, 80 of F 376 127 -> 114, 64 of H 2048 F 200, 500 tokens
+    // 66 -> 62, of H 1544 F 264, 600 tokens 71 -> 66; 160 of F 104, one strip each, 84 -> 85).  With aligned rows it changes nothing
+    // (64 of F 384: 94.4 / 93.5), with two strips a workgroup it is 0.5 to 2 % slower.  Enough (tile, split) units to fill the
+    // 8 XCDs evenly.
     p.g1_xcd = p.halves && F % 64 != 0 && groups_act * p.ksplit1 >= 64;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
