@@ -112,11 +112,12 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             // one expert, weights out of HBM and behind a kernel that filled the caches with other data: H 2048 F 512, 64 rows
             // 30 / 26 and 36 / 35, 128 44 / 27 and 52 / 37; H 5120 F 1536, 64 rows 45 / 45 and 48 / 57, 96 54 / 48 and 57 / 59,
             // 128 63 / 51 and 66 / 63.  Past 64 MiB of weights they gain in the one state what they lose in the other: H 4096
-            // F 4096, 96 rows 63 / 61 and 68 / 81, F 14336 115 / 146 and 120 / 190.  32 experts of H 1024 F 256, 40 rows each: 39 / 36, behind a kernel that filled the caches with other data 46 / 48; 87 rows 59 / 40
-            // and 65 / 52.  The tiles bear such caches badly: 32 of H 2048 F 512, 16 rows each: 55 / 58 and 62 / 93, and 64 of
-            // them, 20 rows: 85 / 106 and 91 / 154.  A wave (part of the layer resident) runs beside the next wave's load,
-            // and there they win, as a strip workgroup needs 128 KiB of LDS on a CU and a tile 80: a pass over three layers of
-            // 128 of H 2048 F 512 in waves of 32, 1024 tokens: 2217 / 2040; in waves of 64 they lose (1620 / 1690).
+            // F 4096, 96 rows 63 / 61 and 68 / 81, F 14336 115 / 146 and 120 / 190.  32 experts of H 1024 F 256, 40 rows each:
+            // 39 / 36 and 46 / 48, 87 rows 59 / 40 and 65 / 52; of H 2048 F 512, 16 rows each: 55 / 58 and 62 / 93, and 64 of
+            // those, 20 rows: 85 / 106 and 91 / 154.  A wave (part of the layer resident) runs beside the next wave's load, and
+            // there they win, likely because a strip workgroup needs 128 KiB of LDS on a CU that decodes and a tile 80: a pass
+            // over three layers of 128 of H 2048 F 512 in waves of 32, 1024 tokens: 2217 / 2040; in waves of 64 they lose
+            // (1620 / 1690).
             // Longer K favours the strips: 20 of H 5120 F 384, 51 rows each: 79 / 99; 8 of H 4096 F 1792, 64 rows: 101 / 109.
             p.tiled = true;
             p.m_tile = 128;
