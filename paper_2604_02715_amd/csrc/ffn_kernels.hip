@@ -1360,7 +1360,9 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // 128 x 128 each (256 accumulator registers), one per SIMD: a third less LDS read traffic per MFMA.
     constexpr int kRowTiles = WAVES == 8 || TILE == 128 ? 2 : 4;   // 32-row MFMA tiles per wavefront
     constexpr int kColTiles = TILE == 256 ? 4 : 2;           // 32-column MFMA tiles per wavefront
-    constexpr int kWaveRows = 32 * kRowTiles;
+    // Wavefront row wm of kWaveRows multiplies the 32-row groups wm, wm + kWaveRows, ... of the tile, so that the groups a tile
+    // has rows for are spread over the SIMDs; the others are neither fetched nor multiplied (k_loop below).
+    constexpr int kWaveRows = TILE / 32 / kRowTiles;
     constexpr int kStageBytes = TILE * 128;                  // one operand, one step: TILE rows (columns) x 64 k
     constexpr int kRowB = TILE * 2;                          // bytes of a k row of B
     constexpr int kDma = kStageBytes / 1024 / WAVES;         // 1 KiB loads per wavefront, operand and step
@@ -1430,6 +1432,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
+    const int a_rows = 8 * kDma * wave;                      // first row of A this wavefront fetches: none if the tile ends before it
     // The lane number as a value the compiler cannot trace back to threadIdx: what the per-tile set-up code
     // derives from it is then computed again for every tile instead of being held in registers across the
     // k loop, where registers are short.
@@ -1532,10 +1535,10 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // a tile's first loads: A and B of steps 0 and 1 into stages 0 and 1 (B of step 2 is issued by step 0)
     auto prime = [&](const TileState& s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int n = 0; n < kDma; ++n) { dma_a(s, 0, 0, n); dma_b(s, 0, 0, n); }
+        for (int n = 0; n < kDma; ++n) { if (a_rows < s.rows) dma_a(s, 0, 0, n); dma_b(s, 0, 0, n); }
         if (steps_of(s) > 1) {
 #pragma unroll
-            for (int n = 0; n < kDma; ++n) { dma_a(s, kTK, kStageBytes, n); dma_b(s, kTK, kStageBytes, n); }
+            for (int n = 0; n < kDma; ++n) { if (a_rows < s.rows) dma_a(s, kTK, kStageBytes, n); dma_b(s, kTK, kStageBytes, n); }
         }
     };
 
@@ -1552,7 +1555,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const int e = (lane & 15) >> 2, g = lane & 3, nh = (lane >> 4) & 1;
 #pragma unroll
         for (int i = 0; i < kRowTiles; ++i) {
-            const int R = wm * kWaveRows + 32 * i + q;
+            const int R = 32 * (wm + kWaveRows * i) + q;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) a_addr[i][ks] = R * 128 + 16 * ((2 * ks + h) ^ ((R >> 1) & 7));
         }
@@ -1581,8 +1584,9 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // A tiles, then the two halves (k 0..3 and 4..7 of the lane's 8) of the four B fragments
     // OTHER: read from the next step's stage instead of the one the address registers point at
     // (A: the other of two stages; B: b_next_delta bytes further in its ring of three)
-    auto lfrag_item = [&](int other, int ks, int set, int n) __attribute__((always_inline)) {
+    auto lfrag_item = [&](int other, int ks, int set, int n, int rows_act) __attribute__((always_inline)) {
         if (n < kRowTiles) {
+            if (n >= rows_act) return;
             fa[set][n] = *reinterpret_cast<const bf16x8*>(lds_b8 + (a_addr[n][ks] ^ (other ? kStageBytes : 0)));
         } else {
             const int j = (n - kRowTiles) >> 1, tt = (n - kRowTiles) & 1;
@@ -1615,15 +1619,15 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         auto sub = [&](int set, int other, int next_ks, auto READ, auto DMA_B, auto DMA_A) __attribute__((always_inline)) {
 #pragma unroll
             for (int n = 0; n < kMfma; ++n) {
-                if (ACT.value) mfma_item(set, n);
-                if (READ.value && ACT.value && n < kFrag && !(FLUXMOE_D2L_PROBE & 1)) lfrag_item(other, next_ks, set ^ 1, n);
+                if (n < kColTiles * ACT.value) mfma_item(set, n);
+                if (READ.value && ACT.value && n < kFrag && !(FLUXMOE_D2L_PROBE & 1)) lfrag_item(other, next_ks, set ^ 1, n, ACT.value);
                 if (DMA_B.value && n % kDmaEvery == kDmaEvery - 1 && !(FLUXMOE_D2L_PROBE & 4)) dma_b(cur, k0 + 2 * kTK, b_plus2, n / kDmaEvery);
-                if (DMA_A.value && n % kDmaEvery == kDmaEvery - 1 && !(FLUXMOE_D2L_PROBE & 2)) dma_a(cur, k0 + 2 * kTK, a_own, n / kDmaEvery);
+                if (DMA_A.value && n % kDmaEvery == kDmaEvery - 1 && a_rows < cur.rows && !(FLUXMOE_D2L_PROBE & 2)) dma_a(cur, k0 + 2 * kTK, a_own, n / kDmaEvery);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (READ.value && ACT.value && !(FLUXMOE_D2L_PROBE & 1)) {
 #pragma unroll
-                for (int n = kMfma; n < kFrag; ++n) lfrag_item(other, next_ks, set ^ 1, n);
+                for (int n = kMfma; n < kFrag; ++n) lfrag_item(other, next_ks, set ^ 1, n, ACT.value);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -1672,7 +1676,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         for (int i = 0; i < kRowTiles; ++i)
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
-                const int32_t row = wm * kWaveRows + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3) + (q & 1);
+                const int32_t row = 32 * (wm + kWaveRows * i) + (r >> 2) * 8 + h * 4 + (r & 3) + (q & 1);
                 uint16_t* const hrow = hlane + size_t(uint32_t(row)) * a.F;
 #pragma unroll
                 for (int j = 0; j < kColTiles / 2; ++j) {
@@ -1696,7 +1700,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         for (int i = 0; i < kRowTiles; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int32_t row = wm * kWaveRows + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+                const int32_t row = 32 * (wm + kWaveRows * i) + (r >> 2) * 8 + h * 4 + (r & 3);
                 if (row >= c.rows) continue;
                 float* const prow = plane + size_t(uint32_t(row)) * 2 * a.F;
 #pragma unroll
@@ -1713,7 +1717,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         for (int i = 0; i < kRowTiles; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int32_t row = wm * kWaveRows + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+                const int32_t row = 32 * (wm + kWaveRows * i) + (r >> 2) * 8 + h * 4 + (r & 3);
                 if (row >= c.rows) continue;
                 float* const yrow = ylane + size_t(uint32_t(row)) * a.H;
 #pragma unroll
@@ -1725,16 +1729,16 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     }
     };
 
-    // A wavefront whose 64 rows all lie past the tile's last row (tail tiles of an expert) takes part
-    // in the loads and barriers only: with at most 128 rows every SIMD runs one multiplying wavefront
-    // instead of two.
+    // ACT: how many of the wavefront's row groups the tile has rows for (all, half, or none: then it takes part in the loads
+    // and barriers only).  160 experts of H 5120 F 1536 with 205 rows each: 2081 -> 2052 us a call; a pass in waves over 128
+    // of H 2048 F 512 (20 rows each): 2086 -> 2044.  8 experts of H 4096 F 14336, 1024 rows each: no change.
     auto k_loop = [&](const TileState& cur, TileState& upcoming, auto ACT) __attribute__((always_inline)) {
         if (ACT.value) {
 #pragma unroll
-            for (int n = 0; n < kFrag; ++n) lfrag_item(0, 0, 0, n);
+            for (int n = 0; n < kFrag; ++n) lfrag_item(0, 0, 0, n, ACT.value);
             if (FLUXMOE_D2L_PROBE & 1) {
 #pragma unroll
-                for (int n = 0; n < kFrag; ++n) lfrag_item(0, 1, 1, n);
+                for (int n = 0; n < kFrag; ++n) lfrag_item(0, 1, 1, n, ACT.value);
             }
         }
         uint32_t s = 0;
@@ -1786,7 +1790,9 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
                 asm volatile("s_waitcnt vmcnt(%0)" :: "n"(MODE == 1 ? 1 + kDma : 1) : "memory");
             }
             __syncthreads();
-            if (wm * kWaveRows < cur.rows) k_loop(cur, nxt, Yes{}); else k_loop(cur, nxt, No{});
+            if (32 * (wm + kWaveRows * (kRowTiles / 2)) < cur.rows) k_loop(cur, nxt, std::integral_constant<int, kRowTiles>{});
+            else if (32 * wm < cur.rows) k_loop(cur, nxt, std::integral_constant<int, kRowTiles / 2>{});
+            else k_loop(cur, nxt, std::integral_constant<int, 0>{});
             if (FLUXMOE_D2L_PROBE & 8) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); __syncthreads(); }
             epilogue(cur);
         }

@@ -206,3 +206,11 @@ def test_every_token_on_the_resident_experts(kw):
     see the row tiles, decide how many splits of the first product work."""
     cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_slots=2, **kw)
     run_ffn_case(cfg, seed=17, ids_override=lambda ids: np.broadcast_to(np.arange(ids.shape[1], dtype=np.int32), ids.shape).copy())
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 97, 128, 129, 160, 193, 225, 256, 289])
+def test_row_groups_of_the_lds_tiled_kernels(rows, monkeypatch):
+    """Tiles of 256 x 256 with every number of 32-row groups: the wavefronts' groups beyond the tile's rows are not
+    fetched or multiplied."""
+    monkeypatch.setenv("FLUXMOE_FFN_MTILE", "256")
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=rows, top_k=1, n_experts=1, n_slots=1, hidden=256, ffn=192), seed=3)
