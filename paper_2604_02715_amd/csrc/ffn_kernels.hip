@@ -1352,7 +1352,8 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // up to ksplit1 ways, FP32 partial sums of gate and up instead of h (swiglu_reduce_kernel adds them up), or h if that is 1.
 // TILE: rows and columns of a workgroup's tile.  256: one workgroup per CU (160 KiB of LDS).  128, with WAVES = 4 as 2 x 2
 // of 64 x 64: two per CU, a quarter of the work per tile, for products whose 256 x 256 tiles leave most CUs without one.
-template <int MODE, int WAVES, bool WALK, int TILE>
+// STREAM: the weight loads carry the non-temporal hint.
+template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false>
 __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kernel(FfnArgs a) {
     constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
     static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
@@ -1522,6 +1523,11 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
                      : "=&s"(saved_m0) : "v"(gptr), "s"(lds_addr) : "memory");
     };
+    auto dma16_nt = [&](const uint8_t* gptr, uint32_t lds_addr) __attribute__((always_inline)) {
+        uint32_t saved_m0;
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt\n\ts_mov_b32 m0, %0"
+                     : "=&s"(saved_m0) : "v"(gptr), "s"(lds_addr) : "memory");
+    };
     // a_stage_off / b_stage_off: byte offset of the destination stage inside the operand's region, uniform
     auto dma_a = [&](const TileState& s, uint32_t k0, int a_stage_off, int n) __attribute__((always_inline)) {
         // (MODE 1 does not split K: its A base and step count are the same for every tile)
@@ -1529,7 +1535,8 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         dma16(base + size_t(k0) * 2 + s.a_off[n], lds_base + a_stage_off + (wave * kDma + n) * 1024);
     };
     auto dma_b = [&](const TileState& s, uint32_t k0, int b_stage_off, int n) __attribute__((always_inline)) {
-        dma16(s.b_base + size_t((FLUXMOE_D2L_PROBE & 16) ? 0u : k0) * N * 2 + s.b_off[n], lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
+        if (STREAM) dma16_nt(s.b_base + size_t((FLUXMOE_D2L_PROBE & 16) ? 0u : k0) * N * 2 + s.b_off[n], lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
+        else dma16(s.b_base + size_t((FLUXMOE_D2L_PROBE & 16) ? 0u : k0) * N * 2 + s.b_off[n], lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
     };
     auto steps_of = [&](const TileState& s) __attribute__((always_inline)) { return MODE == 1 ? n_steps_all : s.n_steps; };
     // a tile's first loads: A and B of steps 0 and 1 into stages 0 and 1 (B of step 2 is issued by step 0)
@@ -1934,6 +1941,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const uint32_t cols1 = a.halves ? strips1 : (strips1 + 1) / 2;
     const dim3 g1 = a.g1_xcd && !routes_itself ? dim3((a.tiles_cap * a.ksplit1 + 7) / 8 * 8 * cols1, 1, 1) : dim3(cols1, a.tiles_cap, a.ksplit1);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
+    // Weights that one row tile reads (experts with about a tile's rows at most) pass the caches by; with several they are
+    // shared through L2.  A wave finds what its load just wrote.  Microseconds a call, default policy / non-temporal: 8 experts of H 4096
+    // F 14336, 256 rows each 989 / 952, 1024 rows 2768 / 2807; 160 of H 5120 F 1536, 205 rows 2080 / 2062; 20 of those, 1200 rows
+    // 1207 / 1279; 32 of H 1024 F 256, 75 rows 39.7 / 37.6; a pass in waves over 128 of H 2048 F 512 2012 / 2040.
+    const bool stream_b = !a.identity && !(a.flags & 2u) && uint64_t(a.T) * a.K <= uint64_t(a.m_tile) * std::min<uint64_t>(a.E, uint64_t(a.T) * a.K);
     if (a.tiled) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
         const bool four = a.tiled_waves == 4;
@@ -1967,7 +1979,13 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
+            for (const void* f : {reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true>)}) {
+                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
+                if (e != hipSuccess) return e;
+            }
             for (const void* f : {reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 4, false, 128>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 4, false, 128>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 4, false, 128, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 4, false, 128, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 4, false, 128>)}) {
                 e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 81920);
                 if (e != hipSuccess) return e;
@@ -2032,11 +2050,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         if (small) {
             const dim3 g = d2l_grid(d2l_all((a.F + 63) / 64, a.ksplit1, false, false), false);
             if (a.ksplit1 > 1) hipLaunchKernelGGL((gemm_d2l_kernel<3, 4, false, 128>), g, dim3(256), 81920, stream, a);
-            else hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 128>), g, dim3(256), 81920, stream, a);
+            else hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<1, 4, false, 128, true> : gemm_d2l_kernel<1, 4, false, 128>), g, dim3(256), 81920, stream, a);
         }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<3, 8, false, 256>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((gemm_d2l_kernel<1, 8, true, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<1, 8, true, 256, true> : gemm_d2l_kernel<1, 8, true, 256>), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<1>, grid_for((a.F + 127) / 128), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<1>, grid_for((a.F + 127) / 128), dim3(512), lds_bytes, stream, a);
         launch_reduce();
@@ -2047,10 +2065,10 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // the record at the end of a tile covers them.  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
         // 1137 / 1104, 20 of H 5120 F 1536, 1638 rows 1642 / 1615, 160 of those 512 rows 4637 / 4581, 205 rows 2127 / 2126.
         const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
-        if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
+        if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
-        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((gemm_d2l_kernel<2, 8, true, 256>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 8, false, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 8, true, 256, true> : gemm_d2l_kernel<2, 8, true, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 8, false, 256, true> : gemm_d2l_kernel<2, 8, false, 256>), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
         mark(3, 0);
