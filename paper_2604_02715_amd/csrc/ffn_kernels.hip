@@ -29,13 +29,13 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "ffn_device.h"
 #include "kernels.h"
 
 namespace fluxmoe {
 
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 union Frag {
@@ -287,7 +287,8 @@ __global__ __launch_bounds__(1024) void route_sort_kernel(FfnArgs a) {
 }
 
 // The shared expert: every token once, in order, on the one expert in slot 0.  What route_sort_kernel would find out
-// from T identical ids is known, so the lists are written by as many workgroups as they need and nothing is counted.
+// from T identical ids is known, so the lists are written by as many workgroups
+// as they need and nothing is counted (gemm_ring_kernel needs none).
 __global__ __launch_bounds__(256) void route_identity_kernel(FfnArgs a) {
     const uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i < a.T) {
@@ -306,13 +307,6 @@ __global__ __launch_bounds__(256) void route_identity_kernel(FfnArgs a) {
         a.n_tiles[0] = int32_t(n_tiles);
         a.n_tiles[1] = int32_t(a.ksplit1);
     }
-}
-
-// SiLU(g) * u (Sec. 2.1's gated FFN) in FP32 with the hardware's exp2 and reciprocal, each within one
-// ulp; the caller rounds the product to BF16.  g -> -inf gives exp2 = +inf, reciprocal 0, product -0.
-__device__ __forceinline__ float swiglu(float g, float u) {
-    const float e = __builtin_amdgcn_exp2f(-1.4426950408889634f * g);
-    return g * __builtin_amdgcn_rcpf(1.0f + e) * u;
 }
 
 // ------------------------------------------------------------------ strip GEMM core
@@ -559,21 +553,13 @@ struct StripGemm {
     }
 };
 
-// Two FP32 values rounded to BF16 (nearest even) and packed, lo in bits 0..15: one v_cvt_pk_bf16_f32.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
-    const f32x2_t v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-
 struct TileInfo {
     int32_t expert, row0, rows, slot;
 };
 
-// One 16-byte load: route_sort_kernel wrote (expert, first row, rows, slot) for every tile number below
+// A strip kernel's tile, one 16-byte load: route_sort_kernel wrote (expert, first row, rows, slot) for every tile number below
 // tiles_cap, with rows = 0 past the last tile.
-__device__ __forceinline__ bool tile_info(const FfnArgs& a, uint32_t tile, TileInfo& t) {
+__device__ __forceinline__ bool strip_tile(const FfnArgs& a, uint32_t tile, TileInfo& t) {
     const int4 r = a.tile_rec[tile];
     t.expert = r.x; t.row0 = r.y; t.rows = r.z; t.slot = r.w;
     return t.rows > 0 && t.slot >= 0;
@@ -787,7 +773,7 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
         if (lists && threadIdx.x == 0) a.tile_rec[tile] = make_int4(t.expert, t.row0, t.rows, t.slot);
         if (threadIdx.x < 64 && valid && leader == first) pair_list[__popcll(mine & ((1ull << lane) - 1ull))] = lane;
         __syncthreads();
-    } else if (!tile_info(a, tile_no, t)) {
+    } else if (!strip_tile(a, tile_no, t)) {
         return;                                       // uniform over the workgroup
     }
     const uint32_t n_split = !SPLIT ? 1u : (ROUTE ? a.ksplit1 : first_splits(a, n_tiles_all));
@@ -863,7 +849,7 @@ __global__ __launch_bounds__(256) void gemm2_kernel(FfnArgs a) {
     if (pair >= a.tiles_cap * a.ksplit) return;
     const uint32_t tile = pair / a.ksplit, split = pair % a.ksplit;
     TileInfo t;
-    if (!tile_info(a, tile, t)) return;
+    if (!strip_tile(a, tile, t)) return;
     if (MI > 1 && t.rows <= 16) gemm2_body<1>(a, t, abuf, col_wg, split);
     else if (MI > 2 && t.rows <= 32) gemm2_body<2>(a, t, abuf, col_wg, split);
     else if (MI > 4 && t.rows <= 64) gemm2_body<4>(a, t, abuf, col_wg, split);
@@ -878,8 +864,8 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(FfnArgs a) {
     const uint32_t per_row = a.F / 8;
     const uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x;
     const uint32_t row = uint32_t(i / per_row), n0 = 8u * uint32_t(i % per_row);
-    const uint32_t n_split = a.tiled && a.m_tile == 256 ? uint32_t(a.n_tiles[1]) : first_splits(a, uint32_t(a.n_tiles[0]));
-    if (n_split == 1 || row >= uint32_t(a.expert_offset[a.E])) return;       // h is there already; rows past the pairs whose expert is mapped
+    const uint32_t n_split = a.identity ? a.ksplit1 : (a.tiled && a.m_tile == 256 ? uint32_t(a.n_tiles[1]) : first_splits(a, uint32_t(a.n_tiles[0])));
+    if (n_split == 1 || row >= (a.identity ? a.T : uint32_t(a.expert_offset[a.E]))) return;       // h is there already; rows past the pairs whose expert is mapped
     float g[8], u[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) g[c] = u[c] = 0.f;
@@ -915,7 +901,6 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(FfnArgs a) {
 // 4 x 8 block of tiles and share operand slices in that XCD's L2.
 // MODE 1: the 256 tile columns are 128 of W1 and the same 128 of W3; a wavefront holds gate
 // and up values of the same elements and applies SwiGLU in registers.  MODE 2: y = h W2.
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kTM = 256, kTK = 64, kLdsPitch = kTK + 8;   // pitch in BF16 elements
 constexpr uint32_t kSuperM = 4, kSuperN = 8;              // tiles per super-tile (one XCD's 32 CUs)
@@ -936,7 +921,7 @@ __global__ __launch_bounds__(512) void gemm_tiled_kernel(FfnArgs a) {
     const uint32_t col_tile = (st % n_sn) * kSuperN + within % kSuperN;
     if (row_tile >= n_rt || col_tile >= n_ct) return;
     TileInfo t;
-    if (!tile_info(a, row_tile, t)) return;
+    if (!strip_tile(a, row_tile, t)) return;
     const uint32_t n_base = col_tile * ncols_tile;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1148,7 +1133,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const uint32_t col_tile = (st % n_sn) * kSuperN + within % kSuperN;
     if (row_tile >= n_rt || col_tile >= n_ct) return;
     TileInfo t;
-    if (!tile_info(a, row_tile, t)) return;
+    if (!strip_tile(a, row_tile, t)) return;
     const uint32_t n_base = col_tile * ncols_tile;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1718,8 +1703,21 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
             }
     } else {
         // one 64-bit address per stored row; the four column groups of a row lie 128 bytes apart
+        // (or, a.direct, the output: one split, row r is token r with gate 1)
         const uint32_t col0 = c.n_base + (TILE / 2u) * wn + q;
-        float* const ylane = a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
+        const bool direct = (WAVES == 8 || TILE == 128) && a.direct;
+        float* const ylane = direct ? a.out + size_t(c.row0) * a.H + col0 : a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
+        if (direct && (a.flags & 1u)) {
+#pragma unroll
+            for (int i = 0; i < kRowTiles; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int32_t row = min(32 * (wm + kWaveRows * i) + (r >> 2) * 8 + h * 4 + (r & 3), c.rows - 1);
+#pragma unroll
+                    for (int j = 0; j < kColTiles; ++j)
+                        if (col0 + 32u * j < N) acc[i][j][r] += ylane[size_t(uint32_t(row)) * a.H + 32 * j];
+                }
+        }
 #pragma unroll
         for (int i = 0; i < kRowTiles; ++i)
 #pragma unroll
@@ -1832,7 +1830,7 @@ __global__ __launch_bounds__(256) void combine_kernel(FfnArgs a) {
 #pragma unroll
         for (uint32_t j = 0; j < kGroup; ++j) {
             const bool in = k0 + j < a.K;
-            pos[j] = in ? a.pair_pos[tok * a.K + k0 + j] : -1;
+            pos[j] = in ? (a.identity ? int32_t(tok) : a.pair_pos[tok * a.K + k0 + j]) : -1;
             gate[j] = in ? (a.identity ? 1.f : a.topk_w[tok * a.K + k0 + j]) : 0.f;
         }
         float4 y[kGroup];
@@ -1908,10 +1906,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
-    if (!routes_itself) mark(1, 1);
-    if (routes_itself) {
-    } else if (a.identity) {
-        hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
+    const bool grouping = !routes_itself && !a.identity;
+    if (grouping) mark(1, 1);
+    const bool lists = a.identity && !a.ring1;
+    if (lists) hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
+    if (!grouping) {
     } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
         if (chooses) hipLaunchKernelGGL((route_sort_kernel<true, true>), dim3(1), dim3(1024), sh, stream, a);
@@ -1920,7 +1919,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     } else {
         launch_done(chooses ? route_sort_kernel<false, true> : route_sort_kernel<false, false>, dim3(1), dim3(1024), sh, stream, with_routing, a);
     }
-    if (!routes_itself) {
+    if (grouping) {
         mark(1, 0);
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
     }
@@ -1941,6 +1940,21 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const uint32_t cols1 = a.halves ? strips1 : (strips1 + 1) / 2;
     const dim3 g1 = a.g1_xcd && !routes_itself ? dim3((a.tiles_cap * a.ksplit1 + 7) / 8 * 8 * cols1, 1, 1) : dim3(cols1, a.tiles_cap, a.ksplit1);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
+    a.direct = a.identity && a.ksplit == 1 && (a.ring2 || (a.tiled && a.tiled_waves == 2));
+    if (a.ring1) {
+        mark(2, 1);
+        if (hipError_t e = launch_ring(a, 1, stream, nullptr); e != hipSuccess) return e;
+        launch_reduce();
+        mark(2, 0);
+        mark(3, 1);
+        if (hipError_t e = launch_ring(a, 2, stream, a.direct ? done : nullptr); e != hipSuccess) return e;
+        mark(3, 0);
+        if (a.direct) return hipSuccess;
+        mark(4, 1);
+        launch_combine(dim3((a.H / 4 + 255) / 256, a.T, 1));
+        mark(4, 0);
+        return hipGetLastError();
+    }
     // Weights that one row tile reads (experts with about a tile's rows at most) pass the caches by; with several they are
     // shared through L2.  A wave finds what its load just wrote.  Microseconds a call, default policy / non-temporal: 8 experts of H 4096
     // F 14336, 256 rows each 989 / 952, 1024 rows 2768 / 2807; 160 of H 5120 F 1536, 205 rows 2080 / 2062; 20 of those, 1200 rows
@@ -2072,6 +2086,10 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
         mark(3, 0);
+        if (a.direct) {
+            if (done) return hipEventRecord(done, stream);
+            return hipGetLastError();
+        }
         const dim3 gc2((a.H / 4 + 255) / 256, a.T, 1);
         mark(4, 1);
         launch_combine(gc2);

@@ -45,7 +45,8 @@ FLUXMOE_HD inline float tiled_cost(const SplitShape& s, uint32_t n_tiles, uint32
 
 struct FfnPlan {
     bool tiled, halves, g1_xcd;
-    uint32_t m_tile, ksplit, ksplit1, split_tiles, pairs_cap, tiles_cap, n_chunks;
+    // ring1, ring2: rows of a tile of gemm_ring_kernel in the first and second product, 0: the kernels that tiled and m_tile name
+    uint32_t m_tile, ksplit, ksplit1, split_tiles, ring1, ring2, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
     uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y;
 };
@@ -248,6 +249,63 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
 inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
     const FfnPlan p = plan_ffn_rules(c, T, K, mapped, true, limit);
     return p.bytes <= limit && p.tiles_cap <= kMaxRowTiles ? p : plan_ffn_rules(c, T, K, mapped, false, limit);
+}
+
+// One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.
+struct RingProduct {
+    uint32_t rows, splits;
+    uint64_t wgs, cap, ns;        // workgroups, how many run at a time, nanoseconds
+};
+// T rows, K x N matrix (first product: gate and up of N columns).  A workgroup takes 4.5 us to start and end and, per step of 64 k,
+// 0.40, 0.49 or 0.60 us (tiles of 32, 64, 128 rows) alone on a CU and 0.65 or 0.80 us for each of two; no faster than weights
+// leave HBM at 5.4 TB/s.  Splits cost a launch and their partial sums at 10 TB/s.  Measured, one product, weights out of HBM, without the
+// launch (model): H 5120 F 1536, first, 512 rows: 128 rows unsplit 50 (53), two splits 36 (36), 64 rows 42 (44), four splits 42;
+// second, 128 rows 20 (19), 64 rows 21 (24), 32 rows 27.
+inline RingProduct ring_product(uint64_t n_cus, uint64_t T, uint64_t K, uint64_t N, bool first) {
+    RingProduct best{0, 0, 0, 0, ~0ull};
+    const uint64_t steps = (K + 63) / 64, col_tiles = first ? (N + 63) / 64 : (N + 127) / 128;
+    const uint64_t bytes = K * N * (first ? 4 : 2), out_bytes = T * N * (first ? 16 : 8);     // of a split, written and read
+    for (const uint64_t rows : {32u, 64u, 128u}) {
+        const uint64_t alone = rows == 32 ? 400 : (rows == 64 ? 490 : 600), paired = rows == 32 ? 650 : 800;
+        const uint64_t cap = rows == 128 ? n_cus : 2 * n_cus, tiles = (T + rows - 1) / rows * col_tiles;
+        for (uint64_t k = 1; k <= 8 && (k == 1 || (2 * k <= steps && tiles * k <= cap)); ++k) {
+            const uint64_t per = (steps + k - 1) / k, wgs = tiles * k, rest = wgs % cap;
+            uint64_t ns = wgs / cap * (per * (rows == 128 ? alone : paired) + 4500);
+            if (rest) ns += per * (rest <= n_cus ? alone : paired) + 4500;
+            ns = std::max(ns, bytes * 10 / 54 / 1000 + 4500) + (k > 1 ? 4500 + k * out_bytes / 10000 : 0);
+            if (ns < best.ns) best = RingProduct{uint32_t(rows), uint32_t(k), wgs, cap, ns};
+        }
+    }
+    return best;
+}
+
+// The shared expert (every token once on one dense expert).  While the first product fits one round of workgroups and the second two,
+// both run in gemm_ring_kernel, which takes any H and F and lets the second product write the output itself where it is not
+// split.  Microseconds a call, weights out of HBM, other kernels / ring: H 5120 F 1536, 1 row 31 / 23, 64 rows 46 / 28, 512 rows 67 / 58;
+// H 2048 F 512, 211 rows 31 / 18, 1024 rows 40 / 27; H 4096 F 14336, 3 rows 88 / 70, 128 rows 128 / 93; H 4504 F 2776, 241 rows
+// 126 / 71, 700 rows 210 / 189; H 1000 F 200, 50 rows 35 / 15.
+// Where H and F are whole steps the other LDS-direct kernels win with two workgroups on a CU in the first product or two long
+// rounds in the second: H 5120 F 1536, 1344 rows 116 / 136, 1024 rows 91 / 97, 2048 rows 134 / 170; but H 5120 F 384, 1024 rows 48 / 41.
+inline FfnPlan plan_shared(const FfnShape& c, uint32_t T, uint64_t limit = ~0ull) {
+    const FfnPlan base = plan_ffn(c, T, 1, limit);
+    const uint64_t n_cus = uint64_t(std::max(c.n_cus, 1));
+    const RingProduct first = ring_product(n_cus, T, c.H, c.F, true), second = ring_product(n_cus, T, c.F, c.H, false);
+    if (c.tiled_waves != 2 || std::getenv("FLUXMOE_FFN_MTILE") || first.wgs > first.cap || second.wgs > 2 * second.cap) return base;
+    if (c.H % 64 == 0 && c.F % 64 == 0 && (first.wgs > first.splits * n_cus || (second.wgs > second.cap && c.F >= 1024))) return base;
+    FfnPlan p = base;
+    p.tiled = p.halves = p.g1_xcd = false;
+    p.ring1 = first.rows;
+    p.ring2 = second.rows;
+    p.ksplit1 = first.splits;
+    p.ksplit = second.splits;
+    auto bytes = [&]() {
+        const uint64_t y = p.ksplit > 1 ? uint64_t(p.ksplit) * T * c.H * 4 : 0, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * T * 2 * c.F * 4 : 0;
+        return p.off_y + align_up(std::max(y, part), 256);
+    };
+    while (p.ksplit1 > 1 && bytes() > limit) --p.ksplit1;
+    while (p.ksplit > 1 && bytes() > limit) --p.ksplit;
+    p.bytes = bytes();
+    return p.bytes <= limit ? p : base;
 }
 
 }  // namespace fluxmoe

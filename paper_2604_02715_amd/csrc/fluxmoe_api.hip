@@ -391,7 +391,7 @@ uint64_t fluxmoe_ffn_workspace_bytes(const fluxmoe_ctx* c, uint32_t T, uint32_t 
         return std::max(plan_ffn_rules(sh, T, k, 0, true, ~0ull).bytes, plan_ffn_rules(sh, T, k, 0, false, ~0ull).bytes);
     };
     uint64_t need = need_of(c->d.n_experts, K);
-    if (shared_expert) need = std::max(need, need_of(1, 1));          // same shapes, a single expert
+    if (shared_expert) need = std::max({need, need_of(1, 1), plan_shared(ffn_shape(c, 1), T).bytes});          // same shapes, a single expert
     return need;
 }
 
@@ -1149,7 +1149,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     if ((uintptr_t(w13) | uintptr_t(w2) | uintptr_t(tokens) | uintptr_t(out)) & 15)
         return set_error(FLUXMOE_EINVAL, "pointers must be 16-byte aligned");
     // this model's shapes, a single always-mapped expert
-    const FfnPlan p = plan_ffn(ffn_shape(c, 1), T, 1, c->ws_bytes - c->pool_ws_bytes);
+    const FfnPlan p = plan_shared(ffn_shape(c, 1), T, c->ws_bytes - c->pool_ws_bytes);
     if (c->pool_ws_bytes + p.bytes > c->ws_bytes)
         return set_error(FLUXMOE_ENOMEM, "workspace has %zu bytes, the shared expert with T=%u needs %llu",
                          c->ws_bytes, T, (unsigned long long)(c->pool_ws_bytes + p.bytes));
@@ -1176,6 +1176,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
     a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.halves = p.halves; a.g1_xcd = p.g1_xcd; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
+    a.ring1 = p.ring1; a.ring2 = p.ring2;
     a.split_tiles = ~0u;                        // the plan knew the rows
     a.n_cus = uint32_t(std::max(c->n_cus, 1));
     a.tiled_waves = c->tune_tiled_waves;

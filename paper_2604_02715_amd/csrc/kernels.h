@@ -52,6 +52,8 @@ struct FfnArgs {
                                  // workgroups), 0 = one workgroup per tile
     uint32_t tiled_sn_log2;      // set per launch by launch_ffn: log2 of the columns of the LDS-direct kernels' super-tile
     uint32_t tiled_total;        // set per launch by launch_ffn: tile numbers of the LDS-direct kernel's launch
+    uint32_t ring1, ring2;       // non-zero (identity): rows of a tile of gemm_ring_kernel in the first and second product
+    uint32_t direct;             // set by launch_ffn: the second product writes the output itself (identity, unsplit)
     uint32_t tiled_group;        // super-rows of the LDS-direct gate/up kernel that share a column block in time;
                                  // 0 = launch_ffn derives it from the rows per expert
 };
@@ -63,6 +65,8 @@ typedef void (*SpanHook)(void* user, int kind, int begin, hipStream_t stream);
 // done is attached to its launch; routed too if attach_routed, else it is recorded behind it (stream capture).
 hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, bool attach_routed,
                       SpanHook hook, void* user);
+// gemm_ring_kernel (ffn_ring.hip) for the first or second product
+hipError_t launch_ring(const FfnArgs& args, int product, hipStream_t stream, hipEvent_t done);
 hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgroups, uint32_t iters,
                              hipStream_t stream);
 // The decode kernel's launch shape and memory accesses without its work (probe_kernels.hip): n_blocks blocks of
