@@ -10,6 +10,9 @@ namespace fluxmoe {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
+// What an LDS-direct load fetches for a 16-byte piece past the end of K.
+static __device__ const uint4 g_zero_piece = {0, 0, 0, 0};
+
 // SiLU(g) * u (Sec. 2.1's gated FFN) in FP32 with the hardware's exp2 and reciprocal, each within one
 // ulp; the caller rounds the product to BF16.  g -> -inf gives exp2 = +inf, reciprocal 0, product -0.
 __device__ __forceinline__ float swiglu(float g, float u) {

@@ -1338,7 +1338,8 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // TILE: rows and columns of a workgroup's tile.  256: one workgroup per CU (160 KiB of LDS).  128, with WAVES = 4 as 2 x 2
 // of 64 x 64: two per CU, a quarter of the work per tile, for products whose 256 x 256 tiles leave most CUs without one.
 // STREAM: the weight loads carry the non-temporal hint.
-template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false>
+// RAGGED: K of either product may be any multiple of 8; the pieces of the last step that lie past its end come from zeros.
+template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false, bool RAGGED = false>
 __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kernel(FfnArgs a) {
     constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
     static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
@@ -1429,7 +1430,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     };
     uint8_t* const lds_b8 = reinterpret_cast<uint8_t*>(lds);
     const size_t mat = size_t(a.H) * a.F;
-    const uint32_t n_steps_all = K / kTK;
+    const uint32_t n_steps_all = RAGGED ? (K + kTK - 1) / kTK : K / kTK;
 
     // What a tile's loads need: the lane's byte offsets of its LDS-direct loads (kDma for A, kDma for B
     // per step) from bases that are uniform over the workgroup, the step range, where the results go.
@@ -1440,6 +1441,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const uint8_t* b_base;
         int32_t rows, row0;
         uint32_t n_base, split, n_steps;
+        uint32_t k_left;                     // RAGGED: k from the tile's first to the end of K
         bool valid;
     };
     // rec: the tile's record, loaded earlier.  Issues the gather of the rows' pair numbers (first product);
@@ -1460,6 +1462,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const uint32_t step_lo = uint32_t(uint64_t(n_steps_all) * split / n_split);
         const uint32_t step_hi = uint32_t(uint64_t(n_steps_all) * (split + 1) / n_split);
         const uint32_t k_begin = step_lo * kTK;
+        if (RAGGED) s.k_left = K - k_begin;
         s.n_steps = MODE == 1 ? 0u : step_hi - step_lo;        // >= 1: the host keeps the splits <= K / 64
         // rows of h are counted from the tile's first: offsets inside all of h would not fit 32 bits
         s.a_base = MODE == 1 ? nullptr
@@ -1517,11 +1520,21 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     auto dma_a = [&](const TileState& s, uint32_t k0, int a_stage_off, int n) __attribute__((always_inline)) {
         // (MODE 1 does not split K: its A base and step count are the same for every tile)
         const uint8_t* base = MODE == 1 ? reinterpret_cast<const uint8_t*>(a.tokens) : s.a_base;
-        dma16(base + size_t(k0) * 2 + s.a_off[n], lds_base + a_stage_off + (wave * kDma + n) * 1024);
+        const uint8_t* src = base + size_t(k0) * 2 + s.a_off[n];
+        if (RAGGED && k0 + kTK > (MODE == 1 ? K : s.k_left)) {              // uniform
+            const int lane = fresh_lane(), r_lds = 8 * (wave * kDma + n) + (lane >> 3);
+            if (k0 + 8u * ((lane & 7) ^ ((r_lds >> 1) & 7)) >= (MODE == 1 ? K : s.k_left)) src = reinterpret_cast<const uint8_t*>(&g_zero_piece);
+        }
+        dma16(src, lds_base + a_stage_off + (wave * kDma + n) * 1024);
     };
     auto dma_b = [&](const TileState& s, uint32_t k0, int b_stage_off, int n) __attribute__((always_inline)) {
-        if (STREAM) dma16_nt(s.b_base + size_t((FLUXMOE_D2L_PROBE & 16) ? 0u : k0) * N * 2 + s.b_off[n], lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
-        else dma16(s.b_base + size_t((FLUXMOE_D2L_PROBE & 16) ? 0u : k0) * N * 2 + s.b_off[n], lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
+        const uint8_t* src = s.b_base + size_t((FLUXMOE_D2L_PROBE & 16) ? 0u : k0) * N * 2 + s.b_off[n];
+        if (RAGGED && k0 + kTK > (MODE == 1 ? K : s.k_left)) {
+            const int lane = fresh_lane();
+            if (k0 + uint32_t((1024 / kRowB) * (wave * kDma + n) + lane / (kRowB / 16)) >= (MODE == 1 ? K : s.k_left)) src = reinterpret_cast<const uint8_t*>(&g_zero_piece);
+        }
+        if (STREAM) dma16_nt(src, lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
+        else dma16(src, lds_base + 2 * kStageBytes + b_stage_off + (wave * kDma + n) * 1024);
     };
     auto steps_of = [&](const TileState& s) __attribute__((always_inline)) { return MODE == 1 ? n_steps_all : s.n_steps; };
     // a tile's first loads: A and B of steps 0 and 1 into stages 0 and 1 (B of step 2 is issued by step 0)
@@ -1956,10 +1969,12 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         return hipGetLastError();
     }
     // Weights that one row tile reads (experts with about a tile's rows at most) pass the caches by; with several they are
-    // shared through L2.  A wave finds what its load just wrote.  Microseconds a call, default policy / non-temporal: 8 experts of H 4096
-    // F 14336, 256 rows each 989 / 952, 1024 rows 2768 / 2807; 160 of H 5120 F 1536, 205 rows 2080 / 2062; 20 of those, 1200 rows
-    // 1207 / 1279; 32 of H 1024 F 256, 75 rows 39.7 / 37.6; a pass in waves over 128 of H 2048 F 512 2012 / 2040.
-    const bool stream_b = !a.identity && !(a.flags & 2u) && uint64_t(a.T) * a.K <= uint64_t(a.m_tile) * std::min<uint64_t>(a.E, uint64_t(a.T) * a.K);
+    // shared through L2.  With many experts skew gives some of them several tiles, and waves find what their load just wrote.
+    // Microseconds a call, default policy / non-temporal: 8 experts of H 4096 F 14336, 250 rows each 950 / 890, 1024 rows 2768 / 2807; 20 of
+    // H 5120 F 1536, 240 rows 377 / 361, 1200 rows 1207 / 1279; 32 of H 1024 F 256, 75 rows 39.7 / 37.6; 160 of H 5120 F 1536, even routing,
+    // 205 rows 2080 / 2062, popularity by rank, 175 rows 2270 / 2291; 512 of H 2048 F 512, 234 rows 1415 / 1438; a pass in waves
+    // over 128 of those 2012 / 2040.
+    const bool stream_b = !a.identity && !(a.flags & 2u) && a.E <= 64 && uint64_t(a.T) * a.K <= uint64_t(a.m_tile) * std::min<uint64_t>(a.E, uint64_t(a.T) * a.K);
     if (a.tiled) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
         const bool four = a.tiled_waves == 4;
@@ -1969,7 +1984,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         if (!d2l && a.ksplit != 1) return hipErrorInvalidValue;     // only the LDS-direct kernels split K
         if (a.tiled_waves != 2 && (a.ksplit1 != 1 || small)) return hipErrorInvalidValue;
         if (!small && a.m_tile != 256) return hipErrorInvalidValue;
-        if (a.ksplit == 0 || a.ksplit > a.F / kTK) return hipErrorInvalidValue;
+        if (a.ksplit == 0 || a.ksplit > std::max(1u, a.F / kTK)) return hipErrorInvalidValue;
+        const bool ragged = a.H % kTK != 0 || a.F % kTK != 0;
+        if (ragged && (a.tiled_waves != 2 || small)) return hipErrorInvalidValue;        // only the eight-wavefront LDS-direct kernels take a partial step
         static bool attr_set = false;
         if (!attr_set) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tiled_kernel<1>),
@@ -1993,7 +2010,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
             if (e != hipSuccess) return e;
-            for (const void* f : {reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true>),
+            for (const void* f : {reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 8, false, 256, false, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true>)}) {
                 e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
                 if (e != hipSuccess) return e;
@@ -2015,6 +2036,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             if (e != hipSuccess) return e;
             attr_set = true;
         }
+        auto pick = [&](auto plain, auto streams, auto partial, auto both) { return ragged ? (stream_b ? both : partial) : (stream_b ? streams : plain); };
         mark(2, 1);
         // register-staged kernels: super-tiles of 4 x 8 tiles, super-row order
         auto grid_for = [&](uint32_t n_ct) {
@@ -2067,8 +2089,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             else hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<1, 4, false, 128, true> : gemm_d2l_kernel<1, 4, false, 128>), g, dim3(256), 81920, stream, a);
         }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 256>), g, dim3(256), 163840, stream, a); }
-        else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<3, 8, false, 256>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<1, 8, true, 256, true> : gemm_d2l_kernel<1, 8, true, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((ragged ? gemm_d2l_kernel<3, 8, false, 256, false, true> : gemm_d2l_kernel<3, 8, false, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((pick(gemm_d2l_kernel<1, 8, true, 256>, gemm_d2l_kernel<1, 8, true, 256, true>, gemm_d2l_kernel<1, 8, true, 256, false, true>, gemm_d2l_kernel<1, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<1>, grid_for((a.F + 127) / 128), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<1>, grid_for((a.F + 127) / 128), dim3(512), lds_bytes, stream, a);
         launch_reduce();
@@ -2081,8 +2103,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
-        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 8, true, 256, true> : gemm_d2l_kernel<2, 8, true, 256>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 8, false, 256, true> : gemm_d2l_kernel<2, 8, false, 256>), g, dim3(512), 163840, stream, a); }
+        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, false, 256>, gemm_d2l_kernel<2, 8, false, 256, true>, gemm_d2l_kernel<2, 8, false, 256, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
         mark(3, 0);

@@ -58,6 +58,7 @@ inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 struct FfnShape {
     uint64_t E, H, F;
     int n_cus, tiled_waves;
+    bool ragged = false;         // the 256 x 256 tiles may be taken where H or F is not a multiple of 64
 };
 
 // split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.
@@ -81,8 +82,9 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // a streaming pass at these sizes.
     auto p_over = [&](double m) { return 0.5 * std::erfc((m + 0.5 - double(avg)) / std::sqrt(2.0 * double(avg))); };
     const bool tileable = H % 64 == 0 && F % 64 == 0;
+    const bool tiles256 = tileable || (split && c.ragged && c.tiled_waves == 2);
     p.m_tile = 128;
-    if (p_over(128) > 0.02 && 1.0 + p_over(128) + p_over(256) + p_over(384) > 1.6 && tileable)
+    if (p_over(128) > 0.02 && 1.0 + p_over(128) + p_over(256) + p_over(384) > 1.6 && tiles256)
         p.m_tile = 256;
     bool forced = false;
     if (const char* v = std::getenv("FLUXMOE_FFN_MTILE")) {
@@ -90,8 +92,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         if (m == 16 || m == 32 || m == 64 || m == 96 || m == 128 || (m == 256 && tileable)) { p.m_tile = uint32_t(m); forced = true; }
     }
     p.tiled = p.m_tile == 256;
+    // H or F that is not a multiple of 64: the 256 x 256 tiles take a partial step, so the same line holds.  Microseconds a call, 128-row strips /
+    // tiles: 8 experts of H 3000 F 7000, 250 rows each 540 / 405, 1024 rows 1712 / 1160; 160 of H 2600 F 1000, 150 rows 1204 / 761;
+    // 64 of H 2000 F 312, 1250 rows 1010 / 673; one of H 5000 F 1496, 2000 rows 199 / 149.
     // Where the launch would leave CUs without a workgroup.  All figures: microseconds per call, weights out of HBM.
-    if (split && !forced && tileable && c.tiled_waves == 2) {
+    if (split && !forced && tiles256 && c.tiled_waves == 2) {
         const double avg_act = double(pairs_act) / double(groups_act);
         const bool few_strips = 2 * ((F + 255) / 256) * groups_act <= n_cus;       // strip workgroups before any K split
         if (p.tiled) {
@@ -102,12 +107,12 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             // bounds the call and two workgroups keep more loads in flight, up to a round and a half: H 4096 F 14336, 512 rows
             // (224): 255 / 237.  Several experts with several row tiles each stay (20 of H 5120 F 1536, 205 rows: 383 / 451).
             // T rows, not the mean of what one of several experts gets: a batch may be routed to it alone.
-            if (groups_act == 1 && (T <= 512 ? 2 : 4) * ((uint64_t(T) + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
+            if (tileable && groups_act == 1 && (T <= 512 ? 2 : 4) * ((uint64_t(T) + 255) / 256) * ((F + 127) / 128) <= 3 * n_cus) p.m_tile = 128;
         } else if (few_strips && groups_act > 1 && 0.5 * std::erfc((128.5 - avg_act) / std::sqrt(2.0 * avg_act)) > 0.02) {
             // Experts that often need a second 128-row strip tile: 8 of H 4096 F 1792, 128 rows each: strips 172, tiles of 256 121.
             p.tiled = true;
             p.m_tile = 256;
-        } else if (few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20)
+        } else if (tileable && few_strips && (groups_act == 1 ? pairs_act >= 64 && H * F * 6 <= (64u << 20)
                                                   : 8 * groups_act <= n_cus && avg_act >= 16 && H <= (mapped && mapped < E ? 2048u : 1024u))) {
             // Row counts that make a matrix tile worth while and K too short for the strips' start-up, strips / tiles of 128:
             // one expert, weights out of HBM and behind a kernel that filled the caches with other data: H 2048 F 512, 64 rows
@@ -142,6 +147,18 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     }
     p.ksplit = uint32_t(ks);
     p.ksplit1 = 1;
+    // Tiles where H or F is no multiple of 64 stand in for strips, and a sum is as long as it would be there at most: the strips'
+    // K splits and halves are kept as splits (8 experts of H 4400 F 3504, 140 rows each: share of tokens with an h
+    // rounded the other way 0.225 in strips' halves, 0.271 unsplit).
+    uint32_t chains = 1;
+    if (p.tiled && !tileable) {
+        FfnShape strips = c;
+        strips.ragged = false;
+        const FfnPlan q = plan_ffn_rules(strips, T, K, mapped, split, limit);
+        chains = q.ksplit1 * (q.halves ? 2u : 1u);
+        if (chains > 1 && H < 256 * chains) return q;            // short K: the sums of the splits cost more (8 experts of H 264 F 400, 250 rows 52 / 53)
+        p.ksplit1 = chains;
+    }
     // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when
     // split k ways.  A tile costs 3 us to start; a step 1.4 us (256 x 256, one workgroup per CU), or 0.56 us (128 x 128)
     // alone on a CU and 0.88 us for each of two.  Partial sums are written and read at 10 TB/s (mostly in the caches).
@@ -196,7 +213,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         } else {
             const uint64_t cols = p.m_tile / 2;
             const uint64_t tiles1 = row_tiles * ((F + cols - 1) / cols), room = p.m_tile == 256 ? n_cus : 2 * n_cus;
-            for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 512 <= H && tiles1 * k <= room)); ++k) {
+            for (uint64_t k = chains; k <= std::max(8u, chains) && (k == chains || (k * 512 <= H && tiles1 * k <= room)); ++k) {
                 const uint64_t cost = tile_ns(tiles1, H / 64, k) + (k > 1 ? 4500 + k * partial_bytes / 10000 : 0);
                 if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); }
             }
@@ -225,8 +242,10 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         return p.off_y + align_up(std::max(y, part), 256);
     };
     if (split) {
-        while (p.ksplit1 > 1 && end() > limit) --p.ksplit1;
-        if (p.ksplit1 > 1 && p.tiled && p.m_tile == 256) {
+        while (p.ksplit1 > chains && end() > limit) --p.ksplit1;
+        if (chains > 1) {
+            p.split_tiles = ~0u;
+        } else if (p.ksplit1 > 1 && p.tiled && p.m_tile == 256) {
             const SplitShape s{uint32_t(H), uint32_t(F), uint32_t(n_cus)};
             const auto cost = [&](uint32_t k) { return tiled_cost(s, uint32_t(row_tiles), uint32_t(pairs_act), k); };
             p.split_tiles = uint32_t(row_tiles);

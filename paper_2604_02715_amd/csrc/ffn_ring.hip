@@ -22,8 +22,6 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 constexpr int kTK = 64;                       // k of a step
 constexpr int kTN = 128;                      // columns of a tile: of y, or 64 of W1 and the same 64 of W3
 
-__device__ const uint4 g_zero_piece = {0, 0, 0, 0};
-
 template <int N> using Int = std::integral_constant<int, N>;
 
 // MODE 1: h = SwiGLU(X W1, X W3).  MODE 2: y = h W2, K split ksplit ways, or the output itself (a.direct).

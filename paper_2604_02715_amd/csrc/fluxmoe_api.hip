@@ -150,7 +150,7 @@ void compute_layout(fluxmoe_ctx* c) {
 }
 
 FfnShape ffn_shape(const fluxmoe_ctx* c, uint32_t n_experts) {
-    return FfnShape{n_experts, c->d.hidden, c->d.ffn, c->n_cus, c->tune_tiled_waves};
+    return FfnShape{n_experts, c->d.hidden, c->d.ffn, c->n_cus, c->tune_tiled_waves, true};
 }
 
 // Pair table of the decode kernel, indexed by the next 12 stream bits (first stream bit in bit 0).

@@ -1,0 +1,83 @@
+"""Launch plans where H or F is not a multiple of 64 (csrc/ffn_plan.h with FfnShape::ragged), compiled on their own: the
+256 x 256 tiles stand in for weight strips."""
+import ctypes as C
+import os
+import random
+import subprocess
+from types import SimpleNamespace
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_02715_amd", "csrc")
+FIELDS = ("tiled", "halves", "m_tile", "ksplit", "ksplit1", "split_tiles", "tiles_cap", "bytes", "off_h", "off_y")
+SHIM = """
+#include "ffn_plan.h"
+using namespace fluxmoe;
+extern "C" void plan(uint64_t E, uint64_t H, uint64_t F, int waves, int ragged, uint32_t T, uint32_t K, uint64_t limit, uint32_t mapped, int split, uint64_t* o) {
+    const FfnShape c{E, H, F, 256, waves, ragged != 0};
+    const FfnPlan p = split ? plan_ffn(c, T, K, limit, mapped) : plan_ffn_rules(c, T, K, mapped, false, ~0ull);
+    %s
+}
+""" % " ".join("o[%d] = p.%s;" % (i, f) for i, f in enumerate(FIELDS))
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("ffn_plan_ragged")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
+    so = C.CDLL(str(d / "shim.so"))
+    u32, u64 = C.c_uint32, C.c_uint64
+    so.plan.argtypes = [u64, u64, u64, C.c_int, C.c_int, u32, u32, u64, u32, C.c_int, C.POINTER(u64)]
+
+    def call(T, K, E, H, F, mapped=0, limit=2 ** 64 - 1, waves=2, ragged=True, split=True):
+        o = (u64 * len(FIELDS))()
+        so.plan(E, H, F, waves, ragged, T, K, limit, mapped, split, o)
+        return SimpleNamespace(**dict(zip(FIELDS, o)))
+    return call
+
+
+@pytest.fixture(autouse=True)
+def no_overrides(monkeypatch):
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+
+
+def test_random_calls_at_any_buffer_size(plan):
+    rng = random.Random(9)
+    tiles = kept = 0
+    for _ in range(3000):
+        E = rng.choice([1, 2, 8, 20, 64, 160, 512])
+        H, F = 8 * rng.randrange(1, 640), 8 * rng.randrange(1, 640)
+        if rng.random() < 0.3:
+            H = 64 * rng.randrange(1, 80)
+        K = rng.randrange(1, min(E, 12) + 1)
+        c = dict(T=max(1, min(65535, int(2 ** rng.uniform(4, 16)))), K=K, E=E, H=H, F=F, mapped=rng.choice([0, 1, E]), waves=rng.choice([2, 2, 2, 1, 8]))
+        best, strips, least = plan(**c), plan(**c, ragged=False), plan(**c, split=False)
+        assert least.__dict__ == plan(**c, split=False, ragged=False).__dict__           # what is always enough stays what it was
+        if H % 64 == 0 and F % 64 == 0 or c["waves"] != 2:
+            assert best.__dict__ == strips.__dict__
+        for limit in (2 ** 64 - 1, least.bytes, (least.bytes + best.bytes) // 2, best.bytes):
+            p = plan(**c, limit=limit)
+            if limit >= least.bytes:
+                assert p.bytes <= limit
+            if not p.tiled or (H % 64 == 0 and F % 64 == 0):
+                continue
+            pairs = c["T"] * K
+            assert p.m_tile == 256 and not p.halves and p.tiles_cap <= 65535
+            assert 1 <= p.ksplit <= max(1, F // 64) and 1 <= p.ksplit1 <= max(1, H // 64)
+            assert p.off_y >= p.off_h + pairs * F * 2
+            assert p.bytes >= p.off_y + p.ksplit * pairs * H * 4
+            assert p.bytes >= p.off_y + (p.ksplit1 * pairs * 2 * F * 4 if p.ksplit1 > 1 else 0)
+            q = plan(**c, ragged=False, limit=limit)     # sums no longer than the strips'
+            chains = q.ksplit1 * (2 if q.halves else 1)
+            assert p.ksplit1 >= chains and (chains == 1 or (p.split_tiles == 2 ** 32 - 1 and H >= 256 * chains))
+            tiles += 1
+            kept += chains > 1
+    assert tiles > 500 and kept > 50
+
+
+def test_the_line_is_that_of_whole_steps(plan):
+    of = lambda T, H, F: (lambda p: (bool(p.tiled), p.m_tile))(plan(T, 2, 8, H, F))
+    for T in (256, 440, 480, 520, 560, 4096):
+        assert of(T, 4104, 14328) == of(T, 4096, 14336)
+    assert of(480, 4104, 14328) == (False, 128) and of(560, 4104, 14328) == (True, 256)

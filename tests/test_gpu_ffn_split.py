@@ -214,3 +214,36 @@ def test_row_groups_of_the_lds_tiled_kernels(rows, monkeypatch):
     fetched or multiplied."""
     monkeypatch.setenv("FLUXMOE_FFN_MTILE", "256")
     run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=rows, top_k=1, n_experts=1, n_slots=1, hidden=256, ffn=192), seed=3)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(tokens=300, top_k=1, n_experts=1, n_slots=1, hidden=8, ffn=40),        # a partial step is all there is
+    dict(tokens=700, top_k=2, n_experts=3, n_slots=3, hidden=200, ffn=328),     # tails of 8 in both products, ragged columns
+    dict(tokens=600, top_k=2, n_experts=4, n_slots=4, hidden=1096, ffn=1000),   # splits that stand for the strips' halves
+    dict(tokens=300, top_k=1, n_experts=2, n_slots=2, hidden=264, ffn=2056),    # second product split, the last with a partial step
+    dict(tokens=2600, top_k=2, n_experts=20, n_slots=20, hidden=136, ffn=72),   # several tiles for a workgroup
+    dict(tokens=520, top_k=1, n_experts=2, n_slots=2, hidden=256, ffn=1032),    # one product whole, one with a partial step
+])
+def test_large_tiles_with_a_partial_step(kw):
+    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=12)
+
+
+def test_infinite_weights_past_whole_steps_stay_where_they_belong():
+    """The pieces past the end of K are zeros: an infinite weight in the last k row of the second product reaches its own
+    column only."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=300, top_k=1, n_experts=1, n_slots=1, hidden=72, ffn=200)
+    pool, dense = build_pool(cfg)
+    try:
+        x, (ids, g) = inputs.activations(cfg), inputs.routing(cfg)
+        out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+        pool.reset_page_table()
+        pool.materialize(0, np.arange(1, dtype=np.int32), np.arange(1, dtype=np.int32))
+        torch.cuda.synchronize()
+        pool.slot2(0).view(torch.bfloat16).view(cfg.ffn, cfg.hidden)[cfg.ffn - 1, 5] = float("inf")
+        pool.expert_ffn(0, x.cuda(), torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda(), out)
+        torch.cuda.synchronize()
+        bad = ~torch.isfinite(out.cpu())
+        assert bool(bad[:, 5].all()) and int(bad.sum()) == cfg.tokens
+    finally:
+        pool.close()
