@@ -1,4 +1,4 @@
-// Offline encoder of the compressed expert pool (host only).
+// Code construction of the offline encoder of the compressed expert pool (host only; the loops over weights: encode_core.h).
 //
 // Paper Sec. 4.2 "Compressed GPU backend": only the exponent bits of the BF16 routed-expert
 // weights are Huffman coded, offline; sign and mantissa bits are stored unchanged.  The
@@ -79,87 +79,6 @@ void canonical_codes(const uint8_t lens[256], uint16_t codes[256]) {
             }
             codes[s] = static_cast<uint16_t>(next);
             prev_len = len;
-        }
-    }
-}
-
-static inline uint32_t exponent_of(uint16_t w) { return (w >> 7) & 0xFFu; }
-
-// Greedy packing in groups of 64 elements: a block takes the largest number of whole groups
-// whose header + raw bytes + code words still fit.
-void plan_tensor(const uint16_t* w, uint64_t n_elems, const uint8_t lens[256],
-                 uint32_t block_bytes, std::vector<uint32_t>& first_elem) {
-    first_elem.clear();
-    first_elem.push_back(0);
-    uint64_t pos = 0;
-    while (pos < n_elems) {
-        uint64_t n = 0, bits = 0;
-        while (pos + n < n_elems) {
-            uint64_t gbits = 0;
-            const uint16_t* g = w + pos + n;
-            for (uint32_t i = 0; i < kGroup; ++i) gbits += lens[exponent_of(g[i])];
-            const uint64_t need = kHeaderBytes + (n + kGroup) + 4 * ((bits + gbits + 31) / 32);
-            if (need > block_bytes) break;
-            n += kGroup;
-            bits += gbits;
-        }
-        pos += n;   // n >= 64 always: 136 + 64 + 96 bytes fit any supported block size
-        first_elem.push_back(static_cast<uint32_t>(pos));
-    }
-}
-
-void encode_tensor(const uint16_t* w, const std::vector<uint32_t>& first_elem,
-                   const uint8_t lens[256], const uint16_t codes[256], uint32_t block_bytes,
-                   uint8_t* dst) {
-    // codes with their first bit in bit 0 (the stream is filled from bit 0 upwards)
-    uint32_t rev[256];
-    for (int s = 0; s < 256; ++s) {
-        uint32_t r = 0;
-        for (uint32_t b = 0; b < lens[s]; ++b) r |= ((codes[s] >> (lens[s] - 1 - b)) & 1u) << b;
-        rev[s] = r;
-    }
-    const size_t n_blocks = first_elem.size() - 1;
-    for (size_t k = 0; k < n_blocks; ++k) {
-        uint8_t* blk = dst + k * static_cast<size_t>(block_bytes);
-        std::memset(blk, 0, block_bytes);
-        const uint32_t e0 = first_elem[k];
-        const uint32_t n = first_elem[k + 1] - e0;
-        const uint16_t* src = w + e0;
-        std::memcpy(blk, &n, 4);
-        std::memcpy(blk + 4, &e0, 4);
-        uint8_t* sm = blk + kHeaderBytes;
-        for (uint32_t m = 0; m < n; ++m)
-            sm[m] = static_cast<uint8_t>(((src[m] >> 8) & 0x80u) | (src[m] & 0x7Fu));
-        // sub-streams are written one after another by a single bit writer
-        uint8_t* area = blk + kHeaderBytes + n;
-        uint64_t acc = 0;
-        uint32_t fill = 0;
-        size_t word = 0;
-        const uint32_t n_runs = n / 8;
-        for (uint32_t j = 0; j < kSubStreams; ++j) {
-            uint32_t bits_j = 0;
-            for (uint32_t r = j; r < n_runs; r += kSubStreams) {
-                const uint16_t* run = src + 8u * r;
-                for (uint32_t i = 0; i < 8; ++i) {
-                    const uint32_t s = exponent_of(run[i]);
-                    acc |= static_cast<uint64_t>(rev[s]) << fill;
-                    fill += lens[s];
-                    bits_j += lens[s];
-                    if (fill >= 32) {
-                        const uint32_t out = static_cast<uint32_t>(acc);
-                        std::memcpy(area + 4 * word, &out, 4);
-                        ++word;
-                        acc >>= 32;
-                        fill -= 32;
-                    }
-                }
-            }
-            const uint16_t sb = static_cast<uint16_t>(bits_j);
-            std::memcpy(blk + 8 + 2 * j, &sb, 2);
-        }
-        if (fill) {
-            const uint32_t out = static_cast<uint32_t>(acc);
-            std::memcpy(area + 4 * word, &out, 4);
         }
     }
 }

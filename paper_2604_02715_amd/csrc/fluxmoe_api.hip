@@ -13,10 +13,15 @@
 #include <atomic>
 #include <cstdlib>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
+#include <mutex>
 #include <new>
+#include <system_error>
 #include <thread>
+#include <type_traits>
 
+#include "encode_core.h"
 #include "fluxmoe_internal.h"
 
 namespace fluxmoe {
@@ -148,6 +153,74 @@ void compute_layout(fluxmoe_ctx* c) {
     c->err_off = c->cmd_off + uint64_t(kRing) * c->cmd_bytes;
     c->pool_ws_bytes = align_up(c->err_off + 256, 4096);
 }
+
+// A set of threads that go through several passes together: take() hands out the numbers 0, 1, .. of the current pass, wait()
+// ends it for everybody, and the last to arrive runs `once` before the next one begins.  The caller is one of them; where the system
+// gives fewer threads than asked for, those that there are do the work.
+class Crew {
+public:
+    explicit Crew(int wanted) {
+        threads_.reserve(size_t(wanted - 1));
+        for (int t = 1; t < wanted; ++t) {
+            try {
+                threads_.emplace_back([this, t]() {
+                    {
+                        std::unique_lock<std::mutex> lock(m_);
+                        cv_.wait(lock, [this]() { return work_ != nullptr || closed_; });
+                        if (!work_) return;
+                    }
+                    work_(user_, uint32_t(t));
+                });
+            } catch (const std::system_error&) {
+                break;
+            }
+        }
+    }
+    ~Crew() {
+        { std::lock_guard<std::mutex> lock(m_); closed_ = true; }
+        cv_.notify_all();
+        for (auto& t : threads_) t.join();
+    }
+    uint32_t size() const { return uint32_t(threads_.size()) + 1; }
+    template <typename F>
+    void run(F&& f) {
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            user_ = &f;
+            work_ = [](void* u, uint32_t me) { (*static_cast<std::remove_reference_t<F>*>(u))(me); };
+        }
+        cv_.notify_all();
+        f(0u);
+        for (auto& t : threads_) t.join();
+        threads_.clear();
+    }
+    uint64_t take() { return next_.fetch_add(1, std::memory_order_relaxed); }
+    template <typename F>
+    void wait(F&& once) {
+        std::unique_lock<std::mutex> lock(m_);
+        const uint64_t pass = pass_;
+        if (++arrived_ == size()) {
+            once();
+            arrived_ = 0;
+            next_.store(0, std::memory_order_relaxed);
+            ++pass_;
+            cv_.notify_all();
+        } else {
+            cv_.wait(lock, [&]() { return pass_ != pass; });
+        }
+    }
+
+private:
+    std::vector<std::thread> threads_;
+    std::mutex m_;
+    std::condition_variable cv_;
+    void (*work_)(void*, uint32_t) = nullptr;
+    void* user_ = nullptr;
+    bool closed_ = false;
+    std::atomic<uint64_t> next_{0};
+    uint64_t pass_ = 0;
+    uint32_t arrived_ = 0;
+};
 
 FfnShape ffn_shape(const fluxmoe_ctx* c, uint32_t n_experts) {
     return FfnShape{n_experts, c->d.hidden, c->d.ffn, c->n_cus, c->tune_tiled_waves, true};
@@ -417,79 +490,67 @@ int fluxmoe_encode_pool(fluxmoe_ctx* c, uint32_t layer, const uint16_t* w13, con
     L.bound = false;
     const uint64_t elems[2] = {c->elems13, c->elems2};
     const uint16_t* base[2] = {w13, w2};
+    const bool vector = encode_vector_available();
+    auto tensor = [&](uint32_t i) { return base[i / E] + size_t(i % E) * elems[i / E]; };      // i: type index * E + expert
 
-    auto parallel_for = [&](uint32_t count, auto&& fn) {
-        std::atomic<uint32_t> next{0};
-        auto worker = [&]() {
-            for (;;) {
-                const uint32_t i = next.fetch_add(1);
-                if (i >= count) break;
-                fn(i);
+    // One set of threads goes through the three passes over the weights; between them the last to arrive does what has to be
+    // done once.  Units are pieces of tensors, so that the threads end together whatever the number of tensors is.
+    constexpr uint64_t kCountElems = 1u << 17, kBlocksPerUnit = 16;
+    Crew crew(n_threads);
+    std::vector<std::array<uint64_t, 512>> hist(crew.size(), std::array<uint64_t, 512>{});
+    Coder coder[2];
+    std::vector<uint64_t> unit_end(2 * size_t(E));           // encode units up to and with each tensor's
+    const uint64_t count_units[2] = {(elems[0] + kCountElems - 1) / kCountElems, (elems[1] + kCountElems - 1) / kCountElems};
+    uint8_t* const out = static_cast<uint8_t*>(dst);
+    bool fits = false;
+    crew.run([&](uint32_t me) {
+        // 1. exponent histograms, one per tensor type over all experts
+        for (uint64_t u; (u = crew.take()) < E * (count_units[0] + count_units[1]);) {
+            const int ti = u < E * count_units[0] ? 0 : 1;
+            const uint64_t v = ti ? u - E * count_units[0] : u, at = v % count_units[ti] * kCountElems;
+            count_exponents(base[ti] + size_t(v / count_units[ti]) * elems[ti] + at, std::min(kCountElems, elems[ti] - at), hist[me].data() + 256 * ti);
+        }
+        crew.wait([&]() {
+            for (int ti = 0; ti < 2; ++ti) {
+                uint64_t total[256] = {};
+                for (const auto& h : hist)
+                    for (int s = 0; s < 256; ++s) total[s] += h[256 * ti + s];
+                uint16_t codes[256];
+                limited_code_lengths(total, c->d.max_code_len, L.lens[ti]);
+                canonical_codes(L.lens[ti], codes);
+                coder[ti] = Coder(L.lens[ti], codes);
+                L.payload_bits[ti] = 0;
+                for (int s = 0; s < 256; ++s) L.payload_bits[ti] += total[s] * L.lens[ti][s];
+                L.tensors[ti].assign(E, TensorMeta());
             }
-        };
-        std::vector<std::thread> th;
-        for (int t = 1; t < n_threads; ++t) th.emplace_back(worker);
-        worker();
-        for (auto& t : th) t.join();
-    };
-
-    // 1. exponent histograms, one per tensor type over all experts
-    std::vector<std::array<uint64_t, 256>> hist(2 * size_t(E));
-    parallel_for(2 * E, [&](uint32_t i) {
-        const int ti = i / E;
-        const uint32_t e = i % E;
-        auto& h = hist[i];
-        h.fill(0);
-        const uint16_t* w = base[ti] + size_t(e) * elems[ti];
-        uint64_t local[4][256] = {};
-        uint64_t m = 0;
-        for (; m + 4 <= elems[ti]; m += 4) {
-            ++local[0][(w[m] >> 7) & 0xFF];
-            ++local[1][(w[m + 1] >> 7) & 0xFF];
-            ++local[2][(w[m + 2] >> 7) & 0xFF];
-            ++local[3][(w[m + 3] >> 7) & 0xFF];
+        });
+        // 2. block plan of every tensor
+        for (uint64_t i; (i = crew.take()) < 2 * uint64_t(E);)
+            plan_tensor(tensor(uint32_t(i)), elems[i / E], coder[i / E], B, L.tensors[i / E][i % E].first_elem, vector);
+        crew.wait([&]() {
+            // blob order: down tensors (type 2) first, then fused gate/up tensors
+            uint64_t nb = 0, units = 0;
+            for (int ti : {1, 0})
+                for (uint32_t e = 0; e < E; ++e) {
+                    L.tensors[ti][e].first_block = nb;
+                    nb += L.tensors[ti][e].n_blocks();
+                }
+            for (uint32_t i = 0; i < 2 * E; ++i) unit_end[i] = units += (L.tensors[i / E][i % E].n_blocks() + kBlocksPerUnit - 1) / kBlocksPerUnit;
+            L.n_blocks = nb;
+            fits = size_t(nb) * B <= dst_cap;
+        });
+        // 3. encode
+        if (!fits) return;
+        for (uint64_t u; (u = crew.take()) < unit_end.back();) {
+            const uint32_t i = uint32_t(std::upper_bound(unit_end.begin(), unit_end.end(), u) - unit_end.begin());
+            const TensorMeta& tm = L.tensors[i / E][i % E];
+            const uint64_t k0 = (u - (i ? unit_end[i - 1] : 0)) * kBlocksPerUnit;
+            encode_blocks(tensor(i), tm.first_elem, k0, std::min(k0 + kBlocksPerUnit, tm.n_blocks()), coder[i / E], B, out + size_t(tm.first_block) * B, vector);
         }
-        for (; m < elems[ti]; ++m) ++local[0][(w[m] >> 7) & 0xFF];
-        for (int s = 0; s < 256; ++s) h[s] = local[0][s] + local[1][s] + local[2][s] + local[3][s];
     });
-    uint16_t codes[2][256];
-    for (int ti = 0; ti < 2; ++ti) {
-        uint64_t total[256] = {};
-        for (uint32_t e = 0; e < E; ++e)
-            for (int s = 0; s < 256; ++s) total[s] += hist[size_t(ti) * E + e][s];
-        limited_code_lengths(total, c->d.max_code_len, L.lens[ti]);
-        canonical_codes(L.lens[ti], codes[ti]);
-        L.payload_bits[ti] = 0;
-        for (int s = 0; s < 256; ++s) L.payload_bits[ti] += total[s] * L.lens[ti][s];
-        L.tensors[ti].assign(E, TensorMeta());
-    }
-    // 2. block plan of every tensor
-    parallel_for(2 * E, [&](uint32_t i) {
-        const int ti = i / E;
-        const uint32_t e = i % E;
-        plan_tensor(base[ti] + size_t(e) * elems[ti], elems[ti], L.lens[ti], B,
-                    L.tensors[ti][e].first_elem);
-    });
-    // 3. blob order: down tensors (type 2) first, then fused gate/up tensors
-    uint64_t nb = 0;
-    for (int ti : {1, 0})
-        for (uint32_t e = 0; e < E; ++e) {
-            L.tensors[ti][e].first_block = nb;
-            nb += L.tensors[ti][e].n_blocks();
-        }
-    L.n_blocks = nb;
-    *dst_used = size_t(nb) * B;
-    if (size_t(nb) * B > dst_cap)
-        return set_error(FLUXMOE_ENOMEM, "layer blob needs %zu bytes, dst_cap is %zu", size_t(nb) * B, dst_cap);
-    // 4. encode
-    uint8_t* out = static_cast<uint8_t*>(dst);
-    parallel_for(2 * E, [&](uint32_t i) {
-        const int ti = i / E;
-        const uint32_t e = i % E;
-        const TensorMeta& tm = L.tensors[ti][e];
-        encode_tensor(base[ti] + size_t(e) * elems[ti], tm.first_elem, L.lens[ti], codes[ti], B,
-                      out + size_t(tm.first_block) * B);
-    });
+    *dst_used = size_t(L.n_blocks) * B;
+    if (!fits)
+        return set_error(FLUXMOE_ENOMEM, "layer blob needs %zu bytes, dst_cap is %zu", size_t(L.n_blocks) * B, dst_cap);
     L.encoded = true;
     return FLUXMOE_OK;
 }

@@ -47,11 +47,4 @@ struct LayerMeta {
     uint64_t host_tensors = 0;           // tensors with n_host > 0
 };
 
-// Encode one flat tensor into consecutive blocks at dst (plan must come from plan_tensor).
-void plan_tensor(const uint16_t* w, uint64_t n_elems, const uint8_t lens[256],
-                 uint32_t block_bytes, std::vector<uint32_t>& first_elem);
-void encode_tensor(const uint16_t* w, const std::vector<uint32_t>& first_elem,
-                   const uint8_t lens[256], const uint16_t codes[256], uint32_t block_bytes,
-                   uint8_t* dst);
-
 }  // namespace fluxmoe
