@@ -247,3 +247,28 @@ def test_infinite_weights_past_whole_steps_stay_where_they_belong():
         assert bool(bad[:, 5].all()) and int(bad.sum()) == cfg.tokens
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("tokens", [8191, 8193])
+def test_sums_on_both_sides_of_the_memory_side_cache(tokens):
+    """268.4 MB of partial sums (8192 tokens, top-1 of 2, H 8192): just below and above, with and without accumulation."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=tokens, top_k=1, n_experts=2, n_slots=2, hidden=8192, ffn=64)
+    pool, dense = build_pool(cfg, gen_device="cuda")
+    try:
+        w13, w2 = dense[0]
+        x, (ids, g) = inputs.activations(cfg), inputs.routing(cfg)
+        out = torch.full((tokens, cfg.hidden), 5.0, dtype=torch.float32, device="cuda")
+        pool.reset_page_table()
+        pool.materialize(0, np.arange(2, dtype=np.int32), np.arange(2, dtype=np.int32))
+        args = (0, x.cuda(), torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda(), out)
+        pool.expert_ffn(*args)
+        once = out.clone()
+        pool.expert_ffn(*args, flags=B.FFN_ACCUMULATE)
+        torch.cuda.synchronize()
+        assert torch.equal(out, once + once)
+        some = np.r_[0:64, tokens - 64:tokens]
+        want = offn.moe_ffn(inputs.bits_u16(x[some].contiguous()), ids[some], g[some], lambda e: (inputs.bits_u16(w13[e]), inputs.bits_u16(w2[e])))
+        assert offn.rel_frobenius(once[torch.from_numpy(some).cuda()].cpu().numpy(), want) <= TOL
+    finally:
+        pool.close()
