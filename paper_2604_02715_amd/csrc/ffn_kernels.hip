@@ -864,8 +864,13 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(FfnArgs a) {
     const uint32_t per_row = a.F / 8;
     const uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x;
     const uint32_t row = uint32_t(i / per_row), n0 = 8u * uint32_t(i % per_row);
-    const uint32_t n_split = a.identity ? a.ksplit1 : (a.tiled && a.m_tile == 256 ? uint32_t(a.n_tiles[1]) : first_splits(a, uint32_t(a.n_tiles[0])));
-    if (n_split == 1 || row >= (a.identity ? a.T : uint32_t(a.expert_offset[a.E]))) return;       // h is there already; rows past the pairs whose expert is mapped
+    uint32_t n_split = a.ksplit1, rows = a.T;
+    if (!a.identity) {                           // the two loads travel together
+        const uint32_t found = uint32_t(a.n_tiles[a.tiled && a.m_tile == 256 ? 1 : 0]);
+        rows = uint32_t(a.expert_offset[a.E]);
+        n_split = a.tiled && a.m_tile == 256 ? found : first_splits(a, found);
+    }
+    if (n_split == 1 || row >= rows) return;       // h is there already; rows past the pairs whose expert is mapped
     float g[8], u[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) g[c] = u[c] = 0.f;
@@ -1843,11 +1848,16 @@ __global__ __launch_bounds__(256) void combine_kernel(FfnArgs a) {
     for (uint32_t k0 = 0; k0 < a.K; k0 += kGroup) {
         int32_t pos[kGroup];
         float gate[kGroup];
+        if (a.identity) {                        // K = 1 (uniform, and a branch of its own: inside the loop below it costs each of its loads a branch)
 #pragma unroll
-        for (uint32_t j = 0; j < kGroup; ++j) {
-            const bool in = k0 + j < a.K;
-            pos[j] = in ? (a.identity ? int32_t(tok) : a.pair_pos[tok * a.K + k0 + j]) : -1;
-            gate[j] = in ? (a.identity ? 1.f : a.topk_w[tok * a.K + k0 + j]) : 0.f;
+            for (uint32_t j = 0; j < kGroup; ++j) { pos[j] = j == 0 ? int32_t(tok) : -1; gate[j] = 1.f; }
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) {
+                const bool in = k0 + j < a.K;
+                pos[j] = in ? a.pair_pos[tok * a.K + k0 + j] : -1;
+                gate[j] = in ? a.topk_w[tok * a.K + k0 + j] : 0.f;
+            }
         }
         float4 y[kGroup];
 #pragma unroll
