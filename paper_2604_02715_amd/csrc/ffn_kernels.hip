@@ -1755,8 +1755,8 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     };
 
     // ACT: how many of the wavefront's row groups the tile has rows for (all, half, or none: then it takes part in the loads
-    // and barriers only).  160 experts of H 5120 F 1536 with 205 rows each: 2081 -> 2052 us a call; a pass in waves over 128
-    // of H 2048 F 512 (20 rows each): 2086 -> 2044.  8 experts of H 4096 F 14336, 1024 rows each: no change.
+    // and barriers only).  160 experts of H 5120 F 1536 with 205 rows each: 2081 -> 2052 us a call;
+    // 8 of H 4096 F 14336, 1024 rows each, and a pass in waves over 128 of H 2048 F 512: no change beyond the runs' spread.
     auto k_loop = [&](const TileState& cur, TileState& upcoming, auto ACT) __attribute__((always_inline)) {
         if (ACT.value) {
 #pragma unroll
