@@ -261,13 +261,21 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     return p;
 }
 
-// limit: bytes the scratch may take (the call's buffer; the size query leaves it open): the splits give way to it, and then
-// the small tiles do, so a buffer that holds the plan without them is always enough.  The small tiles also give way where
-// there would be too many of them.
+// limit: bytes the scratch may take (the call's buffer; the size query leaves it open): the splits give way to it, then the
+// tiles that stand in for strips do, whose halves need no partial sums, and then the small tiles, so a buffer that holds the plan
+// without them is always enough.  The small tiles also give way where there would be too many of them.
 // mapped: experts of the layer known to be resident, 0 = not known (it steers speed, not what is accepted).
 inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limit = ~0ull, uint32_t mapped = 0) {
+    auto fits = [&](const FfnPlan& p) { return p.bytes <= limit && p.tiles_cap <= kMaxRowTiles; };
     const FfnPlan p = plan_ffn_rules(c, T, K, mapped, true, limit);
-    return p.bytes <= limit && p.tiles_cap <= kMaxRowTiles ? p : plan_ffn_rules(c, T, K, mapped, false, limit);
+    if (fits(p)) return p;
+    if (c.ragged && (c.H % 64 != 0 || c.F % 64 != 0)) {
+        FfnShape strips = c;
+        strips.ragged = false;
+        const FfnPlan q = plan_ffn_rules(strips, T, K, mapped, true, limit);
+        if (fits(q)) return q;
+    }
+    return plan_ffn_rules(c, T, K, mapped, false, limit);
 }
 
 // One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.

@@ -81,3 +81,29 @@ def test_the_line_is_that_of_whole_steps(plan):
     for T in (256, 440, 480, 520, 560, 4096):
         assert of(T, 4104, 14328) == of(T, 4096, 14336)
     assert of(480, 4104, 14328) == (False, 128) and of(560, 4104, 14328) == (True, 256)
+
+
+@pytest.mark.parametrize("call", [
+    dict(T=2000, K=1, E=1, H=5000, F=1496), dict(T=560, K=2, E=8, H=4400, F=3504), dict(T=268, K=8, E=8, H=3040, F=264),
+])
+def test_tiles_give_way_to_the_strips_with_their_splits_and_halves(plan, call):
+    """In the bytes the strips' plan takes, and in a buffer of 32 MiB, a call gets no less than that plan."""
+    call = dict(call, mapped=call["E"])
+    best, strips = plan(**call), plan(**call, ragged=False)
+    assert best.tiled and best.bytes > strips.bytes and (strips.halves or strips.ksplit1 > 1)
+    assert plan(**call, limit=strips.bytes).__dict__ == strips.__dict__
+    assert plan(**call, limit=32 << 20).__dict__ == plan(**call, limit=32 << 20, ragged=False).__dict__
+
+
+def test_random_calls_fall_back_on_the_strips_plan(plan):
+    rng = random.Random(10)
+    strips_taken = 0
+    for _ in range(3000):
+        E, H, F = rng.choice([1, 2, 8, 20, 64, 160]), 8 * rng.randrange(1, 640), 8 * rng.randrange(1, 640)
+        c = dict(T=int(2 ** rng.uniform(5, 15)), K=rng.randrange(1, min(E, 12) + 1), E=E, H=H, F=F, mapped=rng.choice([0, E]))
+        strips = plan(**c, ragged=False)
+        for limit in (strips.bytes, strips.bytes - 1, strips.bytes + rng.randrange(1 << 24), 32 << 20):
+            p, q = plan(**c, limit=limit), plan(**c, limit=limit, ragged=False)
+            assert p.tiled or p.__dict__ == q.__dict__
+            strips_taken += not p.tiled and bool(plan(**c).tiled)
+    assert strips_taken > 100
