@@ -147,15 +147,16 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     }
     p.ksplit = uint32_t(ks);
     p.ksplit1 = 1;
-    // Tiles where H or F is no multiple of 64 stand in for strips, and a sum is as long as it would be there at most: the strips'
-    // K splits and halves are kept as splits (8 experts of H 4400 F 3504, 140 rows each: share of tokens with an h
-    // rounded the other way 0.225 in strips' halves, 0.271 unsplit).
-    uint32_t chains = 1;
+    // Tiles where H or F is no multiple of 64 stand in for strips, and a sum of either product is as long as it would be there at
+    // most: the strips' K splits and halves are kept as splits (8 experts of H 4400 F 3504, 140 rows each: share of tokens with
+    // an h rounded the other way 0.225 in strips' halves, 0.271 unsplit).
+    uint32_t chains = 1, chains2 = 1;
     if (p.tiled && !tileable) {
         FfnShape strips = c;
         strips.ragged = false;
         const FfnPlan q = plan_ffn_rules(strips, T, K, mapped, split, limit);
         chains = q.ksplit1 * (q.halves ? 2u : 1u);
+        chains2 = q.ksplit;
         if (chains > 1 && H < 256 * chains) return q;            // short K: the sums of the splits cost more (8 experts of H 264 F 400, 250 rows 52 / 53)
         p.ksplit1 = chains;
     }
@@ -185,7 +186,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             uint64_t k2 = std::max<uint64_t>(1, n_cus / tiles2);
             k2 = std::min<uint64_t>(k2, 8);
             k2 = std::min<uint64_t>(k2, std::max<uint64_t>(1, F / 512));
-            p.ksplit = uint32_t(k2);
+            p.ksplit = std::max(uint32_t(k2), chains2);
         }
     }
     // K split of the first product, for launches that would leave most of the chip without a workgroup: the FP32 partial
@@ -256,6 +257,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             p.split_tiles = uint32_t(std::max((n_cus - 1) / cols, planned));
         }
         while (p.tiled && p.m_tile == 128 && p.ksplit > 1 && end() > limit) --p.ksplit;
+        while (p.tiled && !tileable && p.ksplit > chains2 && end() > limit) --p.ksplit;
     }
     p.bytes = end();
     return p;

@@ -71,6 +71,7 @@ def test_random_calls_at_any_buffer_size(plan):
             q = plan(**c, ragged=False, limit=limit)     # sums no longer than the strips'
             chains = q.ksplit1 * (2 if q.halves else 1)
             assert p.ksplit1 >= chains and (chains == 1 or (p.split_tiles == 2 ** 32 - 1 and H >= 256 * chains))
+            assert p.ksplit >= q.ksplit
             tiles += 1
             kept += chains > 1
     assert tiles > 500 and kept > 50
