@@ -280,6 +280,14 @@ inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limi
     return plan_ffn_rules(c, T, K, mapped, false, limit);
 }
 
+// Scratch the size query asks for: enough for the plan a call prefers and for the one it falls back on.  The splits that tiles
+// take in the strips' place are not asked for: they only keep sums short, and strips halve theirs without any memory (8 experts of
+// H 1856 F 2632, 13170 rows: 167 MB, with them 624).  A call whose buffer has the room takes them.
+inline uint64_t ffn_bytes(FfnShape c, uint32_t T, uint32_t K) {
+    c.ragged = false;
+    return std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
+}
+
 // One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.
 struct RingProduct {
     uint32_t rows, splits;
@@ -335,6 +343,11 @@ inline FfnPlan plan_shared(const FfnShape& c, uint32_t T, uint64_t limit = ~0ull
     while (p.ksplit > 1 && bytes() > limit) --p.ksplit;
     p.bytes = bytes();
     return p.bytes <= limit ? p : base;
+}
+
+inline uint64_t shared_bytes(FfnShape c, uint32_t T) {
+    c.ragged = false;
+    return std::max(ffn_bytes(c, T, 1), plan_shared(c, T).bytes);
 }
 
 }  // namespace fluxmoe

@@ -458,14 +458,8 @@ int fluxmoe_query_sizes(const fluxmoe_ctx* c, fluxmoe_sizes* out) {
 
 uint64_t fluxmoe_ffn_workspace_bytes(const fluxmoe_ctx* c, uint32_t T, uint32_t K, int shared_expert) {
     if (!c) return 0;
-    // enough for the plan a call prefers and for the one it can fall back on
-    auto need_of = [&](uint32_t n_experts, uint32_t k) {
-        const FfnShape sh = ffn_shape(c, n_experts);
-        return std::max(plan_ffn_rules(sh, T, k, 0, true, ~0ull).bytes, plan_ffn_rules(sh, T, k, 0, false, ~0ull).bytes);
-    };
-    uint64_t need = need_of(c->d.n_experts, K);
-    if (shared_expert) need = std::max({need, need_of(1, 1), plan_shared(ffn_shape(c, 1), T).bytes});          // same shapes, a single expert
-    return need;
+    const uint64_t need = ffn_bytes(ffn_shape(c, c->d.n_experts), T, K);
+    return shared_expert ? std::max(need, shared_bytes(ffn_shape(c, 1), T)) : need;          // same shapes, a single expert
 }
 
 int fluxmoe_ffn_plan(const fluxmoe_ctx* c, uint32_t T, uint32_t K, uint32_t* rows_per_tile, uint32_t* k_splits) {
