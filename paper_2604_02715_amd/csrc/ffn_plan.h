@@ -335,14 +335,14 @@ inline FfnPlan plan_shared(const FfnShape& c, uint32_t T, uint64_t limit = ~0ull
     p.ring2 = second.rows;
     p.ksplit1 = first.splits;
     p.ksplit = second.splits;
-    auto bytes = [&]() {
+    // the two products' partial sums lie in the same place: where the buffer is short, the larger of them gives way
+    for (;;) {
         const uint64_t y = p.ksplit > 1 ? uint64_t(p.ksplit) * T * c.H * 4 : 0, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * T * 2 * c.F * 4 : 0;
-        return p.off_y + align_up(std::max(y, part), 256);
-    };
-    while (p.ksplit1 > 1 && bytes() > limit) --p.ksplit1;
-    while (p.ksplit > 1 && bytes() > limit) --p.ksplit;
-    p.bytes = bytes();
-    return p.bytes <= limit ? p : base;
+        p.bytes = p.off_y + align_up(std::max(y, part), 256);
+        if (p.bytes <= limit) return p;
+        if (y == 0 && part == 0) return base;
+        if (part >= y) --p.ksplit1; else --p.ksplit;
+    }
 }
 
 inline uint64_t shared_bytes(FfnShape c, uint32_t T) {

@@ -78,3 +78,11 @@ def test_where_the_ring_kernel_ends(rules):
     assert of(704, 4504, 2776)[0] == 64 and of(705, 4504, 2776)[0] == 0      # not whole steps: 484 workgroups of 64 rows, 528
     assert of(128, 4096, 14336)[0] == 128 and of(129, 4096, 14336)[0] == 0   # 224; 448 of 128 rows, 672 of 64
     assert of(512, waves=1)[0] == 0
+
+
+def test_only_the_larger_partial_sums_give_way(rules):
+    """17 rows of H 2360 F 1848: eight splits of the second product fill the scratch, five of the first do not."""
+    best = rules.shared(17, 2360, 1848)
+    assert best.ring1 and best.ksplit1 == 5 and best.ksplit == 8
+    p = rules.shared(17, 2360, 1848, best.bytes - 1)
+    assert p.ring1 and p.ksplit1 == 5 and p.ksplit == 7 and p.bytes < best.bytes
