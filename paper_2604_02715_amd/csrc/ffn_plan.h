@@ -82,14 +82,15 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // a streaming pass at these sizes.
     auto p_over = [&](double m) { return 0.5 * std::erfc((m + 0.5 - double(avg)) / std::sqrt(2.0 * double(avg))); };
     const bool tileable = H % 64 == 0 && F % 64 == 0;
-    const bool tiles256 = tileable || (split && c.ragged && c.tiled_waves == 2);
+    // (their byte offsets into 256 rows of h have 32 bits)
+    const bool tiles256 = F < (1u << 23) && (tileable || (split && c.ragged && c.tiled_waves == 2));
     p.m_tile = 128;
     if (p_over(128) > 0.02 && 1.0 + p_over(128) + p_over(256) + p_over(384) > 1.6 && tiles256)
         p.m_tile = 256;
     bool forced = false;
     if (const char* v = std::getenv("FLUXMOE_FFN_MTILE")) {
         const int m = std::atoi(v);
-        if (m == 16 || m == 32 || m == 64 || m == 96 || m == 128 || (m == 256 && tileable)) { p.m_tile = uint32_t(m); forced = true; }
+        if (m == 16 || m == 32 || m == 64 || m == 96 || m == 128 || (m == 256 && tileable && tiles256)) { p.m_tile = uint32_t(m); forced = true; }
     }
     p.tiled = p.m_tile == 256;
     // H or F that is not a multiple of 64: the 256 x 256 tiles take a partial step, so the same line holds.  Microseconds a call, 128-row strips /

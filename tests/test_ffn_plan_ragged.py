@@ -124,3 +124,11 @@ def test_the_size_query_asks_for_no_more_than_strips_take(plan, call):
         assert B.fluxmoe_ffn_workspace_bytes(ctx, call["T"], call["K"], True) >= max(asked, plan(**alone, ragged=False).bytes, plan(**alone, split=False).bytes)
     finally:
         B.fluxmoe_destroy(ctx)
+
+
+@pytest.mark.parametrize("hidden", [64, 72])
+def test_rows_of_h_too_long_for_a_tile_of_256_stay_with_the_strips(plan, hidden):
+    """256 rows of F BF16 values in 32-bit byte offsets: F below 2^23."""
+    assert plan(3000, 1, 1, hidden, 2 ** 23 - 64).m_tile == 256
+    p = plan(3000, 1, 1, hidden, 2 ** 23)
+    assert not p.tiled and p.m_tile == 128
