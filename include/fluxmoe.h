@@ -450,14 +450,16 @@ int fluxmoe_device_errors(fluxmoe_ctx* ctx, uint32_t* out_flags);
 
 /*
  * The launch plan fluxmoe_expert_ffn takes for T tokens with K experts each when every expert is
- * resident and scratch is ample (host only; for tests and reports): rows per tile of the grouped
- * products (16..128 = weight-streaming kernels, 256 = LDS-tiled MFMA kernels; these also take 128-row
- * tiles where few workgroups would run, which this number does not tell apart, and where hidden or ffn
- * is no multiple of 64 they take the strips' place at the same row counts while this number stays 128) and the number of K
- * splits of the second product.  The plan depends on the shapes, on T * K / n_experts and on the CU
- * count of the device (256 until a bind call has queried it); a call also goes by the number of
- * resident experts and the bytes of scratch it has, and splits K of the first product by the row tiles
- * it finds.
+ * resident and the scratch is what fluxmoe_ffn_workspace_bytes asks for (host only; for tests and
+ * reports): rows per tile of the grouped products (16..128 = weight-streaming kernels, 256 = LDS-tiled
+ * MFMA kernels; these also take 128-row tiles where few workgroups would run, which this number does
+ * not tell apart) and the number of K splits of the second product.
+ * Where hidden or ffn is no multiple of 64 both numbers are those of the weight-streaming plan.  A call
+ * takes that plan where experts get few rows, and where its scratch holds nothing else; otherwise
+ * 256-row tiles run in its place, with at least as many splits.
+ * The plan depends on the shapes, on T * K / n_experts and on the CU count of the device (256 until a
+ * bind call has queried it); a call also goes by the number of resident experts and the bytes of scratch
+ * it has, and splits K of the first product by the row tiles it finds.
  */
 int fluxmoe_ffn_plan(const fluxmoe_ctx* ctx, uint32_t T, uint32_t K, uint32_t* rows_per_tile,
                      uint32_t* k_splits);

@@ -466,7 +466,7 @@ int fluxmoe_ffn_plan(const fluxmoe_ctx* c, uint32_t T, uint32_t K, uint32_t* row
     if (!c || !rows_per_tile || !k_splits) return set_error(FLUXMOE_EINVAL, "NULL argument");
     if (K == 0 || K > c->d.n_experts) return set_error(FLUXMOE_EINVAL, "K must be in 1..n_experts");
     FfnShape shape = ffn_shape(c, c->d.n_experts);
-    shape.ragged = false;                        // reported as documented: the strips' tile, whose place larger tiles may take
+    shape.ragged = false;                        // as documented: the strips' plan, whose place tiles may take
     const FfnPlan p = plan_ffn(shape, T, K);
     *rows_per_tile = p.m_tile;
     *k_splits = p.ksplit;

@@ -132,3 +132,28 @@ def test_rows_of_h_too_long_for_a_tile_of_256_stay_with_the_strips(plan, hidden)
     assert plan(3000, 1, 1, hidden, 2 ** 23 - 64).m_tile == 256
     p = plan(3000, 1, 1, hidden, 2 ** 23)
     assert not p.tiled and p.m_tile == 128
+
+
+def test_what_the_plan_report_says(plan):
+    """fluxmoe_ffn_plan: the plan of a call with every expert resident and scratch of the size that the query asks for; where H
+    or F is no multiple of 64 the strips' plan, which such a call takes or replaces by tiles with no fewer splits."""
+    from paper_2604_02715_amd import binding as B
+    rng = random.Random(12)
+    tiles = strips = 0
+    calls = [dict(T=1439, K=8, E=8, H=360, F=360), dict(T=4096, K=2, E=8, H=4096, F=14336), dict(T=1024, K=2, E=8, H=4104, F=14344)]
+    for _ in range(300):
+        step = rng.choice([8, 64])
+        calls.append(dict(T=int(2 ** rng.uniform(4, 13)), K=rng.randrange(1, 9), E=rng.choice([8, 20, 64]), H=step * rng.randrange(1, 2400 // step), F=step * rng.randrange(1, 2400 // step)))
+    for c in calls:
+        ctx = B.fluxmoe_create(1, c["E"], c["H"], c["F"], c["E"])
+        try:
+            said, limit = B.fluxmoe_ffn_plan(ctx, c["T"], c["K"]), B.fluxmoe_ffn_workspace_bytes(ctx, c["T"], c["K"])
+        finally:
+            B.fluxmoe_destroy(ctx)
+        p, q = plan(**c, mapped=c["E"], limit=limit), plan(**c, mapped=c["E"], limit=limit, ragged=False)
+        assert said == (q.m_tile, q.ksplit)
+        if p.__dict__ != q.__dict__:
+            assert (c["H"] % 64 or c["F"] % 64) and p.m_tile == 256 and p.ksplit >= q.ksplit
+            tiles += 1
+        strips += not p.tiled
+    assert tiles > 30 and strips > 30

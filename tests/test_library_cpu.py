@@ -164,7 +164,7 @@ def test_ffn_launch_plan_follows_rows_per_expert():
     assert plan(560, 2)[0] == 256                     # 140 rows per expert: the tiled kernels are cheaper
     assert plan(1024, 2) == (256, 2)                  # 8 x 16 tiles of the second product -> two K splits
     assert plan(8192, 2) == (256, 1)
-    # shapes the tiled kernels cannot take (k extents not multiples of 64) stay on 128-row tiles
+    # k extents that are no multiples of 64: the strips' plan, which tiles may take the place of
     assert plan(1024, 2, hidden=4104, ffn=14344)[0] == 128
     # many small experts: one round is already full, no split
     assert plan(256, 10, n_experts=512, hidden=2048, ffn=512, n_slots=256) == (128, 1)
