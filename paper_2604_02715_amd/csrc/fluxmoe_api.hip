@@ -13,14 +13,10 @@
 #include <atomic>
 #include <cstdlib>
 #include <cmath>
-#include <condition_variable>
 #include <cstring>
-#include <mutex>
 #include <new>
-#include <system_error>
-#include <thread>
-#include <type_traits>
 
+#include "crew.h"
 #include "encode_core.h"
 #include "fluxmoe_internal.h"
 
@@ -153,74 +149,6 @@ void compute_layout(fluxmoe_ctx* c) {
     c->err_off = c->cmd_off + uint64_t(kRing) * c->cmd_bytes;
     c->pool_ws_bytes = align_up(c->err_off + 256, 4096);
 }
-
-// A set of threads that go through several passes together: take() hands out the numbers 0, 1, .. of the current pass, wait()
-// ends it for everybody, and the last to arrive runs `once` before the next one begins.  The caller is one of them; where the system
-// gives fewer threads than asked for, those that there are do the work.
-class Crew {
-public:
-    explicit Crew(int wanted) {
-        threads_.reserve(size_t(wanted - 1));
-        for (int t = 1; t < wanted; ++t) {
-            try {
-                threads_.emplace_back([this, t]() {
-                    {
-                        std::unique_lock<std::mutex> lock(m_);
-                        cv_.wait(lock, [this]() { return work_ != nullptr || closed_; });
-                        if (!work_) return;
-                    }
-                    work_(user_, uint32_t(t));
-                });
-            } catch (const std::system_error&) {
-                break;
-            }
-        }
-    }
-    ~Crew() {
-        { std::lock_guard<std::mutex> lock(m_); closed_ = true; }
-        cv_.notify_all();
-        for (auto& t : threads_) t.join();
-    }
-    uint32_t size() const { return uint32_t(threads_.size()) + 1; }
-    template <typename F>
-    void run(F&& f) {
-        {
-            std::lock_guard<std::mutex> lock(m_);
-            user_ = &f;
-            work_ = [](void* u, uint32_t me) { (*static_cast<std::remove_reference_t<F>*>(u))(me); };
-        }
-        cv_.notify_all();
-        f(0u);
-        for (auto& t : threads_) t.join();
-        threads_.clear();
-    }
-    uint64_t take() { return next_.fetch_add(1, std::memory_order_relaxed); }
-    template <typename F>
-    void wait(F&& once) {
-        std::unique_lock<std::mutex> lock(m_);
-        const uint64_t pass = pass_;
-        if (++arrived_ == size()) {
-            once();
-            arrived_ = 0;
-            next_.store(0, std::memory_order_relaxed);
-            ++pass_;
-            cv_.notify_all();
-        } else {
-            cv_.wait(lock, [&]() { return pass_ != pass; });
-        }
-    }
-
-private:
-    std::vector<std::thread> threads_;
-    std::mutex m_;
-    std::condition_variable cv_;
-    void (*work_)(void*, uint32_t) = nullptr;
-    void* user_ = nullptr;
-    bool closed_ = false;
-    std::atomic<uint64_t> next_{0};
-    uint64_t pass_ = 0;
-    uint32_t arrived_ = 0;
-};
 
 FfnShape ffn_shape(const fluxmoe_ctx* c, uint32_t n_experts) {
     return FfnShape{n_experts, c->d.hidden, c->d.ffn, c->n_cus, c->tune_tiled_waves, true};
@@ -490,6 +418,7 @@ int fluxmoe_encode_pool(fluxmoe_ctx* c, uint32_t layer, const uint16_t* w13, con
     // One set of threads goes through the three passes over the weights; between them the last to arrive does what has to be
     // done once.  Units are pieces of tensors, so that the threads end together whatever the number of tensors is.
     constexpr uint64_t kCountElems = 1u << 17, kBlocksPerUnit = 16;
+    try {
     Crew crew(n_threads);
     std::vector<std::array<uint64_t, 512>> hist(crew.size(), std::array<uint64_t, 512>{});
     Coder coder[2];
@@ -547,6 +476,9 @@ int fluxmoe_encode_pool(fluxmoe_ctx* c, uint32_t layer, const uint16_t* w13, con
         return set_error(FLUXMOE_ENOMEM, "layer blob needs %zu bytes, dst_cap is %zu", size_t(L.n_blocks) * B, dst_cap);
     L.encoded = true;
     return FLUXMOE_OK;
+    } catch (const std::bad_alloc&) {
+        return set_error(FLUXMOE_ENOMEM, "out of host memory");
+    }
 }
 
 int fluxmoe_layer_info_get(const fluxmoe_ctx* c, uint32_t layer, fluxmoe_layer_info* out) {
