@@ -158,7 +158,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         const FfnPlan q = plan_ffn_rules(strips, T, K, mapped, split, limit);
         chains = q.ksplit1 * (q.halves ? 2u : 1u);
         chains2 = q.ksplit;
-        if (chains > 1 && H < 256 * chains) return q;            // short K: the sums of the splits cost more (8 experts of H 264 F 400, 250 rows 52 / 53)
+        // Short K: the partial sums cost more than the tiles gain, the more so where the memory-side cache (256 MB) does not hold
+        // them.  Microseconds, strips / two splits: within it 8 experts of H 528 F 2632, 182 rows each 81 / 90, H 816 F 1016, 309 rows
+        // 78 / 68, H 928 F 392, 881 rows 83 / 72; past it H 608 F 896, 9395 rows 748 / 808, 160 of H 728 F 272, 498 rows 480 / 499,
+        // of H 1224 F 896, 134 rows 533 / 493, of H 2496 F 1400, 391 rows 3091 / 2583.
+        if (chains > 1 && H < (chains * pairs_act * 2 * F * 4 > (256u << 20) ? 512u : 384u) * chains) return q;
         p.ksplit1 = chains;
     }
     // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when

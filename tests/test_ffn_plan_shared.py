@@ -13,9 +13,9 @@ SHIM = """
 #include "ffn_plan.h"
 using namespace fluxmoe;
 static void put(const FfnPlan& p, uint64_t* o) { %s }
-extern "C" void shared(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_shared(FfnShape{1, H, F, n_cus, waves}, T, limit), o); }
-extern "C" void base(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_ffn(FfnShape{1, H, F, n_cus, waves}, T, 1, limit), o); }
-extern "C" void least(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t, uint64_t* o) { put(plan_ffn_rules(FfnShape{1, H, F, n_cus, waves}, T, 1, 0, false, ~0ull), o); }
+extern "C" void shared(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_shared(FfnShape{1, H, F, n_cus, waves, true}, T, limit), o); }
+extern "C" void base(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_ffn(FfnShape{1, H, F, n_cus, waves, true}, T, 1, limit), o); }
+extern "C" void least(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t, uint64_t* o) { put(plan_ffn_rules(FfnShape{1, H, F, n_cus, waves, true}, T, 1, 0, false, ~0ull), o); }
 """ % " ".join("o[%d] = p.%s;" % (i, f) for i, f in enumerate(FIELDS))
 
 
