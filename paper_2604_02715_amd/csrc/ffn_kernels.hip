@@ -1831,9 +1831,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
 }
 
 // out[t][:] (+)= sum_k gate * sum_split y
-// STREAM: y is read and the output written with the non-temporal hint.  For partial sums larger than the memory-side cache (256 MB): each
-// is read once, and what it would push out is the sums still to be read.  Microseconds, default policy / non-temporal: 234 MB 42 / 42,
-// 312 MB 78 / 58, 390 MB 109 / 82, 640 MB 164 / 136 (H 5120, top-8), 937 MB 248 / 214 (H 2048, top-10).
+// STREAM: y is read and the output written with the non-temporal hint (combine_streams).
 template <uint32_t kGroup, bool STREAM>
 __global__ __launch_bounds__(256) void combine_kernel(FfnArgs a) {
     const uint32_t tok = blockIdx.y;
@@ -1961,7 +1959,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
     }
     auto launch_combine = [&](dim3 grid) {
-        const bool streams = uint64_t(a.ksplit) * a.T * a.K * a.H * sizeof(float) > (256ull << 20);
+        const bool streams = combine_streams(uint64_t(a.ksplit) * a.T * a.K * a.H * sizeof(float), a.mapped, a.E);
         auto launch = [&](auto plain, auto stream_y) { launch_done(streams ? stream_y : plain, grid, dim3(256), 0, stream, done, a); };
         if (a.K <= 2) launch(combine_kernel<2, false>, combine_kernel<2, true>);
         else if (a.K <= 4) launch(combine_kernel<4, false>, combine_kernel<4, true>);

@@ -293,6 +293,16 @@ inline uint64_t ffn_bytes(FfnShape c, uint32_t T, uint32_t K) {
     return std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
 }
 
+// Whether combine_kernel reads the second product's partial sums (`bytes` for all T * K pairs) and writes the output with the
+// non-temporal hint: for sums larger than the memory-side cache (256 MB), each of which is read once, while what it would push out is
+// the sums still to be read.  Microseconds of the kernel, default policy / non-temporal: 234 MB 42 / 42, 312 MB 78 / 58, 390 MB 109 / 82,
+// 640 MB 164 / 136 (H 5120, top-8), 937 MB 248 / 214 (H 2048, top-10).  A call with part of the layer resident has the sums of
+// those experts only: 4096 tokens, 80, 40 of 160 experts of H 5120, top-8 (336, 168 MB) 80 / 78, 51 / 65; 256 of 512 of H 2048, top-10
+// (168 MB) 39 / 45.
+inline bool combine_streams(uint64_t bytes, uint64_t mapped, uint64_t E) {
+    return (mapped && mapped < E ? bytes / E * mapped : bytes) > (256ull << 20);
+}
+
 // One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.
 struct RingProduct {
     uint32_t rows, splits;

@@ -1070,6 +1070,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.ybuf = reinterpret_cast<float*>(w + p.off_y);
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
     a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.halves = p.halves; a.g1_xcd = p.g1_xcd; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1; a.split_tiles = p.split_tiles;
+    a.mapped = mapped;
     a.n_cus = uint32_t(std::max(c->n_cus, 1));
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);

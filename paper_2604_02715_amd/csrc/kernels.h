@@ -56,6 +56,7 @@ struct FfnArgs {
     uint32_t direct;             // set by launch_ffn: the second product writes the output itself (identity, unsplit)
     uint32_t tiled_group;        // super-rows of the LDS-direct gate/up kernel that share a column block in time;
                                  // 0 = launch_ffn derives it from the rows per expert
+    uint32_t mapped;             // for the launcher: experts of the layer known to be resident, 0 = not known
 };
 
 // hook(user, kind, begin, stream) is called around every kernel when timing is on

@@ -272,3 +272,32 @@ def test_sums_on_both_sides_of_the_memory_side_cache(tokens):
         assert offn.rel_frobenius(once[torch.from_numpy(some).cuda()].cpu().numpy(), want) <= TOL
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("resident", [1, 3])
+def test_sums_of_a_wave_on_both_sides_of_the_memory_side_cache(resident):
+    """12000 tokens, top-1 of 4, H 8192: 393 MB if every pair is there, 98 MB of one expert's, 295 MB of three's; overwritten and
+    accumulated."""
+    from gpu_common import build_pool
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=12000, top_k=1, n_experts=4, n_slots=4, hidden=8192, ffn=64)
+    pool, dense = build_pool(cfg, gen_device="cuda")
+    try:
+        w13, w2 = dense[0]
+        x, (_, g) = inputs.activations(cfg), inputs.routing(cfg)
+        ids = (np.arange(cfg.tokens, dtype=np.int32) % 4)[:, None]
+        here = ids < resident
+        out = torch.full((cfg.tokens, cfg.hidden), 5.0, dtype=torch.float32, device="cuda")
+        pool.reset_page_table()
+        pool.materialize(0, np.arange(resident, dtype=np.int32), np.arange(resident, dtype=np.int32))
+        args = (0, x.cuda(), torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda(), out)
+        pool.expert_ffn(*args, flags=B.FFN_SKIP_UNMAPPED)
+        once = out.clone()
+        pool.expert_ffn(*args, flags=B.FFN_SKIP_UNMAPPED | B.FFN_ACCUMULATE)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 0 and torch.equal(out, once + once)
+        some = np.r_[0:64, cfg.tokens - 64:cfg.tokens]
+        want = offn.moe_ffn(inputs.bits_u16(x[some].contiguous()), ids[some], np.where(here, g, 0).astype(np.float32)[some],
+                            lambda e: (inputs.bits_u16(w13[e]), inputs.bits_u16(w2[e])))
+        assert offn.rel_frobenius(once[torch.from_numpy(some).cuda()].cpu().numpy(), want) <= TOL
+    finally:
+        pool.close()
