@@ -1991,13 +1991,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         mark(4, 0);
         return hipGetLastError();
     }
-    // Weights that one row tile reads (experts with about a tile's rows at most) pass the caches by; with several they are
-    // shared through L2.  With many experts skew gives some of them several tiles, and waves find what their load just wrote.
-    // Microseconds a call, default policy / non-temporal: 8 experts of H 4096 F 14336, 250 rows each 950 / 890, 1024 rows 2768 / 2807; 20 of
-    // H 5120 F 1536, 240 rows 377 / 361, 1200 rows 1207 / 1279; 32 of H 1024 F 256, 75 rows 39.7 / 37.6; 160 of H 5120 F 1536, even routing,
-    // 205 rows 2080 / 2062, popularity by rank, 175 rows 2270 / 2291; 512 of H 2048 F 512, 234 rows 1415 / 1438; a pass in waves
-    // over 128 of those 2012 / 2040.
-    const bool stream_b = !a.identity && !(a.flags & 2u) && a.E <= 64 && uint64_t(a.T) * a.K <= uint64_t(a.m_tile) * std::min<uint64_t>(a.E, uint64_t(a.T) * a.K);
+    const bool stream_b = !a.identity && !(a.flags & 2u) && weights_stream(a.E, a.H, a.F, uint64_t(a.T) * a.K, a.m_tile);
     if (a.tiled) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
         const bool four = a.tiled_waves == 4;

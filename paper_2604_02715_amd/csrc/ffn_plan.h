@@ -303,6 +303,19 @@ inline bool combine_streams(uint64_t bytes, uint64_t mapped, uint64_t E) {
     return (mapped && mapped < E ? bytes / E * mapped : bytes) > (256ull << 20);
 }
 
+// Whether the LDS-direct kernels fetch a layer's weights with the non-temporal hint.  Weights that one row tile reads (experts
+// with about a tile's rows at most) pass the caches by; with several they are shared through L2.  Microseconds a call, default
+// policy / non-temporal: 8 experts of H 4096 F 14336, 250 rows each 950 / 890, 1024 rows 2768 / 2807; 20 of H 5120 F 1536, 240 rows 377 / 361,
+// 1200 rows 1207 / 1279; behind the load of the whole layer, load included, 1880 / 1774 and 693 / 676.
+// A layer that the memory-side cache (256 MB) may hold from the call before is read from there: 32 of H 1024 F 256 (50 MB), 75 rows
+// 32.7 / 36.6 (out of HBM 39.7 / 37.6); of H 2048 F 512 (201 MB), 200 rows, two layers in turn 118 / 110.
+// With many experts skew gives some of them several tiles: 160 of H 5120 F 1536, even routing, 205 rows 2080 / 2062, popularity by
+// rank, 175 rows 2270 / 2291; 512 of H 2048 F 512, 234 rows 1415 / 1438.  Waves find what their load just wrote: a pass over 128 of
+// those 2012 / 2040.
+inline bool weights_stream(uint64_t E, uint64_t H, uint64_t F, uint64_t pairs, uint64_t m_tile) {
+    return E <= 64 && E * H * F * 6 > (128ull << 20) && pairs <= m_tile * std::min(E, pairs);
+}
+
 // One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.
 struct RingProduct {
     uint32_t rows, splits;
