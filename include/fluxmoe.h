@@ -97,8 +97,8 @@ int fluxmoe_query_sizes(const fluxmoe_ctx* ctx, fluxmoe_sizes* out);
 
 /* Device workspace bytes fluxmoe_expert_ffn needs for T tokens with K experts each
  * (shared_expert != 0 adds the always-on shared expert's rows).  More room can make a call faster where
- * hidden or ffn is no multiple of 64 and experts get hundreds of rows: matrix tiles then take the place of
- * weight strips, with 16 * T * K * ffn bytes of partial sums or a small multiple of that. */
+ * hidden or ffn is no multiple of 64 and experts get many hundreds of rows: matrix tiles then take the place
+ * of weight strips, with 16 * T * K * ffn bytes of partial sums or a small multiple of that. */
 uint64_t fluxmoe_ffn_workspace_bytes(const fluxmoe_ctx* ctx, uint32_t T, uint32_t K,
                                      int shared_expert);
 

@@ -286,11 +286,14 @@ inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limi
 }
 
 // Scratch the size query asks for: enough for the plan a call prefers and for the one it falls back on.  The splits that tiles
-// take in the strips' place are not asked for: they only keep sums short, and strips halve theirs without any memory (8 experts of
-// H 1856 F 2632, 13170 rows: 167 MB, with them 624).  A call whose buffer has the room takes them.
+// take in the strips' place only keep sums short, and strips halve theirs without any memory: no more than 64 MB are asked for
+// them (8 experts of H 4400 F 3504, 140 rows each, within it 353 / 262 us; of H 1856 F 2632, 1646 rows each, past it: 167 MB, 624 with the
+// splits).  A call whose buffer has the room takes them all the same.
 inline uint64_t ffn_bytes(FfnShape c, uint32_t T, uint32_t K) {
+    const uint64_t tiles = plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes;
     c.ragged = false;
-    return std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
+    const uint64_t strips = std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
+    return tiles <= strips + (64ull << 20) ? std::max(tiles, strips) : strips;
 }
 
 // Whether combine_kernel reads the second product's partial sums (`bytes` for all T * K pairs) and writes the output with the
@@ -374,8 +377,9 @@ inline FfnPlan plan_shared(const FfnShape& c, uint32_t T, uint64_t limit = ~0ull
 }
 
 inline uint64_t shared_bytes(FfnShape c, uint32_t T) {
+    const uint64_t base = ffn_bytes(c, T, 1);
     c.ragged = false;
-    return std::max(ffn_bytes(c, T, 1), plan_shared(c, T).bytes);
+    return std::max(base, plan_shared(c, T).bytes);
 }
 
 }  // namespace fluxmoe

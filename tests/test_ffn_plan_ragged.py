@@ -110,15 +110,17 @@ def test_random_calls_fall_back_on_the_strips_plan(plan):
     assert strips_taken > 100
 
 
-@pytest.mark.parametrize("call", [dict(T=4390, K=3, E=8, H=1856, F=2632), dict(T=1024, K=2, E=8, H=4104, F=14344), dict(T=333, K=4, E=64, H=2880, F=360)])
-def test_the_size_query_asks_for_no_more_than_strips_take(plan, call):
+@pytest.mark.parametrize("call", [dict(T=4390, K=3, E=8, H=1856, F=2632), dict(T=1024, K=2, E=8, H=4104, F=14344), dict(T=333, K=4, E=64, H=2880, F=360),
+                                  dict(T=560, K=2, E=8, H=4400, F=3504)])
+def test_the_size_query_asks_for_little_more_than_strips_take(plan, call):
     """... and a call in a buffer of that size is accepted; the shared expert's query covers its own plan."""
     from paper_2604_02715_amd import binding as B
-    strips, least = plan(**call, ragged=False), plan(**call, split=False)
+    best, strips, least = plan(**call), plan(**call, ragged=False), plan(**call, split=False)
     ctx = B.fluxmoe_create(1, call["E"], call["H"], call["F"], call["E"])
     try:
         asked = B.fluxmoe_ffn_workspace_bytes(ctx, call["T"], call["K"])
-        assert asked == max(strips.bytes, least.bytes)
+        needed = max(strips.bytes, least.bytes)
+        assert asked == (max(best.bytes, needed) if best.bytes <= needed + (64 << 20) else needed)
         assert plan(**call, mapped=call["E"], limit=asked).bytes <= asked
         alone = dict(T=call["T"], K=1, E=1, H=call["H"], F=call["F"])
         assert B.fluxmoe_ffn_workspace_bytes(ctx, call["T"], call["K"], True) >= max(asked, plan(**alone, ragged=False).bytes, plan(**alone, split=False).bytes)
