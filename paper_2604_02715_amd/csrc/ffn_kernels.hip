@@ -328,9 +328,8 @@ constexpr int kABlock = 128;                 // k per block = 4 chunks
 // v_accvgpr moves than MFMAs in the ring loop).  The matrix-core hazards the compiler would cover
 // are covered here: s_nop 1 gives the two wait states between a VALU write of an operand (the
 // v_perm transposes, the v_accvgpr_write zeroing) and the MFMA that reads it; mfma_drain() must
-// run before anything but another mfma16 reads an accumulator (the compiler, which must not spill or copy one between two of
-// them, does not know: after a change to the 128-row bodies, whose 256 accumulators fill the file, look through the assembly
-// for stores of AGPRs behind a v_mfma).  volatile keeps the statements in
+// run before anything but another mfma16 reads an accumulator (the compiler, which must not spill or copy one within eight wait
+// states of it, does not know: tests/test_mfma_hazards.py looks through the machine code).  volatile keeps the statements in
 // program order (loads and LDS reads stay where the source puts them relative to the MFMAs).
 __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& a, const bf16x8& b) {
     asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
