@@ -1938,11 +1938,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
-    const bool grouping = !routes_itself && !a.identity;
+    const bool grouping = a.identity ? !a.ring1 : !routes_itself;
     if (grouping) mark(1, 1);
-    const bool lists = a.identity && !a.ring1;
-    if (lists) hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
     if (!grouping) {
+    } else if (a.identity) {
+        hipLaunchKernelGGL(route_identity_kernel, dim3((std::max(a.T, a.tiles_cap) + 255) / 256), dim3(256), 0, stream, a);
     } else if (a.n_chunks) {
         hipLaunchKernelGGL(route_count_kernel, dim3(a.n_chunks), dim3(1024), size_t(a.E) * sizeof(int32_t), stream, a);
         if (chooses) hipLaunchKernelGGL((route_sort_kernel<true, true>), dim3(1), dim3(1024), sh, stream, a);

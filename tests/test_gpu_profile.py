@@ -72,3 +72,25 @@ def test_a_kind_without_a_kernel_counts_no_launch():
         assert pool.device_errors() == 0
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("tokens,hidden,ffn,launches", [
+    (64, 256, 128, (0, 1, 1, 0)),              # a few workgroups: no lists, the second product writes the output
+    (4100, 512, 512, (1, 1, 1, 0)),            # 128 x 128 tiles: lists
+])
+def test_kinds_of_the_shared_expert(tokens, hidden, ffn, launches):
+    from paper_2604_02715_amd import harness
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=2, n_slots=2, shared_expert=True, tokens=tokens, hidden=hidden, ffn=ffn)
+    pool = harness.ExpertPool(cfg)
+    try:
+        s13, s2 = inputs.shared_expert_weights(cfg, 0)
+        s13, s2, x = s13.cuda(), s2.cuda(), inputs.activations(cfg).cuda()
+        out = torch.zeros((tokens, hidden), dtype=torch.float32, device="cuda")
+        B.fluxmoe_profile_enable(pool.ctx, True)
+        B.fluxmoe_profile_collect(pool.ctx)
+        pool.shared_expert_ffn(s13, s2, x, out)
+        prof = B.fluxmoe_profile_collect(pool.ctx)
+        kinds = ("grouping", "gemm1_swiglu", "gemm2", "combine")
+        assert tuple(prof[k][1] for k in kinds) == launches and all((prof[k][0] > 0) == (prof[k][1] > 0) for k in kinds)
+    finally:
+        pool.close()
