@@ -558,9 +558,9 @@ struct TileInfo {
     int32_t expert, row0, rows, slot;
 };
 
-// A strip kernel's tile, one 16-byte load: route_sort_kernel wrote (expert, first row, rows, slot) for every tile number below
+// One 16-byte load: route_sort_kernel or route_identity_kernel wrote (expert, first row, rows, slot) for every tile number below
 // tiles_cap, with rows = 0 past the last tile.
-__device__ __forceinline__ bool strip_tile(const FfnArgs& a, uint32_t tile, TileInfo& t) {
+__device__ __forceinline__ bool tile_info(const FfnArgs& a, uint32_t tile, TileInfo& t) {
     const int4 r = a.tile_rec[tile];
     t.expert = r.x; t.row0 = r.y; t.rows = r.z; t.slot = r.w;
     return t.rows > 0 && t.slot >= 0;
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
         if (lists && threadIdx.x == 0) a.tile_rec[tile] = make_int4(t.expert, t.row0, t.rows, t.slot);
         if (threadIdx.x < 64 && valid && leader == first) pair_list[__popcll(mine & ((1ull << lane) - 1ull))] = lane;
         __syncthreads();
-    } else if (!strip_tile(a, tile_no, t)) {
+    } else if (!tile_info(a, tile_no, t)) {
         return;                                       // uniform over the workgroup
     }
     const uint32_t n_split = !SPLIT ? 1u : (ROUTE ? a.ksplit1 : first_splits(a, n_tiles_all));
@@ -850,7 +850,7 @@ __global__ __launch_bounds__(256) void gemm2_kernel(FfnArgs a) {
     if (pair >= a.tiles_cap * a.ksplit) return;
     const uint32_t tile = pair / a.ksplit, split = pair % a.ksplit;
     TileInfo t;
-    if (!strip_tile(a, tile, t)) return;
+    if (!tile_info(a, tile, t)) return;
     if (MI > 1 && t.rows <= 16) gemm2_body<1>(a, t, abuf, col_wg, split);
     else if (MI > 2 && t.rows <= 32) gemm2_body<2>(a, t, abuf, col_wg, split);
     else if (MI > 4 && t.rows <= 64) gemm2_body<4>(a, t, abuf, col_wg, split);
@@ -927,7 +927,7 @@ __global__ __launch_bounds__(512) void gemm_tiled_kernel(FfnArgs a) {
     const uint32_t col_tile = (st % n_sn) * kSuperN + within % kSuperN;
     if (row_tile >= n_rt || col_tile >= n_ct) return;
     TileInfo t;
-    if (!strip_tile(a, row_tile, t)) return;
+    if (!tile_info(a, row_tile, t)) return;
     const uint32_t n_base = col_tile * ncols_tile;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1139,7 +1139,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const uint32_t col_tile = (st % n_sn) * kSuperN + within % kSuperN;
     if (row_tile >= n_rt || col_tile >= n_ct) return;
     TileInfo t;
-    if (!strip_tile(a, row_tile, t)) return;
+    if (!tile_info(a, row_tile, t)) return;
     const uint32_t n_base = col_tile * ncols_tile;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1929,6 +1929,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
                       SpanHook hook, void* user) {
     (void)n_cus;
     if (args.T == 0) return hipSuccess;
+    if (args.identity && (done || routed)) return hipErrorInvalidValue;      // the shared expert's calls have no event to complete
     FfnArgs a = args;
     auto mark = [&](int kind, int begin) { if (hook) hook(user, kind, begin, stream); };
     const size_t sh = (3 * size_t(a.E) + 1024) * sizeof(int32_t);
@@ -1978,11 +1979,11 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     a.direct = a.identity && a.ksplit == 1 && (a.ring2 || (a.tiled && a.tiled_waves == 2));
     if (a.ring1) {
         mark(2, 1);
-        if (hipError_t e = launch_ring(a, 1, stream, nullptr); e != hipSuccess) return e;
+        if (hipError_t e = launch_ring(a, 1, stream); e != hipSuccess) return e;
         launch_reduce();
         mark(2, 0);
         mark(3, 1);
-        if (hipError_t e = launch_ring(a, 2, stream, a.direct ? done : nullptr); e != hipSuccess) return e;
+        if (hipError_t e = launch_ring(a, 2, stream); e != hipSuccess) return e;
         mark(3, 0);
         if (a.direct) return hipSuccess;
         mark(4, 1);
@@ -2124,10 +2125,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
         mark(3, 0);
-        if (a.direct) {
-            if (done) return hipEventRecord(done, stream);
-            return hipGetLastError();
-        }
+        if (a.direct) return hipGetLastError();
         const dim3 gc2((a.H / 4 + 255) / 256, a.T, 1);
         mark(4, 1);
         launch_combine(gc2);

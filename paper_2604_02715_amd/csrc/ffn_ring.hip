@@ -243,8 +243,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(FfnArgs a) {
         if (s + NS - 1 < n_steps) { step(s, stage, Int<2>{}, Int<NS - 2>{}); advance(); }
         while (s + 1 < n_steps) {                            // nothing left to fetch
             const uint32_t later = n_steps - 2 - s;          // steps after the next one, all of them fetched
-            if (later >= 3 && NS > 5) step(s, stage, Int<0>{}, Int<3>{});
-            else if (later >= 2 && NS > 4) step(s, stage, Int<0>{}, Int<2>{});
+            if (later >= 2 && NS > 4) step(s, stage, Int<0>{}, Int<2>{});
             else if (later >= 1) step(s, stage, Int<0>{}, Int<1>{});
             else step(s, stage, Int<0>{}, Int<0>{});
             advance();
@@ -348,7 +347,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(FfnArgs a) {
 }
 
 template <int TM, int NS>
-hipError_t launch(const FfnArgs& a, int mode, hipStream_t stream, hipEvent_t done) {
+hipError_t launch(const FfnArgs& a, int mode, hipStream_t stream) {
     constexpr uint32_t bytes = NS * (TM * 128 + 16384);
     auto* const kernel = mode == 1 ? gemm_ring_kernel<1, TM, NS> : (mode == 2 ? gemm_ring_kernel<2, TM, NS> : gemm_ring_kernel<3, TM, NS>);
     static bool attr_set[3] = {};
@@ -357,7 +356,7 @@ hipError_t launch(const FfnArgs& a, int mode, hipStream_t stream, hipEvent_t don
         attr_set[mode - 1] = true;
     }
     const uint32_t n_ct = mode == 2 ? (a.H + 127) / 128 : (a.F + 63) / 64, splits = mode == 2 ? a.ksplit : (mode == 3 ? a.ksplit1 : 1u);
-    launch_done(kernel, dim3((n_ct * splits + 7) / 8 * 8 * ((a.T + TM - 1) / TM)), dim3(256), bytes, stream, done, a);
+    hipLaunchKernelGGL(kernel, dim3((n_ct * splits + 7) / 8 * 8 * ((a.T + TM - 1) / TM)), dim3(256), bytes, stream, a);
     return hipGetLastError();
 }
 
@@ -366,13 +365,13 @@ hipError_t launch(const FfnArgs& a, int mode, hipStream_t stream, hipEvent_t don
 // Stages: what two workgroups (32 and 64 rows) or one (128) can have of a CU's 160 KiB.  Six and eight stages with one
 // workgroup a CU were no faster where one fits (H 5120 F 1536, 64 rows of 64: 47 / 47 us) and lost where two do (512 rows: 46 / 47,
 // second product 25 / 32).
-hipError_t launch_ring(const FfnArgs& a, int product, hipStream_t stream, hipEvent_t done) {
+hipError_t launch_ring(const FfnArgs& a, int product, hipStream_t stream) {
     const uint32_t splits = product == 2 ? a.ksplit : a.ksplit1, k = product == 2 ? a.F : a.H, rows = product == 2 ? a.ring2 : a.ring1;
     if (!a.identity || splits == 0 || splits > (k + kTK - 1) / kTK) return hipErrorInvalidValue;
     const int mode = product == 2 ? 2 : (a.ksplit1 > 1 ? 3 : 1);
-    if (rows == 128) return launch<128, 5>(a, mode, stream, done);
-    if (rows == 64) return launch<64, 3>(a, mode, stream, done);
-    if (rows == 32) return launch<32, 4>(a, mode, stream, done);
+    if (rows == 128) return launch<128, 5>(a, mode, stream);
+    if (rows == 64) return launch<64, 3>(a, mode, stream);
+    if (rows == 32) return launch<32, 4>(a, mode, stream);
     return hipErrorInvalidValue;
 }
 

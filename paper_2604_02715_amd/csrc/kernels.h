@@ -63,11 +63,11 @@ struct FfnArgs {
 // (kinds: 1 grouping, 2 gate/up product + SwiGLU, 3 down product, 4 combine)
 typedef void (*SpanHook)(void* user, int kind, int begin, hipStream_t stream);
 // done: completes with the call's last kernel; routed: with the kernel that reads the page table last (nullptr: none).
-// done is attached to its launch; routed too if attach_routed, else it is recorded behind it (stream capture).
+// done is attached to its launch (none of either for the shared expert); routed too if attach_routed, else it is recorded behind it (stream capture).
 hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, bool attach_routed,
                       SpanHook hook, void* user);
 // gemm_ring_kernel (ffn_ring.hip) for the first or second product
-hipError_t launch_ring(const FfnArgs& args, int product, hipStream_t stream, hipEvent_t done);
+hipError_t launch_ring(const FfnArgs& args, int product, hipStream_t stream);
 hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgroups, uint32_t iters,
                              hipStream_t stream);
 // The decode kernel's launch shape and memory accesses without its work (probe_kernels.hip): n_blocks blocks of
