@@ -10,6 +10,7 @@ from oracle import paging
 from paper_2604_02715_amd import binding as B
 from paper_2604_02715_amd import inputs
 from test_ffn_plan import rules  # noqa: F401 (fixture)
+from test_ffn_plan_ragged import plan  # noqa: F401 (fixture)
 from test_gpu_ffn import TOL, run_ffn_case
 
 pytestmark = pytest.mark.gpu
@@ -36,7 +37,7 @@ def test_split_first_product_in_waves():
 @pytest.mark.parametrize("tokens", [1, 100, 129, 257, 600])
 @pytest.mark.parametrize("shape", [(1024, 192), (1096, 200)])
 def test_shared_expert(tokens, shape):
-    """Row tiles of one, several and partly filled; the smaller shape takes the LDS-tiled kernels from 129 rows on."""
+    """Row tiles of one, several and partly filled, whole steps and tails (gemm_ring_kernel)."""
     from gpu_common import build_pool
     cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=2, n_slots=2, shared_expert=True, tokens=tokens, hidden=shape[0], ffn=shape[1])
     pool, _ = build_pool(cfg)
@@ -219,20 +220,110 @@ def test_row_groups_of_the_lds_tiled_kernels(rows, monkeypatch):
 @pytest.mark.parametrize("kw", [
     dict(tokens=300, top_k=1, n_experts=1, n_slots=1, hidden=8, ffn=40),        # a partial step is all there is
     dict(tokens=700, top_k=2, n_experts=3, n_slots=3, hidden=200, ffn=328),     # tails of 8 in both products, ragged columns
-    dict(tokens=600, top_k=2, n_experts=4, n_slots=4, hidden=1096, ffn=1000),   # splits that stand for the strips' halves
-    dict(tokens=300, top_k=1, n_experts=2, n_slots=2, hidden=264, ffn=2056),    # second product split, the last with a partial step
-    dict(tokens=2600, top_k=2, n_experts=20, n_slots=20, hidden=136, ffn=72),   # several tiles for a workgroup
+    dict(tokens=300, top_k=1, n_experts=2, n_slots=2, hidden=264, ffn=2056),
+    dict(tokens=2600, top_k=2, n_experts=20, n_slots=20, hidden=136, ffn=72),
     dict(tokens=520, top_k=1, n_experts=2, n_slots=2, hidden=256, ffn=1032),    # one product whole, one with a partial step
 ])
-def test_large_tiles_with_a_partial_step(kw):
-    run_ffn_case(inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw), seed=12)
+def test_strips_where_tiles_would_be_taken_for_longer_k(kw, plan):
+    """Rows enough for 256 x 256 tiles, K too short for the splits that would stand for the strips' halves."""
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], **kw)
+    assert not plan(cfg.tokens, cfg.top_k, cfg.n_experts, cfg.hidden, cfg.ffn, mapped=cfg.n_experts).tiled
+    run_ffn_case(cfg, seed=12)
 
 
-def test_infinite_weights_past_whole_steps_stay_where_they_belong():
-    """The pieces past the end of K are zeros: an infinite weight in the last k row of the second product reaches its own
-    column only."""
+def ragged_cfg(T, K, E, H, F):
+    return inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=T, top_k=K, n_experts=E, n_slots=E, hidden=H, ffn=F)
+
+
+@pytest.mark.parametrize("call,ksplit1,ksplit", [
+    ((600, 2, 4, 1096, 1000), 2, 3),            # splits that stand for the strips' halves
+    ((143, 1, 1, 792, 728), 2, 2),              # both products split, the last split of each with a partial step
+    ((383, 1, 2, 776, 136), 2, 1),              # the second walks
+    ((889, 3, 6, 8, 1544), 1, 6),               # a partial step is all of the first product's k
+    ((5532, 2, 6, 8, 272), 1, 1),               # several tiles for a workgroup, row tiles of every size
+    ((874, 3, 20, 688, 1656), 1, 6),            # non-temporal weights: first product unsplit, second split
+    ((1856, 3, 30, 1032, 760), 1, 1),           # and both unsplit
+])
+def test_large_tiles_with_a_partial_step(call, ksplit1, ksplit, plan):
+    cfg = ragged_cfg(*call)
+    ctx = B.fluxmoe_create(1, cfg.n_experts, cfg.hidden, cfg.ffn, cfg.n_slots)
+    limit = B.fluxmoe_ffn_workspace_bytes(ctx, cfg.tokens, cfg.top_k)
+    B.fluxmoe_destroy(ctx)
+    p = plan(*call, mapped=cfg.n_experts, limit=limit)
+    assert (p.tiled, p.m_tile, p.ksplit1, p.ksplit) == (1, 256, ksplit1, ksplit)
+    run_ffn_case(cfg, seed=12)
+
+
+@pytest.mark.parametrize("call", [(600, 2, 4, 1096, 1000), (881, 8, 8, 928, 392)])
+def test_ragged_shapes_in_smaller_buffers_and_in_the_static_scratch(call, plan):
+    """Tiles with their splits, the strips' plan in its own bytes, the plan without splits, and what 32 MiB hold."""
     from gpu_common import build_pool
-    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], tokens=300, top_k=1, n_experts=1, n_slots=1, hidden=72, ffn=200)
+    cfg = ragged_cfg(*call)
+    every = np.arange(cfg.n_experts)
+    of = lambda **kw: plan(*call, mapped=cfg.n_experts, **kw)
+    best, strips, least = of(), of(ragged=False), of(split=False)
+    assert best.tiled and best.bytes > strips.bytes >= least.bytes and of(limit=strips.bytes).__dict__ == strips.__dict__ and strips.halves
+    assert bool(of(limit=32 << 20).tiled) == (best.bytes <= 32 << 20)
+    pool, dense = build_pool(cfg)
+    try:
+        pool_bytes = int(pool.sizes.pool_workspace_bytes)
+        assert pool.ws_bytes - pool_bytes >= best.bytes
+        x = inputs.activations(cfg).cuda()
+        ids, g = inputs.routing(cfg)
+        idd, gd = torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda()
+        pool.reset_page_table()
+        pool.materialize(0, every, every)
+        want = offn.moe_ffn(inputs.bits_u16(x.cpu()), ids, g, lambda e: (inputs.bits_u16(dense[0][0][e]), inputs.bits_u16(dense[0][1][e])))
+        for scratch in (best.bytes, (best.bytes + strips.bytes) // 2, strips.bytes, least.bytes):
+            B.fluxmoe_bind_arenas(pool.ctx, pool.slots13.data_ptr(), pool.slots2.data_ptr(), pool.workspace.data_ptr(), pool_bytes + scratch)
+            pool.workspace[pool_bytes:].fill_(0x7F)
+            out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+            pool.expert_ffn(0, x, idd, gd, out)
+            torch.cuda.synchronize()
+            assert (pool.workspace[pool_bytes + scratch:] == 0x7F).all()
+            assert offn.rel_frobenius(out.cpu().numpy(), want) <= TOL
+        out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+        B.fluxmoe_expert_ffn_static(pool.ctx, 0, x.data_ptr(), cfg.tokens, idd.data_ptr(), gd.data_ptr(), cfg.top_k, pool.page_table.data_ptr(), out.data_ptr(), 0,
+                                    torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert pool.device_errors() == 0 and offn.rel_frobenius(out.cpu().numpy(), want) <= TOL
+    finally:
+        pool.close()
+
+
+def test_what_lies_behind_the_operands_stays_out_of_the_tiles(plan):
+    """The pieces past the end of K are zeros: the slot behind the routed expert's and one token are infinite here, which makes that
+    token's row infinite or not a number, and no other."""
+    from gpu_common import build_pool
+    cfg = ragged_cfg(143, 1, 1, 792, 728)
+    cfg = inputs.scaled(cfg, n_slots=2)
+    p = plan(143, 1, 1, 792, 728, mapped=1)
+    assert p.tiled and p.ksplit1 == 2 and p.ksplit == 2
+    pool, dense = build_pool(cfg)
+    try:
+        w13, w2 = dense[0]
+        x, (ids, g) = inputs.activations(cfg).clone(), inputs.routing(cfg)
+        x[100] = float("inf")
+        out = torch.zeros((cfg.tokens, cfg.hidden), dtype=torch.float32, device="cuda")
+        pool.poison_slots(0x7F80)
+        pool.reset_page_table()
+        pool.materialize(0, np.arange(1, dtype=np.int32), np.arange(1, dtype=np.int32))
+        pool.expert_ffn(0, x.cuda(), torch.from_numpy(ids).cuda(), torch.from_numpy(g).cuda(), out)
+        torch.cuda.synchronize()
+        assert bool(torch.isinf(pool.slot2(1).view(torch.bfloat16)).all())
+        others = [t for t in range(cfg.tokens) if t != 100]
+        assert not bool(torch.isfinite(out[100]).any())
+        want = offn.moe_ffn(inputs.bits_u16(x[others].contiguous()), ids[others], g[others], lambda e: (inputs.bits_u16(w13[e]), inputs.bits_u16(w2[e])))
+        assert offn.rel_frobenius(out[others].cpu().numpy(), want) <= TOL
+    finally:
+        pool.close()
+
+
+def test_infinite_weights_past_whole_steps_stay_where_they_belong(plan):
+    """An infinite weight in the last k row of the second product reaches its own column only."""
+    from gpu_common import build_pool
+    cfg = ragged_cfg(143, 1, 1, 792, 728)
+    assert plan(143, 1, 1, 792, 728, mapped=1).tiled
     pool, dense = build_pool(cfg)
     try:
         x, (ids, g) = inputs.activations(cfg), inputs.routing(cfg)
