@@ -58,7 +58,7 @@ public:
         threads_.clear();
         if (thrown_) std::rethrow_exception(thrown_);
     }
-    uint64_t take() { return stopped_.load(std::memory_order_relaxed) ? ~0ull : next_.fetch_add(1, std::memory_order_relaxed); }
+    uint64_t take() { return next_.fetch_add(1, std::memory_order_relaxed); }
     template <typename F>
     void wait(F&& once) {
         std::unique_lock<std::mutex> lock(m_);
@@ -87,6 +87,7 @@ private:
                 std::lock_guard<std::mutex> lock(m_);
                 if (!stopped_) thrown_ = std::current_exception();
                 stopped_ = true;
+                next_.store(1ull << 63, std::memory_order_relaxed);      // nothing left to take; no pass ends any more, which would reset it
             }
             cv_.notify_all();
         }
@@ -98,7 +99,7 @@ private:
     void (*work_)(Crew*, void*, uint32_t) = nullptr;
     void* user_ = nullptr;
     bool closed_ = false;
-    std::atomic<bool> stopped_{false};
+    bool stopped_ = false;
     std::exception_ptr thrown_;
     std::atomic<uint64_t> next_{0};
     uint64_t pass_ = 0;
