@@ -94,8 +94,8 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     }
     p.tiled = p.m_tile == 256;
     // H or F that is not a multiple of 64: the 256 x 256 tiles take a partial step, so the same line holds.  Microseconds a call, 128-row strips /
-    // tiles: 8 experts of H 3000 F 7000, 250 rows each 540 / 405, 1024 rows 1712 / 1160; 160 of H 2600 F 1000, 150 rows 1204 / 761;
-    // 64 of H 2000 F 312, 1250 rows 1010 / 673; one of H 5000 F 1496, 2000 rows 199 / 149.
+    // tiles: 8 experts of H 3000 F 7000, 250 rows each 571 / 435, 1024 rows 1720 / 1208; 160 of H 2600 F 1000, 150 rows 1294 / 752; with the
+    // splits that stand for the strips' halves (chains below) 64 of H 2000 F 312, 1250 rows 1089 / 905; one of H 5000 F 1496, 2000 rows 198 / 173.
     // Where the launch would leave CUs without a workgroup.  All figures: microseconds per call, weights out of HBM.
     if (split && !forced && tiles256 && c.tiled_waves == 2) {
         const double avg_act = double(pairs_act) / double(groups_act);
