@@ -45,7 +45,7 @@ union Frag {
 
 constexpr int kStrip = 128;        // output columns per wavefront
 constexpr int kChunk = 32;         // k per MFMA step
-constexpr uint32_t kRoutedPairs = 64;   // batches of up to this many pairs are grouped by the first product's workgroups
+constexpr uint32_t kRoutedPairs = kFewPairs;
 constexpr int kNonTemporal = 2;    // cache policy operand of the buffer loads: bit 1 = nt
 
 // ------------------------------------------------------------------ routing / grouping
@@ -362,15 +362,21 @@ struct StripGemm {
         }
     }
 
+    // column c of the lane's 8 x 8 tile
+    __device__ __forceinline__ static Frag column(const uint4 (&b)[8], int c) {
+        Frag f;
+        const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
+        f.u.x = __builtin_amdgcn_perm(comp(b[1], c >> 1), comp(b[0], c >> 1), sel);
+        f.u.y = __builtin_amdgcn_perm(comp(b[3], c >> 1), comp(b[2], c >> 1), sel);
+        f.u.z = __builtin_amdgcn_perm(comp(b[5], c >> 1), comp(b[4], c >> 1), sel);
+        f.u.w = __builtin_amdgcn_perm(comp(b[7], c >> 1), comp(b[6], c >> 1), sel);
+        return f;
+    }
+
     __device__ __forceinline__ void mma_b(const uint4 (&b)[8], const uint4 (&a)[MI]) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            Frag f;
-            const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
-            f.u.x = __builtin_amdgcn_perm(comp(b[1], c >> 1), comp(b[0], c >> 1), sel);
-            f.u.y = __builtin_amdgcn_perm(comp(b[3], c >> 1), comp(b[2], c >> 1), sel);
-            f.u.z = __builtin_amdgcn_perm(comp(b[5], c >> 1), comp(b[4], c >> 1), sel);
-            f.u.w = __builtin_amdgcn_perm(comp(b[7], c >> 1), comp(b[6], c >> 1), sel);
+            const Frag f = column(b, c);
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) {
                 Frag fa;
@@ -650,7 +656,7 @@ __device__ __forceinline__ void gemm1_swiglu_body(const FfnArgs& a, const TileIn
 
     if (SPLIT && n_split > 1) {                   // partial sums of both matrices, added up by swiglu_reduce_kernel
         if (!col_ok || (HALVES && pair == 1)) return;
-        float* part = a.ybuf + (size_t(split) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
+        float* part = a.part + (size_t(split) * a.pairs_cap + size_t(t.row0)) * 2 * a.F + size_t(mat_id) * a.F + n0;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -715,10 +721,12 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     float (*xch)[64] = reinterpret_cast<float (*)[64]>(smem);
     uint16_t* abuf = reinterpret_cast<uint16_t*>(smem);
     TileInfo t;
-    // column workgroup, row tile, K split: the three dimensions of the grid, or (a.g1_xcd) numbered as in gemm2_kernel so that
+    // column workgroup, K split, row tile: the three dimensions of the grid, or (a.g1_xcd) numbered as in gemm2_kernel so that
     // the column workgroups of a (tile, split) share an XCD and find the tile's activations, and where rows of the weights
     // are not whole 128-byte lines the line that two strips share, in its L2
-    uint32_t col_wg = blockIdx.x, tile_no = blockIdx.y, split = blockIdx.z;
+    // The tiles come last: the numbers past the last tile are then the last ones and every XCD gets its share of the others (160 experts of
+    // H 5120 F 1536, one token, top-8, five splits: 240 of 270 workgroups have work; with the splits last 86 us a call, now 69).
+    uint32_t col_wg = blockIdx.x, tile_no = blockIdx.z, split = blockIdx.y;
     if (!ROUTE && a.g1_xcd) {
         const uint32_t n_cw = HALVES ? (a.F + kStrip - 1) / kStrip : (a.F + 2 * kStrip - 1) / (2 * kStrip);
         const uint32_t xcd = blockIdx.x % 8u, q = blockIdx.x / 8u;
@@ -732,8 +740,8 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     if (ROUTE) {
         static_assert(!ROUTE || (16 * MI >= int(kRoutedPairs) && kRoutedPairs == 64), "a pair per lane, an expert's pairs in one tile");
         const int lane = threadIdx.x & 63;
-        const uint32_t pairs = a.T * a.K, tile = blockIdx.y;
-        const bool lists = blockIdx.x == 0 && blockIdx.z == 0;              // uniform
+        const uint32_t pairs = a.T * a.K, tile = tile_no;
+        const bool lists = blockIdx.x == 0 && split == 0;                   // uniform
         const int32_t id = uint32_t(lane) < pairs ? a.topk_ids[lane] : -1;
         const bool known = id >= 0 && uint32_t(id) < a.E;
         const int32_t slot = known ? a.page_table[id] : -1;
@@ -858,6 +866,179 @@ __global__ __launch_bounds__(256) void gemm2_kernel(FfnArgs a) {
     else gemm2_body<MI>(a, t, abuf, col_wg, split);
 }
 
+// The second product of a call of few pairs, bound by its start-up and by how many CUs have work: a workgroup has one strip of 128
+// columns of one expert and its four wavefronts a quarter of the k range each, so a token's ten experts of F 512 give 160 workgroups
+// where four strips to a workgroup and two K splits gave 80, and there are no partial sums to write (27.8 -> 26.0 us a call).
+// FUSED: the first product's partial sums are added up here, each wavefront its own quarter's, while its first weights are on
+// their way: one launch less (26.0 -> 24.3).  For up to four tokens: every strip's workgroup repeats the sums of its expert's rows.
+// Combining in the workgroup that is the last of its strip was tried: with device-wide fences 33, with stores and loads that pass the
+// L2s by 24.0, which is not worth depending on.
+template <int MI, bool FUSED>
+__device__ __forceinline__ void gemm2_few_body(const FfnArgs& a, const TileInfo& t, uint32_t row_first, uint8_t* smem, uint32_t strip, uint32_t split) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const uint32_t n0 = strip * kStrip + 8u * (lane & 15);
+    const bool col_ok = n0 < a.H;
+    const uint32_t col = col_ok ? n0 : a.H - 8;
+    const uint32_t k_per = ((a.F + a.ksplit - 1) / a.ksplit + kChunk - 1) / kChunk * kChunk;
+    const uint32_t k_lo = min(a.F, split * k_per), k_hi = min(a.F, k_lo + k_per);
+    const uint32_t quarter = ((k_per + 3) / 4 + kChunk - 1) / kChunk * kChunk;
+    const uint32_t k_begin = min(k_hi, k_lo + uint32_t(wave) * quarter), k_end = min(k_hi, k_begin + quarter);
+    const int32_t rows = min(int32_t(16 * MI), t.rows - int32_t(row_first));
+    const uint16_t* w2 = a.slots2 + size_t(t.slot) * a.F * a.H;
+    StripGemm<MI> g;
+    f32x4 sums[8];                               // FUSED: through the compiler's MFMA, which needs no pinned accumulators here
+    if constexpr (FUSED) {
+        static_assert(!FUSED || MI == 1, "up to four tokens");
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sums[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto mma = [&](const uint4 (&b)[8], const uint4& af) __attribute__((always_inline)) {
+            Frag fa;
+            fa.u = af;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) sums[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.v, StripGemm<MI>::column(b, c).v, sums[c], 0, 0, 0);
+        };
+        const uint32_t row_bytes = 2u * a.H;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(w2), 0, int(a.F * row_bytes), 0x00020000);
+        const uint32_t voff = 8u * (uint32_t(lane) >> 4) * row_bytes + 2u * col, chunk_bytes = uint32_t(kChunk) * row_bytes;
+        // whole chunks of 32 k, and what is left of F behind the last of them
+        const uint32_t n = (k_end - k_begin) / kChunk, k_tail = k_begin + n * kChunk;
+        uint4 b[4][8];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (uint32_t(s) < n) StripGemm<MI>::load_b(b[s], rsrc, voff, k_begin * row_bytes + uint32_t(s) * chunk_bytes, row_bytes);
+        const uint32_t n_split = a.ksplit1;
+        // h of this quarter in LDS, 16 rows of `pitch` elements
+        const uint32_t pitch = quarter + 8;
+        uint16_t* const hs = reinterpret_cast<uint16_t*>(smem) + uint32_t(wave) * 16u * pitch;
+        for (uint32_t kb = 0; kb < k_end - k_begin; kb += 128) {
+            const uint32_t k = kb + 4u * (lane & 31);
+            for (int32_t r2 = 0; r2 < rows; r2 += 2) {
+                const int32_t r = r2 + (lane >> 5);
+                const float* part = a.part + (size_t(t.row0) + row_first + uint32_t(min(r, rows - 1))) * 2 * a.F + min(k_begin + k, a.F - 4);
+                float gs[4] = {0.f, 0.f, 0.f, 0.f}, us[4] = {0.f, 0.f, 0.f, 0.f};
+                for (uint32_t s0 = 0; s0 < n_split; s0 += 4) {
+                    float4 gv[4], uv[4];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) {
+                        const float* at = part + size_t(min(s0 + i, n_split - 1)) * a.pairs_cap * 2 * a.F;
+                        gv[i] = *reinterpret_cast<const float4*>(at);
+                        uv[i] = *reinterpret_cast<const float4*>(at + a.F);
+                    }
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i)
+                        if (s0 + i < n_split) {
+                            gs[0] += gv[i].x; gs[1] += gv[i].y; gs[2] += gv[i].z; gs[3] += gv[i].w;
+                            us[0] += uv[i].x; us[1] += uv[i].y; us[2] += uv[i].z; us[3] += uv[i].w;
+                        }
+                }
+                if (k < k_end - k_begin && r < rows)
+                    *reinterpret_cast<uint2*>(hs + uint32_t(r) * pitch + k) = make_uint2(pack_bf16_rne(swiglu(gs[0], us[0]), swiglu(gs[1], us[1])),
+                                                                                         pack_bf16_rne(swiglu(gs[2], us[2]), swiglu(gs[3], us[3])));
+            }
+        }
+        asm volatile("" ::: "memory");           // the wavefront's own LDS writes and reads stay in order
+        const uint16_t* const ha = hs + uint32_t(min(lane & 15, rows - 1)) * pitch + 8u * (uint32_t(lane) >> 4);
+        for (uint32_t base = 0; base < n; base += 4) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (base + s >= n) break;
+                mma(b[s], *reinterpret_cast<const uint4*>(ha + (base + s) * kChunk));
+                if (base + s + 4 < n) StripGemm<MI>::load_b(b[s], rsrc, voff, k_begin * row_bytes + (base + s + 4) * chunk_bytes, row_bytes);
+            }
+        }
+        if (k_tail < k_end) {                    // (lanes past the end contribute zeros)
+            uint4 af = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) b[0][r] = af;
+            if (k_tail + 8u * (uint32_t(lane) >> 4) < k_end) {
+                StripGemm<MI>::load_b(b[0], rsrc, voff, k_tail * row_bytes, row_bytes);
+                af = *reinterpret_cast<const uint4*>(ha + n * kChunk);
+            }
+            mma(b[0], af);
+        }
+        __syncthreads();                         // the memory is used again below
+    } else {
+        g.zero();
+        const uint16_t* arow[MI];
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) arow[mi] = a.hbuf + (size_t(t.row0) + row_first + uint32_t(min(mi * 16 + (lane & 15), rows - 1))) * a.F;
+        g.run(arow, w2 + col, a.H, k_begin, k_end, lane);
+    }
+
+    float* const y = a.ybuf + (size_t(split) * a.pairs_cap + size_t(t.row0) + row_first) * a.H;
+    float (*xch)[64] = reinterpret_cast<float (*)[64]>(smem);
+    if constexpr (MI == 1) {
+        // the four wavefronts' sums through LDS: each adds up two of the lane's eight columns, in the order of k
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) xch[wave * 32 + c * 4 + r][lane] = FUSED ? sums[c][r] : g.acc[0][c][r];
+        __syncthreads();
+        if (col_ok) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int32_t row = 4 * (lane >> 4) + r;
+                if (row >= rows) continue;
+                float v[2];
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    const int at = (2 * wave + d) * 4 + r;
+                    v[d] = ((xch[at][lane] + xch[32 + at][lane]) + xch[64 + at][lane]) + xch[96 + at][lane];
+                }
+                *reinterpret_cast<float2*>(y + size_t(uint32_t(row)) * a.H + n0 + 2 * wave) = make_float2(v[0], v[1]);
+            }
+        }
+    } else {
+        // wavefronts 2 and 3 hand their sums to 0 and 1, then 1 to 0
+#pragma unroll
+        for (int from = 2; from >= 1; from >>= 1) {
+            if (wave >= from && wave < 2 * from) {
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) xch[(wave - from) * (MI * 32) + (mi * 8 + c) * 4 + r][lane] = g.acc[mi][c][r];
+            }
+            __syncthreads();
+            if (wave < from) {
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) g.acc[mi][c][r] += xch[wave * (MI * 32) + (mi * 8 + c) * 4 + r][lane];
+            }
+            __syncthreads();
+        }
+        if (wave == 0 && col_ok) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int32_t row = mi * 16 + 4 * (lane >> 4) + r;
+                    if (row >= rows) continue;
+                    float4* dst = reinterpret_cast<float4*>(y + size_t(uint32_t(row)) * a.H + n0);
+                    dst[0] = make_float4(g.acc[mi][0][r], g.acc[mi][1][r], g.acc[mi][2][r], g.acc[mi][3][r]);
+                    dst[1] = make_float4(g.acc[mi][4][r], g.acc[mi][5][r], g.acc[mi][6][r], g.acc[mi][7][r]);
+                }
+        }
+    }
+}
+
+template <int MI, bool FUSED>
+__global__ __launch_bounds__(256, MI == 1 ? 2 : 1) void gemm2_few_kernel(FfnArgs a) {
+    extern __shared__ __align__(16) uint8_t few_smem[];
+    TileInfo t;
+    if (!tile_info(a, blockIdx.z, t)) return;
+    for (uint32_t r = 0; r < uint32_t(t.rows); r += 16 * MI) {
+        if (r) __syncthreads();
+        if (MI > 1 && t.rows <= 16) gemm2_few_body<1, FUSED>(a, t, r, few_smem, blockIdx.x, blockIdx.y);
+        else gemm2_few_body<MI, FUSED>(a, t, r, few_smem, blockIdx.x, blockIdx.y);
+    }
+}
+
 // h[row][n] = bf16( silu(gate) * up ), gate and up summed over the K splits of the first product in split order.
 // Bound by its launch at the sizes that split (a few hundred kilobytes to 30 MB of sums, still in the caches): a launch
 // of its own is cheaper than the device-wide fence a last-arriver scheme inside the product would take.
@@ -875,7 +1056,7 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(FfnArgs a) {
     float g[8], u[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) g[c] = u[c] = 0.f;
-    const float* part = a.ybuf + size_t(row) * 2 * a.F + n0;
+    const float* part = a.part + size_t(row) * 2 * a.F + n0;
     for (uint32_t sp = 0; sp < n_split; ++sp, part += size_t(a.pairs_cap) * 2 * a.F) {
         const float4 g0 = *reinterpret_cast<const float4*>(part), g1 = *reinterpret_cast<const float4*>(part + 4);
         const float4 u0 = *reinterpret_cast<const float4*>(part + a.F), u1 = *reinterpret_cast<const float4*>(part + a.F + 4);
@@ -1934,7 +2115,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     auto mark = [&](int kind, int begin) { if (hook) hook(user, kind, begin, stream); };
     const size_t sh = (3 * size_t(a.E) + 1024) * sizeof(int32_t);
     // strip kernels, few pairs: the first product's workgroups do the grouping
-    const bool routes_itself = !a.identity && !a.tiled && a.m_tile >= kRoutedPairs && uint64_t(a.T) * a.K <= kRoutedPairs;
+    const bool routes_itself = a.few != 0;
+    if (routes_itself && (a.identity || a.tiled || a.m_tile < kRoutedPairs || uint64_t(a.T) * a.K > kRoutedPairs)) return hipErrorInvalidValue;
     const hipEvent_t with_routing = attach_routed ? routed : nullptr;
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
@@ -1974,7 +2156,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const uint32_t strips2 = (a.H + kStrip - 1) / kStrip;
     if (a.halves && (a.tiled || a.m_tile != 128)) return hipErrorInvalidValue;
     const uint32_t cols1 = a.halves ? strips1 : (strips1 + 1) / 2;
-    const dim3 g1 = a.g1_xcd && !routes_itself ? dim3((a.tiles_cap * a.ksplit1 + 7) / 8 * 8 * cols1, 1, 1) : dim3(cols1, a.tiles_cap, a.ksplit1);
+    const dim3 g1 = a.g1_xcd && !routes_itself ? dim3((a.tiles_cap * a.ksplit1 + 7) / 8 * 8 * cols1, 1, 1) : dim3(cols1, a.ksplit1, a.tiles_cap);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
     a.direct = a.identity && a.ksplit == 1 && (a.ring2 || (a.tiled && a.tiled_waves == 2));
     if (a.ring1) {
@@ -2148,10 +2330,14 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false, false>), g1, dim3(256), 0, stream, a);
     if (routes_itself)
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
-    launch_reduce();
+    if (!a.few_fused) launch_reduce();
     mark(2, 0);
     mark(3, 1);
-    if (a.m_tile == 16) hipLaunchKernelGGL(gemm2_kernel<1>, g2, dim3(256), 0, stream, a);
+    if (a.few2) {
+        const dim3 grid(strips2, a.ksplit, a.tiles_cap);
+        if (a.few_fused) hipLaunchKernelGGL((gemm2_few_kernel<1, true>), grid, dim3(256), std::max(32768u, 4u * 16u * (uint32_t(few_quarter(a.F, a.ksplit)) + 8u) * 2u), stream, a);
+        else hipLaunchKernelGGL((gemm2_few_kernel<4, false>), grid, dim3(256), 65536, stream, a);
+    } else if (a.m_tile == 16) hipLaunchKernelGGL(gemm2_kernel<1>, g2, dim3(256), 0, stream, a);
     else if (a.m_tile == 32) hipLaunchKernelGGL(gemm2_kernel<2>, g2, dim3(256), 0, stream, a);
     else if (a.m_tile == 64) hipLaunchKernelGGL(gemm2_kernel<4>, g2, dim3(256), 0, stream, a);
     else if (a.m_tile == 96) hipLaunchKernelGGL(gemm2_kernel<6>, g2, dim3(256), 0, stream, a);

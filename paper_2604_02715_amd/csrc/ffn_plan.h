@@ -14,6 +14,8 @@ namespace fluxmoe {
 // experts: 12288 pairs 17.3 / 18.3, 16384 20.7 / 18.7, 32768 35.4 / 20.6, 163840 - / 31.
 constexpr uint32_t kRouteChunkThreshold = 14336;
 constexpr uint32_t kRouteChunkPairs = 4096;
+// Calls of up to this many pairs on strip kernels have no grouping kernel: the first product's workgroups group the pairs.
+constexpr uint32_t kFewPairs = 64;
 // Row tiles a call may have (the y dimension of the strip kernels' grid).
 constexpr uint32_t kMaxRowTiles = 65535;
 
@@ -45,10 +47,14 @@ FLUXMOE_HD inline float tiled_cost(const SplitShape& s, uint32_t n_tiles, uint32
 
 struct FfnPlan {
     bool tiled, halves, g1_xcd;
+    // few: the first product's workgroups group the pairs.  few_splits: K splits of gemm2_few_kernel, 0: gemm2_kernel with ksplit.
+    // few_fused: it also adds up the first product's partial sums, which then lie at off_part behind y
+    bool few, few_fused;
+    uint32_t few_splits;
     // ring1, ring2: rows of a tile of gemm_ring_kernel in the first and second product, 0: the kernels that tiled and m_tile name
     uint32_t m_tile, ksplit, ksplit1, split_tiles, ring1, ring2, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
-    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y;
+    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y, off_part;
 };
 
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -60,6 +66,22 @@ struct FfnShape {
     int n_cus, tiled_waves;
     bool ragged = false;         // the 256 x 256 tiles may be taken where H or F is not a multiple of 64
 };
+
+// k rows of a wavefront of gemm2_few_kernel: a quarter of its workgroup's
+inline uint64_t few_quarter(uint64_t F, uint64_t splits) { return align_up((align_up((F + splits - 1) / splits, 32) + 3) / 4, 32); }
+
+// First product of a call of few pairs with K split k ways, in k rows of a workgroup (about 32 ns each): rounds of one workgroup per
+// CU, each with a start-up of 128 rows; the launch that adds up the partial sums costs as much again and a split `partial` / 1024 rows.  A
+// large number where the rows do not make k splits of whole units.  cols: column workgroups, halves: the two pairs of wavefronts share the rows.
+constexpr uint32_t kFewSplits = 16;
+inline uint32_t few_cost(uint32_t H, uint32_t n_cus, uint32_t cols, uint32_t n_tiles, bool halves, uint32_t partial, uint32_t k) {
+    const uint32_t unit = halves ? 256u : 128u, k_per = ((H + k - 1) / k + unit - 1) / unit * unit;
+    if (k > 1 && (k * 256 > H || (H + k_per - 1) / k_per != k)) return 1u << 30;
+    const uint32_t rounds = (cols * n_tiles * k + n_cus - 1) / n_cus;
+    return rounds * ((k_per < H ? k_per : H) / (halves ? 2u : 1u) + 128u) + (k > 1 ? 128u + k * partial / 1024u : 0u);
+}
+
+inline uint32_t few_partial(uint64_t pairs, uint64_t F, uint64_t n_cus) { return uint32_t(pairs * 2 * F * 8 / n_cus); }
 
 // split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.
 inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_t mapped, bool split, uint64_t limit) {
@@ -165,6 +187,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         if (chains > 1 && H < (chains * pairs_act * 2 * F * 4 > (256u << 20) ? 512u : 384u) * chains) return q;
         p.ksplit1 = chains;
     }
+    p.few = !p.tiled && p.m_tile >= kFewPairs && pairs <= kFewPairs;
+    // experts that T tokens of K distinct ones each are expected to touch
+    double touched = p.few ? std::max(1.0, double(act) * (1.0 - std::pow(1.0 - double(K) / double(E), double(T)))) : 0.0;
+    // (a call that touches more of them than expected would take another round)
+    if (p.few && (T > 1 || act < E)) touched = std::min({touched + 0.4 * std::sqrt(touched * (1.0 - touched / double(act))), double(act), double(pairs)});
     // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when
     // split k ways.  A tile costs 3 us to start; a step 1.4 us (256 x 256, one workgroup per CU), or 0.56 us (128 x 128)
     // alone on a CU and 0.88 us for each of two.  Partial sums are written and read at 10 TB/s (mostly in the caches).
@@ -216,6 +243,21 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             };
             consider(false);
             if (p.m_tile == 128 && !forced && (strips1 % 2 || (strips1 + 1) / 2 * tiles1 < n_cus)) consider(true);
+            if (p.few) {
+                // The same with the experts the call is expected to touch for its row tiles, whole strips where they are as good (their
+                // rows of weights are 512 bytes of a matrix, not 256), and no sum longer than above.  Microseconds a call, above / here:
+                // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
+                // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
+                const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
+                const uint64_t longest = chain(p.ksplit1, p.halves);
+                const uint32_t tiles = uint32_t(touched + 0.5), partial = few_partial(pairs_act, F, n_cus);
+                uint32_t least = ~0u;
+                for (const bool halves : {false, true})
+                    for (uint32_t k = 1; k <= kFewSplits && !(halves && (forced || p.m_tile != 128)); ++k) {
+                        const uint32_t cost = few_cost(uint32_t(H), uint32_t(n_cus), uint32_t(halves ? strips1 : (strips1 + 1) / 2), tiles, halves, partial, k);
+                        if (chain(k, halves) <= longest && (halves ? cost + cost / 64 < least : cost < least)) { least = cost; p.ksplit1 = k; p.halves = halves; }
+                    }
+            }
         } else {
             const uint64_t cols = p.m_tile / 2;
             const uint64_t tiles1 = row_tiles * ((F + cols - 1) / cols), room = p.m_tile == 256 ? n_cus : 2 * n_cus;
@@ -231,6 +273,24 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // (64 of F 384: 94.4 / 93.5), with two strips a workgroup it is 0.5 to 2 % slower.  Enough (tile, split) units to fill the
     // 8 XCDs evenly.
     p.g1_xcd = p.halves && F % 64 != 0 && groups_act * p.ksplit1 >= 64;
+    // Few pairs: the second product in gemm2_few_kernel while its workgroups make one round and a wavefront's quarter of K is short.
+    // Microseconds a call, gemm2_kernel / gemm2_few_kernel: 8 experts of H 1856 F 432, 7 tokens, top-8 (15 strips of 8 experts) 37.6 / 31.4,
+    // 46 of H 488 F 416 34.0 / 27.6, one of H 4096 F 14336, one token (quarters of 448 k) 84 / 67; but 160 of H 5120 F 384, 2 tokens, top-8
+    // (640 workgroups) 42.4 / 45.6, 64 of H 2048 F 512 (1024) 71 / 76, 4 of H 4096 F 14336, 8 tokens (quarters of 1792 k) 215 / 230.
+    // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
+    // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
+    if (p.few) {
+        uint64_t least = ~0ull;
+        const uint64_t tiles = uint64_t(touched + 0.5);
+        for (uint64_t k = 1; k <= 8 && (k == 1 || k * 256 <= F); ++k) {
+            const uint64_t rounds = (strips2 * tiles * k + n_cus - 1) / n_cus, cost = rounds * (few_quarter(F, k) + 96) + (k > 1 ? 32 * k : 0);
+            if (cost < least) { least = cost; p.few_splits = uint32_t(k); }
+        }
+        const uint64_t wgs = strips2 * tiles;
+        p.few_fused = split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && 2 * wgs <= 3 * n_cus;
+        if (!p.few_fused && (wgs > n_cus || few_quarter(F, p.few_splits) > (tiles <= 2 ? 1024u : 512u))) p.few_splits = 0;
+        if (!split) p.few_splits = std::min(p.few_splits, p.ksplit);
+    }
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
     p.off_count = take((E + 1) * 4);
@@ -245,8 +305,12 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // the partial sums of the first product are read before the second product writes its own in the same place
     auto end = [&]() {
         const uint64_t y = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4 : 0;
-        return p.off_y + align_up(std::max(y, part), 256);
+        const uint64_t y_few = p.few_splits ? align_up(uint64_t(p.few_splits) * p.pairs_cap * H * 4, 256) : 0;
+        p.off_part = p.few_fused ? p.off_y + y_few : p.off_y;
+        return std::max(p.off_y + align_up(std::max(std::max(y, y_few), part), 256), p.off_part + align_up(part, 256));
     };
+    if (p.few && end() > limit) p.few_fused = false;
+    while (p.few_splits > 1 && end() > limit) --p.few_splits;
     if (split) {
         while (p.ksplit1 > chains && end() > limit) --p.ksplit1;
         if (chains > 1) {
@@ -290,7 +354,10 @@ inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limi
 // them (8 experts of H 4400 F 3504, 140 rows each, within it 353 / 262 us; of H 1856 F 2632, 1646 rows each, past it: 167 MB, 624 with the
 // splits).  A call whose buffer has the room takes them all the same.
 inline uint64_t ffn_bytes(FfnShape c, uint32_t T, uint32_t K) {
-    const uint64_t tiles = plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes;
+    uint64_t tiles = plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes;
+    // few pairs: with part of the layer resident there are fewer row tiles and more splits
+    if (uint64_t(T) * K <= kFewPairs)
+        for (const uint64_t part : {2, 4, 8}) tiles = std::max(tiles, plan_ffn_rules(c, T, K, uint32_t(std::max<uint64_t>(1, c.E / part)), true, ~0ull).bytes);
     c.ragged = false;
     const uint64_t strips = std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
     return tiles <= strips + (64ull << 20) ? std::max(tiles, strips) : strips;

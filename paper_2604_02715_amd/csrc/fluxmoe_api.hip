@@ -1071,6 +1071,11 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
     a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.halves = p.halves; a.g1_xcd = p.g1_xcd; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1; a.split_tiles = p.split_tiles;
     a.mapped = mapped;
+    a.part = reinterpret_cast<float*>(w + p.off_part);
+    a.few = p.few;
+    a.few_fused = p.few_fused;
+    a.few2 = p.few_splits != 0;
+    if (a.few2) a.ksplit = p.few_splits;
     a.n_cus = uint32_t(std::max(c->n_cus, 1));
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);
@@ -1167,6 +1172,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     a.error_word = reinterpret_cast<uint32_t*>(c->ws + c->err_off);
     a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.halves = p.halves; a.g1_xcd = p.g1_xcd; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1;
     a.ring1 = p.ring1; a.ring2 = p.ring2;
+    a.part = a.ybuf;
     a.split_tiles = ~0u;                        // the plan knew the rows
     a.n_cus = uint32_t(std::max(c->n_cus, 1));
     a.tiled_waves = c->tune_tiled_waves;

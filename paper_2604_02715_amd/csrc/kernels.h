@@ -34,6 +34,8 @@ struct FfnArgs {
     uint16_t* hbuf;              // BF16 [pairs_cap][F]
     float* ybuf;                 // FP32 [ksplit][pairs_cap][H]; with ksplit1 > 1 the first product's partial sums
                                  // [ksplit1][pairs_cap][2][F] (gate, up) lie here before the second product runs
+    float* part;                 // where the strip kernels' first product puts its partial sums: ybuf, or behind y where the second product
+                                 // adds them up itself (few_fused)
     uint32_t* error_word;
     uint32_t pairs_cap, tiles_cap, m_tile, ksplit;
     uint32_t ksplit1;            // most K splits of the first product (the launch covers as many, first_splits says how many work).
@@ -56,6 +58,9 @@ struct FfnArgs {
     uint32_t direct;             // set by launch_ffn: the second product writes the output itself (identity, unsplit)
     uint32_t tiled_group;        // super-rows of the LDS-direct gate/up kernel that share a column block in time;
                                  // 0 = launch_ffn derives it from the rows per expert
+    uint32_t few;                // non-zero (strip kernels, at most kFewPairs pairs): the first product's workgroups group the pairs
+    uint32_t few2;               // non-zero: gemm2_few_kernel is the second product
+    uint32_t few_fused;          // it also adds up the first product's partial sums
     uint32_t mapped;             // for the launcher: experts of the layer known to be resident, 0 = not known
 };
 

@@ -1,0 +1,83 @@
+"""The launch plan of calls of up to 64 pairs (csrc/ffn_plan.h), compiled on its own."""
+import ctypes as C
+import os
+import random
+import subprocess
+from types import SimpleNamespace
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_02715_amd", "csrc")
+FIELDS = ("few", "few_fused", "few_splits", "halves", "ksplit", "ksplit1", "bytes", "off_y", "off_part", "tiled")
+SHIM = """
+#include "ffn_plan.h"
+using namespace fluxmoe;
+extern "C" void plan(uint64_t E, uint64_t H, uint64_t F, uint32_t T, uint32_t K, uint64_t limit, uint32_t mapped, uint64_t* o) {
+    const FfnPlan p = plan_ffn(FfnShape{E, H, F, 256, 2, true}, T, K, limit, mapped); %s
+}
+extern "C" uint64_t asked(uint64_t E, uint64_t H, uint64_t F, uint32_t T, uint32_t K) { return ffn_bytes(FfnShape{E, H, F, 256, 2, true}, T, K); }
+extern "C" uint64_t quarter(uint64_t F, uint64_t k) { return few_quarter(F, k); }
+""" % " ".join("o[%d] = p.%s;" % (i, f) for i, f in enumerate(FIELDS))
+
+
+@pytest.fixture(scope="module")
+def few(tmp_path_factory):
+    d = tmp_path_factory.mktemp("ffn_plan_few")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
+    so = C.CDLL(str(d / "shim.so"))
+    so.plan.argtypes = [C.c_uint64] * 3 + [C.c_uint32] * 2 + [C.c_uint64, C.c_uint32, C.POINTER(C.c_uint64)]
+    so.asked.argtypes, so.asked.restype = [C.c_uint64] * 3 + [C.c_uint32] * 2, C.c_uint64
+    so.quarter.argtypes, so.quarter.restype = [C.c_uint64] * 2, C.c_uint64
+
+    def plan(T, K, E, H, F, mapped=0, limit=2 ** 64 - 1):
+        o = (C.c_uint64 * len(FIELDS))()
+        so.plan(E, H, F, T, K, limit, mapped, o)
+        return SimpleNamespace(**dict(zip(FIELDS, o)))
+    return SimpleNamespace(plan=plan, asked=so.asked, quarter=so.quarter)
+
+
+def test_random_calls_at_any_buffer_size(few, monkeypatch):
+    """The scratch covers what the kernels write, sums that the second product adds up itself lie behind its own, its K splits have
+    work, and shorter buffers are given way to."""
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+    rng = random.Random(7)
+    seen = {"fused": 0, "few": 0, "split": 0, "old": 0}
+    for _ in range(3000):
+        E = rng.choice([1, 2, 8, 20, 64, 160, 512])
+        K = rng.randrange(1, min(E, 16) + 1)
+        T = rng.randrange(1, 64 // K + 1)
+        H, F = 8 * rng.randrange(1, 700), 8 * rng.randrange(1, rng.choice([20, 80, 1000]))
+        mapped = rng.choice([0, E, max(1, E // 2)])
+        c = dict(T=T, K=K, E=E, H=H, F=F, mapped=mapped)
+        best = few.plan(**c)
+        for limit in (2 ** 64 - 1, best.bytes - 1, best.off_y + T * K * H * 4 + 255, rng.randrange(best.off_y, best.bytes + 1)):
+            p = few.plan(**c, limit=limit)
+            if p.tiled:
+                continue
+            pairs = T * K
+            assert p.few and (p.bytes <= limit or p.ksplit1 == 1)
+            y = (p.few_splits or p.ksplit) * pairs * H * 4
+            part = p.ksplit1 * pairs * 2 * F * 4 if p.ksplit1 > 1 else 0
+            assert p.bytes >= p.off_y + y and p.bytes >= p.off_part + part and p.off_part % 256 == 0
+            assert p.off_part == p.off_y or (p.few_fused and p.off_part >= p.off_y + y)
+            assert p.ksplit1 <= max(1, H // 64)
+            if p.few_fused:
+                assert p.few_splits and p.ksplit1 > 1 and T <= 4 and few.quarter(F, p.few_splits) <= 128
+            if p.few_splits > 1:
+                assert (p.few_splits - 1) * 256 < F
+            seen["fused" if p.few_fused else "split" if p.few_splits > 1 else "few" if p.few_splits else "old"] += 1
+        if not best.tiled and mapped in (0, E):
+            assert few.asked(E, H, F, T, K) >= few.plan(**dict(c, mapped=0)).bytes
+    assert all(v > 100 for v in seen.values()), seen
+
+
+def test_both_sides_of_the_lines(few):
+    of = lambda **kw: few.plan(**kw)
+    token = dict(K=10, E=512, H=2048, F=512)
+    assert of(T=1, **token).few_fused and of(T=1, **dict(token, F=520)).few_splits == 1 and not of(T=1, **dict(token, F=520)).few_fused
+    assert of(T=4, K=2, E=64, H=2048, F=512).few_fused and not of(T=5, K=2, E=64, H=2048, F=512).few_fused
+    assert of(T=6, K=10, E=512, H=2048, F=512).few_splits == 0               # 16 strips of about 57 experts
+    assert of(T=1, K=1, E=8, H=4096, F=14336).few_splits == 8                # 32 strips of one
+    assert of(T=1, K=8, E=8, H=4096, F=14336).few_splits == 0                # quarters of 3584 k
+    assert of(T=7, K=10, E=512, H=2048, F=512).few == 0                      # 70 pairs
