@@ -1518,6 +1518,42 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 #define FLUXMOE_D2L_PROBE 0
 #endif
 
+// The last round of a second product in 256 x 256 tiles.  Super-tiles of 4 x 8 tiles are dealt to the 8 XCDs in turn; where the last
+// round has four of them at most, K of each is split over as many XCDs as there are for one, and last_round_kernel adds the parts up.
+// 8 experts of H 4096 F 14336, 4096 tokens, top-2 (18 super-tiles, two XCDs ran a third round while six had nothing to do): 913 -> 863 us
+// with the sums, the call 2618 -> 2563; 2 of those, 6000 tokens (12 row tiles each) 1872 -> 1766.
+struct LastRound {
+    uint32_t first, parts;       // first super-tile of the round, parts of K
+};
+constexpr uint32_t kTailBlock = 256 * 256;       // floats of a tile's partial sums
+__device__ __forceinline__ LastRound last_round(uint32_t supers) {
+    const uint32_t rest = supers % 8u;
+    return LastRound{supers - rest, rest == 1 ? 8u : (rest == 2 ? 4u : (rest == 3 || rest == 4 ? 2u : 1u))};
+}
+
+// y of the last round's tiles += their other parts of K, in the order of k.  A workgroup has 16 rows of a tile.  Bound by its launch (5 us where
+// nothing was split) and by the parts' bytes, 60 MB at most, still in the caches: 8 us on the first, 16 on the second case above.
+__global__ __launch_bounds__(256) void last_round_kernel(FfnArgs a) {
+    const uint32_t n_rt = uint32_t(a.n_tiles[0]), n_ct = (a.H + 255) / 256, n_sn = (n_ct + 7) / 8;
+    const LastRound last = last_round((n_rt + 3) / 4 * n_sn);
+    const uint32_t st = last.first + blockIdx.z, within = blockIdx.y;
+    const uint32_t row_tile = st / n_sn * 4 + within / 8, col_tile = st % n_sn * 8 + within % 8;
+    TileInfo t;
+    if (last.parts == 1 || row_tile >= n_rt || col_tile >= n_ct || !tile_info(a, row_tile, t)) return;
+    const uint32_t col = 4u * (threadIdx.x & 63u);
+    if (col_tile * 256 + col >= a.H) return;
+    for (int32_t row = int32_t(blockIdx.x * 16 + (threadIdx.x >> 6)); row < min(t.rows, int32_t(blockIdx.x * 16 + 16)); row += 4) {
+        float4* const y = reinterpret_cast<float4*>(a.ybuf + (size_t(t.row0) + uint32_t(row)) * a.H + col_tile * 256 + col);
+        float4 s = *y;
+        const float* part = a.tail + (size_t(blockIdx.z) * (last.parts - 1) * 32u + within) * kTailBlock + uint32_t(row) * 256u + col;
+        for (uint32_t k = 1; k < last.parts; ++k, part += 32 * size_t(kTailBlock)) {
+            const float4 v = *reinterpret_cast<const float4*>(part);
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+        *y = s;
+    }
+}
+
 // WALK: a workgroup takes several tiles one after the other (see the tile loop at the end); without it the
 // launch has one workgroup per tile number and the code for the upcoming tile falls away.
 // MODE 1: h = SwiGLU(X W1, X W3).  MODE 2: y = h W2, K split ksplit ways.  MODE 3: the first product with K split
@@ -1571,11 +1607,16 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // all numbers), so all of them lie on the XCD that runs this workgroup and at the same place of
     // successive super-tiles.
     const uint32_t total = a.tiled_total;
+    const LastRound last = MODE == 2 && !WALK && a.tail ? last_round(((n_rt + sm - 1) / sm) * n_sn) : LastRound{0u, 1u};
     auto locate_unchecked = [&](uint32_t L, uint32_t& row_tile, uint32_t& col_tile, uint32_t& split) __attribute__((always_inline)) {
         const uint32_t xcd = L % 8u, jj = L / 8u;
         const uint32_t pair = (jj / 32u) * 8u + xcd;
-        const uint32_t st = pair / n_split;
+        uint32_t st = pair / n_split;
         split = pair % n_split;
+        if (last.parts > 1 && pair >= last.first) {
+            st = last.first + (pair - last.first) / last.parts;
+            split = (pair - last.first) % last.parts;
+        }
         const uint32_t within = jj % 32u;
         const uint32_t grp = st / per_group, in_grp = st % per_group;
         row_tile = (grp * group + in_grp % group) * sm + (within >> sn_log2);
@@ -1628,6 +1669,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const uint8_t* b_base;
         int32_t rows, row0;
         uint32_t n_base, split, n_steps;
+        uint32_t tail;                       // 1 + number of the last round's block of partial sums, 0: the sums go to y
         uint32_t k_left;                     // RAGGED: k from the tile's first to the end of K
         bool valid;
     };
@@ -1644,10 +1686,14 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         if (!s.valid) { s.rows = 1; s.row0 = 0; }
         s.n_base = col_tile * ncols_tile;
         s.split = split;
+        // (a super-tile of the last round: the host lets it be split where K has steps enough)
+        const bool tail = last.parts > 1 && (id.L / 256u) * 8u >= last.first;
+        const uint32_t n_parts = tail ? last.parts : n_split;
+        if (MODE == 2 && !WALK) s.tail = tail && split > 0 ? (id.L / 256u * 8u + id.L % 8u - last.first) / last.parts * (last.parts - 1) + split : 0u;
         // split K: this tile multiplies steps [step_lo, step_hi) of the K / 64
         // and writes its own FP32 partial, which combine_kernel or swiglu_reduce_kernel sums in split order
-        const uint32_t step_lo = uint32_t(uint64_t(n_steps_all) * split / n_split);
-        const uint32_t step_hi = uint32_t(uint64_t(n_steps_all) * (split + 1) / n_split);
+        const uint32_t step_lo = uint32_t(uint64_t(n_steps_all) * split / n_parts);
+        const uint32_t step_hi = uint32_t(uint64_t(n_steps_all) * (split + 1) / n_parts);
         const uint32_t k_begin = step_lo * kTK;
         if (RAGGED) s.k_left = K - k_begin;
         s.n_steps = MODE == 1 ? 0u : step_hi - step_lo;        // >= 1: the host keeps the splits <= K / 64
@@ -1906,7 +1952,16 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         // (or, a.direct, the output: one split, row r is token r with gate 1)
         const uint32_t col0 = c.n_base + (TILE / 2u) * wn + q;
         const bool direct = (WAVES == 8 || TILE == 128) && a.direct;
-        float* const ylane = direct ? a.out + size_t(c.row0) * a.H + col0 : a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
+        float* ylane = direct ? a.out + size_t(c.row0) * a.H + col0 : a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
+        uint32_t pitch = a.H;
+        if (MODE == 2 && !WALK && last.parts > 1) {
+            if (c.tail) {
+                ylane = a.tail + (size_t(c.tail - 1) * 32u + blockIdx.x / 8u % 32u) * kTailBlock + (col0 - c.n_base);
+                pitch = 256;
+            } else {
+                ylane = a.ybuf + size_t(c.row0) * a.H + col0;
+            }
+        }
         if (direct && (a.flags & 1u)) {
 #pragma unroll
             for (int i = 0; i < kRowTiles; ++i)
@@ -1924,7 +1979,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
             for (int r = 0; r < 16; ++r) {
                 const int32_t row = 32 * (wm + kWaveRows * i) + (r >> 2) * 8 + h * 4 + (r & 3);
                 if (row >= c.rows) continue;
-                float* const yrow = ylane + size_t(uint32_t(row)) * a.H;
+                float* const yrow = ylane + size_t(uint32_t(row)) * pitch;
 #pragma unroll
                 for (int j = 0; j < kColTiles; ++j) {
                     if (col0 + 32u * j >= N) continue;
@@ -2300,12 +2355,14 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // the record at the end of a tile covers them.  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
         // 1137 / 1104, 20 of H 5120 F 1536, 1638 rows 1642 / 1615, 160 of those 512 rows 4637 / 4581, 205 rows 2127 / 2126.
         const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
+        if (walk2 || !d2l || d2l4 || small || a.ksplit != 1 || a.identity) a.tail = nullptr;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, false, 256>, gemm_d2l_kernel<2, 8, false, 256, true>, gemm_d2l_kernel<2, 8, false, 256, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
+        if (a.tail) hipLaunchKernelGGL(last_round_kernel, dim3(16, 32, 4), dim3(256), 0, stream, a);
         mark(3, 0);
         if (a.direct) return hipGetLastError();
         const dim3 gc2((a.H / 4 + 255) / 256, a.T, 1);

@@ -16,6 +16,8 @@ constexpr uint32_t kRouteChunkThreshold = 14336;
 constexpr uint32_t kRouteChunkPairs = 4096;
 // Calls of up to this many pairs on strip kernels have no grouping kernel: the first product's workgroups group the pairs.
 constexpr uint32_t kFewPairs = 64;
+// Partial sums of a last round (last_round_kernel): at most seven blocks of a super-tile's 32 tiles of 256 x 256.
+constexpr uint64_t kTailBytes = 7ull * 32 * 256 * 256 * 4;
 // Row tiles a call may have (the y dimension of the strip kernels' grid).
 constexpr uint32_t kMaxRowTiles = 65535;
 
@@ -50,11 +52,12 @@ struct FfnPlan {
     // few: the first product's workgroups group the pairs.  few_splits: K splits of gemm2_few_kernel, 0: gemm2_kernel with ksplit.
     // few_fused: it also adds up the first product's partial sums, which then lie at off_part behind y
     bool few, few_fused;
+    bool tail;                   // the last round of the second product may be split: its partial sums lie at off_tail behind y
     uint32_t few_splits;
     // ring1, ring2: rows of a tile of gemm_ring_kernel in the first and second product, 0: the kernels that tiled and m_tile name
     uint32_t m_tile, ksplit, ksplit1, split_tiles, ring1, ring2, pairs_cap, tiles_cap, n_chunks;
     uint64_t bytes;
-    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y, off_part;
+    uint64_t off_count, off_offset, off_sorted, off_pos, off_tile, off_ntiles, off_h, off_y, off_part, off_tail;
 };
 
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -291,6 +294,8 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         if (!p.few_fused && (wgs > n_cus || few_quarter(F, p.few_splits) > (tiles <= 2 ? 1024u : 512u))) p.few_splits = 0;
         if (!split) p.few_splits = std::min(p.few_splits, p.ksplit);
     }
+    // The last round of the second product: tiles of 256 x 256, unsplit, long K (shorter ones walk), more than a round of them.
+    p.tail = split && p.tiled && p.m_tile == 256 && c.tiled_waves == 2 && p.ksplit == 1 && F > 2048 && row_tiles * ((H + 255) / 256) > n_cus;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
     p.off_count = take((E + 1) * 4);
@@ -307,8 +312,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         const uint64_t y = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4 : 0;
         const uint64_t y_few = p.few_splits ? align_up(uint64_t(p.few_splits) * p.pairs_cap * H * 4, 256) : 0;
         p.off_part = p.few_fused ? p.off_y + y_few : p.off_y;
-        return std::max(p.off_y + align_up(std::max(std::max(y, y_few), part), 256), p.off_part + align_up(part, 256));
+        const uint64_t sums = std::max(p.off_y + align_up(std::max(std::max(y, y_few), part), 256), p.off_part + align_up(part, 256));
+        p.off_tail = sums;
+        return p.tail ? sums + kTailBytes : sums;
     };
+    if (p.tail && end() > limit) p.tail = false;
     if (p.few && end() > limit) p.few_fused = false;
     while (p.few_splits > 1 && end() > limit) --p.few_splits;
     if (split) {
@@ -354,13 +362,14 @@ inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limi
 // them (8 experts of H 4400 F 3504, 140 rows each, within it 353 / 262 us; of H 1856 F 2632, 1646 rows each, past it: 167 MB, 624 with the
 // splits).  A call whose buffer has the room takes them all the same.
 inline uint64_t ffn_bytes(FfnShape c, uint32_t T, uint32_t K) {
-    uint64_t tiles = plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes;
+    const FfnPlan p = plan_ffn_rules(c, T, K, 0, true, ~0ull);
+    uint64_t tiles = p.bytes - (p.tail ? kTailBytes : 0);
     // few pairs: with part of the layer resident there are fewer row tiles and more splits
     if (uint64_t(T) * K <= kFewPairs)
         for (const uint64_t part : {2, 4, 8}) tiles = std::max(tiles, plan_ffn_rules(c, T, K, uint32_t(std::max<uint64_t>(1, c.E / part)), true, ~0ull).bytes);
     c.ragged = false;
     const uint64_t strips = std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
-    return tiles <= strips + (64ull << 20) ? std::max(tiles, strips) : strips;
+    return tiles <= strips + (64ull << 20) ? std::max(tiles + (p.tail ? kTailBytes : 0), strips) : strips;
 }
 
 // Whether combine_kernel reads the second product's partial sums (`bytes` for all T * K pairs) and writes the output with the

@@ -1072,6 +1072,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.pairs_cap = p.pairs_cap; a.tiles_cap = p.tiles_cap; a.m_tile = p.m_tile; a.tiled = p.tiled; a.halves = p.halves; a.g1_xcd = p.g1_xcd; a.ksplit = p.ksplit; a.ksplit1 = p.ksplit1; a.split_tiles = p.split_tiles;
     a.mapped = mapped;
     a.part = reinterpret_cast<float*>(w + p.off_part);
+    a.tail = p.tail ? reinterpret_cast<float*>(w + p.off_tail) : nullptr;
     a.few = p.few;
     a.few_fused = p.few_fused;
     a.few2 = p.few_splits != 0;

@@ -36,6 +36,7 @@ struct FfnArgs {
                                  // [ksplit1][pairs_cap][2][F] (gate, up) lie here before the second product runs
     float* part;                 // where the strip kernels' first product puts its partial sums: ybuf, or behind y where the second product
                                  // adds them up itself (few_fused)
+    float* tail;                 // partial sums of the last round of the second product's 256 x 256 tiles (last_round_kernel), nullptr: not split
     uint32_t* error_word;
     uint32_t pairs_cap, tiles_cap, m_tile, ksplit;
     uint32_t ksplit1;            // most K splits of the first product (the launch covers as many, first_splits says how many work).
