@@ -1562,7 +1562,8 @@ __global__ __launch_bounds__(256) void last_round_kernel(FfnArgs a) {
 // of 64 x 64: two per CU, a quarter of the work per tile, for products whose 256 x 256 tiles leave most CUs without one.
 // STREAM: the weight loads carry the non-temporal hint.
 // RAGGED: K of either product may be any multiple of 8; the pieces of the last step that lie past its end come from zeros.
-template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false, bool RAGGED = false>
+// ROWS: the tiles are taken row by row and not in super-tiles.
+template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false, bool RAGGED = false, bool ROWS = false>
 __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kernel(FfnArgs a) {
     constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
     static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
@@ -1618,6 +1619,12 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
             split = (pair - last.first) % last.parts;
         }
         const uint32_t within = jj % 32u;
+        if (ROWS) {                                          // an XCD's 32 tiles one after the other, row by row
+            const uint32_t tile = st * 32u + within;
+            row_tile = tile / n_ct;
+            col_tile = tile % n_ct;
+            return;
+        }
         const uint32_t grp = st / per_group, in_grp = st % per_group;
         row_tile = (grp * group + in_grp % group) * sm + (within >> sn_log2);
         col_tile = (in_grp / group) * sn + (within & (sn - 1u));
@@ -2268,6 +2275,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 8, false, 256, false, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, false, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true, false, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, false, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true, false, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true>)}) {
                 e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
@@ -2308,7 +2317,19 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // one per XCD).  Sets the launch's fields in `a`.
         const uint64_t pairs_all = uint64_t(a.T) * a.K;
         const uint64_t avg_rows = pairs_all / std::max<uint64_t>(1, std::min<uint64_t>(a.E, pairs_all));
+        // Experts of about one row tile share no weights between their tiles, and what is left to share are the activations: with few
+        // column tiles an XCD's 32 tiles are taken row by row, so that a row's columns run together (12 column tiles in super-tiles of 8 x 4
+        // fetched every row of activations three times) and no place stays empty.  Microseconds a call, super-tiles / rows: 160 experts
+        // of H 5120 F 1536, 205 rows each 2032 / 1992, 300 rows 3599 / 3491, 80 of them, popularity by rank, 137 rows 1046 / 1021; 20 of them, 1392 rows
+        // 1369 / 1392; 8 of H 4096 F 3584 (28 column tiles), 412 rows 336 / 337, of F 14336 (112), 543 rows 1687 / 1767.
+        bool in_rows = false;                                       // of the launch that d2l_all was asked for last
         auto d2l_all = [&](uint32_t n_ct, uint32_t n_split, bool grouped, bool walk) {
+            in_rows = walk && !ragged && n_ct <= 24 && avg_rows <= 384;
+            if (in_rows) {
+                a.tiled_sn_log2 = 3;
+                a.tiled_group = 1;
+                return dim3((a.tiles_cap * n_ct + 255) / 256 * 256, 1, 1);
+            }
             uint32_t best_log2 = 3, best_pad = ~0u;
             for (uint32_t lg : {3u, 2u, 4u, 1u}) {
                 if (!walk && lg != 3u) continue;
@@ -2344,7 +2365,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((ragged ? gemm_d2l_kernel<3, 8, false, 256, false, true> : gemm_d2l_kernel<3, 8, false, 256>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((pick(gemm_d2l_kernel<1, 8, true, 256>, gemm_d2l_kernel<1, 8, true, 256, true>, gemm_d2l_kernel<1, 8, true, 256, false, true>, gemm_d2l_kernel<1, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<1, 8, true, 256, true, false, true> : gemm_d2l_kernel<1, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<1, 8, true, 256>, gemm_d2l_kernel<1, 8, true, 256, true>, gemm_d2l_kernel<1, 8, true, 256, false, true>, gemm_d2l_kernel<1, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<1>, grid_for((a.F + 127) / 128), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<1>, grid_for((a.F + 127) / 128), dim3(512), lds_bytes, stream, a);
         launch_reduce();
@@ -2358,7 +2379,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         if (walk2 || !d2l || d2l4 || small || a.ksplit != 1 || a.identity) a.tail = nullptr;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
-        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
+        else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<2, 8, true, 256, true, false, true> : gemm_d2l_kernel<2, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, false, 256>, gemm_d2l_kernel<2, 8, false, 256, true>, gemm_d2l_kernel<2, 8, false, 256, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
