@@ -122,8 +122,8 @@ struct fluxmoe_ctx {
     uint64_t half_capture[2] = {0, 0};
     bool copied_valid[2] = {false, false};  // ev_copied[h] has been recorded
     // launch shape of the decode kernel (FLUXMOE_DECODE_WAVES / FLUXMOE_DECODE_BLOCKS_PER_WAVE override)
-    int tune_waves = 0;                   // 0 = by the number of blocks, where the launch is made
-    int tune_blocks_per_wave = 1;
+    int tune_waves = 8;
+    int tune_blocks_per_wave = 0;         // 0 = by the number of blocks, where the launch is made
     int tune_tiled_waves = 2;             // FLUXMOE_FFN_TILED_WAVES: 2 = LDS-direct loads (default), 8 = register-staged,
                                           // 4 = register-staged with four wavefronts of 128 x 128
     int tune_tiled_persist = 1;           // FLUXMOE_FFN_TILED_PERSIST: 0 = one workgroup per tile, n = n x 256 workgroups walking the tiles
@@ -908,14 +908,13 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     for (const DenseCopy& dc : dense_copies)
         HIPCHECK(hipMemcpyAsync(dc.dst, dc.src, dc.bytes, hipMemcpyDeviceToDevice, stream));
     const uint64_t total = uint64_t(cmd->total_blocks[0]) + cmd->total_blocks[1];
-    // One block to a wavefront: a workgroup's life is then as short as it can be, and that is what a launch's ramp-up and its end cost.  Microseconds a
-    // call, 8 wavefronts with up to three blocks / 8 with one / 4 with one (4 with two): 10 experts of 6 MB 23.7 / 23.6 / 23.1, 20 of them
-    // 44.7 / 40.6 / 40.1 (41.5), 40 81.8 / 75.8 / 75.0, 145 292 / 286 / 281, 4 of 47 MB 62.7 / 57.5 / 56.8, 60 854 / 862 / 834 (837), 8 of 352 MB
-    // 830 / 832 / 811 (811); 16 wavefronts 895.  Four wavefronts are the faster ones alone, but not beside an FFN on another stream, where a wave of a few
-    // dozen experts usually runs (waves of 32 of 6 MB, 35000 blocks, a pass: 2042 / 2025 / 2062, again 2089 / 2086 / 2131; five workgroups of
-    // 32 KiB take all of a CU's LDS, three of 48 leave some), nor where the blocks just fit the chip at once (24 a CU in workgroups of 8, 20 in those
-    // of 4; 5300 blocks 13.7-14.0 against 14.7-15.2).  So they get the large launches only, where they save 2 to 3 %.
-    const int waves_per_wg = c->tune_waves ? c->tune_waves : total <= 256ull * uint64_t(std::max(c->n_cus, 1)) ? 8 : 4;
+    // Up to 256 blocks per CU a wavefront takes one block: a workgroup's life is then as short as it can be, and that is what a launch's ramp-up
+    // and its end cost (up to three blocks / one, microseconds a call: 20 experts of 6 MB 44.7 / 40.6, 40 of them 81.8 / 75.8, 4 of 47 MB 62.7 / 57.5).
+    // Beyond, three: 60 of 47 MB 854 / 862, 8 of 352 MB 830 / 832.  Workgroups of four wavefronts with one block are faster alone (8 of 352 MB
+    // 811), but not before or beside an FFN (the same load with its FFN in turn 1.317 / 1.317 / 1.331 ms a step; a pass with waves of 35000 blocks
+    // 2042 / 2025 / 2062).
+    const int waves_per_wg = c->tune_waves;
+    const int blocks_per_wave = c->tune_blocks_per_wave ? c->tune_blocks_per_wave : total <= 256ull * uint64_t(std::max(c->n_cus, 1)) ? 1 : 3;
     if (total == 0) {
         // every listed tensor is an uncompressed host tensor: nothing to decode, only the page table changes
         load_done = nullptr;
@@ -924,7 +923,7 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     } else {
     // blocks per workgroup: one per wavefront, or as many as asked for, fewer when that would leave CUs without work
     const uint64_t fill = total / (3ull * uint64_t(std::max(c->n_cus, 1)));
-    const uint64_t per_wg = std::max<uint64_t>(waves_per_wg, std::min<uint64_t>(uint64_t(waves_per_wg) * c->tune_blocks_per_wave, fill));
+    const uint64_t per_wg = std::max<uint64_t>(waves_per_wg, std::min<uint64_t>(uint64_t(waves_per_wg) * blocks_per_wave, fill));
     auto wgs_for = [&](uint64_t blocks) { return uint32_t(std::min<uint64_t>((blocks + per_wg - 1) / per_wg, 1u << 20)); };
     if (two_streams && cmd->total_blocks[0] && cmd->total_blocks[1]) {
         // one launch per tensor type: the type-2 list on the second stream (after everything this call has

@@ -1,4 +1,4 @@
-"""The decode launch's two shapes: 8 wavefronts to a workgroup up to 256 blocks per CU, 4 beyond (one block per wavefront in both)."""
+"""The decode launch's two shapes: one block per wavefront up to 256 blocks per CU, up to three beyond."""
 import pytest
 
 from paper_2604_02715_amd import inputs
