@@ -192,7 +192,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     }
     p.few = !p.tiled && p.m_tile >= kFewPairs && pairs <= kFewPairs;
     // experts that T tokens of K distinct ones each are expected to touch
-    double touched = p.few ? std::max(1.0, double(act) * (1.0 - std::pow(1.0 - double(K) / double(E), double(T)))) : 0.0;
+    double touched = p.few ? std::max(1.0, double(act) * (1.0 - std::pow(1.0 - std::min(1.0, double(K) / double(E)), double(T)))) : 0.0;
     // (a call that touches more of them than expected would take another round)
     if (p.few && (T > 1 || act < E)) touched = std::min({touched + 0.4 * std::sqrt(touched * (1.0 - touched / double(act))), double(act), double(pairs)});
     // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when

@@ -81,3 +81,18 @@ def test_both_sides_of_the_lines(few):
     assert of(T=1, K=1, E=8, H=4096, F=14336).few_splits == 8                # 32 strips of one
     assert of(T=1, K=8, E=8, H=4096, F=14336).few_splits == 0                # quarters of 3584 k
     assert of(T=7, K=10, E=512, H=2048, F=512).few == 0                      # 70 pairs
+
+
+def test_more_experts_a_token_than_the_layer_has(tmp_path):
+    """The size query takes any number of experts a token: no conversion of a number that is none."""
+    (tmp_path / "m.cpp").write_text("""
+#include "ffn_plan.h"
+int main() {
+    for (uint64_t E = 1; E <= 4; ++E)
+        for (uint32_t T = 1; T <= 8; ++T)
+            for (uint32_t K = 1; T * K <= 64; ++K) fluxmoe::ffn_bytes(fluxmoe::FfnShape{E, 512, 512, 256, 2, true}, T, K);
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=float-cast-overflow", "-fsanitize-undefined-trap-on-error", "-I", CSRC, str(tmp_path / "m.cpp"),
+                    "-o", str(tmp_path / "m")], check=True)
+    subprocess.run([str(tmp_path / "m")], check=True)
