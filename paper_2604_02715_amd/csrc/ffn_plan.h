@@ -68,6 +68,7 @@ struct FfnShape {
     uint64_t E, H, F;
     int n_cus, tiled_waves;
     bool ragged = false;         // the 256 x 256 tiles may be taken where H or F is not a multiple of 64
+    bool routed = true;          // false: the shared expert, whose call has neither the kernels for few pairs nor a split last round
 };
 
 // k rows of a wavefront of gemm2_few_kernel: a quarter of its workgroup's
@@ -190,7 +191,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         if (chains > 1 && H < (chains * pairs_act * 2 * F * 4 > (256u << 20) ? 512u : 384u) * chains) return q;
         p.ksplit1 = chains;
     }
-    p.few = !p.tiled && p.m_tile >= kFewPairs && pairs <= kFewPairs;
+    p.few = c.routed && !p.tiled && p.m_tile >= kFewPairs && pairs <= kFewPairs;
     // experts that T tokens of K distinct ones each are expected to touch
     double touched = p.few ? std::max(1.0, double(act) * (1.0 - std::pow(1.0 - std::min(1.0, double(K) / double(E)), double(T)))) : 0.0;
     // (a call that touches more of them than expected would take another round)
@@ -295,7 +296,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         if (!split) p.few_splits = std::min(p.few_splits, p.ksplit);
     }
     // The last round of the second product: tiles of 256 x 256, unsplit, long K (shorter ones walk), more than a round of them.
-    p.tail = split && p.tiled && p.m_tile == 256 && c.tiled_waves == 2 && p.ksplit == 1 && F > 2048 && row_tiles * ((H + 255) / 256) > n_cus;
+    p.tail = c.routed && split && p.tiled && p.m_tile == 256 && c.tiled_waves == 2 && p.ksplit == 1 && F > 2048 && row_tiles * ((H + 255) / 256) > n_cus;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
     p.off_count = take((E + 1) * 4);
@@ -430,7 +431,8 @@ inline RingProduct ring_product(uint64_t n_cus, uint64_t T, uint64_t K, uint64_t
 // 126 / 71, 700 rows 210 / 189; H 1000 F 200, 50 rows 35 / 15.
 // Where H and F are whole steps the other LDS-direct kernels win with two workgroups on a CU in the first product or two long
 // rounds in the second: H 5120 F 1536, 1344 rows 116 / 136, 1024 rows 91 / 97, 2048 rows 134 / 170; but H 5120 F 384, 1024 rows 48 / 41.
-inline FfnPlan plan_shared(const FfnShape& c, uint32_t T, uint64_t limit = ~0ull) {
+inline FfnPlan plan_shared(FfnShape c, uint32_t T, uint64_t limit = ~0ull) {
+    c.routed = false;
     const FfnPlan base = plan_ffn(c, T, 1, limit);
     const uint64_t n_cus = uint64_t(std::max(c.n_cus, 1));
     const RingProduct first = ring_product(n_cus, T, c.H, c.F, true), second = ring_product(n_cus, T, c.F, c.H, false);
@@ -453,6 +455,7 @@ inline FfnPlan plan_shared(const FfnShape& c, uint32_t T, uint64_t limit = ~0ull
 }
 
 inline uint64_t shared_bytes(FfnShape c, uint32_t T) {
+    c.routed = false;
     const uint64_t base = ffn_bytes(c, T, 1);
     c.ragged = false;
     return std::max(base, plan_shared(c, T).bytes);

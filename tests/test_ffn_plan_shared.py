@@ -14,7 +14,8 @@ SHIM = """
 using namespace fluxmoe;
 static void put(const FfnPlan& p, uint64_t* o) { %s }
 extern "C" void shared(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_shared(FfnShape{1, H, F, n_cus, waves, true}, T, limit), o); }
-extern "C" void base(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_ffn(FfnShape{1, H, F, n_cus, waves, true}, T, 1, limit), o); }
+extern "C" void base(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t limit, uint64_t* o) { put(plan_ffn(FfnShape{1, H, F, n_cus, waves, true, false}, T, 1, limit), o); }
+extern "C" uint64_t asked(uint64_t H, uint64_t F, uint32_t T) { return shared_bytes(FfnShape{1, H, F, 256, 2, true}, T); }
 extern "C" void least(uint64_t H, uint64_t F, int n_cus, int waves, uint32_t T, uint64_t, uint64_t* o) { put(plan_ffn_rules(FfnShape{1, H, F, n_cus, waves, true}, T, 1, 0, false, ~0ull), o); }
 """ % " ".join("o[%d] = p.%s;" % (i, f) for i, f in enumerate(FIELDS))
 
@@ -35,7 +36,8 @@ def rules(tmp_path_factory):
             fn(H, F, n_cus, waves, T, limit, o)
             return SimpleNamespace(**dict(zip(FIELDS, o)))
         return f
-    return SimpleNamespace(**{n: call(n) for n in ("shared", "base", "least")})
+    so.asked.argtypes, so.asked.restype = [C.c_uint64] * 2 + [C.c_uint32], C.c_uint64
+    return SimpleNamespace(asked=so.asked, **{n: call(n) for n in ("shared", "base", "least")})
 
 
 @pytest.fixture(autouse=True)
@@ -86,3 +88,15 @@ def test_only_the_larger_partial_sums_give_way(rules):
     assert best.ring1 and best.ksplit1 == 5 and best.ksplit == 8
     p = rules.shared(17, 2360, 1848, best.bytes - 1)
     assert p.ring1 and p.ksplit1 == 5 and p.ksplit == 7 and p.bytes < best.bytes
+
+
+def test_the_query_asks_for_nothing_that_only_routed_calls_use(rules):
+    """H and F of whole steps and neither product split: the scratch is h and one set of sums."""
+    rng = random.Random(4)
+    seen = 0
+    for T, H, F in [(8192, 4096, 4096), (8192, 4096, 14336)] + [(rng.randrange(1, 16000), 64 * rng.randrange(1, 80), 64 * rng.randrange(1, 120)) for _ in range(2000)]:
+        p, least = rules.shared(T, H, F), rules.least(T, H, F)
+        if not p.ring1 and p.ksplit == p.ksplit1 == 1:
+            assert rules.asked(H, F, T) <= max(p.off_y + T * H * 4, least.bytes) + 256
+            seen += T > 2000
+    assert seen > 200
