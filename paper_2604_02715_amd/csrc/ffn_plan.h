@@ -71,8 +71,9 @@ struct FfnShape {
     bool routed = true;          // false: the shared expert, whose call has neither the kernels for few pairs nor a split last round
 };
 
-// k rows of a wavefront of gemm2_few_kernel: a quarter of its workgroup's
-inline uint64_t few_quarter(uint64_t F, uint64_t splits) { return align_up((align_up((F + splits - 1) / splits, 32) + 3) / 4, 32); }
+// k rows of a wavefront of gemm2_few_kernel: a quarter of its workgroup's, in whole MFMA steps
+constexpr uint64_t kFewChunk = 32;
+inline uint64_t few_quarter(uint64_t F, uint64_t splits) { return align_up((align_up((F + splits - 1) / splits, kFewChunk) + 3) / 4, kFewChunk); }
 
 // First product of a call of few pairs with K split k ways, in k rows of a workgroup (about 32 ns each): rounds of one workgroup per
 // CU, each with a start-up of 128 rows; the launch that adds up the partial sums costs as much again and a split `partial` / 1024 rows.  A
@@ -284,9 +285,12 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
     // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
     if (p.few) {
+        // (no sum longer than there)
+        const uint64_t longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
         uint64_t least = ~0ull;
         const uint64_t tiles = uint64_t(touched + 0.5);
         for (uint64_t k = 1; k <= 8 && (k == 1 || k * 256 <= F); ++k) {
+            if (std::min(F, few_quarter(F, k)) > longest) continue;
             const uint64_t rounds = (strips2 * tiles * k + n_cus - 1) / n_cus, cost = rounds * (few_quarter(F, k) + 96) + (k > 1 ? 32 * k : 0);
             if (cost < least) { least = cost; p.few_splits = uint32_t(k); }
         }

@@ -15,9 +15,12 @@ using namespace fluxmoe;
 extern "C" void plan(uint64_t E, uint64_t H, uint64_t F, uint32_t T, uint32_t K, uint64_t limit, uint32_t mapped, uint64_t* o) {
     const FfnPlan p = plan_ffn(FfnShape{E, H, F, 256, 2, true}, T, K, limit, mapped); %s
 }
+extern "C" void general(uint64_t E, uint64_t H, uint64_t F, uint32_t T, uint32_t K, uint64_t limit, uint32_t mapped, uint64_t* o) {
+    const FfnPlan p = plan_ffn(FfnShape{E, H, F, 256, 2, true, false}, T, K, limit, mapped); %s
+}
 extern "C" uint64_t asked(uint64_t E, uint64_t H, uint64_t F, uint32_t T, uint32_t K) { return ffn_bytes(FfnShape{E, H, F, 256, 2, true}, T, K); }
 extern "C" uint64_t quarter(uint64_t F, uint64_t k) { return few_quarter(F, k); }
-""" % " ".join("o[%d] = p.%s;" % (i, f) for i, f in enumerate(FIELDS))
+""" % ((" ".join("o[%d] = p.%s;" % (i, f) for i, f in enumerate(FIELDS)),) * 2)
 
 
 @pytest.fixture(scope="module")
@@ -26,15 +29,33 @@ def few(tmp_path_factory):
     (d / "shim.cpp").write_text(SHIM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
     so = C.CDLL(str(d / "shim.so"))
-    so.plan.argtypes = [C.c_uint64] * 3 + [C.c_uint32] * 2 + [C.c_uint64, C.c_uint32, C.POINTER(C.c_uint64)]
+    so.plan.argtypes = so.general.argtypes = [C.c_uint64] * 3 + [C.c_uint32] * 2 + [C.c_uint64, C.c_uint32, C.POINTER(C.c_uint64)]
     so.asked.argtypes, so.asked.restype = [C.c_uint64] * 3 + [C.c_uint32] * 2, C.c_uint64
     so.quarter.argtypes, so.quarter.restype = [C.c_uint64] * 2, C.c_uint64
 
-    def plan(T, K, E, H, F, mapped=0, limit=2 ** 64 - 1):
-        o = (C.c_uint64 * len(FIELDS))()
-        so.plan(E, H, F, T, K, limit, mapped, o)
-        return SimpleNamespace(**dict(zip(FIELDS, o)))
-    return SimpleNamespace(plan=plan, asked=so.asked, quarter=so.quarter)
+    def call(fn):
+        def plan(T, K, E, H, F, mapped=0, limit=2 ** 64 - 1):
+            o = (C.c_uint64 * len(FIELDS))()
+            fn(E, H, F, T, K, limit, mapped, o)
+            return SimpleNamespace(**dict(zip(FIELDS, o)))
+        return plan
+    return SimpleNamespace(plan=call(so.plan), general=call(so.general), asked=so.asked, quarter=so.quarter)
+
+
+def k_per(k, splits, unit):
+    return min(k, -(-(-(-k // splits)) // unit) * unit)
+
+
+def chains(few, p, H, F):
+    """k rows that the first and the second product add up in one accumulator"""
+    return (k_per(H, p.ksplit1, 256 if p.halves else 128) // (2 if p.halves else 1),
+            min(F, few.quarter(F, p.few_splits)) if p.few_splits else k_per(F, p.ksplit, 32))
+
+
+def random_call(rng):
+    E = rng.choice([1, 2, 8, 20, 64, 160, 512])
+    K = rng.randrange(1, min(E, 16) + 1)
+    return dict(T=rng.randrange(1, 64 // K + 1), K=K, E=E, H=8 * rng.randrange(1, 700), F=8 * rng.randrange(1, rng.choice([80, 300, 1800])))
 
 
 def test_random_calls_at_any_buffer_size(few, monkeypatch):
@@ -96,3 +117,19 @@ int main() {
     subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=float-cast-overflow", "-fsanitize-undefined-trap-on-error", "-I", CSRC, str(tmp_path / "m.cpp"),
                     "-o", str(tmp_path / "m")], check=True)
     subprocess.run([str(tmp_path / "m")], check=True)
+
+
+def test_no_sum_is_longer_than_in_the_general_kernels(few, monkeypatch):
+    """Against the plan of a call that is not routed, which has the same rules without those for few pairs."""
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+    rng = random.Random(8)
+    calls = [dict(E=8, H=2176, F=1736, T=8, K=7), dict(E=20, H=2480, F=1904, T=1, K=10), dict(E=4, H=4280, F=1816, T=22, K=2)]
+    seen = 0
+    for c in calls + [random_call(rng) for _ in range(20000)]:
+        mapped = rng.randrange(c["E"] + 1)
+        p, g = few.plan(**c, mapped=mapped), few.general(**c, mapped=mapped)
+        if p.few:
+            a, b = chains(few, p, c["H"], c["F"]), chains(few, g, c["H"], c["F"])
+            assert a[0] <= b[0] and a[1] <= b[1], (c, mapped)
+            seen += p.few_splits > 0 and p.few_splits != g.ksplit
+    assert seen > 1000
