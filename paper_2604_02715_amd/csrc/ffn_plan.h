@@ -88,6 +88,61 @@ inline uint32_t few_cost(uint32_t H, uint32_t n_cus, uint32_t cols, uint32_t n_t
 
 inline uint32_t few_partial(uint64_t pairs, uint64_t F, uint64_t n_cus) { return uint32_t(pairs * 2 * F * 8 / n_cus); }
 
+// The few pairs' part of the plan p, which holds the general kernels' K splits, as many of them as fit `limit`: no sum is longer than
+// with those, and what is chosen fits as well (split: K splits of the first product are allowed, and then every choice goes by the buffer).
+inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint64_t act, uint64_t pairs_act, bool split, bool halves_too,
+                     uint64_t limit) {
+    const uint64_t H = c.H, F = c.F, pairs = p.pairs_cap, n_cus = uint64_t(std::max(c.n_cus, 1));
+    const uint64_t strips1 = (F + 127) / 128, strips2 = (H + 127) / 128;
+    const uint64_t room = limit > p.off_y ? limit - p.off_y : 0;
+    const auto sums1 = [&](uint64_t k) { return k > 1 ? align_up(k * pairs * 2 * F * 4, 256) : 0; };
+    const auto sums2 = [&](uint64_t k) { return align_up(k * pairs * H * 4, 256); };
+    // experts that T tokens of K distinct ones each are expected to touch
+    double touched = std::max(1.0, double(act) * (1.0 - std::pow(1.0 - std::min(1.0, double(K) / double(c.E)), double(T))));
+    // (a call that touches more of them than expected would take another round)
+    if (T > 1 || act < c.E) touched = std::min({touched + 0.4 * std::sqrt(touched * (1.0 - touched / double(act))), double(act), double(pairs)});
+    const uint64_t tiles = uint64_t(touched + 0.5);
+    if (split) {
+        // The first product with the experts the call is expected to touch for its row tiles, and whole strips where they are as good (their
+        // rows of weights are 512 bytes of a matrix, not 256).  Microseconds a call, general rule / here:
+        // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
+        // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
+        const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
+        const uint64_t longest = chain(p.ksplit1, p.halves);
+        const uint32_t partial = few_partial(pairs_act, F, n_cus);
+        uint32_t least = ~0u;
+        for (const bool halves : {false, true})
+            for (uint32_t k = 1; k <= kFewSplits && !(halves && !halves_too); ++k) {
+                const uint32_t cost = few_cost(uint32_t(H), uint32_t(n_cus), uint32_t(halves ? strips1 : (strips1 + 1) / 2), uint32_t(tiles), halves, partial, k);
+                if (chain(k, halves) <= longest && sums1(k) <= room && (halves ? cost + cost / 64 < least : cost < least)) { least = cost; p.ksplit1 = k; p.halves = halves; }
+            }
+    }
+    // The second product in gemm2_few_kernel while its workgroups make one round and a wavefront's quarter of K is short.
+    // Microseconds a call, gemm2_kernel / gemm2_few_kernel: 8 experts of H 1856 F 432, 7 tokens, top-8 (15 strips of 8 experts) 37.6 / 31.4,
+    // 46 of H 488 F 416 34.0 / 27.6, one of H 4096 F 14336, one token (quarters of 448 k) 84 / 67; but 160 of H 5120 F 384, 2 tokens, top-8
+    // (640 workgroups) 42.4 / 45.6, 64 of H 2048 F 512 (1024) 71 / 76, 4 of H 4096 F 14336, 8 tokens (quarters of 1792 k) 215 / 230.
+    // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
+    // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
+    const uint64_t wgs = strips2 * tiles, longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
+    const auto splits_in = [&](uint64_t free) {                     // 0: none of them
+        uint64_t least = ~0ull;
+        uint32_t best = 0;
+        for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 256 <= F && (split || k <= p.ksplit))); ++k) {
+            if (std::min(F, few_quarter(F, k)) > longest || sums2(k) > free) continue;
+            const uint64_t rounds = (wgs * k + n_cus - 1) / n_cus, cost = rounds * (few_quarter(F, k) + 96) + (k > 1 ? 32 * k : 0);
+            if (cost < least) { least = cost; best = uint32_t(k); }
+        }
+        return best;
+    };
+    if (split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && 2 * wgs <= 3 * n_cus)
+        if (sums1(p.ksplit1) + sums2(p.ksplit) <= room) p.few_splits = splits_in(room - sums1(p.ksplit1));
+    p.few_fused = p.few_splits != 0;
+    if (!p.few_fused && wgs <= n_cus) {
+        p.few_splits = splits_in(std::max(room, sums2(p.ksplit)));  // (without room for those of gemm2_kernel there is no call)
+        if (few_quarter(F, std::max(1u, p.few_splits)) > (tiles <= 2 ? 1024u : 512u)) p.few_splits = 0;
+    }
+}
+
 // split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.
 inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_t mapped, bool split, uint64_t limit) {
     FfnPlan p{};
@@ -193,10 +248,6 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         p.ksplit1 = chains;
     }
     p.few = c.routed && !p.tiled && p.m_tile >= kFewPairs && pairs <= kFewPairs;
-    // experts that T tokens of K distinct ones each are expected to touch
-    double touched = p.few ? std::max(1.0, double(act) * (1.0 - std::pow(1.0 - std::min(1.0, double(K) / double(E)), double(T)))) : 0.0;
-    // (a call that touches more of them than expected would take another round)
-    if (p.few && (T > 1 || act < E)) touched = std::min({touched + 0.4 * std::sqrt(touched * (1.0 - touched / double(act))), double(act), double(pairs)});
     // LDS-tiled kernels: row tiles to expect, and nanoseconds a product of `tiles` tiles and `steps` steps of 64 k takes when
     // split k ways.  A tile costs 3 us to start; a step 1.4 us (256 x 256, one workgroup per CU), or 0.56 us (128 x 128)
     // alone on a CU and 0.88 us for each of two.  Partial sums are written and read at 10 TB/s (mostly in the caches).
@@ -248,21 +299,6 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
             };
             consider(false);
             if (p.m_tile == 128 && !forced && (strips1 % 2 || (strips1 + 1) / 2 * tiles1 < n_cus)) consider(true);
-            if (p.few) {
-                // The same with the experts the call is expected to touch for its row tiles, whole strips where they are as good (their
-                // rows of weights are 512 bytes of a matrix, not 256), and no sum longer than above.  Microseconds a call, above / here:
-                // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
-                // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
-                const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
-                const uint64_t longest = chain(p.ksplit1, p.halves);
-                const uint32_t tiles = uint32_t(touched + 0.5), partial = few_partial(pairs_act, F, n_cus);
-                uint32_t least = ~0u;
-                for (const bool halves : {false, true})
-                    for (uint32_t k = 1; k <= kFewSplits && !(halves && (forced || p.m_tile != 128)); ++k) {
-                        const uint32_t cost = few_cost(uint32_t(H), uint32_t(n_cus), uint32_t(halves ? strips1 : (strips1 + 1) / 2), tiles, halves, partial, k);
-                        if (chain(k, halves) <= longest && (halves ? cost + cost / 64 < least : cost < least)) { least = cost; p.ksplit1 = k; p.halves = halves; }
-                    }
-            }
         } else {
             const uint64_t cols = p.m_tile / 2;
             const uint64_t tiles1 = row_tiles * ((F + cols - 1) / cols), room = p.m_tile == 256 ? n_cus : 2 * n_cus;
@@ -277,28 +313,7 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // 66 -> 62, of H 1544 F 264, 600 tokens 71 -> 66; 160 of F 104, one strip each, 84 -> 85).  With aligned rows it changes nothing
     // (64 of F 384: 94.4 / 93.5), with two strips a workgroup it is 0.5 to 2 % slower.  Enough (tile, split) units to fill the
     // 8 XCDs evenly.
-    p.g1_xcd = p.halves && F % 64 != 0 && groups_act * p.ksplit1 >= 64;
-    // Few pairs: the second product in gemm2_few_kernel while its workgroups make one round and a wavefront's quarter of K is short.
-    // Microseconds a call, gemm2_kernel / gemm2_few_kernel: 8 experts of H 1856 F 432, 7 tokens, top-8 (15 strips of 8 experts) 37.6 / 31.4,
-    // 46 of H 488 F 416 34.0 / 27.6, one of H 4096 F 14336, one token (quarters of 448 k) 84 / 67; but 160 of H 5120 F 384, 2 tokens, top-8
-    // (640 workgroups) 42.4 / 45.6, 64 of H 2048 F 512 (1024) 71 / 76, 4 of H 4096 F 14336, 8 tokens (quarters of 1792 k) 215 / 230.
-    // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
-    // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
-    if (p.few) {
-        // (no sum longer than there)
-        const uint64_t longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
-        uint64_t least = ~0ull;
-        const uint64_t tiles = uint64_t(touched + 0.5);
-        for (uint64_t k = 1; k <= 8 && (k == 1 || k * 256 <= F); ++k) {
-            if (std::min(F, few_quarter(F, k)) > longest) continue;
-            const uint64_t rounds = (strips2 * tiles * k + n_cus - 1) / n_cus, cost = rounds * (few_quarter(F, k) + 96) + (k > 1 ? 32 * k : 0);
-            if (cost < least) { least = cost; p.few_splits = uint32_t(k); }
-        }
-        const uint64_t wgs = strips2 * tiles;
-        p.few_fused = split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && 2 * wgs <= 3 * n_cus;
-        if (!p.few_fused && (wgs > n_cus || few_quarter(F, p.few_splits) > (tiles <= 2 ? 1024u : 512u))) p.few_splits = 0;
-        if (!split) p.few_splits = std::min(p.few_splits, p.ksplit);
-    }
+    p.g1_xcd = !p.few && p.halves && F % 64 != 0 && groups_act * p.ksplit1 >= 64;
     // The last round of the second product: tiles of 256 x 256, unsplit, long K (shorter ones walk), more than a round of them.
     p.tail = c.routed && split && p.tiled && p.m_tile == 256 && c.tiled_waves == 2 && p.ksplit == 1 && F > 2048 && row_tiles * ((H + 255) / 256) > n_cus;
     uint64_t o = 0;
@@ -314,18 +329,19 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     p.off_y = o;
     // the partial sums of the first product are read before the second product writes its own in the same place
     auto end = [&]() {
-        const uint64_t y = uint64_t(p.ksplit) * p.pairs_cap * H * 4, part = p.ksplit1 > 1 ? uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4 : 0;
-        const uint64_t y_few = p.few_splits ? align_up(uint64_t(p.few_splits) * p.pairs_cap * H * 4, 256) : 0;
-        p.off_part = p.few_fused ? p.off_y + y_few : p.off_y;
-        const uint64_t sums = std::max(p.off_y + align_up(std::max(std::max(y, y_few), part), 256), p.off_part + align_up(part, 256));
+        // (with room for gemm2_kernel's splits also where gemm2_few_kernel takes fewer: a buffer without it was never enough)
+        const uint64_t y = align_up(uint64_t(std::max(p.few_splits, p.ksplit)) * p.pairs_cap * H * 4, 256);
+        const uint64_t part = p.ksplit1 > 1 ? align_up(uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4, 256) : 0;
+        p.off_part = p.few_fused ? p.off_y + y : p.off_y;
+        const uint64_t sums = std::max(p.off_y + y, p.off_part + part);
         p.off_tail = sums;
         return p.tail ? sums + kTailBytes : sums;
     };
     if (p.tail && end() > limit) p.tail = false;
-    if (p.few && end() > limit) p.few_fused = false;
-    while (p.few_splits > 1 && end() > limit) --p.few_splits;
-    if (split) {
+    if (split)
         while (p.ksplit1 > chains && end() > limit) --p.ksplit1;
+    if (p.few) plan_few(p, c, T, K, act, pairs_act, split, p.m_tile == 128 && !forced, limit);
+    if (split) {
         if (chains > 1) {
             p.split_tiles = ~0u;
         } else if (p.ksplit1 > 1 && p.tiled && p.m_tile == 256) {

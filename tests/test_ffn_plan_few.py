@@ -133,3 +133,27 @@ def test_no_sum_is_longer_than_in_the_general_kernels(few, monkeypatch):
             assert a[0] <= b[0] and a[1] <= b[1], (c, mapped)
             seen += p.few_splits > 0 and p.few_splits != g.ksplit
     assert seen > 1000
+
+
+def test_short_buffers_keep_the_sums_short(few, monkeypatch):
+    """In any buffer that holds the general plan: no sum longer than in it, and no quarter past the rule's line."""
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+    rng = random.Random(9)
+    calls = [dict(E=8, H=4096, F=14336, T=1, K=1), dict(E=8, H=4928, F=9552, T=1, K=2), dict(E=512, H=2048, F=512, T=1, K=10)]
+    gave = 0
+    for c in calls + [random_call(rng) for _ in range(8000)]:
+        mapped = rng.randrange(c["E"] + 1)
+        best = few.plan(**c, mapped=mapped)
+        for limit in (best.bytes - 1, rng.randrange(best.off_y, best.bytes + 1)):
+            p, g = few.plan(**c, mapped=mapped, limit=limit), few.general(**c, mapped=mapped, limit=limit)
+            assert (p.bytes <= limit) == (g.bytes <= limit)
+            if p.few and p.bytes <= limit:
+                a, b = chains(few, p, c["H"], c["F"]), chains(few, g, c["H"], c["F"])
+                assert a[0] <= b[0] and a[1] <= b[1], (c, mapped, limit)
+                assert p.few_fused or not p.few_splits or few.quarter(c["F"], p.few_splits) <= 1024
+                gave += (p.few_splits, p.few_fused, p.ksplit1) != (best.few_splits, best.few_fused, best.ksplit1)
+    assert gave > 1000
+    # the first product's sums are what does not fit: the second product keeps its splits
+    whole = few.plan(**calls[0])
+    short = few.plan(**calls[0], limit=whole.bytes - 1)
+    assert whole.few_splits == short.few_splits == 8 and short.ksplit1 < whole.ksplit1
