@@ -89,9 +89,10 @@ inline uint32_t few_cost(uint32_t H, uint32_t n_cus, uint32_t cols, uint32_t n_t
 inline uint32_t few_partial(uint64_t pairs, uint64_t F, uint64_t n_cus) { return uint32_t(pairs * 2 * F * 8 / n_cus); }
 
 // The few pairs' part of the plan p, which holds the general kernels' K splits, as many of them as fit `limit`: no sum is longer than
-// with those, and what is chosen fits as well (split: K splits of the first product are allowed, and then every choice goes by the buffer).
+// with those, and what is chosen fits as well.  split: K splits of the first product are allowed; the general rule's would be splits_any
+// in a buffer of any size.
 inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint64_t act, uint64_t pairs_act, bool split, bool halves_too,
-                     uint64_t limit) {
+                     uint32_t splits_any, uint64_t limit) {
     const uint64_t H = c.H, F = c.F, pairs = p.pairs_cap, n_cus = uint64_t(std::max(c.n_cus, 1));
     const uint64_t strips1 = (F + 127) / 128, strips2 = (H + 127) / 128;
     const uint64_t room = limit > p.off_y ? limit - p.off_y : 0;
@@ -108,14 +109,21 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
         // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
         // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
         const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
-        const uint64_t longest = chain(p.ksplit1, p.halves);
         const uint32_t partial = few_partial(pairs_act, F, n_cus);
-        uint32_t least = ~0u;
-        for (const bool halves : {false, true})
-            for (uint32_t k = 1; k <= kFewSplits && !(halves && !halves_too); ++k) {
-                const uint32_t cost = few_cost(uint32_t(H), uint32_t(n_cus), uint32_t(halves ? strips1 : (strips1 + 1) / 2), uint32_t(tiles), halves, partial, k);
-                if (chain(k, halves) <= longest && sums1(k) <= room && (halves ? cost + cost / 64 < least : cost < least)) { least = cost; p.ksplit1 = k; p.halves = halves; }
-            }
+        // (as short as in a buffer that holds all of the general rule's splits, if something that is fits)
+        for (const uint64_t longest : {chain(splits_any, p.halves), chain(p.ksplit1, p.halves)}) {
+            uint32_t least[2] = {~0u, ~0u}, best[2] = {0, 0};
+            for (uint32_t k = 1; k <= kFewSplits; ++k)
+                for (const bool halves : {false, true}) {
+                    if ((halves && !halves_too) || chain(k, halves) > longest || sums1(k) > room) continue;
+                    const uint32_t cost = few_cost(uint32_t(H), uint32_t(n_cus), uint32_t(halves ? strips1 : (strips1 + 1) / 2), uint32_t(tiles), halves, partial, k);
+                    if (cost < least[halves]) { least[halves] = cost; best[halves] = k; }
+                }
+            if (best[0] == 0 && best[1] == 0) continue;
+            p.halves = best[1] && (best[0] == 0 || least[1] + least[1] / 64 < least[0]);
+            p.ksplit1 = best[p.halves];
+            break;
+        }
     }
     // The second product in gemm2_few_kernel while its workgroups make one round and a wavefront's quarter of K is short.
     // Microseconds a call, gemm2_kernel / gemm2_few_kernel: 8 experts of H 1856 F 432, 7 tokens, top-8 (15 strips of 8 experts) 37.6 / 31.4,
@@ -124,22 +132,22 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
     // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
     // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
     const uint64_t wgs = strips2 * tiles, longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
-    const auto splits_in = [&](uint64_t free) {                     // 0: none of them
+    const auto splits_in = [&](uint64_t free, uint64_t most) {      // quarters of `most` rows, 0: there are none
         uint64_t least = ~0ull;
         uint32_t best = 0;
         for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 256 <= F && (split || k <= p.ksplit))); ++k) {
-            if (std::min(F, few_quarter(F, k)) > longest || sums2(k) > free) continue;
+            if (std::min(F, few_quarter(F, k)) > most || sums2(k) > free) continue;
             const uint64_t rounds = (wgs * k + n_cus - 1) / n_cus, cost = rounds * (few_quarter(F, k) + 96) + (k > 1 ? 32 * k : 0);
             if (cost < least) { least = cost; best = uint32_t(k); }
         }
         return best;
     };
     if (split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && 2 * wgs <= 3 * n_cus)
-        if (sums1(p.ksplit1) + sums2(p.ksplit) <= room) p.few_splits = splits_in(room - sums1(p.ksplit1));
+        if (sums1(p.ksplit1) + sums2(p.ksplit) <= room) p.few_splits = splits_in(room - sums1(p.ksplit1), longest);
     p.few_fused = p.few_splits != 0;
     if (!p.few_fused && wgs <= n_cus) {
-        p.few_splits = splits_in(std::max(room, sums2(p.ksplit)));  // (without room for those of gemm2_kernel there is no call)
-        if (few_quarter(F, std::max(1u, p.few_splits)) > (tiles <= 2 ? 1024u : 512u)) p.few_splits = 0;
+        const uint64_t free = std::max(room, sums2(p.ksplit));      // (without room for gemm2_kernel's splits there is no call)
+        if (few_quarter(F, splits_in(free, F)) <= (tiles <= 2 ? 1024u : 512u)) p.few_splits = splits_in(free, longest);
     }
 }
 
@@ -338,9 +346,10 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         return p.tail ? sums + kTailBytes : sums;
     };
     if (p.tail && end() > limit) p.tail = false;
+    const uint32_t splits_any = p.ksplit1;
     if (split)
         while (p.ksplit1 > chains && end() > limit) --p.ksplit1;
-    if (p.few) plan_few(p, c, T, K, act, pairs_act, split, p.m_tile == 128 && !forced, limit);
+    if (p.few) plan_few(p, c, T, K, act, pairs_act, split, p.m_tile == 128 && !forced, splits_any, limit);
     if (split) {
         if (chains > 1) {
             p.split_tiles = ~0u;
@@ -384,12 +393,13 @@ inline FfnPlan plan_ffn(const FfnShape& c, uint32_t T, uint32_t K, uint64_t limi
 // splits).  A call whose buffer has the room takes them all the same.
 inline uint64_t ffn_bytes(FfnShape c, uint32_t T, uint32_t K) {
     const FfnPlan p = plan_ffn_rules(c, T, K, 0, true, ~0ull);
-    uint64_t tiles = p.bytes - (p.tail ? kTailBytes : 0);
-    // few pairs: with part of the layer resident there are fewer row tiles and more splits
-    if (uint64_t(T) * K <= kFewPairs)
-        for (const uint64_t part : {2, 4, 8}) tiles = std::max(tiles, plan_ffn_rules(c, T, K, uint32_t(std::max<uint64_t>(1, c.E / part)), true, ~0ull).bytes);
+    const uint64_t tiles = p.bytes - (p.tail ? kTailBytes : 0);
     c.ragged = false;
-    const uint64_t strips = std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
+    uint64_t strips = std::max(plan_ffn_rules(c, T, K, 0, true, ~0ull).bytes, plan_ffn_rules(c, T, K, 0, false, ~0ull).bytes);
+    // few pairs: with part of the layer resident there are fewer row tiles and more splits, the most with some number between
+    // one and all of them (16 experts of H 2048 F 12728, 7 tokens, top-7: 4.5 MB with all, 21 with 6)
+    if (p.few)
+        for (uint32_t mapped = 1; mapped < c.E; ++mapped) strips = std::max(strips, plan_ffn_rules(c, T, K, mapped, true, ~0ull).bytes);
     return tiles <= strips + (64ull << 20) ? std::max(tiles + (p.tail ? kTailBytes : 0), strips) : strips;
 }
 

@@ -157,3 +157,14 @@ def test_short_buffers_keep_the_sums_short(few, monkeypatch):
     whole = few.plan(**calls[0])
     short = few.plan(**calls[0], limit=whole.bytes - 1)
     assert whole.few_splits == short.few_splits == 8 and short.ksplit1 < whole.ksplit1
+
+
+def test_the_query_covers_every_number_of_resident_experts(few, monkeypatch):
+    """A wave of any part of the layer takes the plan it would take without a limit in a buffer of the size asked for."""
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+    rng = random.Random(10)
+    calls = [(dict(E=16, H=2048, F=12728, T=7, K=7), 6), (dict(E=8, H=1952, F=10232, T=6, K=8), 7), (dict(E=8, H=4928, F=9552, T=1, K=2), 6)]
+    calls += [(c, rng.randrange(1, c["E"] + 1)) for c in (random_call(rng) for _ in range(3000))]
+    for c, mapped in calls:
+        best, p = few.plan(**c, mapped=mapped), few.plan(**c, mapped=mapped, limit=few.asked(c["E"], c["H"], c["F"], c["T"], c["K"]))
+        assert vars(p) == vars(best), (c, mapped)
