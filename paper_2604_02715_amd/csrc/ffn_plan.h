@@ -49,7 +49,7 @@ FLUXMOE_HD inline float tiled_cost(const SplitShape& s, uint32_t n_tiles, uint32
 
 struct FfnPlan {
     bool tiled, halves, g1_xcd;
-    // few: the first product's workgroups group the pairs.  few_splits: K splits of gemm2_few_kernel, 0: gemm2_kernel with ksplit.
+    // few: the first product's workgroups group the pairs.  few_splits: gemm2_few_kernel runs with as many K splits, which ksplit tells too.
     // few_fused: it also adds up the first product's partial sums, which then lie at off_part behind y
     bool few, few_fused;
     bool tail;                   // the last round of the second product may be split: its partial sums lie at off_tail behind y
@@ -335,10 +335,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     p.n_chunks = pairs > kRouteChunkThreshold ? uint32_t((pairs + kRouteChunkPairs - 1) / kRouteChunkPairs) : 0u;
     p.off_h = take(std::max<uint64_t>(uint64_t(p.pairs_cap) * F * 2, uint64_t(p.n_chunks) * E * 4));
     p.off_y = o;
+    uint32_t general2 = 0;
     // the partial sums of the first product are read before the second product writes its own in the same place
     auto end = [&]() {
         // (with room for gemm2_kernel's splits also where gemm2_few_kernel takes fewer: a buffer without it was never enough)
-        const uint64_t y = align_up(uint64_t(std::max(p.few_splits, p.ksplit)) * p.pairs_cap * H * 4, 256);
+        const uint64_t y = align_up(uint64_t(std::max(p.ksplit, general2)) * p.pairs_cap * H * 4, 256);
         const uint64_t part = p.ksplit1 > 1 ? align_up(uint64_t(p.ksplit1) * p.pairs_cap * 2 * F * 4, 256) : 0;
         p.off_part = p.few_fused ? p.off_y + y : p.off_y;
         const uint64_t sums = std::max(p.off_y + y, p.off_part + part);
@@ -349,7 +350,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     const uint32_t splits_any = p.ksplit1;
     if (split)
         while (p.ksplit1 > chains && end() > limit) --p.ksplit1;
-    if (p.few) plan_few(p, c, T, K, act, pairs_act, split, p.m_tile == 128 && !forced, splits_any, limit);
+    if (p.few) {
+        plan_few(p, c, T, K, act, pairs_act, split, p.m_tile == 128 && !forced, splits_any, limit);
+        general2 = p.ksplit;
+        if (p.few_splits) p.ksplit = p.few_splits;
+    }
     if (split) {
         if (chains > 1) {
             p.split_tiles = ~0u;

@@ -1082,7 +1082,6 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
     a.few = p.few;
     a.few_fused = p.few_fused;
     a.few2 = p.few_splits != 0;
-    if (a.few2) a.ksplit = p.few_splits;
     a.n_cus = uint32_t(std::max(c->n_cus, 1));
     a.tiled_waves = c->tune_tiled_waves;
     a.tiled_group = uint32_t(c->tune_tiled_group);

@@ -168,3 +168,21 @@ def test_the_query_covers_every_number_of_resident_experts(few, monkeypatch):
     for c, mapped in calls:
         best, p = few.plan(**c, mapped=mapped), few.plan(**c, mapped=mapped, limit=few.asked(c["E"], c["H"], c["F"], c["T"], c["K"]))
         assert vars(p) == vars(best), (c, mapped)
+
+
+def test_the_plan_report_tells_the_splits_that_run(few, monkeypatch):
+    from paper_2604_02715_amd import binding as B
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+    rng = random.Random(11)
+    other = 0
+    for c in [dict(E=512, H=2048, F=512, T=1, K=10)] + [random_call(rng) for _ in range(200)]:
+        ctx = B.fluxmoe_create(1, c["E"], c["H"], c["F"], c["E"])
+        try:
+            said = B.fluxmoe_ffn_plan(ctx, c["T"], c["K"])
+        finally:
+            B.fluxmoe_destroy(ctx)
+        p, g = few.plan(**c, mapped=c["E"]), few.general(**c, mapped=c["E"])
+        if p.few:
+            assert said == (128, p.few_splits or g.ksplit)
+            other += said[1] != g.ksplit
+    assert other > 20
