@@ -75,18 +75,18 @@ struct FfnShape {
 constexpr uint64_t kFewChunk = 32;
 inline uint64_t few_quarter(uint64_t F, uint64_t splits) { return align_up((align_up((F + splits - 1) / splits, kFewChunk) + 3) / 4, kFewChunk); }
 
-// First product of a call of few pairs with K split k ways, in k rows of a workgroup (about 32 ns each): rounds of one workgroup per
-// CU, each with a start-up of 128 rows; the launch that adds up the partial sums costs as much again and a split `partial` / 1024 rows.  A
-// large number where the rows do not make k splits of whole units.  cols: column workgroups, halves: the two pairs of wavefronts share the rows.
-constexpr uint32_t kFewSplits = 16;
-inline uint32_t few_cost(uint32_t H, uint32_t n_cus, uint32_t cols, uint32_t n_tiles, bool halves, uint32_t partial, uint32_t k) {
-    const uint32_t unit = halves ? 256u : 128u, k_per = ((H + k - 1) / k + unit - 1) / unit * unit;
-    if (k > 1 && (k * 256 > H || (H + k_per - 1) / k_per != k)) return 1u << 30;
-    const uint32_t rounds = (cols * n_tiles * k + n_cus - 1) / n_cus;
-    return rounds * ((k_per < H ? k_per : H) / (halves ? 2u : 1u) + 128u) + (k > 1 ? 128u + k * partial / 1024u : 0u);
+// First product in weight strips with K split k ways, in k rows of a workgroup (about 30 ns each when the memory system is not
+// saturated): rounds of one workgroup per CU, each with a start-up of 128 rows; the launch that adds up the partial sums costs as much again,
+// and their bytes, written and read, a row of a workgroup per KiB and CU.  kNoSplits where the rows do not make k splits of whole units.  cols:
+// column workgroups, halves: the two pairs of wavefronts share the rows.
+constexpr uint32_t kStripSplits = 16;
+constexpr uint64_t kNoSplits = ~0ull;
+inline uint64_t strip_cost(uint64_t H, uint64_t n_cus, uint64_t cols, uint64_t n_tiles, bool halves, uint64_t partial_bytes, uint64_t k) {
+    const uint64_t unit = halves ? 256 : 128, k_per = align_up((H + k - 1) / k, unit);      // the kernel splits at multiples of that
+    if (k > 1 && (k * 256 > H || (H + k_per - 1) / k_per != k)) return kNoSplits;
+    const uint64_t rounds = (cols * n_tiles * k + n_cus - 1) / n_cus;
+    return rounds * (std::min(k_per, H) / (halves ? 2 : 1) + 128) + (k > 1 ? 128 + k * partial_bytes / (n_cus * 1024) : 0);
 }
-
-inline uint32_t few_partial(uint64_t pairs, uint64_t F, uint64_t n_cus) { return uint32_t(pairs * 2 * F * 8 / n_cus); }
 
 // The few pairs' part of the plan p, which holds the general kernels' K splits, as many of them as fit `limit`: no sum is longer than
 // with those, and what is chosen fits as well.  split: K splits of the first product are allowed; the general rule's would be splits_any
@@ -109,14 +109,14 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
         // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
         // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
         const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
-        const uint32_t partial = few_partial(pairs_act, F, n_cus);
         // (as short as in a buffer that holds all of the general rule's splits, if something that is fits)
         for (const uint64_t longest : {chain(splits_any, p.halves), chain(p.ksplit1, p.halves)}) {
-            uint32_t least[2] = {~0u, ~0u}, best[2] = {0, 0};
-            for (uint32_t k = 1; k <= kFewSplits; ++k)
+            uint64_t least[2] = {kNoSplits, kNoSplits};
+            uint32_t best[2] = {0, 0};
+            for (uint32_t k = 1; k <= kStripSplits; ++k)
                 for (const bool halves : {false, true}) {
                     if ((halves && !halves_too) || chain(k, halves) > longest || sums1(k) > room) continue;
-                    const uint32_t cost = few_cost(uint32_t(H), uint32_t(n_cus), uint32_t(halves ? strips1 : (strips1 + 1) / 2), uint32_t(tiles), halves, partial, k);
+                    const uint64_t cost = strip_cost(H, n_cus, halves ? strips1 : (strips1 + 1) / 2, tiles, halves, pairs_act * 2 * F * 8, k);
                     if (cost < least[halves]) { least[halves] = cost; best[halves] = k; }
                 }
             if (best[0] == 0 && best[1] == 0) continue;
@@ -293,16 +293,11 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
         const uint64_t partial_bytes = pairs_act * 2 * F * 8;             // written and read, per split
         uint64_t best = ~0ull;
         if (!p.tiled) {
-            // units of k rows of a workgroup (about 30 ns each when the memory system is not saturated)
             const uint64_t strips1 = (F + 127) / 128, tiles1 = std::max<uint64_t>(pairs_act / p.m_tile, groups_act);
             auto consider = [&](bool halves) {
-                const uint64_t wgs1 = (halves ? strips1 : (strips1 + 1) / 2) * tiles1, unit = halves ? 256 : 128;
-                for (uint64_t k = 1; k <= 16 && (k == 1 || k * 256 <= H); ++k) {
-                    const uint64_t k_per = align_up((H + k - 1) / k, unit);    // the kernel splits at multiples of that
-                    if ((H + k_per - 1) / k_per != k) continue;
-                    const uint64_t rounds = (wgs1 * k + n_cus - 1) / n_cus;
-                    const uint64_t cost = rounds * (std::min(k_per, H) / (halves ? 2 : 1) + 128) + (k > 1 ? 128 + k * partial_bytes / (n_cus * 1024) : 0);
-                    if (cost < best) { best = cost; p.ksplit1 = uint32_t(k); p.halves = halves; }
+                for (uint32_t k = 1; k <= kStripSplits; ++k) {
+                    const uint64_t cost = strip_cost(H, n_cus, halves ? strips1 : (strips1 + 1) / 2, tiles1, halves, partial_bytes, k);
+                    if (cost < best) { best = cost; p.ksplit1 = k; p.halves = halves; }
                 }
             };
             consider(false);
