@@ -2317,14 +2317,9 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // one per XCD).  Sets the launch's fields in `a`.
         const uint64_t pairs_all = uint64_t(a.T) * a.K;
         const uint64_t avg_rows = pairs_all / std::max<uint64_t>(1, std::min<uint64_t>(a.E, pairs_all));
-        // Experts of about one row tile share no weights between their tiles, and what is left to share are the activations: with few
-        // column tiles an XCD's 32 tiles are taken row by row, so that a row's columns run together (12 column tiles in super-tiles of 8 x 4
-        // fetched every row of activations three times) and no place stays empty.  Microseconds a call, super-tiles / rows: 160 experts
-        // of H 5120 F 1536, 205 rows each 2032 / 1992, 300 rows 3599 / 3491, 80 of them, popularity by rank, 137 rows 1046 / 1021; 20 of them, 1392 rows
-        // 1369 / 1392; 8 of H 4096 F 3584 (28 column tiles), 412 rows 336 / 337, of F 14336 (112), 543 rows 1687 / 1767.
         bool in_rows = false;                                       // of the launch that d2l_all was asked for last
         auto d2l_all = [&](uint32_t n_ct, uint32_t n_split, bool grouped, bool walk) {
-            in_rows = walk && !ragged && n_ct <= 24 && avg_rows <= 384;
+            in_rows = walk && !ragged && tiles_by_rows(n_ct, avg_rows, grouped ? args.tiled_group : 0u);
             if (in_rows) {
                 a.tiled_sn_log2 = 3;
                 a.tiled_group = 1;

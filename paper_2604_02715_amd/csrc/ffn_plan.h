@@ -426,6 +426,15 @@ inline bool weights_stream(uint64_t E, uint64_t H, uint64_t F, uint64_t pairs, u
     return E <= 64 && E * H * F * 6 > (128ull << 20) && pairs <= m_tile * std::min(E, pairs);
 }
 
+// Whether a walking launch of 256 x 256 tiles with n_ct column tiles takes them row by row and not in super-tiles.  group: super-rows
+// in a group of super-tiles that were asked for, 0 for none.
+// Experts of about one row tile share no weights between their tiles, and what is left to share are the activations: with few
+// column tiles an XCD's 32 tiles are taken row by row, so that a row's columns run together (12 column tiles in super-tiles of 8 x 4
+// fetched every row of activations three times) and no place stays empty.  Microseconds a call, super-tiles / rows: 160 experts
+// of H 5120 F 1536, 205 rows each 2032 / 1992, 300 rows 3599 / 3491, 80 of them, popularity by rank, 137 rows 1046 / 1021; 20 of them, 1392 rows
+// 1369 / 1392; 8 of H 4096 F 3584 (28 column tiles), 412 rows 336 / 337, of F 14336 (112), 543 rows 1687 / 1767.
+inline bool tiles_by_rows(uint64_t n_ct, uint64_t avg_rows, uint32_t group) { return group == 0 && n_ct <= 24 && avg_rows <= 384; }
+
 // One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.
 struct RingProduct {
     uint32_t rows, splits;

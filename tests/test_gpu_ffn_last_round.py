@@ -1,5 +1,8 @@
 """GPU parity of a second product whose last round of 256 x 256 tiles is split over K: super-tiles of 4 x 8 tiles left over by the 8 XCDs,
 from one (eight parts) to five (whole), K of whole steps and not, a buffer without room for the parts, against torch in 64 bits."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -8,7 +11,7 @@ from paper_2604_02715_amd import binding as B
 from paper_2604_02715_amd import harness, inputs
 from test_gpu_ffn import TOL
 
-pytestmark = pytest.mark.gpu
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_02715_amd", "csrc")
 
 
 def reference(x, w13, w2):
@@ -16,33 +19,53 @@ def reference(x, w13, w2):
     return (g / (1.0 + torch.exp(-g)) * u).to(torch.bfloat16).double() @ w2.double()
 
 
-@pytest.mark.parametrize("row_tiles,hidden,ffn,rows_last", [
-    (33, 2048, 2112, 1),             # one super-tile left, eight parts; its row tile has a single row
-    (38, 2048, 2112, 100),           # two: four parts
-    (41, 2048, 2120, 256),           # three: two parts, a partial step
-    (48, 2048, 2112, 77),            # four: two parts
-    (52, 2048, 2112, 256),           # five: whole
-    (34, 2112, 2112, 256),           # two column blocks, the second with one tile of 64 columns: 18 super-tiles
-])
-def test_last_round(row_tiles, hidden, ffn, rows_last):
-    """Two experts, the first with whole row tiles and the second with the rest, a token to one of them."""
-    first = 256 * (row_tiles // 2)
+CASES = [
+    (2, 33, 2048, 2112, 1),          # one super-tile left, eight parts; its row tile has a single row
+    (2, 38, 2048, 2112, 100),        # two: four parts
+    (2, 41, 2048, 2120, 256),        # three: two parts, a partial step
+    (2, 48, 2048, 2112, 77),         # four: two parts
+    (2, 52, 2048, 2112, 256),        # five: whole
+    (2, 34, 2112, 2112, 256),        # two column blocks, the second with one tile of 64 columns: 18 super-tiles
+    (41, 41, 2048, 2112, 30),        # a row tile an expert and 1 GB of weights: they pass the caches by
+]
+
+
+@pytest.mark.parametrize("experts,row_tiles,hidden,ffn,rows_last", CASES)
+def test_the_plan_splits_the_last_round(experts, row_tiles, hidden, ffn, rows_last, tmp_path):
     T = 256 * (row_tiles - 1) + rows_last
-    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=2, n_slots=2, top_k=1, tokens=T, hidden=hidden, ffn=ffn)
+    (tmp_path / "m.cpp").write_text("""
+#include "ffn_plan.h"
+int main() {
+    const fluxmoe::FfnShape c{%d, %d, %d, 256, 2, true};
+    const fluxmoe::FfnPlan p = fluxmoe::plan_ffn(c, %d, 1, fluxmoe::ffn_bytes(c, %d, 1), %d);
+    return p.tail && p.m_tile == 256 && fluxmoe::weights_stream(c.E, c.H, c.F, %d, 256) == (c.E > 2) ? 0 : 1;
+}
+""" % (experts, hidden, ffn, T, T, experts, T))
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    subprocess.run([str(tmp_path / "m")], check=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("experts,row_tiles,hidden,ffn,rows_last", CASES)
+def test_last_round(experts, row_tiles, hidden, ffn, rows_last):
+    """The experts with whole row tiles but for the last, which has the rest; a token to one of them."""
+    each = 256 * (row_tiles // experts)
+    T = 256 * (row_tiles - 1) + rows_last
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=experts, n_slots=experts, top_k=1, tokens=T, hidden=hidden, ffn=ffn)
     pool = harness.ExpertPool(cfg)
     try:
         gen = torch.Generator(device="cuda").manual_seed(row_tiles)
         draw = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
         x = draw(T, hidden).bfloat16()
-        w = [((0.02 * draw(2, hidden, ffn)).bfloat16(), (0.02 * draw(ffn, hidden)).bfloat16()) for _ in range(2)]
+        w = [((0.02 * draw(2, hidden, ffn)).bfloat16(), (0.02 * draw(ffn, hidden)).bfloat16()) for _ in range(experts)]
         for e, (w13, w2) in enumerate(w):
             pool.slot13(e).copy_(w13.view(torch.int16).reshape(-1))
             pool.slot2(e).copy_(w2.view(torch.int16).reshape(-1))
-        pool.page_table.copy_(torch.tensor([[0, 1]], dtype=torch.int32))
-        who = np.where(np.random.default_rng(row_tiles).permutation(T) < first, 0, 1).astype(np.int32)
+        pool.page_table.copy_(torch.arange(experts, dtype=torch.int32)[None])
+        who = np.minimum(np.random.default_rng(row_tiles).permutation(T) // each, experts - 1).astype(np.int32)
         ids, gates = torch.from_numpy(who[:, None]).cuda(), torch.rand(T, 1, generator=gen, device="cuda") + 0.5
         want = torch.empty(T, hidden, dtype=torch.float64, device="cuda")
-        for e in range(2):
+        for e in range(experts):
             t = torch.from_numpy(np.flatnonzero(who == e)).cuda()
             want[t] = gates[t].double() * reference(x[t], *w[e])
         room = pool.ws_bytes - int(pool.sizes.pool_workspace_bytes)
