@@ -125,30 +125,31 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
             break;
         }
     }
-    // The second product in gemm2_few_kernel while its workgroups make one round and a wavefront's quarter of K is short.
-    // Microseconds a call, gemm2_kernel / gemm2_few_kernel: 8 experts of H 1856 F 432, 7 tokens, top-8 (15 strips of 8 experts) 37.6 / 31.4,
-    // 46 of H 488 F 416 34.0 / 27.6, one of H 4096 F 14336, one token (quarters of 448 k) 84 / 67; but 160 of H 5120 F 384, 2 tokens, top-8
-    // (640 workgroups) 42.4 / 45.6, 64 of H 2048 F 512 (1024) 71 / 76, 4 of H 4096 F 14336, 8 tokens (quarters of 1792 k) 215 / 230.
-    // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
-    // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
+    // The second product in gemm2_few_kernel while its workgroups make one round, a wavefront's quarter of K is short and no longer than the sums
+    // of gemm2_kernel, which is the faster one past either line.  Microseconds a call, gemm2_kernel / gemm2_few_kernel: 8 experts of H 2232,
+    // 9 tokens, top-5 (144 workgroups), F 432 39.9 / 32.1, 864 (quarters of 224 k; gemm2_kernel sums 288) 41.0 / 38.8, 1024 (256; 256)
+    // 39.7 / 39.5, but 1280 (320; 256) 42.3 / 43.4, 1728 (448; 288) 50.1 / 51.8; with three splits, 432 workgroups, the last two 45.2 and
+    // 52.6; 160 of H 5120 F 384, 2 tokens, top-8 (640 workgroups) 42.4 / 45.6.  4 of H 4752 F 1680, 4 rows of each (quarters of 448 k against 288 k) 51.3 / 54.0, 15 rows 58.1 / 65.8.  One of H 4096 F 14336, one token
+    // (256 workgroups, 448 k) 83 / 66, two (896 k) 122 / 119, but four (1792 k) 218 / 220.
     const uint64_t wgs = strips2 * tiles, longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
-    const auto splits_in = [&](uint64_t free, uint64_t most) {      // quarters of `most` rows, 0: there are none
+    const auto splits_in = [&](uint64_t free, uint64_t most_wgs, uint64_t most_rows) {      // 0: there are none
         uint64_t least = ~0ull;
         uint32_t best = 0;
         for (uint64_t k = 1; k <= 8 && (k == 1 || (k * 256 <= F && (split || k <= p.ksplit))); ++k) {
-            if (std::min(F, few_quarter(F, k)) > most || sums2(k) > free) continue;
-            const uint64_t rounds = (wgs * k + n_cus - 1) / n_cus, cost = rounds * (few_quarter(F, k) + 96) + (k > 1 ? 32 * k : 0);
+            const uint64_t rows = few_quarter(F, k);
+            if (std::min(F, rows) > longest || rows > most_rows || wgs * k > most_wgs || sums2(k) > free) continue;
+            const uint64_t rounds = (wgs * k + n_cus - 1) / n_cus, cost = rounds * (rows + 96) + (k > 1 ? 32 * k : 0);
             if (cost < least) { least = cost; best = uint32_t(k); }
         }
         return best;
     };
-    if (split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && 2 * wgs <= 3 * n_cus)
-        if (sums1(p.ksplit1) + sums2(p.ksplit) <= room) p.few_splits = splits_in(room - sums1(p.ksplit1), longest);
+    // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
+    // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
+    if (split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && sums1(p.ksplit1) + sums2(p.ksplit) <= room)
+        p.few_splits = splits_in(room - sums1(p.ksplit1), 3 * n_cus / 2, 128);
     p.few_fused = p.few_splits != 0;
-    if (!p.few_fused && wgs <= n_cus) {
-        const uint64_t free = std::max(room, sums2(p.ksplit));      // (without room for gemm2_kernel's splits there is no call)
-        if (few_quarter(F, splits_in(free, F)) <= (tiles <= 2 ? 1024u : 512u)) p.few_splits = splits_in(free, longest);
-    }
+    // (without room for gemm2_kernel's splits there is no call)
+    if (!p.few_fused) p.few_splits = splits_in(std::max(room, sums2(p.ksplit)), n_cus, tiles <= 2 ? 1024 : 512);
 }
 
 // split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.

@@ -102,6 +102,9 @@ def test_both_sides_of_the_lines(few):
     assert of(T=1, K=1, E=8, H=4096, F=14336).few_splits == 8                # 32 strips of one
     assert of(T=1, K=8, E=8, H=4096, F=14336).few_splits == 0                # quarters of 3584 k
     assert of(T=7, K=10, E=512, H=2048, F=512).few == 0                      # 70 pairs
+    five = dict(T=9, K=5, E=8, H=2232)                                       # 144 workgroups, no second round of them
+    assert [of(F=F, **five).few_splits for F in (432, 864, 1024, 1280, 1728, 2048)] == [1, 1, 1, 0, 0, 0]
+    assert of(T=59, K=1, E=4, H=4752, F=1680).few_splits == 0 and of(T=11, K=4, E=4, H=4768, F=3736).few_splits == 0
 
 
 def test_more_experts_a_token_than_the_layer_has(tmp_path):
