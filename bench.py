@@ -262,7 +262,7 @@ def access_pattern_probe(n_blocks, out_bytes_per_block, reps=5):
     from paper_2604_02715_amd import binding as B
     small = max(128, int(round((out_bytes_per_block - 48) / 128.0)) * 128)   # three blocks of eight write 128 more
     waves = int(os.environ.get("FLUXMOE_DECODE_WAVES", "8"))
-    per_wave = int(os.environ.get("FLUXMOE_DECODE_BLOCKS_PER_WAVE", "1" if n_blocks <= 256 * 256 else "3"))
+    per_wave = int(os.environ.get("FLUXMOE_DECODE_BLOCKS_PER_WAVE", "1" if n_blocks <= 1536 * 256 else "3"))
     if n_blocks < 1 or waves not in (4, 8, 16) or not 1 <= per_wave <= 1024:
         return None
     src = torch.empty(n_blocks * 4096, dtype=torch.uint8, device="cuda").random_(0, 256)

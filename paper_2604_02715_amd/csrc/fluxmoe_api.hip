@@ -17,6 +17,7 @@
 #include <new>
 
 #include "crew.h"
+#include "decode_plan.h"
 #include "encode_core.h"
 #include "fluxmoe_internal.h"
 
@@ -908,22 +909,14 @@ static int materialize_enqueue(fluxmoe_ctx* c, uint32_t layer, const int32_t* ex
     for (const DenseCopy& dc : dense_copies)
         HIPCHECK(hipMemcpyAsync(dc.dst, dc.src, dc.bytes, hipMemcpyDeviceToDevice, stream));
     const uint64_t total = uint64_t(cmd->total_blocks[0]) + cmd->total_blocks[1];
-    // Up to 256 blocks per CU a wavefront takes one block: a workgroup's life is then as short as it can be, and that is what a launch's ramp-up
-    // and its end cost (up to three blocks / one, microseconds a call: 20 experts of 6 MB 44.7 / 40.6, 40 of them 81.8 / 75.8, 4 of 47 MB 62.7 / 57.5).
-    // Beyond, three: 60 of 47 MB 854 / 862, 8 of 352 MB 830 / 832.  Workgroups of four wavefronts with one block are faster alone (8 of 352 MB
-    // 811), but not before or beside an FFN (the same load with its FFN in turn 1.317 / 1.317 / 1.331 ms a step; a pass with waves of 35000 blocks
-    // 2042 / 2025 / 2062).
     const int waves_per_wg = c->tune_waves;
-    const int blocks_per_wave = c->tune_blocks_per_wave ? c->tune_blocks_per_wave : total <= 256ull * uint64_t(std::max(c->n_cus, 1)) ? 1 : 3;
     if (total == 0) {
         // every listed tensor is an uncompressed host tensor: nothing to decode, only the page table changes
         load_done = nullptr;
         if (!touched.empty())
             HIPCHECK(launch_apply_updates(page_table, dcmd + upd_off, uint32_t(touched.size()), stream, nullptr));
     } else {
-    // blocks per workgroup: one per wavefront, or as many as asked for, fewer when that would leave CUs without work
-    const uint64_t fill = total / (3ull * uint64_t(std::max(c->n_cus, 1)));
-    const uint64_t per_wg = std::max<uint64_t>(waves_per_wg, std::min<uint64_t>(uint64_t(waves_per_wg) * blocks_per_wave, fill));
+    const uint64_t per_wg = decode_per_workgroup(total, uint64_t(std::max(c->n_cus, 1)), uint64_t(waves_per_wg), uint64_t(c->tune_blocks_per_wave));
     auto wgs_for = [&](uint64_t blocks) { return uint32_t(std::min<uint64_t>((blocks + per_wg - 1) / per_wg, 1u << 20)); };
     if (two_streams && cmd->total_blocks[0] && cmd->total_blocks[1]) {
         // one launch per tensor type: the type-2 list on the second stream (after everything this call has
