@@ -143,10 +143,14 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
         }
         return best;
     };
-    // Fused up to a round and a half, where a quarter is at most 128 k: one token's top-10 of 512 of H 2048 F 512 26.0 / 24.3, three tokens,
-    // top-8 (F 256, 384 workgroups) 27.2 / 26.3; 16 tokens' rows or quarters of 384 k cost more than the launch (48.6 / 50.9).
-    if (split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= 128 && sums1(p.ksplit1) + sums2(p.ksplit) <= room)
-        p.few_splits = splits_in(room - sums1(p.ksplit1), 3 * n_cus / 2, 128);
+    // Fused where a quarter is at most 256 k in one round, 128 in a round and a half.  Microseconds a call, apart / fused: one token's top-10
+    // of 512 of H 2048 F 512 26.0 / 24.3, of 64 of H 2048 F 640 28.6 / 27.4, F 1024 35.7 / 34.9, top-4 of H 4096 F 640 27.7 / 28.0, F 1024
+    // 32.8 / 29.1, top-6 of H 5120 F 768 37.2 / 37.4, 4 tokens, top-4 of H 512 F 1024 20.8 / 20.9; three tokens, top-8 (F 256, 384
+    // workgroups) 27.2 / 26.3; but one token's top-8 of H 5120 (320 workgroups) F 768 43.5 / 45.3; 16 tokens' rows cost more than the launch
+    // (48.6 / 50.9).
+    const bool one_round = wgs <= n_cus;
+    if (split && p.ksplit1 > 1 && T <= 4 && few_quarter(F, 1) <= (one_round ? 256 : 128) && sums1(p.ksplit1) + sums2(p.ksplit) <= room)
+        p.few_splits = splits_in(room - sums1(p.ksplit1), one_round ? n_cus : 3 * n_cus / 2, 256);
     p.few_fused = p.few_splits != 0;
     // (without room for gemm2_kernel's splits there is no call)
     if (!p.few_fused) p.few_splits = splits_in(std::max(room, sums2(p.ksplit)), n_cus, tiles <= 2 ? 1024 : 512);
@@ -432,8 +436,11 @@ inline bool weights_stream(uint64_t E, uint64_t H, uint64_t F, uint64_t pairs, u
 // Experts of about one row tile share no weights between their tiles, and what is left to share are the activations: with few
 // column tiles an XCD's 32 tiles are taken row by row, so that a row's columns run together (12 column tiles in super-tiles of 8 x 4
 // fetched every row of activations three times) and no place stays empty.  Microseconds a call, super-tiles / rows: 160 experts
-// of H 5120 F 1536, 205 rows each 2032 / 1992, 300 rows 3599 / 3491, 80 of them, popularity by rank, 137 rows 1046 / 1021; 20 of them, 1392 rows
-// 1369 / 1392; 8 of H 4096 F 3584 (28 column tiles), 412 rows 336 / 337, of F 14336 (112), 543 rows 1687 / 1767.
+// of H 5120 F 1536, 205 rows each 2032 / 1992, 300 rows 3599 / 3491, 80 of them, popularity by rank, 137 rows 1046 / 1021; one to eight
+// column tiles are the same order, or nearly: 512 of H 2048 F 512, 200 rows 1071 / 1067, 256 of them, 300 rows 1005 / 1011.  More rows:
+// 400 to 450 of them still gain (160 of H 5120 F 1536, 450 rows 4069 / 3853), 512 do not (4536 / 4541; 31 of H 2048 F 5120 1104 / 1123), 20
+// experts with 1392 rows 1369 / 1392.  More columns, up to 384 rows: what even routing gains (40 of H 2048 F 3200, 205 rows 458 / 435, 31 of F 5120
+// 502 / 502, 22 of F 7168 543 / 512), popularity by rank loses (64 of F 4096, 187 rows 967 / 991, 8 of H 4096 F 3584, 300 rows 310 / 326).
 inline bool tiles_by_rows(uint64_t n_ct, uint64_t avg_rows, uint32_t group) { return group == 0 && n_ct <= 24 && avg_rows <= 384; }
 
 // One product of the shared expert in gemm_ring_kernel: rows of a tile and K splits with the least estimated time.

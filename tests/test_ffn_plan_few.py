@@ -84,7 +84,7 @@ def test_random_calls_at_any_buffer_size(few, monkeypatch):
             assert p.off_part == p.off_y or (p.few_fused and p.off_part >= p.off_y + y)
             assert p.ksplit1 <= max(1, H // 64)
             if p.few_fused:
-                assert p.few_splits and p.ksplit1 > 1 and T <= 4 and few.quarter(F, p.few_splits) <= 128
+                assert p.few_splits and p.ksplit1 > 1 and T <= 4 and few.quarter(F, p.few_splits) <= 256
             if p.few_splits > 1:
                 assert (p.few_splits - 1) * 256 < F
             seen["fused" if p.few_fused else "split" if p.few_splits > 1 else "few" if p.few_splits else "old"] += 1
@@ -96,7 +96,9 @@ def test_random_calls_at_any_buffer_size(few, monkeypatch):
 def test_both_sides_of_the_lines(few):
     of = lambda **kw: few.plan(**kw)
     token = dict(K=10, E=512, H=2048, F=512)
-    assert of(T=1, **token).few_fused and of(T=1, **dict(token, F=520)).few_splits == 1 and not of(T=1, **dict(token, F=520)).few_fused
+    assert of(T=1, **token).few_fused and of(T=1, **dict(token, F=1024)).few_fused and not of(T=1, **dict(token, F=1032)).few_fused
+    wide = dict(T=1, K=8, E=160, H=5120)                                     # 320 workgroups
+    assert of(F=512, **wide).few_fused and not of(F=520, **wide).few_fused
     assert of(T=4, K=2, E=64, H=2048, F=512).few_fused and not of(T=5, K=2, E=64, H=2048, F=512).few_fused
     assert of(T=6, K=10, E=512, H=2048, F=512).few_splits == 0               # 16 strips of about 57 experts
     assert of(T=1, K=1, E=8, H=4096, F=14336).few_splits == 8                # 32 strips of one

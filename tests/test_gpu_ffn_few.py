@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     (dict(tokens=1, top_k=2, hidden=1032, ffn=136), "fused"),                   # a strip of 8 columns, wavefronts of 64, 64, 8 and no k
     (dict(tokens=4, top_k=2, hidden=1024, ffn=512), "fused"),                   # the most tokens and the longest quarters, no tail
     (dict(tokens=3, top_k=3, hidden=2056, ffn=504), "fused"),                   # a tail in the last quarter, eight splits
+    (dict(tokens=4, top_k=4, n_experts=16, n_slots=16, hidden=2048, ffn=1016), "fused"),     # quarters of 256 k, the last of them short
+    (dict(tokens=1, top_k=8, n_experts=16, n_slots=16, hidden=3080, ffn=776), "fused"),      # of 224 k, a strip of 8 columns
     (dict(tokens=5, top_k=3, hidden=520, ffn=72), "few"),                       # h from the first product
     (dict(tokens=20, top_k=3, hidden=136, ffn=264), "few"),                     # tiles of more and of fewer than 16 rows
     (dict(tokens=2, top_k=1, hidden=1024, ffn=2056), "split"),                  # K splits, the last of them short
