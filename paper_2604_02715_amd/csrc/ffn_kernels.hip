@@ -286,6 +286,57 @@ __global__ __launch_bounds__(1024) void route_sort_kernel(FfnArgs a) {
     for (uint32_t p = tid + 1024u * kKept; p < pairs; p += 1024) place(p, classify(a.topk_ids[p], false));
 }
 
+// The rows of an expert in the order of their pairs, for a split last round.  Grouping puts them where its atomics happen to arrive, and no result
+// depends on that while every tile sums alike; where some of an expert's tiles are summed in parts, a row's tile decides the order of
+// its sum.  Rows that share one tile stay as they are.  A workgroup per expert, a stretch of the pairs to each wavefront: bound by its launch and one
+// trip to memory, on which the first 512 pairs of a stretch and the expert's place go together; what they were found to be is kept.  8192 pairs of 8 experts
+// 4.4 us; the call without / with it 2645 / 2648 us (2671 / 2681 where the pairs were read twice and after the expert's place).
+__global__ __launch_bounds__(1024) void route_order_kernel(FfnArgs a) {
+    __shared__ uint32_t found[16];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, pairs = a.T * a.K;
+    const int32_t e = int32_t(blockIdx.x);
+    const uint32_t stretch = (pairs + 1023) / 1024 * 64, first = min(pairs, wave * stretch), last = min(pairs, first + stretch);
+    auto look = [&](uint32_t base, uint64_t (&mine)[8]) __attribute__((always_inline)) {
+        int32_t id[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) id[i] = a.topk_ids[min(base + 64 * i + lane, pairs - 1)];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) mine[i] = __ballot(base + 64 * i + lane < last && id[i] == e);
+    };
+    uint64_t kept[8], more[8];
+    look(first, kept);
+    const uint32_t rows = uint32_t(a.expert_count[e]), row0 = uint32_t(a.expert_offset[e]);
+    if (rows <= a.m_tile) return;                            // uniform
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 8; ++i) n += uint32_t(__popcll(kept[i]));
+    for (uint32_t base = first + 512; base < last; base += 512) {
+        look(base, more);
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) n += uint32_t(__popcll(more[i]));
+    }
+    if (lane == 0) found[wave] = n;
+    __syncthreads();
+    uint32_t at = row0;
+    for (uint32_t w = 0; w < wave; ++w) at += found[w];
+    auto place = [&](uint32_t base, const uint64_t (&mine)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) {
+            const uint32_t p = base + 64 * i + lane, pos = at + uint32_t(__popcll(mine[i] & ((1ull << lane) - 1)));
+            if (((mine[i] >> lane) & 1) && pos < row0 + rows) {
+                a.sorted_pair[pos] = int32_t(p);
+                a.pair_pos[p] = int32_t(pos);
+            }
+            at += uint32_t(__popcll(mine[i]));
+        }
+    };
+    place(first, kept);
+    for (uint32_t base = first + 512; base < last; base += 512) {
+        look(base, more);
+        place(base, more);
+    }
+}
+
 // The shared expert: every token once, in order, on the one expert in slot 0.  What route_sort_kernel would find out
 // from T identical ids is known, so the lists are written by as many workgroups
 // as they need and nothing is counted (gemm_ring_kernel needs none).
@@ -2181,6 +2232,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     if (routes_itself && (a.identity || a.tiled || a.m_tile < kRoutedPairs || uint64_t(a.T) * a.K > kRoutedPairs)) return hipErrorInvalidValue;
     const hipEvent_t with_routing = attach_routed ? routed : nullptr;
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
+    // (F > 2048: the second product does not walk)
+    if (a.identity || !a.tiled || a.m_tile != 256 || a.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048) a.tail = nullptr;
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
     const bool grouping = a.identity ? !a.ring1 : !routes_itself;
@@ -2196,6 +2249,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     } else {
         launch_done(chooses ? route_sort_kernel<false, true> : route_sort_kernel<false, false>, dim3(1), dim3(1024), sh, stream, with_routing, a);
     }
+    if (a.tail) hipLaunchKernelGGL(route_order_kernel, dim3(a.E), dim3(1024), 0, stream, a);
     if (grouping) {
         mark(1, 0);
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
@@ -2371,7 +2425,6 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // the record at the end of a tile covers them.  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
         // 1137 / 1104, 20 of H 5120 F 1536, 1638 rows 1642 / 1615, 160 of those 512 rows 4637 / 4581, 205 rows 2127 / 2126.
         const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
-        if (walk2 || !d2l || d2l4 || small || a.ksplit != 1 || a.identity) a.tail = nullptr;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<2, 8, true, 256, true, false, true> : gemm_d2l_kernel<2, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }

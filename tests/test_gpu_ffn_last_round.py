@@ -87,3 +87,43 @@ def test_last_round(experts, row_tiles, hidden, ffn, rows_last):
         assert torch.equal(outs[0], outs[1]) == (row_tiles == 52)            # parts end a sum elsewhere
     finally:
         pool.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("experts,row_tiles,rows_last,top_k", [
+    (2, 38, 100, 1),                 # a token's rows change between whole tiles and those in four parts within the second expert
+    (2, 66, 100, 1),                 # 16740 pairs: grouped in chunks
+    (5, 42, 100, 2),                 # several experts' last tiles in the last round, two rows a token
+])
+def test_the_same_bits_on_every_call(experts, row_tiles, rows_last, top_k):
+    hidden, ffn = 2048, 2112
+    T = (256 * (row_tiles - 1) + rows_last) // top_k
+    cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=experts, n_slots=experts, top_k=top_k, tokens=T, hidden=hidden, ffn=ffn)
+    pool = harness.ExpertPool(cfg)
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(row_tiles)
+        draw = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
+        x = draw(T, hidden).bfloat16()
+        w = [((0.02 * draw(2, hidden, ffn)).bfloat16(), (0.02 * draw(ffn, hidden)).bfloat16()) for _ in range(experts)]
+        for e, (w13, w2) in enumerate(w):
+            pool.slot13(e).copy_(w13.view(torch.int16).reshape(-1))
+            pool.slot2(e).copy_(w2.view(torch.int16).reshape(-1))
+        pool.page_table.copy_(torch.arange(experts, dtype=torch.int32)[None])
+        ids = draw(T, experts).topk(top_k).indices.int().contiguous()
+        gates = torch.rand(T, top_k, generator=gen, device="cuda") + 0.5
+        want = torch.zeros(T, hidden, dtype=torch.float64, device="cuda")
+        for e in range(experts):
+            t, k = (ids == e).nonzero(as_tuple=True)
+            want[t] += gates[t, k, None].double() * reference(x[t], *w[e])
+        first = None
+        for call in range(8):
+            out = torch.full((T, hidden), 7.0, device="cuda")
+            pool.expert_ffn(0, x, ids, gates, out)
+            torch.cuda.synchronize()
+            if first is None:
+                first = out
+                assert pool.device_errors() == 0
+                assert float(((out.double() - want).norm(dim=1) / want.norm(dim=1)).max()) <= 10 * TOL
+            assert torch.equal(out, first), f"call {call}"
+    finally:
+        pool.close()
