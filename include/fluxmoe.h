@@ -510,7 +510,7 @@ int fluxmoe_mfma_probe(const void* operands, float* out, uint32_t n_workgroups, 
  *   kind 0 decode + paged scatter, 1 token grouping, 2 gate/up product + SwiGLU (with the sum of its
  *   K splits where it has them), 3 down product, 4 gated combine.
  * On the weight-streaming kernels a call of up to 64 pairs groups them inside kind 2 and has no launch
- * of kind 1.
+ * of kind 1; with few tokens and short ffn it also adds up the gate/up product's K splits inside kind 3.
  * on: 0 = off, 1 = every kind, FLUXMOE_PROFILE_ONLY(mask) = only the kinds whose bit is set in
  * mask (an event between two kernels costs a few microseconds of idle device time; a benchmark
  * that times whole steps brackets only the kernel it reports).

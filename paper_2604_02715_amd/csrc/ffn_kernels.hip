@@ -1616,6 +1616,7 @@ __global__ __launch_bounds__(256) void last_round_kernel(FfnArgs a) {
 // ROWS: the tiles are taken row by row and not in super-tiles.
 template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false, bool RAGGED = false, bool ROWS = false>
 __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kernel(FfnArgs a) {
+    constexpr bool kLastRound = MODE == 2 && !WALK && WAVES == 8 && TILE == 256;      // the last round may be split
     constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
     static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
     // WAVES = 8: wavefronts 4 (rows) x 2 (columns), 64 x 128 each, two per SIMD.  WAVES = 4: 2 x 2,
@@ -1659,7 +1660,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // all numbers), so all of them lie on the XCD that runs this workgroup and at the same place of
     // successive super-tiles.
     const uint32_t total = a.tiled_total;
-    const LastRound last = MODE == 2 && !WALK && a.tail ? last_round(((n_rt + sm - 1) / sm) * n_sn) : LastRound{0u, 1u};
+    const LastRound last = kLastRound && a.tail ? last_round(((n_rt + sm - 1) / sm) * n_sn) : LastRound{0u, 1u};
     auto locate_unchecked = [&](uint32_t L, uint32_t& row_tile, uint32_t& col_tile, uint32_t& split) __attribute__((always_inline)) {
         const uint32_t xcd = L % 8u, jj = L / 8u;
         const uint32_t pair = (jj / 32u) * 8u + xcd;
@@ -1747,7 +1748,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         // (a super-tile of the last round: the host lets it be split where K has steps enough)
         const bool tail = last.parts > 1 && (id.L / 256u) * 8u >= last.first;
         const uint32_t n_parts = tail ? last.parts : n_split;
-        if (MODE == 2 && !WALK) s.tail = tail && split > 0 ? (id.L / 256u * 8u + id.L % 8u - last.first) / last.parts * (last.parts - 1) + split : 0u;
+        if (kLastRound) s.tail = tail && split > 0 ? (id.L / 256u * 8u + id.L % 8u - last.first) / last.parts * (last.parts - 1) + split : 0u;
         // split K: this tile multiplies steps [step_lo, step_hi) of the K / 64
         // and writes its own FP32 partial, which combine_kernel or swiglu_reduce_kernel sums in split order
         const uint32_t step_lo = uint32_t(uint64_t(n_steps_all) * split / n_parts);
@@ -2012,7 +2013,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const bool direct = (WAVES == 8 || TILE == 128) && a.direct;
         float* ylane = direct ? a.out + size_t(c.row0) * a.H + col0 : a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
         uint32_t pitch = a.H;
-        if (MODE == 2 && !WALK && last.parts > 1) {
+        if (kLastRound && last.parts > 1) {
             if (c.tail) {
                 ylane = a.tail + (size_t(c.tail - 1) * 32u + blockIdx.x / 8u % 32u) * kTailBlock + (col0 - c.n_base);
                 pitch = 256;

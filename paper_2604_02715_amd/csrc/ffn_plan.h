@@ -18,7 +18,7 @@ constexpr uint32_t kRouteChunkPairs = 4096;
 constexpr uint32_t kFewPairs = 64;
 // Partial sums of a last round (last_round_kernel): at most seven blocks of a super-tile's 32 tiles of 256 x 256.
 constexpr uint64_t kTailBytes = 7ull * 32 * 256 * 256 * 4;
-// Row tiles a call may have (the y dimension of the strip kernels' grid).
+// Row tiles a call may have (the z dimension of the strip kernels' grid).
 constexpr uint32_t kMaxRowTiles = 65535;
 
 #if defined(__HIPCC__)
