@@ -2220,21 +2220,21 @@ hipError_t launch_mfma_probe(const void* operands, float* out, uint32_t n_workgr
     return hipGetLastError();
 }
 
-hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, bool attach_routed,
+hipError_t launch_ffn(const FfnCall& call, int n_cus, hipStream_t stream, hipEvent_t done, hipEvent_t routed, bool attach_routed,
                       SpanHook hook, void* user) {
     (void)n_cus;
-    if (args.T == 0) return hipSuccess;
-    if (args.identity && (done || routed)) return hipErrorInvalidValue;      // the shared expert's calls have no event to complete
-    FfnArgs a = args;
+    if (call.T == 0) return hipSuccess;
+    if (call.identity && (done || routed)) return hipErrorInvalidValue;      // the shared expert's calls have no event to complete
+    FfnArgs a = call;
     auto mark = [&](int kind, int begin) { if (hook) hook(user, kind, begin, stream); };
     const size_t sh = (3 * size_t(a.E) + 1024) * sizeof(int32_t);
     // strip kernels, few pairs: the first product's workgroups do the grouping
-    const bool routes_itself = a.few != 0;
+    const bool routes_itself = call.few != 0;
     if (routes_itself && (a.identity || a.tiled || a.m_tile < kRoutedPairs || uint64_t(a.T) * a.K > kRoutedPairs)) return hipErrorInvalidValue;
     const hipEvent_t with_routing = attach_routed ? routed : nullptr;
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     // (F > 2048: the second product does not walk)
-    if (a.identity || !a.tiled || a.m_tile != 256 || a.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048) a.tail = nullptr;
+    if (a.identity || !a.tiled || a.m_tile != 256 || call.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048) a.tail = nullptr;
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
     const bool grouping = a.identity ? !a.ring1 : !routes_itself;
@@ -2256,7 +2256,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
     }
     auto launch_combine = [&](dim3 grid) {
-        const bool streams = combine_streams(uint64_t(a.ksplit) * a.T * a.K * a.H * sizeof(float), a.mapped, a.E);
+        const bool streams = combine_streams(uint64_t(a.ksplit) * a.T * a.K * a.H * sizeof(float), call.mapped, a.E);
         auto launch = [&](auto plain, auto stream_y) { launch_done(streams ? stream_y : plain, grid, dim3(256), 0, stream, done, a); };
         if (a.identity) launch(combine_kernel<1, false, true>, combine_kernel<1, true, true>);
         else if (a.K <= 2) launch(combine_kernel<2, false>, combine_kernel<2, true>);
@@ -2275,7 +2275,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const uint32_t cols1 = a.halves ? strips1 : (strips1 + 1) / 2;
     const dim3 g1 = a.g1_xcd && !routes_itself ? dim3((a.tiles_cap * a.ksplit1 + 7) / 8 * 8 * cols1, 1, 1) : dim3(cols1, a.ksplit1, a.tiles_cap);
     const dim3 g2(((a.tiles_cap * a.ksplit + 7) / 8 * 8) * ((strips2 + 3) / 4), 1, 1);
-    a.direct = a.identity && a.ksplit == 1 && (a.ring2 || (a.tiled && a.tiled_waves == 2));
+    a.direct = a.identity && a.ksplit == 1 && (a.ring2 || (a.tiled && call.tiled_waves == 2));
     if (a.ring1) {
         mark(2, 1);
         if (hipError_t e = launch_ring(a, 1, stream); e != hipSuccess) return e;
@@ -2293,16 +2293,16 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     const bool stream_b = !a.identity && !(a.flags & 2u) && weights_stream(a.E, a.H, a.F, uint64_t(a.T) * a.K, a.m_tile);
     if (a.tiled) {
         const size_t lds_bytes = 4 * size_t(kTM) * kLdsPitch * sizeof(uint16_t);
-        const bool four = a.tiled_waves == 4;
+        const bool four = call.tiled_waves == 4;
         const bool small = a.m_tile == 128;                         // LDS-direct loads, tiles of 128 x 128
-        const bool d2l4 = a.tiled_waves == 1;                       // LDS-direct loads, four wavefronts of 128 x 128
-        const bool d2l = a.tiled_waves == 2 || d2l4;
+        const bool d2l4 = call.tiled_waves == 1;                       // LDS-direct loads, four wavefronts of 128 x 128
+        const bool d2l = call.tiled_waves == 2 || d2l4;
         if (!d2l && a.ksplit != 1) return hipErrorInvalidValue;     // only the LDS-direct kernels split K
-        if (a.tiled_waves != 2 && (a.ksplit1 != 1 || small)) return hipErrorInvalidValue;
+        if (call.tiled_waves != 2 && (a.ksplit1 != 1 || small)) return hipErrorInvalidValue;
         if (!small && a.m_tile != 256) return hipErrorInvalidValue;
         if (a.ksplit == 0 || a.ksplit > std::max(1u, a.F / kTK)) return hipErrorInvalidValue;
         const bool ragged = a.H % kTK != 0 || a.F % kTK != 0;
-        if (ragged && (a.tiled_waves != 2 || small)) return hipErrorInvalidValue;        // only the eight-wavefront LDS-direct kernels take a partial step
+        if (ragged && (call.tiled_waves != 2 || small)) return hipErrorInvalidValue;        // only the eight-wavefront LDS-direct kernels take a partial step
         static bool attr_set = false;
         if (!attr_set) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tiled_kernel<1>),
@@ -2374,7 +2374,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         const uint64_t avg_rows = pairs_all / std::max<uint64_t>(1, std::min<uint64_t>(a.E, pairs_all));
         bool in_rows = false;                                       // of the launch that d2l_all was asked for last
         auto d2l_all = [&](uint32_t n_ct, uint32_t n_split, bool grouped, bool walk) {
-            in_rows = walk && !ragged && tiles_by_rows(n_ct, avg_rows, grouped ? args.tiled_group : 0u);
+            in_rows = walk && !ragged && tiles_by_rows(n_ct, avg_rows, grouped ? call.tiled_group : 0u);
             if (in_rows) {
                 a.tiled_sn_log2 = 3;
                 a.tiled_group = 1;
@@ -2390,7 +2390,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
             const uint32_t sm = 32u >> best_log2;
             const uint64_t per_super_row = uint64_t(a.m_tile) * sm;
             a.tiled_group = !grouped ? 1u : uint32_t(std::min<uint64_t>(8, std::max<uint64_t>(1,
-                args.tiled_group ? args.tiled_group : (avg_rows + per_super_row / 2) / per_super_row)));
+                call.tiled_group ? call.tiled_group : (avg_rows + per_super_row / 2) / per_super_row)));
             const uint32_t n_sm = ((a.tiles_cap + sm - 1) / sm + a.tiled_group - 1) / a.tiled_group * a.tiled_group;
             const uint32_t n_sn = (n_ct + (1u << best_log2) - 1) >> best_log2;
             const uint32_t supers = (n_sm * n_sn * n_split + 7) / 8 * 8;      // whole rounds over the 8 XCDs
@@ -2405,8 +2405,8 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // a super-tile row is partly empty (workgroups with no tile there idle), hence the choice of shapes above.
         auto d2l_grid = [&](const dim3& all, bool walk) {
             a.tiled_total = all.x;
-            const uint32_t cap = a.tiled_persist * 256u;
-            return (walk && a.tiled_persist && all.x > cap) ? dim3(cap, 1, 1) : all;
+            const uint32_t cap = call.tiled_persist * 256u;
+            return (walk && call.tiled_persist && all.x > cap) ? dim3(cap, 1, 1) : all;
         };
         if (small) {
             const dim3 g = d2l_grid(d2l_all((a.F + 63) / 64, a.ksplit1, false, false), false);
@@ -2415,7 +2415,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<1, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && a.ksplit1 > 1) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, a.ksplit1, false, false), false); hipLaunchKernelGGL((ragged ? gemm_d2l_kernel<3, 8, false, 256, false, true> : gemm_d2l_kernel<3, 8, false, 256>), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, a.tiled_persist != 0), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<1, 8, true, 256, true, false, true> : gemm_d2l_kernel<1, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<1, 8, true, 256>, gemm_d2l_kernel<1, 8, true, 256, true>, gemm_d2l_kernel<1, 8, true, 256, false, true>, gemm_d2l_kernel<1, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.F + 127) / 128, 1, true, call.tiled_persist != 0), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<1, 8, true, 256, true, false, true> : gemm_d2l_kernel<1, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<1, 8, true, 256>, gemm_d2l_kernel<1, 8, true, 256, true>, gemm_d2l_kernel<1, 8, true, 256, false, true>, gemm_d2l_kernel<1, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<1>, grid_for((a.F + 127) / 128), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<1>, grid_for((a.F + 127) / 128), dim3(512), lds_bytes, stream, a);
         launch_reduce();
@@ -2425,7 +2425,7 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
         // first loads are on their way while the 256 KiB a tile stores leave.  The stores themselves are not hidden: the wait for
         // the record at the end of a tile covers them.  Microseconds per call without / with: 512 experts of H 2048 F 512, 200 rows each
         // 1137 / 1104, 20 of H 5120 F 1536, 1638 rows 1642 / 1615, 160 of those 512 rows 4637 / 4581, 205 rows 2127 / 2126.
-        const bool walk2 = a.tiled_persist && a.ksplit == 1 && a.F <= 2048;
+        const bool walk2 = call.tiled_persist && a.ksplit == 1 && a.F <= 2048;
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<2, 8, true, 256, true, false, true> : gemm_d2l_kernel<2, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
@@ -2457,12 +2457,12 @@ hipError_t launch_ffn(const FfnArgs& args, int n_cus, hipStream_t stream, hipEve
     else hipLaunchKernelGGL((gemm1_swiglu_kernel<8, false, false, false>), g1, dim3(256), 0, stream, a);
     if (routes_itself)
         if (hipError_t e = record_routed(); e != hipSuccess) return e;
-    if (!a.few_fused) launch_reduce();
+    if (!call.few_fused) launch_reduce();
     mark(2, 0);
     mark(3, 1);
-    if (a.few2) {
+    if (call.few2) {
         const dim3 grid(strips2, a.ksplit, a.tiles_cap);
-        if (a.few_fused) hipLaunchKernelGGL((gemm2_few_kernel<1, true>), grid, dim3(256), std::max(32768u, 4u * 16u * (uint32_t(few_quarter(a.F, a.ksplit)) + 8u) * 2u), stream, a);
+        if (call.few_fused) hipLaunchKernelGGL((gemm2_few_kernel<1, true>), grid, dim3(256), std::max(32768u, 4u * 16u * (uint32_t(few_quarter(a.F, a.ksplit)) + 8u) * 2u), stream, a);
         else hipLaunchKernelGGL((gemm2_few_kernel<4, false>), grid, dim3(256), 65536, stream, a);
     } else if (a.m_tile == 16) hipLaunchKernelGGL(gemm2_kernel<1>, g2, dim3(256), 0, stream, a);
     else if (a.m_tile == 32) hipLaunchKernelGGL(gemm2_kernel<2>, g2, dim3(256), 0, stream, a);

@@ -1047,7 +1047,7 @@ static int expert_ffn_enqueue(fluxmoe_ctx* c, uint32_t layer, const uint16_t* to
                          (unsigned long long)w_bytes, T, K, (unsigned long long)p.bytes);
     if (p.tiles_cap > kMaxRowTiles) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    FfnArgs a{};
+    FfnCall a{};
     a.tokens = tokens;
     a.topk_ids = topk_ids;
     a.topk_w = topk_w;
@@ -1150,7 +1150,7 @@ int fluxmoe_shared_expert_ffn(fluxmoe_ctx* c, const uint16_t* w13, const uint16_
     if (p.tiles_cap > kMaxRowTiles) return set_error(FLUXMOE_EINVAL, "too many row tiles (%u)", p.tiles_cap);
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     uint8_t* w = c->ws + c->pool_ws_bytes;
-    FfnArgs a{};
+    FfnCall a{};
     a.tokens = tokens;
     a.identity = 1;
     a.slots13 = w13;
