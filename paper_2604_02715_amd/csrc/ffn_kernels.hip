@@ -295,6 +295,7 @@ __global__ __launch_bounds__(1024) void route_order_kernel(FfnArgs a) {
     __shared__ uint32_t found[16];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, pairs = a.T * a.K;
     const int32_t e = int32_t(blockIdx.x);
+    if (last_round((uint32_t(a.n_tiles[0]) + 3) / 4 * ((a.H + 2047) / 2048)).parts == 1) return;
     const uint32_t stretch = (pairs + 1023) / 1024 * 64, first = min(pairs, wave * stretch), last = min(pairs, first + stretch);
     auto look = [&](uint32_t base, uint64_t (&mine)[8]) __attribute__((always_inline)) {
         int32_t id[8];
@@ -1569,21 +1570,11 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 #define FLUXMOE_D2L_PROBE 0
 #endif
 
-// The last round of a second product in 256 x 256 tiles.  Super-tiles of 4 x 8 tiles are dealt to the 8 XCDs in turn; where the last
-// round has four of them at most, K of each is split over as many XCDs as there are for one, and last_round_kernel adds the parts up.
-// 8 experts of H 4096 F 14336, 4096 tokens, top-2 (18 super-tiles, two XCDs ran a third round while six had nothing to do): 913 -> 863 us
-// with the sums, the call 2618 -> 2563; 2 of those, 6000 tokens (12 row tiles each) 1872 -> 1766.
-struct LastRound {
-    uint32_t first, parts;       // first super-tile of the round, parts of K
-};
 constexpr uint32_t kTailBlock = 256 * 256;       // floats of a tile's partial sums
-__device__ __forceinline__ LastRound last_round(uint32_t supers) {
-    const uint32_t rest = supers % 8u;
-    return LastRound{supers - rest, rest == 1 ? 8u : (rest == 2 ? 4u : (rest == 3 || rest == 4 ? 2u : 1u))};
-}
 
 // y of the last round's tiles += their other parts of K, in the order of k.  A workgroup has 16 rows of a tile.  Bound by its launch (5 us where
-// nothing was split) and by the parts' bytes, 60 MB at most, still in the caches: 8 us on the first, 16 on the second case above.
+// nothing was split) and by the parts' bytes, 60 MB at most, still in the caches: 8 us on 8 experts of H 4096, 4096 tokens, top-2, three
+// parts of two super-tiles.
 __global__ __launch_bounds__(256) void last_round_kernel(FfnArgs a) {
     const uint32_t n_rt = uint32_t(a.n_tiles[0]), n_ct = (a.H + 255) / 256, n_sn = (n_ct + 7) / 8;
     const LastRound last = last_round((n_rt + 3) / 4 * n_sn);
@@ -2234,7 +2225,8 @@ hipError_t launch_ffn(const FfnCall& call, int n_cus, hipStream_t stream, hipEve
     const hipEvent_t with_routing = attach_routed ? routed : nullptr;
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     // (F > 2048: the second product does not walk)
-    if (a.identity || !a.tiled || a.m_tile != 256 || call.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048) a.tail = nullptr;
+    if (a.identity || !a.tiled || a.m_tile != 256 || call.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048 || !last_round_may_split(uint64_t(a.T) * a.K, call.mapped, a.E, a.H))
+        a.tail = nullptr;
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
     const bool grouping = a.identity ? !a.ring1 : !routes_itself;

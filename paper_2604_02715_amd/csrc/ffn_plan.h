@@ -47,6 +47,32 @@ FLUXMOE_HD inline float tiled_cost(const SplitShape& s, uint32_t n_tiles, uint32
     return float((tiles + per_xcd - 1) / per_xcd) * (steps * 1400.f + 3000.f) + (k > 1 ? 4500.f + float(k) * float(rows) * float(s.F) * 16.f / 10000.f : 0.f);
 }
 
+// The last round of a second product in 256 x 256 tiles.  Super-tiles of 4 x 8 tiles are dealt to the 8 XCDs in turn; where the last
+// round has four of them at most, K of each is split over as many XCDs as there are for one, and last_round_kernel adds the parts up.
+// 8 experts of H 4096 F 14336, 4096 tokens, top-2 (18 super-tiles, two XCDs ran a third round while six had nothing to do): 916 -> 840 us
+// with the sums and route_order_kernel.
+struct LastRound {
+    uint32_t first, parts;       // first super-tile of the round, parts of K
+};
+FLUXMOE_HD inline LastRound last_round(uint32_t supers) {
+    const uint32_t rest = supers % 8u;
+    return LastRound{supers - rest, rest == 1 ? 8u : (rest == 2 ? 4u : (rest == 3 || rest == 4 ? 2u : 1u))};
+}
+// From this F on it pays.  Microseconds a call, whole / split last round, two experts, one to four super-tiles left and five (whole, but for the
+// launches): H 2048 F 2112 324 / 318, 342 / 343, 358 / 358, 385 / 388, 427 / 434; F 3072 411 / 395, 411 / 394, 471 / 454, 497 / 494, 538 / 546; F 4096
+// 513 / 481, 514 / 488, 586 / 560, 617 / 598, 659 / 669; F 7168 870 / 796, 858 / 794, 939 / 886, 1015 / 975, 1090 / 1099.
+constexpr uint64_t kLastRoundF = 3072;
+// Whether the last round of a call of `pairs` pairs may be one that is split: for some number of row tiles that the routing can make.  Where all pairs
+// count; with part of the layer resident it can be any.  Only the device knows the number, and where it is none of those the launches for a
+// split round are 5 to 10 us for nothing.
+inline bool last_round_may_split(uint64_t pairs, uint64_t mapped, uint64_t E, uint64_t H) {
+    if (pairs == 0 || (mapped && mapped < E)) return pairs != 0;
+    const uint64_t most = (pairs + 255 * std::min(E, pairs)) / 256, n_sn = ((H + 255) / 256 + 7) / 8;
+    for (uint64_t groups = ((pairs + 255) / 256 + 3) / 4; groups <= (most + 3) / 4; ++groups)
+        if (last_round(uint32_t(groups * n_sn)).parts > 1) return true;
+    return false;
+}
+
 struct FfnPlan {
     bool tiled, halves, g1_xcd;
     // few: the first product's workgroups group the pairs.  few_splits: gemm2_few_kernel runs with as many K splits, which ksplit tells too.
@@ -322,8 +348,8 @@ inline FfnPlan plan_ffn_rules(const FfnShape& c, uint32_t T, uint32_t K, uint32_
     // (64 of F 384: 94.4 / 93.5), with two strips a workgroup it is 0.5 to 2 % slower.  Enough (tile, split) units to fill the
     // 8 XCDs evenly.
     p.g1_xcd = !p.few && p.halves && F % 64 != 0 && groups_act * p.ksplit1 >= 64;
-    // The last round of the second product: tiles of 256 x 256, unsplit, long K (shorter ones walk), more than a round of them.
-    p.tail = c.routed && split && p.tiled && p.m_tile == 256 && c.tiled_waves == 2 && p.ksplit == 1 && F > 2048 && row_tiles * ((H + 255) / 256) > n_cus;
+    // The last round of the second product: tiles of 256 x 256, unsplit, long K, more than a round of them.
+    p.tail = c.routed && split && p.tiled && p.m_tile == 256 && c.tiled_waves == 2 && p.ksplit == 1 && F >= kLastRoundF && row_tiles * ((H + 255) / 256) > n_cus;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { uint64_t at = o; o = align_up(o + bytes, 256); return at; };
     p.off_count = take((E + 1) * 4);

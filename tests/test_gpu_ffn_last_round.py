@@ -20,13 +20,13 @@ def reference(x, w13, w2):
 
 
 CASES = [
-    (2, 33, 2048, 2112, 1),          # one super-tile left, eight parts; its row tile has a single row
-    (2, 38, 2048, 2112, 100),        # two: four parts
-    (2, 41, 2048, 2120, 256),        # three: two parts, a partial step
-    (2, 48, 2048, 2112, 77),         # four: two parts
-    (2, 52, 2048, 2112, 256),        # five: whole
-    (2, 34, 2112, 2112, 256),        # two column blocks, the second with one tile of 64 columns: 18 super-tiles
-    (41, 41, 2048, 2112, 30),        # a row tile an expert and 1 GB of weights: they pass the caches by
+    (2, 33, 2048, 3136, 1),          # one super-tile left, eight parts; its row tile has a single row
+    (2, 38, 2048, 3136, 100),        # two: four parts
+    (2, 41, 2048, 3272, 256),        # three: two parts, a partial step
+    (2, 48, 2048, 3136, 77),         # four: two parts
+    (2, 52, 2048, 3136, 256),        # five: whole
+    (2, 34, 2112, 3136, 256),        # two column blocks, the second with one tile of 64 columns: 18 super-tiles
+    (41, 41, 2048, 3136, 30),        # a row tile an expert and 1.6 GB of weights: they pass the caches by
 ]
 
 
@@ -43,6 +43,34 @@ int main() {
 """ % (experts, hidden, ffn, T, T, experts, T))
     subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     subprocess.run([str(tmp_path / "m")], check=True)
+
+
+def test_which_calls_may_split(tmp_path):
+    """Every number of row tiles that a routing of all pairs can make, against the rule; the line in F."""
+    (tmp_path / "m.cpp").write_text("""
+#include "ffn_plan.h"
+using namespace fluxmoe;
+int main() {
+    for (uint64_t E = 1; E <= 3; ++E)
+        for (uint64_t H : {256, 2048, 2056, 4096, 8192})
+            for (uint64_t pairs = 1; pairs <= 12000; pairs += 61) {
+                bool any = false;
+                for (uint64_t a = 0; a <= (E > 1 ? pairs : 0); a += 1 + pairs / 40)
+                    for (uint64_t b = 0; b <= (E > 2 ? pairs - a : 0); b += 1 + pairs / 40) {
+                        const uint64_t n = (a + 255) / 256 + (b + 255) / 256 + (pairs - a - b + 255) / 256;
+                        const uint64_t supers = (n + 3) / 4 * (((H + 255) / 256 + 7) / 8);
+                        any |= supers % 8 >= 1 && supers % 8 <= 4;
+                    }
+                if (any && !last_round_may_split(pairs, E, E, H)) return 1;
+                if (E == 1 && any != last_round_may_split(pairs, 0, E, H)) return 2;
+                if (E > 1 && !last_round_may_split(pairs, E - 1, E, H)) return 3;
+            }
+    const FfnShape at{2, 2048, 3072, 256, 2, true}, below{2, 2048, 3064, 256, 2, true};
+    return plan_ffn(at, 9000, 1).tail && !plan_ffn(below, 9000, 1).tail ? 0 : 4;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    assert subprocess.run([str(tmp_path / "m")]).returncode == 0
 
 
 @pytest.mark.gpu
@@ -96,7 +124,7 @@ def test_last_round(experts, row_tiles, hidden, ffn, rows_last):
     (5, 42, 100, 2),                 # several experts' last tiles in the last round, two rows a token
 ])
 def test_the_same_bits_on_every_call(experts, row_tiles, rows_last, top_k):
-    hidden, ffn = 2048, 2112
+    hidden, ffn = 2048, 3136
     T = (256 * (row_tiles - 1) + rows_last) // top_k
     cfg = inputs.scaled(inputs.CONFIGS["c1_tiny"], n_experts=experts, n_slots=experts, top_k=top_k, tokens=T, hidden=hidden, ffn=ffn)
     pool = harness.ExpertPool(cfg)
