@@ -1604,10 +1604,11 @@ __global__ __launch_bounds__(256) void last_round_kernel(FfnArgs a) {
 // of 64 x 64: two per CU, a quarter of the work per tile, for products whose 256 x 256 tiles leave most CUs without one.
 // STREAM: the weight loads carry the non-temporal hint.
 // RAGGED: K of either product may be any multiple of 8; the pieces of the last step that lie past its end come from zeros.
-// ROWS: the tiles are taken row by row and not in super-tiles.
-template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false, bool RAGGED = false, bool ROWS = false>
+// ROWS: the tiles are taken row by row and not in super-tiles.  LAST: the last round may be split (a.tail); instances of its own, since
+// the look-up costs the others registers.
+template <int MODE, int WAVES, bool WALK, int TILE, bool STREAM = false, bool RAGGED = false, bool ROWS = false, bool LAST = false>
 __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kernel(FfnArgs a) {
-    constexpr bool kLastRound = MODE == 2 && !WALK && WAVES == 8 && TILE == 256;      // the last round may be split
+    static_assert(!LAST || (MODE == 2 && !WALK && WAVES == 8 && TILE == 256), "a second product with long K");
     constexpr bool kFirst = MODE != 2;                       // gate/up operands: rows gathered from the tokens, two weight matrices
     static_assert(MODE != 3 || !WALK, "the split first product has few tiles");
     // WAVES = 8: wavefronts 4 (rows) x 2 (columns), 64 x 128 each, two per SIMD.  WAVES = 4: 2 x 2,
@@ -1651,7 +1652,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
     // all numbers), so all of them lie on the XCD that runs this workgroup and at the same place of
     // successive super-tiles.
     const uint32_t total = a.tiled_total;
-    const LastRound last = kLastRound && a.tail ? last_round(((n_rt + sm - 1) / sm) * n_sn) : LastRound{0u, 1u};
+    const LastRound last = LAST ? last_round(((n_rt + sm - 1) / sm) * n_sn) : LastRound{0u, 1u};
     auto locate_unchecked = [&](uint32_t L, uint32_t& row_tile, uint32_t& col_tile, uint32_t& split) __attribute__((always_inline)) {
         const uint32_t xcd = L % 8u, jj = L / 8u;
         const uint32_t pair = (jj / 32u) * 8u + xcd;
@@ -1739,7 +1740,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         // (a super-tile of the last round: the host lets it be split where K has steps enough)
         const bool tail = last.parts > 1 && (id.L / 256u) * 8u >= last.first;
         const uint32_t n_parts = tail ? last.parts : n_split;
-        if (kLastRound) s.tail = tail && split > 0 ? (id.L / 256u * 8u + id.L % 8u - last.first) / last.parts * (last.parts - 1) + split : 0u;
+        if (LAST) s.tail = tail && split > 0 ? (id.L / 256u * 8u + id.L % 8u - last.first) / last.parts * (last.parts - 1) + split : 0u;
         // split K: this tile multiplies steps [step_lo, step_hi) of the K / 64
         // and writes its own FP32 partial, which combine_kernel or swiglu_reduce_kernel sums in split order
         const uint32_t step_lo = uint32_t(uint64_t(n_steps_all) * split / n_parts);
@@ -2004,7 +2005,7 @@ __global__ __launch_bounds__(WAVES * 64, TILE == 128 ? 2 : 1) void gemm_d2l_kern
         const bool direct = (WAVES == 8 || TILE == 128) && a.direct;
         float* ylane = direct ? a.out + size_t(c.row0) * a.H + col0 : a.ybuf + (size_t(c.split) * a.pairs_cap + size_t(c.row0)) * a.H + col0;
         uint32_t pitch = a.H;
-        if (kLastRound && last.parts > 1) {
+        if (LAST && last.parts > 1) {
             if (c.tail) {
                 ylane = a.tail + (size_t(c.tail - 1) * 32u + blockIdx.x / 8u % 32u) * kTailBlock + (col0 - c.n_base);
                 pitch = 256;
@@ -2225,7 +2226,7 @@ hipError_t launch_ffn(const FfnCall& call, int n_cus, hipStream_t stream, hipEve
     const hipEvent_t with_routing = attach_routed ? routed : nullptr;
     auto record_routed = [&]() { return routed && !attach_routed ? hipEventRecord(routed, stream) : hipSuccess; };
     // (F > 2048: the second product does not walk)
-    if (a.identity || !a.tiled || a.m_tile != 256 || call.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048 || !last_round_may_split(uint64_t(a.T) * a.K, call.mapped, a.E, a.H))
+    if (a.identity || !a.tiled || a.m_tile != 256 || call.tiled_waves != 2 || a.ksplit != 1 || a.F <= 2048 || !last_round_pays(uint64_t(a.T) * a.K, call.mapped, a.E, a.H, a.F))
         a.tail = nullptr;
     const bool chooses = a.tiled && a.m_tile == 256 && a.ksplit1 > 1;
     if (routes_itself) a.split_tiles = ~0u;                         // few rows, and the lists are not there yet: as planned
@@ -2324,6 +2325,8 @@ hipError_t launch_ffn(const FfnCall& call, int n_cus, hipStream_t stream, hipEve
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<3, 8, false, 256, false, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, false, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true, false, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, false, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true, false, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, false, false, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true, false, false, true>),
+                                  reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, false, true, false, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true, true, false, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<1, 8, true, 256, true>), reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, true, 256, true>),
                                   reinterpret_cast<const void*>(&gemm_d2l_kernel<2, 8, false, 256, true>)}) {
                 e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
@@ -2421,7 +2424,7 @@ hipError_t launch_ffn(const FfnCall& call, int n_cus, hipStream_t stream, hipEve
         if (small) { const dim3 g = d2l_grid(d2l_all((a.H + 127) / 128, a.ksplit, false, false), false); hipLaunchKernelGGL((stream_b ? gemm_d2l_kernel<2, 4, false, 128, true> : gemm_d2l_kernel<2, 4, false, 128>), g, dim3(256), 81920, stream, a); }
         else if (d2l4) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((gemm_d2l_kernel<2, 4, false, 256>), g, dim3(256), 163840, stream, a); }
         else if (d2l && walk2) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, 1, false, true), true); hipLaunchKernelGGL((in_rows ? (stream_b ? gemm_d2l_kernel<2, 8, true, 256, true, false, true> : gemm_d2l_kernel<2, 8, true, 256, false, false, true>) : pick(gemm_d2l_kernel<2, 8, true, 256>, gemm_d2l_kernel<2, 8, true, 256, true>, gemm_d2l_kernel<2, 8, true, 256, false, true>, gemm_d2l_kernel<2, 8, true, 256, true, true>)), g, dim3(512), 163840, stream, a); }
-        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((pick(gemm_d2l_kernel<2, 8, false, 256>, gemm_d2l_kernel<2, 8, false, 256, true>, gemm_d2l_kernel<2, 8, false, 256, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, true>)), g, dim3(512), 163840, stream, a); }
+        else if (d2l) { const dim3 g = d2l_grid(d2l_all((a.H + 255) / 256, a.ksplit, false, false), false); hipLaunchKernelGGL((a.tail ? pick(gemm_d2l_kernel<2, 8, false, 256, false, false, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, false, false, true>, gemm_d2l_kernel<2, 8, false, 256, false, true, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, true, false, true>) : pick(gemm_d2l_kernel<2, 8, false, 256>, gemm_d2l_kernel<2, 8, false, 256, true>, gemm_d2l_kernel<2, 8, false, 256, false, true>, gemm_d2l_kernel<2, 8, false, 256, true, true>)), g, dim3(512), 163840, stream, a); }
         else if (four) hipLaunchKernelGGL(gemm_tiled4_kernel<2>, grid_for((a.H + 255) / 256), dim3(256), lds_bytes, stream, a);
         else hipLaunchKernelGGL(gemm_tiled_kernel<2>, grid_for((a.H + 255) / 256), dim3(512), lds_bytes, stream, a);
         if (a.tail) hipLaunchKernelGGL(last_round_kernel, dim3(16, 32, 4), dim3(256), 0, stream, a);

@@ -62,15 +62,19 @@ FLUXMOE_HD inline LastRound last_round(uint32_t supers) {
 // launches): H 2048 F 2112 324 / 318, 342 / 343, 358 / 358, 385 / 388, 427 / 434; F 3072 411 / 395, 411 / 394, 471 / 454, 497 / 494, 538 / 546; F 4096
 // 513 / 481, 514 / 488, 586 / 560, 617 / 598, 659 / 669; F 7168 870 / 796, 858 / 794, 939 / 886, 1015 / 975, 1090 / 1099.
 constexpr uint64_t kLastRoundF = 3072;
-// Whether the last round of a call of `pairs` pairs may be one that is split: for some number of row tiles that the routing can make.  Where all pairs
-// count; with part of the layer resident it can be any.  Only the device knows the number, and where it is none of those the launches for a
-// split round are 5 to 10 us for nothing.
-inline bool last_round_may_split(uint64_t pairs, uint64_t mapped, uint64_t E, uint64_t H) {
-    if (pairs == 0 || (mapped && mapped < E)) return pairs != 0;
-    const uint64_t most = (pairs + 255 * std::min(E, pairs)) / 256, n_sn = ((H + 255) / 256 + 7) / 8;
-    for (uint64_t groups = ((pairs + 255) / 256 + 3) / 4; groups <= (most + 3) / 4; ++groups)
-        if (last_round(uint32_t(groups * n_sn)).parts > 1) return true;
-    return false;
+// Whether a call of `pairs` pairs launches what a split last round needs.  Only the device knows the number of row tiles; where the round turns out
+// whole, the two launches are 8 us for nothing (8 experts of H 4096 F 3584, 936 rows each 661 / 668).  So the gain, 3/8 of what the round's length
+// promises, has to cover them, counting two thirds on rows dealt evenly and one on any number of tiles that a routing can make.
+inline bool last_round_pays(uint64_t pairs, uint64_t mapped, uint64_t E, uint64_t H, uint64_t F) {
+    const uint64_t act = mapped ? std::min(mapped, E) : E, rows = pairs * act / E, n_sn = ((H + 255) / 256 + 7) / 8;
+    if (rows == 0) return false;
+    const uint64_t experts = std::min(act, rows), least = (rows + 255) / 256, most = (rows + 255 * experts) / 256;
+    const double round_us = 3.0 + 1.4 * double((F + 63) / 64);
+    const auto gain = [&](uint64_t tiles) { return 0.375 * round_us * (1.0 - 1.0 / last_round(uint32_t((tiles + 3) / 4 * n_sn)).parts); };
+    double any = 0.0;
+    for (uint64_t n = least; n <= most; ++n) any += gain(n);
+    const uint64_t even = experts * (((rows + experts - 1) / experts + 255) / 256);
+    return (2.0 * gain(even) + any / double(most - least + 1)) / 3.0 > 8.0;
 }
 
 struct FfnPlan {

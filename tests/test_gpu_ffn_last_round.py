@@ -38,35 +38,31 @@ def test_the_plan_splits_the_last_round(experts, row_tiles, hidden, ffn, rows_la
 int main() {
     const fluxmoe::FfnShape c{%d, %d, %d, 256, 2, true};
     const fluxmoe::FfnPlan p = fluxmoe::plan_ffn(c, %d, 1, fluxmoe::ffn_bytes(c, %d, 1), %d);
-    return p.tail && p.m_tile == 256 && fluxmoe::weights_stream(c.E, c.H, c.F, %d, 256) == (c.E > 2) ? 0 : 1;
+    const bool pays = fluxmoe::last_round_pays(%d, c.E, c.E, c.H, c.F);
+    return p.tail && pays == %d && p.m_tile == 256 && fluxmoe::weights_stream(c.E, c.H, c.F, %d, 256) == (c.E > 2) ? 0 : 1;
 }
-""" % (experts, hidden, ffn, T, T, experts, T))
+""" % (experts, hidden, ffn, T, T, experts, T, row_tiles != 52, T))
     subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     subprocess.run([str(tmp_path / "m")], check=True)
 
 
-def test_which_calls_may_split(tmp_path):
-    """Every number of row tiles that a routing of all pairs can make, against the rule; the line in F."""
+def test_both_sides_of_the_lines(tmp_path):
     (tmp_path / "m.cpp").write_text("""
 #include "ffn_plan.h"
 using namespace fluxmoe;
 int main() {
-    for (uint64_t E = 1; E <= 3; ++E)
-        for (uint64_t H : {256, 2048, 2056, 4096, 8192})
-            for (uint64_t pairs = 1; pairs <= 12000; pairs += 61) {
-                bool any = false;
-                for (uint64_t a = 0; a <= (E > 1 ? pairs : 0); a += 1 + pairs / 40)
-                    for (uint64_t b = 0; b <= (E > 2 ? pairs - a : 0); b += 1 + pairs / 40) {
-                        const uint64_t n = (a + 255) / 256 + (b + 255) / 256 + (pairs - a - b + 255) / 256;
-                        const uint64_t supers = (n + 3) / 4 * (((H + 255) / 256 + 7) / 8);
-                        any |= supers % 8 >= 1 && supers % 8 <= 4;
-                    }
-                if (any && !last_round_may_split(pairs, E, E, H)) return 1;
-                if (E == 1 && any != last_round_may_split(pairs, 0, E, H)) return 2;
-                if (E > 1 && !last_round_may_split(pairs, E - 1, E, H)) return 3;
-            }
     const FfnShape at{2, 2048, 3072, 256, 2, true}, below{2, 2048, 3064, 256, 2, true};
-    return plan_ffn(at, 9000, 1).tail && !plan_ffn(below, 9000, 1).tail ? 0 : 4;
+    if (!plan_ffn(at, 9000, 1).tail || plan_ffn(below, 9000, 1).tail) return 1;
+    // one expert: the number of row tiles is known
+    for (uint64_t n = 1; n <= 200; ++n) {
+        const uint64_t rest = (n + 3) / 4 % 8;
+        if (last_round_pays(256 * n - 255, 0, 1, 2048, 3072) != (rest >= 1 && rest <= 4)) return 2;
+        if (last_round_pays(256 * n, 1, 1, 4096, 3072) != (rest % 4 == 1 || rest % 4 == 2)) return 3;
+    }
+    // 8 of H 4096, 936 rows each: 32 row tiles, a whole round; short K does not wager on other routings, long K does
+    if (last_round_pays(7488, 8, 8, 4096, 3584) || !last_round_pays(7488, 8, 8, 4096, 14336)) return 4;
+    if (!last_round_pays(8192, 0, 8, 4096, 14336) || last_round_pays(0, 0, 8, 4096, 14336) || last_round_pays(1, 1, 8, 4096, 14336)) return 5;
+    return 0;
 }
 """)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
