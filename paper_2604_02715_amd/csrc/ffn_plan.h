@@ -138,6 +138,10 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
         // rows of weights are 512 bytes of a matrix, not 256).  Microseconds a call, general rule / here:
         // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
         // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
+        // Halves, as in the general rule, only where whole strips leave a wavefront or a CU without work: past a round of them it is the rows' bytes that
+        // count.  Whole / halves: 32 of H 1080 F 6360, 5 tokens, top-8 166 / 186, 64 of H 872 F 6032, 7, top-4 134 / 151, 64 of H 2920 F 3064,
+        // 5, top-10 396 / 420, 160 of H 928 F 2728, 13, top-4 161 / 175; 114 of H 2240 F 4544, 9, top-4 319 / 316.
+        const bool halves_pay = halves_too && (strips1 % 2 || (strips1 + 1) / 2 * tiles < n_cus);
         const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
         // (as short as in a buffer that holds all of the general rule's splits, if something that is fits)
         for (const uint64_t longest : {chain(splits_any, p.halves), chain(p.ksplit1, p.halves)}) {
@@ -145,7 +149,7 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
             uint32_t best[2] = {0, 0};
             for (uint32_t k = 1; k <= kStripSplits; ++k)
                 for (const bool halves : {false, true}) {
-                    if ((halves && !halves_too) || chain(k, halves) > longest || sums1(k) > room) continue;
+                    if ((halves && !halves_pay) || chain(k, halves) > longest || sums1(k) > room) continue;
                     const uint64_t cost = strip_cost(H, n_cus, halves ? strips1 : (strips1 + 1) / 2, tiles, halves, pairs_act * 2 * F * 8, k);
                     if (cost < least[halves]) { least[halves] = cost; best[halves] = k; }
                 }

@@ -109,6 +109,20 @@ def test_both_sides_of_the_lines(few):
     assert of(T=59, K=1, E=4, H=4752, F=1680).few_splits == 0 and of(T=11, K=4, E=4, H=4768, F=3736).few_splits == 0
 
 
+def test_halved_strips_only_where_whole_ones_leave_cus_without_work(few, monkeypatch):
+    monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
+    for E, H, F, T, K in [(32, 1080, 6360, 5, 8), (64, 872, 6032, 7, 4), (64, 2920, 3064, 5, 10), (160, 928, 2728, 13, 4), (20, 992, 3552, 10, 6)]:
+        assert -(-F // 128) % 2 == 0 and not few.plan(E=E, H=H, F=F, T=T, K=K).halves
+    rng, halved = random.Random(12), 0
+    for c in (random_call(rng) for _ in range(8000)):
+        c["F"] = c["F"] // 256 * 256 or 256                                  # an even number of strips
+        p = few.plan(**c, mapped=c["E"])
+        if p.few and c["T"] == 1:                                            # K row tiles
+            assert not p.halves or c["F"] // 256 * c["K"] < 256, c
+            halved += p.halves
+    assert halved > 20
+
+
 def test_more_experts_a_token_than_the_layer_has(tmp_path):
     """The size query takes any number of experts a token: no conversion of a number that is none."""
     (tmp_path / "m.cpp").write_text("""
