@@ -777,7 +777,9 @@ __global__ __launch_bounds__(256) void gemm1_swiglu_kernel(FfnArgs a) {
     // the column workgroups of a (tile, split) share an XCD and find the tile's activations, and where rows of the weights
     // are not whole 128-byte lines the line that two strips share, in its L2
     // The tiles come last: the numbers past the last tile are then the last ones and every XCD gets its share of the others (160 experts of
-    // H 5120 F 1536, one token, top-8, five splits: 240 of 270 workgroups have work; with the splits last 86 us a call, now 69).
+    // H 5120 F 1536, one token, top-8, five splits: 240 of 270 workgroups have work; with the splits last 86 us a call, now 69).  In several rounds, splits
+    // last / tiles last: 8 of H 4568 F 6480, 5 tokens, top-8 306 / 289, of H 4584 F 10616, 7 497 / 469, 32 of H 4824 F 1160, 6, top-6 168 / 167, but 60 of
+    // H 3968 F 4864, 8 tokens 119 / 122, 290 of H 4608 F 872, 41 tokens 156 / 160.
     uint32_t col_wg = blockIdx.x, tile_no = blockIdx.z, split = blockIdx.y;
     if (!ROUTE && a.g1_xcd) {
         const uint32_t n_cw = HALVES ? (a.F + kStrip - 1) / kStrip : (a.F + 2 * kStrip - 1) / (2 * kStrip);

@@ -112,8 +112,9 @@ inline uint64_t few_quarter(uint64_t F, uint64_t splits) { return align_up((alig
 constexpr uint32_t kStripSplits = 16;
 constexpr uint64_t kNoSplits = ~0ull;
 inline uint64_t strip_cost(uint64_t H, uint64_t n_cus, uint64_t cols, uint64_t n_tiles, bool halves, uint64_t partial_bytes, uint64_t k) {
+    if (k > 1 && k * 256 > H) return kNoSplits;
     const uint64_t unit = halves ? 256 : 128, k_per = align_up((H + k - 1) / k, unit);      // the kernel splits at multiples of that
-    if (k > 1 && (k * 256 > H || (H + k_per - 1) / k_per != k)) return kNoSplits;
+    if (k > 1 && (H + k_per - 1) / k_per != k) return kNoSplits;
     const uint64_t rounds = (cols * n_tiles * k + n_cus - 1) / n_cus;
     return rounds * (std::min(k_per, H) / (halves ? 2 : 1) + 128) + (k > 1 ? 128 + k * partial_bytes / (n_cus * 1024) : 0);
 }
@@ -133,15 +134,13 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
     // (a call that touches more of them than expected would take another round)
     if (T > 1 || act < c.E) touched = std::min({touched + 0.4 * std::sqrt(touched * (1.0 - touched / double(act))), double(act), double(pairs)});
     const uint64_t tiles = uint64_t(touched + 0.5);
-    if (split) {
+    if (split && (strips1 + 1) / 2 * tiles < n_cus) {
         // The first product with the experts the call is expected to touch for its row tiles, and whole strips where they are as good (their
         // rows of weights are 512 bytes of a matrix, not 256).  Microseconds a call, general rule / here:
         // 160 experts of H 5120 F 1536, top-8, 4 tokens 242 / 228, 64 of H 2048 F 512, 17 tokens, top-2 44.6 / 41.6, 160 of H 5120
-        // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.
-        // Halves, as in the general rule, only where whole strips leave a wavefront or a CU without work: past a round of them it is the rows' bytes that
-        // count.  Whole / halves: 32 of H 1080 F 6360, 5 tokens, top-8 166 / 186, 64 of H 872 F 6032, 7, top-4 134 / 151, 64 of H 2920 F 3064,
-        // 5, top-10 396 / 420, 160 of H 928 F 2728, 13, top-4 161 / 175; 114 of H 2240 F 4544, 9, top-4 319 / 316.
-        const bool halves_pay = halves_too && (strips1 % 2 || (strips1 + 1) / 2 * tiles < n_cus);
+        // F 1536, 2 tokens, top-2 54 / 45, 64 of H 3000 F 136, 9 tokens, top-4 36.5 / 31.  Where whole strips are a round of workgroups already, the
+        // general rule stays: other splits or halves then gain nothing that the estimate could see.  32 of H 1080 F 6360, 5 tokens, top-8 166 / 186, 64 of
+        // H 2560 F 2176, 10, top-4 166 / 180, 42 of H 2960 F 9336, 10, top-4 809 / 882, 32 of H 3480 F 3200, 6, top-10 337 / 351.
         const auto chain = [&](uint64_t k, bool halves) { return std::min(H, align_up((H + k - 1) / k, halves ? 256 : 128)) / (halves ? 2 : 1); };
         // (as short as in a buffer that holds all of the general rule's splits, if something that is fits)
         for (const uint64_t longest : {chain(splits_any, p.halves), chain(p.ksplit1, p.halves)}) {
@@ -149,7 +148,7 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
             uint32_t best[2] = {0, 0};
             for (uint32_t k = 1; k <= kStripSplits; ++k)
                 for (const bool halves : {false, true}) {
-                    if ((halves && !halves_pay) || chain(k, halves) > longest || sums1(k) > room) continue;
+                    if ((halves && !halves_too) || chain(k, halves) > longest || sums1(k) > room) continue;
                     const uint64_t cost = strip_cost(H, n_cus, halves ? strips1 : (strips1 + 1) / 2, tiles, halves, pairs_act * 2 * F * 8, k);
                     if (cost < least[halves]) { least[halves] = cost; best[halves] = k; }
                 }
@@ -165,6 +164,10 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
     // 39.7 / 39.5, but 1280 (320; 256) 42.3 / 43.4, 1728 (448; 288) 50.1 / 51.8; with three splits, 432 workgroups, the last two 45.2 and
     // 52.6; 160 of H 5120 F 384, 2 tokens, top-8 (640 workgroups) 42.4 / 45.6.  4 of H 4752 F 1680, 4 rows of each (quarters of 448 k against 288 k) 51.3 / 54.0, 15 rows 58.1 / 65.8.  One of H 4096 F 14336, one token
     // (256 workgroups, 448 k) 83 / 66, two (896 k) 122 / 119, but four (1792 k) 218 / 220.
+    // Tiles of more than 16 rows take the body for 64, which is slower than gemm2_kernel: not where they are likely.  Two tokens' experts of 4, H 512 F 256,
+    // 26 tokens 24.5 / 26.6, H 4736 F 512, 28 tokens 33.2 / 35.3; 15 tokens with all four, H 4192 F 232 36.5 / 32.
+    const double rows_mean = double(pairs) / double(c.E), rows_most = rows_mean + 1.5 * std::sqrt(rows_mean * (1.0 - std::min(1.0, double(K) / double(c.E))));
+    const bool short_tiles = T <= 16 || rows_most <= 16.0;
     const uint64_t wgs = strips2 * tiles, longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
     const auto splits_in = [&](uint64_t free, uint64_t most_wgs, uint64_t most_rows) {      // 0: there are none
         uint64_t least = ~0ull;
@@ -187,7 +190,7 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
         p.few_splits = splits_in(room - sums1(p.ksplit1), one_round ? n_cus : 3 * n_cus / 2, 256);
     p.few_fused = p.few_splits != 0;
     // (without room for gemm2_kernel's splits there is no call)
-    if (!p.few_fused) p.few_splits = splits_in(std::max(room, sums2(p.ksplit)), n_cus, tiles <= 2 ? 1024 : 512);
+    if (!p.few_fused && short_tiles) p.few_splits = splits_in(std::max(room, sums2(p.ksplit)), n_cus, tiles <= 2 ? 1024 : 512);
 }
 
 // split: with K splits of the first product and 128 x 128 tiles; without them the plan takes the least scratch.

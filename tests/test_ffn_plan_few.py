@@ -109,10 +109,15 @@ def test_both_sides_of_the_lines(few):
     assert of(T=59, K=1, E=4, H=4752, F=1680).few_splits == 0 and of(T=11, K=4, E=4, H=4768, F=3736).few_splits == 0
 
 
-def test_halved_strips_only_where_whole_ones_leave_cus_without_work(few, monkeypatch):
+def test_a_round_of_whole_strips_keeps_the_general_first_product(few, monkeypatch):
     monkeypatch.delenv("FLUXMOE_FFN_MTILE", raising=False)
-    for E, H, F, T, K in [(32, 1080, 6360, 5, 8), (64, 872, 6032, 7, 4), (64, 2920, 3064, 5, 10), (160, 928, 2728, 13, 4), (20, 992, 3552, 10, 6)]:
-        assert -(-F // 128) % 2 == 0 and not few.plan(E=E, H=H, F=F, T=T, K=K).halves
+    for E, H, F, T, K in [(32, 1080, 6360, 5, 8), (64, 2560, 2176, 10, 4), (42, 2960, 9336, 10, 4), (32, 3480, 3200, 6, 10), (20, 992, 3552, 10, 6)]:
+        p, g = (f(E=E, H=H, F=F, T=T, K=K) for f in (few.plan, few.general))
+        assert p.few and (p.ksplit1, p.halves) == (g.ksplit1, g.halves)
+    # tiles of more than 16 rows are unlikely, or not
+    few_rows = dict(E=4, H=512, F=256)
+    assert [few.plan(T=T, K=2, **few_rows).few_splits > 0 for T in (16, 20, 26, 32)] == [True, True, False, False]
+    assert few.plan(T=15, K=4, **few_rows).few_splits and few.plan(T=40, K=1, E=8, H=512, F=256).few_splits
     rng, halved = random.Random(12), 0
     for c in (random_call(rng) for _ in range(8000)):
         c["F"] = c["F"] // 256 * 256 or 256                                  # an even number of strips
