@@ -164,10 +164,12 @@ inline void plan_few(FfnPlan& p, const FfnShape& c, uint32_t T, uint32_t K, uint
     // 39.7 / 39.5, but 1280 (320; 256) 42.3 / 43.4, 1728 (448; 288) 50.1 / 51.8; with three splits, 432 workgroups, the last two 45.2 and
     // 52.6; 160 of H 5120 F 384, 2 tokens, top-8 (640 workgroups) 42.4 / 45.6.  4 of H 4752 F 1680, 4 rows of each (quarters of 448 k against 288 k) 51.3 / 54.0, 15 rows 58.1 / 65.8.  One of H 4096 F 14336, one token
     // (256 workgroups, 448 k) 83 / 66, two (896 k) 122 / 119, but four (1792 k) 218 / 220.
-    // Tiles of more than 16 rows take the body for 64, which is slower than gemm2_kernel: not where they are likely.  Two tokens' experts of 4, H 512 F 256,
-    // 26 tokens 24.5 / 26.6, H 4736 F 512, 28 tokens 33.2 / 35.3; 15 tokens with all four, H 4192 F 232 36.5 / 32.
+    // Tiles of more than 16 rows take the body for 64, which is slower than gemm2_kernel: not where they are likely, with even routing or where
+    // the most popular expert gets 0.3 of the tokens for each of their experts (16 experts by rank^-1.1).  Two of 4 experts a token, H 512 F 256, 26 tokens 24.5 / 26.6,
+    // H 4736 F 512, 28 tokens 33.2 / 35.3; of 16 of H 2048 F 1024, 28 tokens by rank 39.7 / 44.4 (even 47.5 / 45.3), F 512, 32 tokens 32.5 / 36.4 (33.9 / 33.2); one of 8 of H 880
+    // F 1960, 42 tokens 36.9 / 34.4; 15 tokens with four of 4, H 4192 F 232 36.5 / 32.
     const double rows_mean = double(pairs) / double(c.E), rows_most = rows_mean + 1.5 * std::sqrt(rows_mean * (1.0 - std::min(1.0, double(K) / double(c.E))));
-    const bool short_tiles = T <= 16 || rows_most <= 16.0;
+    const bool short_tiles = T <= 16 || std::max(rows_most, double(T) * std::min(1.0, 0.3 * double(K))) <= 16.0;
     const uint64_t wgs = strips2 * tiles, longest = std::min(F, align_up((F + p.ksplit - 1) / p.ksplit, kFewChunk));
     const auto splits_in = [&](uint64_t free, uint64_t most_wgs, uint64_t most_rows) {      // 0: there are none
         uint64_t least = ~0ull;

@@ -118,6 +118,8 @@ def test_a_round_of_whole_strips_keeps_the_general_first_product(few, monkeypatc
     few_rows = dict(E=4, H=512, F=256)
     assert [few.plan(T=T, K=2, **few_rows).few_splits > 0 for T in (16, 20, 26, 32)] == [True, True, False, False]
     assert few.plan(T=15, K=4, **few_rows).few_splits and few.plan(T=40, K=1, E=8, H=512, F=256).few_splits
+    skewed = dict(H=512, F=256, E=16)                                        # 0.3 of the tokens for each of their experts
+    assert [few.plan(T=T, K=K, **skewed).few_splits > 0 for T, K in ((53, 1), (54, 1), (26, 2), (27, 2), (17, 3), (18, 3))] == [True, False] * 3
     rng, halved = random.Random(12), 0
     for c in (random_call(rng) for _ in range(8000)):
         c["F"] = c["F"] // 256 * 256 or 256                                  # an even number of strips

@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
     (dict(tokens=4, top_k=4, n_experts=16, n_slots=16, hidden=2048, ffn=1016), "fused"),     # quarters of 256 k, the last of them short
     (dict(tokens=1, top_k=8, n_experts=16, n_slots=16, hidden=3080, ffn=776), "fused"),      # of 224 k, a strip of 8 columns
     (dict(tokens=5, top_k=3, hidden=520, ffn=72), "few"),                       # h from the first product
-    (dict(tokens=20, top_k=3, hidden=136, ffn=264), "few"),                     # tiles of more and of fewer than 16 rows
+    (dict(tokens=50, top_k=1, hidden=136, ffn=264, routing="zipf"), "few"),     # tiles of 28 rows and of fewer than 16
+    (dict(tokens=50, top_k=1, hidden=1000, ffn=520, routing="zipf"), "few"),    # the same in 8 strips, two MFMA tails of 8 k
+    (dict(tokens=20, top_k=3, hidden=136, ffn=264), "old"),                     # more than 16 rows are likely where routing is skewed
     (dict(tokens=2, top_k=1, hidden=1024, ffn=2056), "split"),                  # K splits, the last of them short
     (dict(tokens=32, top_k=2, n_experts=64, n_slots=64, hidden=2048, ffn=64), "old"),    # more strips than CUs
 ])
